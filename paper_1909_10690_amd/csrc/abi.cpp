@@ -74,8 +74,9 @@ int check_q(const double* q, int32_t n_q) {
 }
 
 // Bytes of the moving volume's gather layout on the Parzen path: fp32
-// quads for float volumes; for integer ones 16-bit quads on full sweeps and
-// 16-bit octs on sampled sweeps (one cache line per random sample).
+// quads for float volumes; for integer ones 16-bit quads on full sweeps.
+// Sampled sweeps keep a plain copy in a region of the same size (integer
+// volumes: of 16 bytes per voxel).
 size_t parzen_gather_bytes(const mi_volume* m, bool sampled = false) {
   if (m->dtype == MI_F32) return quad_f32_bytes(m->nx, m->ny, m->nz);
   return sampled ? oct_volume_bytes(m->nx, m->ny, m->nz) : quad16_bytes(m->nx, m->ny, m->nz);
@@ -133,8 +134,8 @@ int check_common(const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins
 //   hard:        moving oct volume u16x8[mnz][mny][mnx],
 //                hist u32[n][B][B]          (only when the caller passes no hist_out)
 //                count u64[n], MI partial sums (reduce_part_bytes)
-//   Parzen:      moving oct volume (integer moving volume) or f32x4 quad
-//                volume [mnz+1][mny][mnx] (float moving volume),
+//   Parzen:      16-bit quad volume (integer moving volume) or f32x4 quad volume
+//                [mnz+1][mny][mnx] (float moving volume); sampled: a plain copy,
 //                occupied-row map, wave-tile slot masks u32[tiles] and
 //                their per-row-group ORs u32[row groups],
 //                table f64[n][B][B], count u64[n]
@@ -322,9 +323,12 @@ struct mi_context {
 
 namespace {
 
-// Key of a per-call preparation (path, workspace, both volumes, bins).
-std::vector<uint64_t> prep_key(int path, const void* ws, const mi_volume* f, const mi_volume* m, int32_t bins) {
-  std::vector<uint64_t> k = {(uint64_t)path, (uint64_t)(uintptr_t)ws, (uint64_t)bins};
+// Key of a per-call preparation (path, where in which workspace, both
+// volumes, bins; the regions' offsets depend on the number of transforms).
+std::vector<uint64_t> prep_key(int path, const void* ws, const Layout& L, const mi_volume* f, const mi_volume* m,
+                               int32_t bins) {
+  std::vector<uint64_t> k = {(uint64_t)path, (uint64_t)(uintptr_t)ws, (uint64_t)bins, (uint64_t)L.fbins,
+                             (uint64_t)L.gvol};
   for (const mi_volume* v : {f, m}) {
     uint64_t lo, hi;
     memcpy(&lo, &v->lo, 8);
@@ -366,6 +370,13 @@ struct TimedLaunch {
   }
 };
 
+// The layout a hard-binned call prepares, and its path in the record of the
+// last preparation.
+int32_t call_gather(const mi_volume* m, int32_t n, int32_t flags) {
+  return hard_gather(m->lo, m->hi, n, (flags & MI_VOLUMES_UNCHANGED) != 0, (flags & MI_COMPACT_SLABS) != 0);
+}
+int hard_prep_path(int32_t gather) { return gather == kCopy16 ? 4 : 1; }
+
 // Slabs per transform that keep one slab's share of the moving gather
 // volume near 1.5 MiB: the workgroups of an XCD sweep one slab for many
 // transforms at once, and their moving footprint must stay in the XCD's
@@ -373,27 +384,27 @@ struct TimedLaunch {
 // 32 cut the L2 miss traffic and the sweep time by 8%).
 int64_t l2_slabs(size_t gather_volume_bytes) {
   const int64_t target = 3 << 19;  // 1.5 MiB
-  const int64_t c = ((int64_t)gather_volume_bytes + target - 1) / target;
-  return c < 32 ? 32 : c;
+  return ((int64_t)gather_volume_bytes + target - 1) / target;
 }
 
 // Workgroups per transform for the histogram sweep.  The fixed volume is
-// swept in groups of 4 rows; a transform's groups are split into `c`
-// slabs: enough workgroups to fill the chip several times over, in
-// slab-major order enough thin slabs that a slab's moving footprint fits
-// an XCD's L2 (l2_slabs), a multiple of 8 (one share per XCD), and -- with
-// 16-bit packed LDS counters -- few enough voxels per workgroup that no
-// counter can exceed 65535.
-int plan_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, int32_t n,
-                bool packed, const HardTune& tune) {
+// swept in groups of 4 rows; a transform's groups are split into slabs:
+// planned_slabs' best count, in slab-major order at least as many as keep a
+// slab's moving footprint in an XCD's L2 (l2_slabs), a multiple of 8 (one
+// share per XCD), and -- with 16-bit packed LDS counters -- few enough voxels
+// per workgroup that no counter can exceed 65535.
+int plan_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins, bool packed,
+                const HardTune& tune, int32_t gather) {
   const int64_t groups = (int64_t)((f->ny + 3) / 4) * f->nz;
   int64_t c;
   if (tune.chunks) {
     c = tune.chunks;
   } else {
-    c = ((int64_t)ctx->cu_count * 8 + n - 1) / n;
-    const int64_t l2 = l2_slabs(hard_gather_bytes(m));
-    if (tune.slab_major && c < l2) c = l2;
+    // workgroups a CU holds: 32 waves, 160 KiB of LDS
+    const int64_t resident = std::max<int64_t>(
+        1, std::min<int64_t>(2048 / tune.block, (int64_t)(160 * 1024 / hist_lds_bytes(bins, packed))));
+    const int64_t l2 = tune.slab_major ? l2_slabs(gather_volume_bytes(gather, m->nx, m->ny, m->nz)) : 1;
+    c = planned_slabs((int64_t)voxels(f), n, resident * ctx->cu_count, bins, l2);
   }
   if (c > groups) c = groups;
   if (packed) {
@@ -405,12 +416,11 @@ int plan_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, i
   return (int)c;
 }
 
-
 // Workgroups per transform and band for the Parzen sweeps (as plan_chunks).
 int plan_parzen_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, int64_t units) {
   const int64_t groups = (int64_t)((f->ny + 3) / 4) * f->nz;
   int64_t c = ((int64_t)ctx->cu_count * 8 + units - 1) / units;
-  const int64_t l2 = l2_slabs(parzen_gather_bytes(m));
+  const int64_t l2 = std::max<int64_t>(32, l2_slabs(parzen_gather_bytes(m)));
   if (c < l2) c = l2;
   if (c > groups) c = groups;
   return (int)(((c + 7) / 8) * 8);
@@ -481,14 +491,15 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   const bool fq = moving->dtype == MI_F32;
   void* gvol = ws + L.gvol;
   // a sampled call always prepares (its list is not part of the record)
-  if (smp || !reuse_prep(ctx, flags, prep_key(2, ws, fixed, moving, bins))) {
+  if (smp || !reuse_prep(ctx, flags, prep_key(2, ws, L, fixed, moving, bins))) {
     if ((e = launch_prebin_fixed(desc(fixed), bins, fb, s)) != hipSuccess) return hip_fail(e, "prebin");
     if ((e = launch_row_map(fb, voxels(fixed), bins, rows, s)) != hipSuccess) return hip_fail(e, "row map");
     if ((e = launch_tile_mask(fb, fixed->nx, fixed->ny, fixed->nz, (uint32_t*)(ws + L.tmask), s)) != hipSuccess)
       return hip_fail(e, "tile mask");
-    e = fq  ? launch_pack_quads_f32(desc(moving), (float4*)gvol, s)
-        : smp ? launch_pack_octs(desc(moving), (uint4*)gvol, s)
-              : launch_pack_quads16(desc(moving), (uint2*)gvol, s);
+    if (smp)
+      e = fq ? launch_pack_copy_f32(desc(moving), (float*)gvol, s) : launch_pack_copy(desc(moving), (uint16_t*)gvol, s);
+    else
+      e = fq ? launch_pack_quads_f32(desc(moving), (float4*)gvol, s) : launch_pack_quads16(desc(moving), (uint2*)gvol, s);
     if (e != hipSuccess) return hip_fail(e, "pack");
   }
   uint2* list = (uint2*)(ws + L.list);
@@ -607,7 +618,7 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
 struct PairsPlan {
   size_t tables = 0, table_bytes = 0, counters = 0, transforms = 0, hist = 0, count = 0, part = 0, total = 0;
   size_t off_desc = 0, off_frow = 0, off_mrow = 0, off_tbase = 0, off_xcd = 0;
-  std::vector<size_t> fbins, octs;
+  std::vector<size_t> fbins, gvol;
   std::vector<int32_t> chunks;
   std::vector<int64_t> fchunk_base, mchunk_base, t_base, xcd_base;  // xcd_base: [8][P+1]
   int64_t total_t = 0;
@@ -625,7 +636,7 @@ int plan_pairs(const mi_pair* pairs, int32_t n_pairs, int32_t bins, int32_t n_q,
   if (n_q < 1 || n_q > MI_MAX_Q) return MI_ERR_Q;
   const int P = n_pairs;
   plan.fbins.resize(P);
-  plan.octs.resize(P);
+  plan.gvol.resize(P);
   plan.chunks.resize(P);
   plan.fchunk_base.assign(P + 1, 0);
   plan.mchunk_base.assign(P + 1, 0);
@@ -693,7 +704,7 @@ int plan_pairs(const mi_pair* pairs, int32_t n_pairs, int32_t bins, int32_t n_q,
   for (int p = 0; p < P; ++p) {
     plan.fbins[p] = w;
     w += align256(voxels(&pairs[p].fixed));
-    plan.octs[p] = w;
+    plan.gvol[p] = w;
     const mi_volume& mv = pairs[p].moving;
     w += align256(plan.oct8 ? oct8_volume_bytes(mv.nx, mv.ny, mv.nz) : oct_volume_bytes(mv.nx, mv.ny, mv.nz));
   }
@@ -862,27 +873,30 @@ int graph_run(mi_context* ctx, const std::vector<uint64_t>& key, hipStream_t s, 
 
 // ---- the hard-binned path ---------------------------------------------------
 
-// Fixed bins, oct volume, zeroed histograms and the sweep (no reduction).
+// Fixed bins, moving volume, zeroed histograms and the sweep (no reduction).
 int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
                      const double* transforms, int32_t n, int32_t bins, int32_t flags,
                      uint32_t* hist, char* ws, const Layout& L, hipStream_t s,
                      const HardTune& tune, bool prepare, const SampleSpec* smp = nullptr) {
   hipError_t e;
   uint8_t* fb = (uint8_t*)(ws + L.fbins);
-  void* octs = ws + L.gvol;
+  void* gvol = ws + L.gvol;
+  const int32_t gather = call_gather(moving, smp ? kCopyTransforms + 1 : n, flags);  // samples: always octs
   const size_t bb = (size_t)bins * bins;
   // a sampled call always prepares (its list is not part of the record)
-  if (prepare && (smp || !reuse_prep(ctx, flags, prep_key(1, ws, fixed, moving, bins)))) {
+  if (prepare && (smp || !reuse_prep(ctx, flags, prep_key(hard_prep_path(gather), ws, L, fixed, moving, bins)))) {
     if ((e = launch_prebin_fixed(desc(fixed), bins, fb, s)) != hipSuccess) return hip_fail(e, "prebin");
-    e = oct8_range(moving->lo, moving->hi) ? launch_pack_oct8(desc(moving), (uint2*)octs, s)
-                                           : launch_pack_octs(desc(moving), (uint4*)octs, s);
+    e = gather == kCopy16 ? launch_pack_copy(desc(moving), (uint16_t*)gvol, s)
+        : gather == kOct8 ? launch_pack_oct8(desc(moving), (uint2*)gvol, s)
+                          : launch_pack_octs(desc(moving), (uint4*)gvol, s);
     if (e != hipSuccess) return hip_fail(e, "pack");
   }
   if ((e = launch_fill_u32(hist, bb * n, 0u, s)) != hipSuccess) return hip_fail(e, "fill");
   HardLaunch H{};
   H.transforms = transforms;
   H.fbins = fb;
-  H.octs = octs;
+  H.gvol = gvol;
+  H.gather = gather;
   H.fixed = desc(fixed);
   H.moving = desc(moving);
   H.hist = hist;
@@ -904,7 +918,7 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
     H.packed = bins > 128 ? 1 : 0;
     H.chunks = plan_sampled_chunks(ctx, expected_samples(fixed, *smp), n);
   } else {
-    H.chunks = plan_chunks(ctx, fixed, moving, n, H.packed != 0, tune);
+    H.chunks = plan_chunks(ctx, fixed, moving, n, bins, H.packed != 0, tune, gather);
   }
   // one launch covers at most 2^31 - 1 workgroups: split the transforms
   int64_t per_launch = 0x7FFFFFFFll / H.chunks;
@@ -1129,11 +1143,7 @@ int run_pairs(mi_context* ctx, const mi_pair* pairs, int32_t n_pairs, int32_t bi
     d.transforms = pr.transforms;
     d.geo = geometry(&pr.fixed, &pr.moving);
     d.geom = make_hard_geom(desc(&pr.fixed), desc(&pr.moving), (const uint8_t*)(ws + plan.fbins[p]),
-                            (const void*)(ws + plan.octs[p]), bins);
-    // one layout for every pair of the launch
-    d.geom.oct8 = plan.oct8 ? 1 : 0;
-    d.geom.oct_bytes = (uint32_t)(plan.oct8 ? oct8_volume_bytes(pr.moving.nx, pr.moving.ny, pr.moving.nz)
-                                            : oct_volume_bytes(pr.moving.nx, pr.moving.ny, pr.moving.nz));
+                            (const void*)(ws + plan.gvol[p]), plan.oct8 ? kOct8 : kOct16, bins);  // one layout for the launch
     d.fdtype = pr.fixed.dtype;
     d.mdtype = pr.moving.dtype;
     d.flo = pr.fixed.lo;
@@ -1409,7 +1419,7 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   HardTune best = ctx->hard_default;
   float best_ms = 3.4e38f;
   HardTune base = ctx->hard_default;
-  base.chunks = plan_chunks(ctx, fixed, moving, n, use_packed(base, bins), base);
+  base.chunks = plan_chunks(ctx, fixed, moving, n, bins, use_packed(base, bins), base, call_gather(moving, n, flags));
   const int32_t chunk_opts[3] = {base.chunks / 2, base.chunks, base.chunks * 2};
   // LDS counter layouts: u32 or packed 16-bit pairs (only packed fits above 128 bins)
   const int32_t n_layouts = bins > 128 ? 1 : 2;
@@ -1529,7 +1539,8 @@ int mi_eval(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   key_volume(key, moving);
   key_q(key, q, n_q);
   st = graph_run(ctx, key, s, body);
-  ctx->last_prep = prep_key(parzen ? 2 : 1, ws, fixed, moving, bins);  // the graph prepared them
+  // the graph prepared them
+  ctx->last_prep = prep_key(parzen ? 2 : hard_prep_path(call_gather(moving, n, run_flags)), ws, L, fixed, moving, bins);
   return st;
 }
 
@@ -1645,7 +1656,7 @@ int mi_grad(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   key_volume(key, moving);
   key_q(key, q, n_q);
   st = graph_run(ctx, key, s, body);
-  ctx->last_prep = prep_key(2, workspace, fixed, moving, bins);  // the graph prepared them
+  ctx->last_prep = prep_key(2, workspace, L, fixed, moving, bins);  // the graph prepared them
   return st;
 }
 

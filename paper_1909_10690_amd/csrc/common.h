@@ -156,6 +156,33 @@ __device__ __forceinline__ uint32_t clamp_offset(int32_t v, int32_t lo, int32_t 
   return (uint32_t)(v - lo);
 }
 
+typedef unsigned int vec4u __attribute__((ext_vector_type(4)));
+typedef unsigned int vec2u __attribute__((ext_vector_type(2)));
+
+// Eight consecutive voxels at p (aligned to eight elements), clamped, offset
+// and packed as 16-bit values: one load of 8 or 16 bytes.
+__device__ __forceinline__ vec4u load_offset8(const __attribute__((address_space(1))) uint8_t* p, int32_t lo,
+                                              int32_t hi) {
+  const vec2u w = *(const __attribute__((address_space(1))) vec2u*)p;
+  vec4u o;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t h = w[k >> 1] >> (16 * (k & 1));
+    o[k] = clamp_offset((int32_t)(h & 0xFFu), lo, hi) | (clamp_offset((int32_t)((h >> 8) & 0xFFu), lo, hi) << 16);
+  }
+  return o;
+}
+template <typename T>
+__device__ __forceinline__ vec4u load_offset8(const __attribute__((address_space(1))) T* p, int32_t lo, int32_t hi) {
+  static_assert(sizeof(T) == 2, "u16 or i16");
+  const vec4u w = *(const __attribute__((address_space(1))) vec4u*)p;
+  vec4u o;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    o[k] = clamp_offset((int32_t)(T)(w[k] & 0xFFFFu), lo, hi) | (clamp_offset((int32_t)(T)(w[k] >> 16), lo, hi) << 16);
+  return o;
+}
+
 // ---------------------------------------------------------------------------
 // the fixed-volume sweep shared by the histogram kernels
 // ---------------------------------------------------------------------------
@@ -280,11 +307,11 @@ struct GroupWalkBrick {
 // Geometry of one fixed/moving pair for the hard-binned sweep.
 struct HardGeom {
   const uint8_t* fbins;  // fixed bins, [fnz][fny][fnx]
-  const void* octs;      // moving oct volume, [mnz][mny][mnx]: u16x8, or u8x8 when oct8
+  const void* gvol;      // moving gather volume in layout `gather`
   int32_t fnx, fny, fnz;
   int32_t mnx, mny, mnz;
-  uint32_t oct_bytes;
-  int32_t oct8;          // 1: 8-bit corners (moving range R <= 256)
+  uint32_t gvol_bytes;
+  int32_t gather;        // Gather
   int32_t bins;
   double scale;  // B / (R 2^48), R = moving hi - lo + 1
   Divider div;   // floor(X / R) for the exact fallback
@@ -300,9 +327,10 @@ struct VolumeDesc {
 struct HardLaunch {
   const double* transforms;  // [n][12]
   const uint8_t* fbins;      // fixed-volume bins, [fnz][fny][fnx]
-  const void* octs;          // moving oct volume, [mnz][mny][mnx] (u16x8 or u8x8)
+  const void* gvol;          // moving gather volume in layout `gather` (Gather)
   VolumeDesc fixed, moving;
   uint32_t* hist;  // [n][B][B]
+  int32_t gather;
   int32_t n, bins, clamp;
   int32_t chunks;  // workgroups per transform, multiple of 8
   int32_t packed;  // 1: two 16-bit counters per LDS word (bins > 128)
@@ -344,6 +372,42 @@ inline size_t oct_volume_bytes(int32_t nx, int32_t ny, int32_t nz) {
 inline bool oct8_range(double lo, double hi) { return hi - lo + 1.0 <= 256.0; }
 inline size_t oct8_volume_bytes(int32_t nx, int32_t ny, int32_t nz) {
   return (size_t)nx * (size_t)ny * (size_t)nz * 8;
+}
+
+// Bytes of the plain 16-bit copy of an integer moving volume: the clamped,
+// offset intensities u16[nz][ny][nx] and a pad of one slice, one row and two
+// voxels (never more than the oct volume's bytes, whose region holds it).  A
+// voxel's neighbourhood is four 32-bit loads, the pairs (x, x + 1) of rows y
+// and y + 1 of slices z and z + 1; at the volume's upper faces these read
+// past the row, slice or volume, where the weight is 0, so the pad needs no
+// defined contents.  Float volumes on the sampled Parzen path: the same in
+// fp32, with the pad set to 0.
+inline size_t moving_copy_pad(int32_t nx, int32_t ny) { return (size_t)nx * ny + (size_t)nx + 2; }
+inline size_t moving_copy_bytes(int32_t nx, int32_t ny, int32_t nz) {
+  return ((size_t)nx * ny * (size_t)nz + moving_copy_pad(nx, ny)) * 2;
+}
+
+// Layouts of the hard sweeps' moving volume, and which one a call prepares.
+enum Gather : int32_t { kOct16 = 0, kOct8 = 1, kCopy16 = 2 };
+__host__ __device__ constexpr int32_t gather_record(int32_t gather) {
+  return gather == kOct16 ? 16 : (gather == kOct8 ? 8 : 2);
+}
+inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_t nz) {
+  return gather == kCopy16 ? moving_copy_bytes(nx, ny, nz) : (size_t)nx * ny * nz * gather_record(gather);
+}
+// A gather instruction costs the texture unit about the same whatever its
+// width, so a sweep over an oct volume (one gather per voxel) runs twice as
+// fast as over the copy (four): 12.3 against 27.5 us a transform over a batch
+// of 1000 of 256x256x180 u16.  But the oct volume is 8 times the moving
+// volume to write and then to fetch, 36 us at that size against 8 us for the
+// copy, so a call that prepares its volumes for a few transforms uses the
+// copy (us a call, oct and copy: 256x256x180 u16, 128 bins, one transform 122
+// and 97, four 257 and 229, six 328 and 338; 128^3 u8, 64 bins, four 66 and
+// 65, six 80 and 86).
+constexpr int32_t kCopyTransforms = 4;
+inline int32_t hard_gather(double lo, double hi, int32_t n, bool reused, bool brick) {
+  if (n <= kCopyTransforms && !reused && !brick) return kCopy16;
+  return oct8_range(lo, hi) ? kOct8 : kOct16;
 }
 
 // Bytes of the 16-bit quad volume of an integer moving volume on the Parzen
@@ -423,7 +487,7 @@ struct ParzenArgs {
   const RowMap* rows;
   const uint32_t* tile_mask;  // [row groups][x tiles]: slot groups present in each 16 x 4 wave tile
   const uint32_t* row_mask;   // [row groups]: the OR of each row group's tile masks
-  const void* gvol;    // integer moving: 16-bit quads (full sweeps) or octs (sampled); float: f32 quads
+  const void* gvol;    // integer moving: 16-bit quads (full sweeps) or the 16-bit copy (sampled); float: f32 quads (sampled: f32 copy)
   double* table;       // [n][B][B] forward masses (fp64)
   uint64_t* count;     // [n] voxels that took part
   const float* gtab;   // [n][n_q][B][B] d MI / d p
@@ -479,7 +543,7 @@ __host__ __device__ inline int32_t parzen_hot_cells(int32_t bins) { return kHotC
 
 struct ParzenLaunch {
   ParzenArgs args;
-  int32_t float_quads;  // 1: moving volume is fp32 (float4 quads, else uint4 octs)
+  int32_t float_quads;  // 1: moving volume is fp32 (float4 quads)
   int32_t clamp;
   int32_t block;        // threads per workgroup of the sweeps: 256, 512 or 1024
 };
@@ -506,6 +570,8 @@ hipError_t launch_fill_f64(double* p, size_t n, hipStream_t s);
 hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, hipStream_t s);
 hipError_t launch_pack_octs(const VolumeDesc& m, uint4* out, hipStream_t s);
 hipError_t launch_pack_oct8(const VolumeDesc& m, uint2* out, hipStream_t s);
+hipError_t launch_pack_copy(const VolumeDesc& m, uint16_t* out, hipStream_t s);
+hipError_t launch_pack_copy_f32(const VolumeDesc& m, float* out, hipStream_t s);
 hipError_t launch_hist_hard(const HardLaunch& L, hipStream_t s);
 // Random subsampling (sample.hip): the kept fixed voxels as list entries
 // {x | y << 12 | fixed bin << 24, z}; n_list must be zero beforehand.
@@ -561,7 +627,7 @@ struct PairsLaunch {
 hipError_t launch_pairs_prep(const PairsLaunch& L, hipStream_t s, bool volumes = true);
 hipError_t launch_pairs_hist(const PairsLaunch& L, hipStream_t s);
 HardGeom make_hard_geom(const VolumeDesc& fixed, const VolumeDesc& moving, const uint8_t* fbins,
-                        const void* octs, int32_t bins);
+                        const void* gvol, int32_t gather, int32_t bins);
 hipError_t launch_mi_reduce(const ReduceLaunch& L, hipStream_t s);
 hipError_t launch_pack_quads_f32(const VolumeDesc& m, float4* out, hipStream_t s);
 hipError_t launch_pack_quads16(const VolumeDesc& m, uint2* out, hipStream_t s);

@@ -237,6 +237,37 @@ hipError_t launch_pack_octs(const VolumeDesc& m, uint4* out, hipStream_t s) {
   return hipGetLastError();
 }
 
+// out[i] = clamp(v[i], lo, hi) - lo as 16 bits (moving_copy_bytes), 8 voxels
+// per lane with one load and one 16-byte store where the source is aligned
+// to 8 voxels.
+template <typename T>
+__global__ __launch_bounds__(256) void pack_copy_kernel(const T* __restrict__ v, size_t nvox, int32_t lo,
+                                                          int32_t hi, uint16_t* __restrict__ out) {
+  typedef const __attribute__((address_space(1))) T gT;
+  const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+  const size_t n8 = ((uintptr_t)v & (8 * sizeof(T) - 1)) == 0 ? nvox / 8 : 0;
+  for (size_t i = i0; i < n8; i += step) ((vec4u*)out)[i] = load_offset8((gT*)v + 8 * i, lo, hi);
+  for (size_t i = 8 * n8 + i0; i < nvox; i += step) out[i] = (uint16_t)clamp_offset((int32_t)v[i], lo, hi);
+}
+
+hipError_t launch_pack_copy(const VolumeDesc& m, uint16_t* out, hipStream_t s) {
+  const size_t nvox = (size_t)m.nx * m.ny * m.nz;
+  const unsigned grid = fill_grid((nvox + 7) / 8);
+  const int32_t lo = (int32_t)m.lo, hi = (int32_t)m.hi;
+  if (m.dtype == 0)
+    hipLaunchKernelGGL(pack_copy_kernel<uint8_t>, dim3(grid), dim3(256), 0, s, (const uint8_t*)m.data, nvox, lo, hi,
+                       out);
+  else if (m.dtype == 1)
+    hipLaunchKernelGGL(pack_copy_kernel<uint16_t>, dim3(grid), dim3(256), 0, s, (const uint16_t*)m.data, nvox, lo,
+                       hi, out);
+  else if (m.dtype == 2)
+    hipLaunchKernelGGL(pack_copy_kernel<int16_t>, dim3(grid), dim3(256), 0, s, (const int16_t*)m.data, nvox, lo, hi,
+                       out);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // the histogram sweep
 // ---------------------------------------------------------------------------
@@ -260,7 +291,7 @@ struct HardArgs {
 // 64 KiB LDS histograms; the sweep waits on its gathers and gains from the
 // extra waves.  Smaller workgroups keep their registers.
 // BRICK: slabs as bricks (GroupWalkBrick) rather than thin slabs.
-template <bool CLAMP, bool PACKED, bool OCT8, int NT, bool BRICK = false>
+template <bool CLAMP, bool PACKED, int GL, int NT, bool BRICK = false>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 ? 8 : 1)))
 void hist_hard_kernel(HardArgs a) {
   extern __shared__ uint32_t lds_hist[];
@@ -275,9 +306,9 @@ void hist_hard_kernel(HardArgs a) {
   __syncthreads();
   if (ok) {
     if (BRICK)  // bricks keep the per-voxel test (row ranges measured 0.7% slower on rotation maps)
-      sweep_hard<CLAMP, PACKED, OCT8, NT / 64, GroupWalkBrick, false>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
+      sweep_hard<CLAMP, PACKED, GL, NT / 64, GroupWalkBrick, false>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
     else
-      sweep_hard<CLAMP, PACKED, OCT8, NT / 64>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
+      sweep_hard<CLAMP, PACKED, GL, NT / 64>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
   }
   __syncthreads();
   if (ok) flush_hist<PACKED, NT>(lds_hist, B, a.hist + (size_t)t * B * B, false);
@@ -288,7 +319,7 @@ void hist_hard_kernel(HardArgs a) {
 // coordinates formed straight from the matrix.  With 16-bit counters the
 // share is counted in spans of at most 65535 samples, each flushed before
 // the next, so no counter can overflow whatever the sample count.
-template <bool CLAMP, bool PACKED, bool OCT8, int NT>
+template <bool CLAMP, bool PACKED, int GL, int NT>
 __global__ __launch_bounds__(NT) void hist_sampled_kernel(HardArgs a, const uint2* __restrict__ list,
                                                           const unsigned long long* __restrict__ n_list) {
   extern __shared__ uint32_t lds_hist[];
@@ -301,7 +332,7 @@ __global__ __launch_bounds__(NT) void hist_sampled_kernel(HardArgs a, const uint
   const int64_t ns = (int64_t)*n_list;
   const int64_t s0 = ns * chunk / a.chunks, s1 = ns * (chunk + 1) / a.chunks;
   const int64_t span = PACKED ? 65535 : s1 - s0;
-  const HardStep hs(a.geom, lds_hist, OCT8);
+  const HardStep hs(a.geom, lds_hist, GL);
   uint32_t* out = a.hist + (size_t)t * B * B;
   for (int64_t p0 = s0; p0 < s1; p0 += span) {
     const int64_t p1 = p0 + span < s1 ? p0 + span : s1;
@@ -314,7 +345,7 @@ __global__ __launch_bounds__(NT) void hist_sampled_kernel(HardArgs a, const uint
         const int64_t qx = Mq[0] * x + Mq[1] * y + Mq[2] * z + Mq[3];
         const int64_t qy = Mq[4] * x + Mq[5] * y + Mq[6] * z + Mq[7];
         const int64_t qz = Mq[8] * x + Mq[9] * y + Mq[10] * z + Mq[11];
-        hs.count<CLAMP, PACKED, OCT8>(qx, qy, qz, [&] { return fb; }, lds_hist);
+        hs.count<CLAMP, PACKED, GL>(qx, qy, qz, [&] { return fb; }, lds_hist);
       }
     }
     __syncthreads();
@@ -322,60 +353,74 @@ __global__ __launch_bounds__(NT) void hist_sampled_kernel(HardArgs a, const uint
   }
 }
 
-constexpr int kSampledBlock = 512;
+// Threads per workgroup of a sampled sweep: 512, or 1024 where the table
+// leaves room for fewer than four workgroups in a CU's 160 KiB of LDS (above
+// about 100 bins): the sweep waits on its gathers and needs the waves (256
+// bins, 25% of 181x217x181, 150 affines: 2.34 -> 1.95 ms a call).
+static int32_t sampled_block(size_t lds) { return 4 * lds > 160 * 1024 ? 1024 : 512; }
 
-template <bool CLAMP, bool PACKED, bool OCT8>
-static hipError_t launch_sampled_variant(const HardArgs& a, const uint2* list, const unsigned long long* n_list,
-                                         size_t lds, hipStream_t s) {
-  const hipError_t e =
-      lds_guard((const void*)hist_sampled_kernel<CLAMP, PACKED, OCT8, kSampledBlock>, lds, kHardLdsMax, true);
+template <bool CLAMP, bool PACKED, int GL, int NT>
+static hipError_t launch_sampled_nt(const HardArgs& a, const uint2* list, const unsigned long long* n_list,
+                                    size_t lds, hipStream_t s) {
+  const hipError_t e = lds_guard((const void*)hist_sampled_kernel<CLAMP, PACKED, GL, NT>, lds, kHardLdsMax, true);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((hist_sampled_kernel<CLAMP, PACKED, OCT8, kSampledBlock>), dim3((unsigned)(a.n * a.chunks)),
-                     dim3(kSampledBlock), lds, s, a, list, n_list);
+  hipLaunchKernelGGL((hist_sampled_kernel<CLAMP, PACKED, GL, NT>), dim3((unsigned)(a.n * a.chunks)), dim3(NT), lds,
+                     s, a, list, n_list);
   return hipGetLastError();
 }
 
-template <bool CLAMP, bool PACKED, bool OCT8, int NT, bool BRICK>
+template <bool CLAMP, bool PACKED, int GL>
+static hipError_t launch_sampled_variant(const HardArgs& a, const uint2* list, const unsigned long long* n_list,
+                                         size_t lds, hipStream_t s) {
+  return sampled_block(lds) == 1024 ? launch_sampled_nt<CLAMP, PACKED, GL, 1024>(a, list, n_list, lds, s)
+                                    : launch_sampled_nt<CLAMP, PACKED, GL, 512>(a, list, n_list, lds, s);
+}
+
+template <bool CLAMP, bool PACKED, int GL, int NT, bool BRICK>
 static hipError_t launch_variant(const HardArgs& a, int n, size_t lds, hipStream_t s) {
   const hipError_t e =
-      lds_guard((const void*)hist_hard_kernel<CLAMP, PACKED, OCT8, NT, BRICK>, lds, kHardLdsMax, true);
+      lds_guard((const void*)hist_hard_kernel<CLAMP, PACKED, GL, NT, BRICK>, lds, kHardLdsMax, true);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((hist_hard_kernel<CLAMP, PACKED, OCT8, NT, BRICK>), dim3((unsigned)(n * a.chunks)),
+  hipLaunchKernelGGL((hist_hard_kernel<CLAMP, PACKED, GL, NT, BRICK>), dim3((unsigned)(n * a.chunks)),
                      dim3(NT), lds, s, a);
   return hipGetLastError();
 }
 
-template <bool OCT8, int NT, bool BRICK>
+template <int GL, int NT, bool BRICK>
 static hipError_t launch_layout(const HardArgs& a, int n, bool clamp, bool packed, size_t lds,
                                 hipStream_t s) {
   if (clamp)
-    return packed ? launch_variant<true, true, OCT8, NT, BRICK>(a, n, lds, s)
-                  : launch_variant<true, false, OCT8, NT, BRICK>(a, n, lds, s);
-  return packed ? launch_variant<false, true, OCT8, NT, BRICK>(a, n, lds, s)
-                : launch_variant<false, false, OCT8, NT, BRICK>(a, n, lds, s);
+    return packed ? launch_variant<true, true, GL, NT, BRICK>(a, n, lds, s)
+                  : launch_variant<true, false, GL, NT, BRICK>(a, n, lds, s);
+  return packed ? launch_variant<false, true, GL, NT, BRICK>(a, n, lds, s)
+                : launch_variant<false, false, GL, NT, BRICK>(a, n, lds, s);
 }
 
 template <int NT, bool BRICK = false>
 static hipError_t launch_nt(const HardArgs& a, int n, bool clamp, bool packed, size_t lds,
                             hipStream_t s) {
-  return a.geom.oct8 ? launch_layout<true, NT, BRICK>(a, n, clamp, packed, lds, s)
-                     : launch_layout<false, NT, BRICK>(a, n, clamp, packed, lds, s);
+  switch (a.geom.gather) {
+  case kOct8: return launch_layout<kOct8, NT, BRICK>(a, n, clamp, packed, lds, s);
+  case kOct16: return launch_layout<kOct16, NT, BRICK>(a, n, clamp, packed, lds, s);
+  default:
+    if constexpr (BRICK) return hipErrorInvalidValue;  // the copy serves thin slabs only
+    else return launch_layout<kCopy16, NT, BRICK>(a, n, clamp, packed, lds, s);
+  }
 }
 
 HardGeom make_hard_geom(const VolumeDesc& fixed, const VolumeDesc& moving, const uint8_t* fbins,
-                        const void* octs, int32_t bins) {
+                        const void* gvol, int32_t gather, int32_t bins) {
   HardGeom g;
   g.fbins = fbins;
-  g.octs = octs;
+  g.gvol = gvol;
+  g.gather = gather;
   g.fnx = fixed.nx;
   g.fny = fixed.ny;
   g.fnz = fixed.nz;
   g.mnx = moving.nx;
   g.mny = moving.ny;
   g.mnz = moving.nz;
-  g.oct8 = oct8_range(moving.lo, moving.hi) ? 1 : 0;
-  g.oct_bytes = (uint32_t)(g.oct8 ? oct8_volume_bytes(moving.nx, moving.ny, moving.nz)
-                                  : oct_volume_bytes(moving.nx, moving.ny, moving.nz));
+  g.gvol_bytes = (uint32_t)gather_volume_bytes(gather, moving.nx, moving.ny, moving.nz);
   g.bins = bins;
   const uint32_t R = (uint32_t)((int32_t)moving.hi - (int32_t)moving.lo + 1);
   g.scale = ldexp((double)bins / (double)R, -48);
@@ -388,7 +433,7 @@ hipError_t launch_hist_hard(const HardLaunch& L, hipStream_t s) {
   HardArgs a;
   a.transforms = L.transforms;
   a.hist = L.hist;
-  a.geom = make_hard_geom(L.fixed, L.moving, L.fbins, L.octs, L.bins);
+  a.geom = make_hard_geom(L.fixed, L.moving, L.fbins, L.gvol, L.gather, L.bins);
   a.n = L.n;
   a.chunks = L.chunks;
   a.slab_major = L.slab_major;
@@ -428,27 +473,27 @@ hipError_t launch_hist_sampled(const HardLaunch& L, const uint2* list, const uns
   HardArgs a;
   a.transforms = L.transforms;
   a.hist = L.hist;
-  a.geom = make_hard_geom(L.fixed, L.moving, L.fbins, L.octs, L.bins);
+  a.geom = make_hard_geom(L.fixed, L.moving, L.fbins, L.gvol, L.gather, L.bins);
   a.n = L.n;
   a.chunks = L.chunks;
   a.slab_major = 1;
   a.order = nullptr;  // the sampled sweep keeps the batch order
   a.order_base = 0;
   const size_t lds = hist_lds_bytes(L.bins, L.packed);
-  const bool o8 = a.geom.oct8 != 0;
+  const bool o8 = a.geom.gather == kOct8;
   auto one = [&](const HardArgs& b) -> hipError_t {
     if (L.clamp) {
-      if (L.packed) return o8 ? launch_sampled_variant<true, true, true>(b, list, n_list, lds, s)
-                              : launch_sampled_variant<true, true, false>(b, list, n_list, lds, s);
-      return o8 ? launch_sampled_variant<true, false, true>(b, list, n_list, lds, s)
-                : launch_sampled_variant<true, false, false>(b, list, n_list, lds, s);
+      if (L.packed) return o8 ? launch_sampled_variant<true, true, kOct8>(b, list, n_list, lds, s)
+                              : launch_sampled_variant<true, true, kOct16>(b, list, n_list, lds, s);
+      return o8 ? launch_sampled_variant<true, false, kOct8>(b, list, n_list, lds, s)
+                : launch_sampled_variant<true, false, kOct16>(b, list, n_list, lds, s);
     }
-    if (L.packed) return o8 ? launch_sampled_variant<false, true, true>(b, list, n_list, lds, s)
-                            : launch_sampled_variant<false, true, false>(b, list, n_list, lds, s);
-    return o8 ? launch_sampled_variant<false, false, true>(b, list, n_list, lds, s)
-              : launch_sampled_variant<false, false, false>(b, list, n_list, lds, s);
+    if (L.packed) return o8 ? launch_sampled_variant<false, true, kOct8>(b, list, n_list, lds, s)
+                            : launch_sampled_variant<false, true, kOct16>(b, list, n_list, lds, s);
+    return o8 ? launch_sampled_variant<false, false, kOct8>(b, list, n_list, lds, s)
+              : launch_sampled_variant<false, false, kOct16>(b, list, n_list, lds, s);
   };
-  const int32_t step = transforms_per_launch(L.chunks, kSampledBlock);
+  const int32_t step = transforms_per_launch(L.chunks, sampled_block(lds));
   for (int32_t t0 = 0; t0 < L.n; t0 += step) {
     HardArgs b = a;
     b.n = L.n - t0 < step ? L.n - t0 : step;
@@ -460,17 +505,13 @@ hipError_t launch_hist_sampled(const HardLaunch& L, const uint2* list, const uns
   return hipSuccess;
 }
 
-template <int NT, bool BRICK = false>
+template <int GL, int NT, bool BRICK = false>
 static hipError_t allow_big_lds() {
   const int bytes = (int)kHardLdsMax;
-  const void* fns[8] = {(const void*)hist_hard_kernel<false, false, false, NT, BRICK>,
-                        (const void*)hist_hard_kernel<true, false, false, NT, BRICK>,
-                        (const void*)hist_hard_kernel<false, true, false, NT, BRICK>,
-                        (const void*)hist_hard_kernel<true, true, false, NT, BRICK>,
-                        (const void*)hist_hard_kernel<false, false, true, NT, BRICK>,
-                        (const void*)hist_hard_kernel<true, false, true, NT, BRICK>,
-                        (const void*)hist_hard_kernel<false, true, true, NT, BRICK>,
-                        (const void*)hist_hard_kernel<true, true, true, NT, BRICK>};
+  const void* fns[4] = {(const void*)hist_hard_kernel<false, false, GL, NT, BRICK>,
+                        (const void*)hist_hard_kernel<true, false, GL, NT, BRICK>,
+                        (const void*)hist_hard_kernel<false, true, GL, NT, BRICK>,
+                        (const void*)hist_hard_kernel<true, true, GL, NT, BRICK>};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e != hipSuccess || (e = lds_register(f)) != hipSuccess) return e;
@@ -478,27 +519,41 @@ static hipError_t allow_big_lds() {
   return hipSuccess;
 }
 
-hipError_t configure_hard_kernels() {
+template <int NT>
+static hipError_t allow_big_lds_nt() {
   hipError_t e;
-  const void* sampled[8] = {
-      (const void*)hist_sampled_kernel<false, false, false, kSampledBlock>,
-      (const void*)hist_sampled_kernel<true, false, false, kSampledBlock>,
-      (const void*)hist_sampled_kernel<false, true, false, kSampledBlock>,
-      (const void*)hist_sampled_kernel<true, true, false, kSampledBlock>,
-      (const void*)hist_sampled_kernel<false, false, true, kSampledBlock>,
-      (const void*)hist_sampled_kernel<true, false, true, kSampledBlock>,
-      (const void*)hist_sampled_kernel<false, true, true, kSampledBlock>,
-      (const void*)hist_sampled_kernel<true, true, true, kSampledBlock>};
-  for (const void* f : sampled)
-    if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kHardLdsMax)) != hipSuccess ||
-        (e = lds_register(f)) != hipSuccess)
-      return e;
-  if ((e = allow_big_lds<256>()) != hipSuccess) return e;
-  if ((e = allow_big_lds<512>()) != hipSuccess) return e;
-  if ((e = allow_big_lds<1024, true>()) != hipSuccess) return e;
-  return allow_big_lds<1024>();
+  if ((e = allow_big_lds<kOct16, NT>()) != hipSuccess) return e;
+  if ((e = allow_big_lds<kOct8, NT>()) != hipSuccess) return e;
+  return allow_big_lds<kCopy16, NT>();
 }
 
+template <int NT>
+static hipError_t allow_sampled_lds() {
+  const void* fns[8] = {(const void*)hist_sampled_kernel<false, false, kOct16, NT>,
+                        (const void*)hist_sampled_kernel<true, false, kOct16, NT>,
+                        (const void*)hist_sampled_kernel<false, true, kOct16, NT>,
+                        (const void*)hist_sampled_kernel<true, true, kOct16, NT>,
+                        (const void*)hist_sampled_kernel<false, false, kOct8, NT>,
+                        (const void*)hist_sampled_kernel<true, false, kOct8, NT>,
+                        (const void*)hist_sampled_kernel<false, true, kOct8, NT>,
+                        (const void*)hist_sampled_kernel<true, true, kOct8, NT>};
+  for (const void* f : fns) {
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kHardLdsMax);
+    if (e != hipSuccess || (e = lds_register(f)) != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t configure_hard_kernels() {
+  hipError_t e;
+  if ((e = allow_sampled_lds<512>()) != hipSuccess) return e;
+  if ((e = allow_sampled_lds<1024>()) != hipSuccess) return e;
+  if ((e = allow_big_lds_nt<256>()) != hipSuccess) return e;
+  if ((e = allow_big_lds_nt<512>()) != hipSuccess) return e;
+  if ((e = allow_big_lds_nt<1024>()) != hipSuccess) return e;
+  if ((e = allow_big_lds<kOct16, 1024, true>()) != hipSuccess) return e;
+  return allow_big_lds<kOct8, 1024, true>();
+}
 
 // ---------------------------------------------------------------------------
 // processing order of a batch

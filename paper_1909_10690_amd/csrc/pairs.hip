@@ -186,7 +186,7 @@ __global__ void prep_moving_kernel(PairsArgs a, int64_t items) {
     const uint32_t nzb = nz - z0 < (uint32_t)kPrepSlices ? nz - z0 : (uint32_t)kPrepSlices;  // slices in the block
     const uint32_t vp = run * kPrepPlaneRun + 2u * (uint32_t)lane;  // plane index of the lane's first voxel
     if (vp >= plane) return;
-    if (d.geom.oct8 && d.mdtype == 0 && (nx & 1) == 0 && ((uintptr_t)d.moving & 1) == 0) {
+    if (d.geom.gather == kOct8 && d.mdtype == 0 && (nx & 1) == 0 && ((uintptr_t)d.moving & 1) == 0) {
       // u8 rows of even length: the lane's two voxels (vp even) lie in one
       // row.  Per slice and source row (y, y + 1 clamped): a 2-byte load at
       // x and the byte at x + 2 (clamped to the last column).
@@ -227,7 +227,7 @@ __global__ void prep_moving_kernel(PairsArgs a, int64_t items) {
       for (int k = 0; k < kPrepSlices; ++k) {
         if ((uint32_t)k >= nzb) break;
         // entries: byte 4 dz + 2 dy + dx' (layout of pack_oct8_kernel)
-        *(global_out4*)((global_out2*)d.geom.octs + (size_t)(z0 + k) * plane + vp) =
+        *(global_out4*)((global_out2*)d.geom.gvol + (size_t)(z0 + k) * plane + vp) =
             uint4_t{cw[k][0] | (cw[k][1] << 16), cw[k + 1][0] | (cw[k + 1][1] << 16),
                     t[k][0] | (t[k][1] << 16), t[k + 1][0] | (t[k + 1][1] << 16)};
       }
@@ -245,13 +245,13 @@ __global__ void prep_moving_kernel(PairsArgs a, int64_t items) {
         const size_t s0 = (size_t)z * plane, s1 = z + 1 < nz ? s0 + plane : s0;  // slices z, z + 1 (clamped)
         const size_t a0 = s0 + row0, a1 = s0 + row1, b0 = s1 + row0, b1 = s1 + row1;
         const size_t out = s0 + v;
-        if (d.geom.oct8) {
+        if (d.geom.gather == kOct8) {
           // 8-bit corners: byte 4 dz + 2 dy + dx' (layout of pack_oct8_kernel)
-          ((global_out2*)d.geom.octs)[out] =
+          ((global_out2*)d.geom.gvol)[out] =
               uint2_t{val(a0 + x) | (val(a0 + x1) << 8) | (val(a1 + x) << 16) | (val(a1 + x1) << 24),
                       val(b0 + x) | (val(b0 + x1) << 8) | (val(b1 + x) << 16) | (val(b1 + x1) << 24)};
         } else {
-          ((global_out4*)d.geom.octs)[out] =
+          ((global_out4*)d.geom.gvol)[out] =
               uint4_t{val(a0 + x) | (val(a0 + x1) << 16), val(a1 + x) | (val(a1 + x1) << 16),
                       val(b0 + x) | (val(b0 + x1) << 16), val(b1 + x) | (val(b1 + x1) << 16)};
         }
@@ -260,7 +260,7 @@ __global__ void prep_moving_kernel(PairsArgs a, int64_t items) {
   });
 }
 
-template <bool CLAMP, bool PACKED, bool OCT8, int NT>
+template <bool CLAMP, bool PACKED, int GL, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void hist_pairs_kernel(PairsArgs a) {
   extern __shared__ uint32_t lds_hist[];
   const int B = a.bins;
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void hi
       int64_t Ms[12];
 #pragma unroll
       for (int e = 0; e < 12; ++e) Ms[e] = uniform64(Mq[e]);
-      sweep_hard<CLAMP, PACKED, OCT8, NT / 64, GroupWalkBrick, false>(geom, Md, Ms, chunks, chunk, lds_hist);
+      sweep_hard<CLAMP, PACKED, GL, NT / 64, GroupWalkBrick, false>(geom, Md, Ms, chunks, chunk, lds_hist);
     }
     __syncthreads();
     if (ok) flush_hist<PACKED, NT>(lds_hist, B, a.hist + (size_t)t * B * B, true);
@@ -353,12 +353,12 @@ hipError_t launch_pairs_prep(const PairsLaunch& L, hipStream_t s, bool volumes) 
 // pairs above, and the work-item slot after it).
 constexpr size_t kPairsLdsMax = 150 * 1024;
 
-template <bool CLAMP, bool PACKED, bool OCT8, int NT>
+template <bool CLAMP, bool PACKED, int GL, int NT>
 static hipError_t pairs_variant(const PairsLaunch& L, hipStream_t s) {
   const int B = L.args.bins;
   const size_t words = (size_t)B * hist_row_words(B, PACKED);
   const size_t lds = ((words + 1) & ~(size_t)1) * 4 + 8;  // histogram, then the 8-byte item slot
-  const void* fn = (const void*)hist_pairs_kernel<CLAMP, PACKED, OCT8, NT>;
+  const void* fn = (const void*)hist_pairs_kernel<CLAMP, PACKED, GL, NT>;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPairsLdsMax);
   if (e != hipSuccess || (e = lds_guard(fn, lds, kPairsLdsMax, true)) != hipSuccess) return e;
   int per_cu = 0;
@@ -367,27 +367,27 @@ static hipError_t pairs_variant(const PairsLaunch& L, hipStream_t s) {
   if (per_cu < 1) per_cu = 1;
   // every queue needs workgroups: a multiple of 8 (one share per XCD)
   const unsigned grid = (unsigned)(((per_cu * L.cu_count + 7) / 8) * 8);
-  hipLaunchKernelGGL((hist_pairs_kernel<CLAMP, PACKED, OCT8, NT>), dim3(grid), dim3(NT), lds, s, L.args);
+  hipLaunchKernelGGL((hist_pairs_kernel<CLAMP, PACKED, GL, NT>), dim3(grid), dim3(NT), lds, s, L.args);
   return hipGetLastError();
 }
 
-template <bool CLAMP, bool PACKED, bool OCT8>
+template <bool CLAMP, bool PACKED, int GL>
 static hipError_t pairs_block(const PairsLaunch& L, hipStream_t s) {
   switch (L.block) {
-  case 256: return pairs_variant<CLAMP, PACKED, OCT8, 256>(L, s);
-  case 1024: return pairs_variant<CLAMP, PACKED, OCT8, 1024>(L, s);
-  default: return pairs_variant<CLAMP, PACKED, OCT8, 512>(L, s);
+  case 256: return pairs_variant<CLAMP, PACKED, GL, 256>(L, s);
+  case 1024: return pairs_variant<CLAMP, PACKED, GL, 1024>(L, s);
+  default: return pairs_variant<CLAMP, PACKED, GL, 512>(L, s);
   }
 }
 
-template <bool OCT8>
+template <int GL>
 static hipError_t pairs_layout(const PairsLaunch& L, hipStream_t s) {
-  if (L.clamp) return L.packed ? pairs_block<true, true, OCT8>(L, s) : pairs_block<true, false, OCT8>(L, s);
-  return L.packed ? pairs_block<false, true, OCT8>(L, s) : pairs_block<false, false, OCT8>(L, s);
+  if (L.clamp) return L.packed ? pairs_block<true, true, GL>(L, s) : pairs_block<true, false, GL>(L, s);
+  return L.packed ? pairs_block<false, true, GL>(L, s) : pairs_block<false, false, GL>(L, s);
 }
 
 hipError_t launch_pairs_hist(const PairsLaunch& L, hipStream_t s) {
-  return L.oct8 ? pairs_layout<true>(L, s) : pairs_layout<false>(L, s);
+  return L.oct8 ? pairs_layout<kOct8>(L, s) : pairs_layout<kOct16>(L, s);
 }
 
 }  // namespace gemi

@@ -50,6 +50,37 @@ inline bool lds_fits(size_t dynamic_bytes, size_t static_bytes, size_t configure
          dynamic_bytes <= device_max - static_bytes;
 }
 
+// Slabs per transform (a multiple of 8, at least `least` rounded up) of a
+// hard sweep of n transforms over `voxels` fixed voxels, with `slots`
+// workgroups resident on the device at once.  Workgroups are dealt out as
+// slots free up, so a launch takes about `rounds` workgroup times: n c / slots
+// and a share of the last workgroup, or as many whole ones as its slots need;
+// a workgroup takes its voxels and the clearing and flushing of its LDS
+// histogram, worth 4096 + B^2 / 8 voxels; and a transform's slabs add into
+// the same few busy cells of one histogram, 8 voxels each.  The constants
+// are fitted to sweeps of 64^3 to 256x256x180 volumes, 1 to 200 transforms
+// and 32 to 256 bins over 8 to 1024 slabs, where the choice is within a few
+// percent of the best.  Against max(2048 / n, 32) slabs, whole calls: 64^3,
+// 21 transforms, 32 bins 62 -> 46 us; 128^3, one, 64 bins 68 -> 46 us;
+// 256x256x180, one, 128 bins 117 -> 97 us.
+inline int64_t planned_slabs(int64_t voxels, int64_t n, int64_t slots, int32_t bins, int64_t least) {
+  const double over = 4096.0 + bins * (double)bins / 8.0;
+  int64_t best = (least + 7) / 8 * 8;
+  if (best < 8) best = 8;
+  double least_cost = 1e300;
+  for (int64_t c = best; c <= 1024; c += 8) {
+    const double r = (double)(n * c) / (double)slots;
+    const double whole = (double)((n * c + slots - 1) / slots);
+    const double rounds = r + 0.3 > whole ? r + 0.3 : whole;
+    const double cost = rounds * ((double)voxels / (double)c + over) + 8.0 * (double)c;
+    if (cost < least_cost) {
+      least_cost = cost;
+      best = c;
+    }
+  }
+  return best;
+}
+
 // ---------------------------------------------------------------------------
 // the fixed-volume walk shared by the sweep kernels
 // ---------------------------------------------------------------------------

@@ -23,6 +23,8 @@ __device__ uint4_t struct_load_b128(__amdgpu_buffer_rsrc_t rsrc, int vindex, int
     __asm("llvm.amdgcn.struct.ptr.buffer.load.v4i32");
 __device__ uint2_t struct_load_b64(__amdgpu_buffer_rsrc_t rsrc, int vindex, int voffset, int soffset, int aux)
     __asm("llvm.amdgcn.struct.ptr.buffer.load.v2i32");
+__device__ uint32_t struct_load_b32(__amdgpu_buffer_rsrc_t rsrc, int vindex, int voffset, int soffset, int aux)
+    __asm("llvm.amdgcn.struct.ptr.buffer.load.i32");
 
 // v0 (1 - w) + v1 w at 16-bit weight w = fx >> 16, exact: the pair's low
 // half times (65535 - w), high half times w, plus the low half once more.
@@ -54,18 +56,20 @@ struct HardStep {
   double scale;
   Divider div;
 
-  // oct8: the gather volume's records are 8-bit corners (8 bytes), as the
-  // kernel's OCT8 instance reads them; else 16-bit ones (16 bytes)
-  __device__ __forceinline__ HardStep(const HardGeom& g, uint32_t* lds_hist, bool oct8) {
+  int32_t to_row, to_slice;  // kCopy16: bytes to the next row, next slice
+
+  // gather: the layout the kernel's GL instance reads
+  __device__ __forceinline__ HardStep(const HardGeom& g, uint32_t* lds_hist, int32_t gather) {
     topx = (uint64_t)(g.mnx - 1) << 32;
     topy = (uint64_t)(g.mny - 1) << 32;
     topz = (uint64_t)(g.mnz - 1) << 32;
     NY = (uint32_t)g.mny;
     MX = (uint32_t)g.mnx;
-    // records of 8 (OCT8) or 16 bytes, indexed by voxel; the record bound is
+    // records of 16, 8 or 2 bytes, indexed by voxel; the record bound is
     // given in bytes, which is no tighter than any record count
-    rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)g.octs, (short)(oct8 ? 8 : 16), (int)g.oct_bytes,
-                                             0x00020000);
+    rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)g.gvol, (short)gather_record(gather), (int)g.gvol_bytes, 0x00020000);
+    to_row = 2 * g.mnx;
+    to_slice = 2 * g.mnx * g.mny;
     Bu = (uint32_t)g.bins;
     // LDS histogram row pitch: in bytes (u32 counters), in 16-bit cells
     // (packed counters)
@@ -80,7 +84,7 @@ struct HardStep {
   // axis; fixed_bin() supplies its fixed bin (read after the gather is
   // issued).  CHECK false: the caller has established that the voxel lies
   // inside on every axis, where clamping and skipping change nothing.
-  template <bool CLAMP, bool PACKED, bool OCT8, bool CHECK = true, typename FB>
+  template <bool CLAMP, bool PACKED, int GL, bool CHECK = true, typename FB>
   __device__ __forceinline__ void count(int64_t qx, int64_t qy, int64_t qz, FB&& fixed_bin,
                                         uint32_t* lds_hist) const {
     uint64_t cx = (uint64_t)qx, cy = (uint64_t)qy, cz = (uint64_t)qz;
@@ -97,13 +101,18 @@ struct HardStep {
     // rows iz ny + iy < ny nz <= 2^24 and edges <= 4096: 24-bit operands
     const uint32_t vox = mad24(mad24(iz, NY, iy), MX, ix);
     uint4_t oc;
-    if (OCT8) {
+    if (GL == kOct8) {
       // bytes (x,y), (x1,y), (x,y1), (x1,y1) of slice z in .x, of z1 in .y
       const uint2_t d = struct_load_b64(rsrc, (int)vox, 0, 0, 0);
       oc.x = __builtin_amdgcn_perm(0u, d.x, 0x0C010C00u);  // (b0, b1) as 16-bit halves
       oc.y = __builtin_amdgcn_perm(0u, d.x, 0x0C030C02u);  // (b2, b3)
       oc.z = __builtin_amdgcn_perm(0u, d.y, 0x0C010C00u);
       oc.w = __builtin_amdgcn_perm(0u, d.y, 0x0C030C02u);
+    } else if (GL == kCopy16) {
+      oc.x = struct_load_b32(rsrc, (int)vox, 0, 0, 0);
+      oc.y = struct_load_b32(rsrc, (int)vox, 0, to_row, 0);
+      oc.z = struct_load_b32(rsrc, (int)vox, 0, to_slice, 0);
+      oc.w = struct_load_b32(rsrc, (int)vox, 0, to_slice + to_row, 0);
     } else {
       oc = struct_load_b128(rsrc, (int)vox, 0, 0, 0);
     }
@@ -184,13 +193,13 @@ struct RowRanges {
 // Sweeps one slab of the fixed volume for one transform (Mq) into the
 // workgroup's LDS histogram.  NW waves share the slab's 4-row groups, in
 // the order of Walk (thin slabs, or bricks).
-// OCT8: the oct volume holds 8-bit corners (one 64-bit gather), unpacked
-// into the 16-bit pairs of the x-lerp with byte permutes.
+// GL: the moving volume's layout (Gather); kOct8 corners (one 64-bit gather)
+// are unpacked into the 16-bit pairs of the x-lerp with byte permutes.
 // Md: the transform as stored; Mq: its Q32 rounding, in scalar registers
 // (quantize_transform_wave).  RANGES false: every
 // voxel is tested (the range lanes' registers would not fit a kernel already
 // at its register budget).
-template <bool CLAMP, bool PACKED, bool OCT8, int NW, typename Walk = GroupWalk, bool RANGES = true>
+template <bool CLAMP, bool PACKED, int GL, int NW, typename Walk = GroupWalk, bool RANGES = true>
 __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, const int64_t* Mq,
                                            int32_t chunks, uint32_t chunk, uint32_t* lds_hist) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -203,7 +212,7 @@ __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, 
   Walk w;
   w.init(M, g.fny, g.fnz, chunks, chunk, wave, NW, dx, dy);
   const int64_t sx = w.step[0], sy = w.step[1], sz = w.step[2];
-  const HardStep hs(g, lds_hist, OCT8);
+  const HardStep hs(g, lds_hist, GL);
   // fixed bins through a buffer descriptor: the lane's offset within the
   // tile in a vector register, the tile's in a scalar one (fixed voxels
   // < 2^28: 32-bit offsets)
@@ -224,8 +233,8 @@ __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, 
       int64_t qx = w.r[0] + w.lane_off[0], qy = w.r[1] + w.lane_off[1], qz = w.r[2] + w.lane_off[2];
       auto fixed_bin = [&] { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(frsrc, lane_f, (int)soff, 0); };
       for (int32_t it = 0; it < full; ++it, soff += kTileX, qx += sx, qy += sy, qz += sz)
-        hs.count<CLAMP, PACKED, OCT8>(qx, qy, qz, fixed_bin, lds_hist);
-      if (tail) hs.count<CLAMP, PACKED, OCT8>(qx, qy, qz, fixed_bin, lds_hist);
+        hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
+      if (tail) hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
     }
     return;
   }
@@ -246,17 +255,17 @@ __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, 
     auto fixed_bin = [&] { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(frsrc, lane_f, (int)soff, 0); };
     int32_t it = sp.u0;
     for (; it < sp.c0; ++it, soff += kTileX, qx += sx, qy += sy, qz += sz)
-      hs.count<CLAMP, PACKED, OCT8>(qx, qy, qz, fixed_bin, lds_hist);
+      hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
     for (; it < sp.c1; ++it, soff += kTileX, qx += sx, qy += sy, qz += sz)
-      hs.count<CLAMP, PACKED, OCT8, false>(qx, qy, qz, fixed_bin, lds_hist);
+      hs.count<CLAMP, PACKED, GL, false>(qx, qy, qz, fixed_bin, lds_hist);
     for (; it < sp.u1; ++it, soff += kTileX, qx += sx, qy += sy, qz += sz)
-      hs.count<CLAMP, PACKED, OCT8>(qx, qy, qz, fixed_bin, lds_hist);
+      hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
     if (has_tail && tail) {
       soff = row + (uint32_t)full * kTileX;
       qx = w.r[0] + sx * full + w.lane_off[0];
       qy = w.r[1] + sy * full + w.lane_off[1];
       qz = w.r[2] + sz * full + w.lane_off[2];
-      hs.count<CLAMP, PACKED, OCT8>(qx, qy, qz, fixed_bin, lds_hist);
+      hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
     }
   }
 }
