@@ -492,7 +492,7 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   void* gvol = ws + L.gvol;
   // a sampled call always prepares (its list is not part of the record)
   if (smp || !reuse_prep(ctx, flags, prep_key(2, ws, L, fixed, moving, bins))) {
-    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, s)) != hipSuccess) return hip_fail(e, "prebin");
+    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, false, s)) != hipSuccess) return hip_fail(e, "prebin");
     if ((e = launch_row_map(fb, voxels(fixed), bins, rows, s)) != hipSuccess) return hip_fail(e, "row map");
     if ((e = launch_tile_mask(fb, fixed->nx, fixed->ny, fixed->nz, (uint32_t*)(ws + L.tmask), s)) != hipSuccess)
       return hip_fail(e, "tile mask");
@@ -885,10 +885,10 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   const size_t bb = (size_t)bins * bins;
   // a sampled call always prepares (its list is not part of the record)
   if (prepare && (smp || !reuse_prep(ctx, flags, prep_key(hard_prep_path(gather), ws, L, fixed, moving, bins)))) {
-    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, s)) != hipSuccess) return hip_fail(e, "prebin");
+    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, smp == nullptr, s)) != hipSuccess) return hip_fail(e, "prebin");
     e = gather == kCopy16 ? launch_pack_copy(desc(moving), (uint16_t*)gvol, s)
         : gather == kOct8 ? launch_pack_oct8(desc(moving), (uint2*)gvol, s)
-                          : launch_pack_octs(desc(moving), (uint4*)gvol, s);
+                          : launch_pack_octs(desc(moving), gather == kOctD, (uint4*)gvol, s);
     if (e != hipSuccess) return hip_fail(e, "pack");
   }
   if ((e = launch_fill_u32(hist, bb * n, 0u, s)) != hipSuccess) return hip_fail(e, "fill");

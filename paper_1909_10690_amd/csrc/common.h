@@ -306,7 +306,7 @@ struct GroupWalkBrick {
 
 // Geometry of one fixed/moving pair for the hard-binned sweep.
 struct HardGeom {
-  const uint8_t* fbins;  // fixed bins, [fnz][fny][fnx]
+  const uint8_t* fbins;  // fixed bins, [fnz][fny][fnx], rows in the order fixed_run_x
   const void* gvol;      // moving gather volume in layout `gather`
   int32_t fnx, fny, fnz;
   int32_t mnx, mny, mnz;
@@ -326,7 +326,7 @@ struct VolumeDesc {
 
 struct HardLaunch {
   const double* transforms;  // [n][12]
-  const uint8_t* fbins;      // fixed-volume bins, [fnz][fny][fnx]
+  const uint8_t* fbins;      // fixed-volume bins, [fnz][fny][fnx], rows in the order fixed_run_x
   const void* gvol;          // moving gather volume in layout `gather` (Gather)
   VolumeDesc fixed, moving;
   uint32_t* hist;  // [n][B][B]
@@ -387,10 +387,14 @@ inline size_t moving_copy_bytes(int32_t nx, int32_t ny, int32_t nz) {
   return ((size_t)nx * ny * (size_t)nz + moving_copy_pad(nx, ny)) * 2;
 }
 
-// Layouts of the hard sweeps' moving volume, and which one a call prepares.
-enum Gather : int32_t { kOct16 = 0, kOct8 = 1, kCopy16 = 2 };
+// Layouts of the hard sweeps' moving volume, and which one a call prepares:
+// octs of 16-bit corners, or (kOctD, moving ranges of at most 2^14) of each
+// row's difference and negated sum, from which a signed dot product forms the
+// exact x-lerp in one instruction instead of two; octs of 8-bit corners; the
+// plain copy.
+enum Gather : int32_t { kOct16 = 0, kOct8 = 1, kCopy16 = 2, kOctD = 3 };
 __host__ __device__ constexpr int32_t gather_record(int32_t gather) {
-  return gather == kOct16 ? 16 : (gather == kOct8 ? 8 : 2);
+  return gather == kOct8 ? 8 : (gather == kCopy16 ? 2 : 16);
 }
 inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_t nz) {
   return gather == kCopy16 ? moving_copy_bytes(nx, ny, nz) : (size_t)nx * ny * nz * gather_record(gather);
@@ -407,7 +411,7 @@ inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_
 constexpr int32_t kCopyTransforms = 4;
 inline int32_t hard_gather(double lo, double hi, int32_t n, bool reused, bool brick) {
   if (n <= kCopyTransforms && !reused && !brick) return kCopy16;
-  return oct8_range(lo, hi) ? kOct8 : kOct16;
+  return oct8_range(lo, hi) ? kOct8 : (hi - lo < 16384.0 ? kOctD : kOct16);
 }
 
 // Bytes of the 16-bit quad volume of an integer moving volume on the Parzen
@@ -567,8 +571,10 @@ hipError_t launch_compose(const double* P, int64_t n, const Geometry& g, double*
 // G_P[r][3] = G_M[r][3] / msp[r].
 hipError_t launch_grad_physical(double* grad, int64_t rows, const Geometry& g, hipStream_t s);
 hipError_t launch_fill_f64(double* p, size_t n, hipStream_t s);
-hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, hipStream_t s);
-hipError_t launch_pack_octs(const VolumeDesc& m, uint4* out, hipStream_t s);
+// sweep_order: the bins in the order the hard sweeps read (fixed_run_x), else
+// in voxel order.
+hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, bool sweep_order, hipStream_t s);
+hipError_t launch_pack_octs(const VolumeDesc& m, bool differences, uint4* out, hipStream_t s);
 hipError_t launch_pack_oct8(const VolumeDesc& m, uint2* out, hipStream_t s);
 hipError_t launch_pack_copy(const VolumeDesc& m, uint16_t* out, hipStream_t s);
 hipError_t launch_pack_copy_f32(const VolumeDesc& m, float* out, hipStream_t s);

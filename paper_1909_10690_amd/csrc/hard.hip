@@ -6,22 +6,27 @@
 // moving volume to an "oct volume": each 16-byte element holds the clamped,
 // offset intensities of a voxel's whole 2x2x2 trilinear neighbourhood as
 // 16-bit values, so a lane gathers its neighbourhood with one aligned
-// 128-bit load.  The sweep is limited by gather instruction issue about as
-// much as by arithmetic, so one 16-byte gather beats two 8-byte gathers of
-// the same bytes.
+// 128-bit load (the texture unit's 16 cycles per load, whatever its width,
+// make one 16-byte gather beat two 8-byte gathers of the same bytes).
 //
 // One workgroup = one transform x one slab of fixed rows.  Each wave64
 // walks its own run of 4-row groups with scalar coordinates; its 64 lanes
 // cover a 16 x 4 tile of fixed voxels (a compact footprint in the moving
 // volume even under rotation, so few cache lines per load) and step the
 // exact Q32 moving coordinate by 16 * M[:,0] per iteration.  Each lane forms the exact
-// 16-bit-weight trilinear value: x-lerps with v_dot2_u32_u16 in integers
-// (< 2^32), y-lerps in fp64 (exact: integers < 2^48), the z-lerp as one
-// fp64 fma (the exact value rounded once).  The bin floor(V B / (R 2^48))
-// is read off the rounded value unless it lies within 2^-29 of a bin edge;
-// those lanes redo the sum in 64-bit integers, so every bin is exact.  One
-// count goes to the workgroup's private joint histogram in LDS; at the end
-// the non-zero LDS bins are added once into the transform's HBM histogram.
+// 16-bit-weight x-lerps with dot products in integers (< 2^32) and the y- and
+// z-lerps in fp32; the bin is read off the fp32 value, whose error is bounded
+// (kBinGuard in sweep.h), unless it lies too near a bin edge: those lanes redo
+// the sum in 64-bit integers, so every bin is exact.  One count goes to the
+// workgroup's private joint histogram in LDS; at the end the non-zero LDS
+// bins are added once into the transform's HBM histogram.
+//
+// 28 VALU instructions per voxel and step (37 with the y- and z-lerps in fp64
+// and two instructions per x-lerp), one gather per step and one 32-bit load of
+// fixed bins per four (a load of any width costs the texture unit 16 cycles a
+// wave).  1000 transforms of 256x256x180 u16, 128 bins: 12.87 -> 11.99 ms a
+// call.  The step now takes about 35 cycles of a CU: VALU 28, L1 accesses 26
+// (64 records of 16 bytes that start anywhere), LDS 17 with conflicts.
 #include "common.h"
 #include "sweep.h"
 
@@ -115,41 +120,74 @@ hipError_t launch_fill_f64(double* p, size_t n, hipStream_t s) {
 // fixed-volume binning, once per call
 // ---------------------------------------------------------------------------
 
-template <typename T>
-__global__ void prebin_int_kernel(const T* __restrict__ u, size_t nvox, int32_t lo, int32_t hi,
-                                  uint32_t bins, Divider div, uint8_t* __restrict__ out) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nvox;
-       i += (size_t)gridDim.x * blockDim.x)
-    out[i] = (uint8_t)fixed_bin_int((int32_t)u[i], lo, hi, bins, div);
+// The bins in voxel order, or (SWEEP) in the order the hard sweeps read them
+// (fixed_run_x), four stored bytes of a row per thread.
+template <bool SWEEP, typename F>
+__device__ __forceinline__ void prebin(int32_t nx, uint32_t rows, uint8_t* __restrict__ out, F&& bin) {
+  const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  if (!SWEEP) {
+    const uint32_t nvox = rows * (uint32_t)nx;  // < 2^28
+    for (uint32_t i = i0; i < nvox; i += step) out[i] = (uint8_t)bin(i);
+    return;
+  }
+  const uint32_t quads = ((uint32_t)nx + 3) / 4;
+  for (uint32_t i = i0; i < rows * quads; i += step) {
+    const uint32_t row = i / quads, p0 = 4 * (i - row * quads), base = row * (uint32_t)nx;
+    uint32_t b[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+      b[k] = p0 + k < (uint32_t)nx ? bin(base + (uint32_t)fixed_run_x((int32_t)(p0 + k), nx)) : 0u;
+    if (((base + p0) & 3) == 0 && p0 + 4 <= (uint32_t)nx) {
+      *(uint32_t*)(out + base + p0) = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
+    } else {
+      for (uint32_t k = 0; k < 4 && p0 + k < (uint32_t)nx; ++k) out[base + p0 + k] = (uint8_t)b[k];
+    }
+  }
 }
 
-__global__ void prebin_f32_kernel(const float* __restrict__ u, size_t nvox, double lo, double hi,
-                                  int32_t bins, uint8_t* __restrict__ out) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nvox;
-       i += (size_t)gridDim.x * blockDim.x)
-    out[i] = (uint8_t)fixed_bin_real((double)u[i], lo, hi, bins);
+template <bool SWEEP, typename T>
+__global__ __launch_bounds__(256) void prebin_int_kernel(const T* __restrict__ u, int32_t nx, uint32_t rows, int32_t lo,
+                                                         int32_t hi, uint32_t bins, Divider div,
+                                                         uint8_t* __restrict__ out) {
+  prebin<SWEEP>(nx, rows, out, [&](uint32_t i) { return fixed_bin_int((int32_t)u[i], lo, hi, bins, div); });
 }
 
-hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, hipStream_t s) {
+template <bool SWEEP>
+__global__ __launch_bounds__(256) void prebin_f32_kernel(const float* __restrict__ u, int32_t nx, uint32_t rows,
+                                                         double lo, double hi, int32_t bins,
+                                                         uint8_t* __restrict__ out) {
+  prebin<SWEEP>(nx, rows, out, [&](uint32_t i) { return fixed_bin_real((double)u[i], lo, hi, bins); });
+}
+
+template <bool SWEEP>
+static hipError_t prebin_variant(const VolumeDesc& f, int bins, uint8_t* out, hipStream_t s) {
   const size_t nvox = (size_t)f.nx * f.ny * f.nz;
-  const unsigned grid = fill_grid(nvox);
-  if (f.dtype == 3) {
-    hipLaunchKernelGGL(prebin_f32_kernel, dim3(grid), dim3(256), 0, s, (const float*)f.data, nvox,
-                       f.lo, f.hi, bins, out);
-  } else {
-    const int32_t lo = (int32_t)f.lo, hi = (int32_t)f.hi;
-    const Divider d = make_divider((uint32_t)(hi - lo + 1));
-    if (f.dtype == 0)
-      hipLaunchKernelGGL(prebin_int_kernel<uint8_t>, dim3(grid), dim3(256), 0, s,
-                         (const uint8_t*)f.data, nvox, lo, hi, (uint32_t)bins, d, out);
-    else if (f.dtype == 1)
-      hipLaunchKernelGGL(prebin_int_kernel<uint16_t>, dim3(grid), dim3(256), 0, s,
-                         (const uint16_t*)f.data, nvox, lo, hi, (uint32_t)bins, d, out);
-    else
-      hipLaunchKernelGGL(prebin_int_kernel<int16_t>, dim3(grid), dim3(256), 0, s,
-                         (const int16_t*)f.data, nvox, lo, hi, (uint32_t)bins, d, out);
+  const uint32_t rows = (uint32_t)f.ny * (uint32_t)f.nz;
+  const unsigned grid = fill_grid(SWEEP ? (size_t)rows * ((f.nx + 3) / 4) : nvox);
+  const int32_t lo = (int32_t)f.lo, hi = (int32_t)f.hi;
+  const Divider d = f.dtype == 3 ? Divider{0, 0} : make_divider((uint32_t)(hi - lo + 1));
+  switch (f.dtype) {
+  case 0:
+    hipLaunchKernelGGL((prebin_int_kernel<SWEEP, uint8_t>), dim3(grid), dim3(256), 0, s, (const uint8_t*)f.data, f.nx,
+                       rows, lo, hi, (uint32_t)bins, d, out);
+    break;
+  case 1:
+    hipLaunchKernelGGL((prebin_int_kernel<SWEEP, uint16_t>), dim3(grid), dim3(256), 0, s, (const uint16_t*)f.data, f.nx,
+                       rows, lo, hi, (uint32_t)bins, d, out);
+    break;
+  case 2:
+    hipLaunchKernelGGL((prebin_int_kernel<SWEEP, int16_t>), dim3(grid), dim3(256), 0, s, (const int16_t*)f.data, f.nx,
+                       rows, lo, hi, (uint32_t)bins, d, out);
+    break;
+  default:
+    hipLaunchKernelGGL((prebin_f32_kernel<SWEEP>), dim3(grid), dim3(256), 0, s, (const float*)f.data, f.nx, rows, f.lo,
+                       f.hi, bins, out);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, bool sweep_order, hipStream_t s) {
+  return sweep_order ? prebin_variant<true>(f, bins, out, s) : prebin_variant<false>(f, bins, out, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -164,7 +202,9 @@ hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, hipS
 // index is thus clamped to the volume, as in the trilinear rule; on those
 // corners the hard path's weight is 0, and the Parzen path's derivative
 // along that axis vanishes.
-template <typename T>
+// DIFF (kOctD): each word holds -(v0' + v1') in its low half and v1' - v0' in
+// its high half instead.
+template <typename T, bool DIFF>
 __global__ void pack_octs_kernel(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz,
                                  int32_t lo, int32_t hi, uint4* __restrict__ out) {
   const int32_t y = blockIdx.y, z = blockIdx.z;
@@ -177,8 +217,11 @@ __global__ void pack_octs_kernel(const T* __restrict__ v, int32_t nx, int32_t ny
   auto c = [&](T raw) -> uint32_t { return clamp_offset((int32_t)raw, lo, hi); };
   for (int32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < nx; x += gridDim.x * blockDim.x) {
     const int32_t x1 = x + 1 < nx ? x + 1 : nx - 1;
-    orow[x] = make_uint4(c(r00[x]) | (c(r00[x1]) << 16), c(r10[x]) | (c(r10[x1]) << 16),
-                         c(r01[x]) | (c(r01[x1]) << 16), c(r11[x]) | (c(r11[x1]) << 16));
+    auto pair = [&](const T* r) -> uint32_t {
+      const uint32_t v0 = c(r[x]), v1 = c(r[x1]);
+      return DIFF ? ((0u - v0 - v1) & 0xFFFFu) | ((v1 - v0) << 16) : v0 | (v1 << 16);
+    };
+    orow[x] = make_uint4(pair(r00), pair(r10), pair(r01), pair(r11));
   }
 }
 
@@ -220,21 +263,26 @@ hipError_t launch_pack_oct8(const VolumeDesc& m, uint2* out, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_pack_octs(const VolumeDesc& m, uint4* out, hipStream_t s) {
+template <bool DIFF>
+static hipError_t pack_octs_variant(const VolumeDesc& m, uint4* out, hipStream_t s) {
   const dim3 grid((unsigned)((m.nx + 255) / 256), (unsigned)m.ny, (unsigned)m.nz);
   const int32_t lo = (int32_t)m.lo, hi = (int32_t)m.hi;
   if (m.dtype == 0)
-    hipLaunchKernelGGL(pack_octs_kernel<uint8_t>, grid, dim3(256), 0, s, (const uint8_t*)m.data,
-                       m.nx, m.ny, m.nz, lo, hi, out);
+    hipLaunchKernelGGL((pack_octs_kernel<uint8_t, DIFF>), grid, dim3(256), 0, s, (const uint8_t*)m.data, m.nx, m.ny,
+                       m.nz, lo, hi, out);
   else if (m.dtype == 1)
-    hipLaunchKernelGGL(pack_octs_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t*)m.data,
-                       m.nx, m.ny, m.nz, lo, hi, out);
+    hipLaunchKernelGGL((pack_octs_kernel<uint16_t, DIFF>), grid, dim3(256), 0, s, (const uint16_t*)m.data, m.nx, m.ny,
+                       m.nz, lo, hi, out);
   else if (m.dtype == 2)
-    hipLaunchKernelGGL(pack_octs_kernel<int16_t>, grid, dim3(256), 0, s, (const int16_t*)m.data,
-                       m.nx, m.ny, m.nz, lo, hi, out);
+    hipLaunchKernelGGL((pack_octs_kernel<int16_t, DIFF>), grid, dim3(256), 0, s, (const int16_t*)m.data, m.nx, m.ny,
+                       m.nz, lo, hi, out);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+hipError_t launch_pack_octs(const VolumeDesc& m, bool differences, uint4* out, hipStream_t s) {
+  return differences ? pack_octs_variant<true>(m, out, s) : pack_octs_variant<false>(m, out, s);
 }
 
 // out[i] = clamp(v[i], lo, hi) - lo as 16 bits (moving_copy_bytes), 8 voxels
@@ -332,7 +380,7 @@ __global__ __launch_bounds__(NT) void hist_sampled_kernel(HardArgs a, const uint
   const int64_t ns = (int64_t)*n_list;
   const int64_t s0 = ns * chunk / a.chunks, s1 = ns * (chunk + 1) / a.chunks;
   const int64_t span = PACKED ? 65535 : s1 - s0;
-  const HardStep hs(a.geom, lds_hist, GL);
+  const HardStep hs(a.geom, PACKED, GL);
   uint32_t* out = a.hist + (size_t)t * B * B;
   for (int64_t p0 = s0; p0 < s1; p0 += span) {
     const int64_t p1 = p0 + span < s1 ? p0 + span : s1;
@@ -401,6 +449,7 @@ static hipError_t launch_nt(const HardArgs& a, int n, bool clamp, bool packed, s
                             hipStream_t s) {
   switch (a.geom.gather) {
   case kOct8: return launch_layout<kOct8, NT, BRICK>(a, n, clamp, packed, lds, s);
+  case kOctD: return launch_layout<kOctD, NT, BRICK>(a, n, clamp, packed, lds, s);
   case kOct16: return launch_layout<kOct16, NT, BRICK>(a, n, clamp, packed, lds, s);
   default:
     if constexpr (BRICK) return hipErrorInvalidValue;  // the copy serves thin slabs only
@@ -480,18 +529,20 @@ hipError_t launch_hist_sampled(const HardLaunch& L, const uint2* list, const uns
   a.order = nullptr;  // the sampled sweep keeps the batch order
   a.order_base = 0;
   const size_t lds = hist_lds_bytes(L.bins, L.packed);
-  const bool o8 = a.geom.gather == kOct8;
+  auto layout = [&]<int GL>(const HardArgs& b) -> hipError_t {
+    if (L.clamp)
+      return L.packed ? launch_sampled_variant<true, true, GL>(b, list, n_list, lds, s)
+                      : launch_sampled_variant<true, false, GL>(b, list, n_list, lds, s);
+    return L.packed ? launch_sampled_variant<false, true, GL>(b, list, n_list, lds, s)
+                    : launch_sampled_variant<false, false, GL>(b, list, n_list, lds, s);
+  };
   auto one = [&](const HardArgs& b) -> hipError_t {
-    if (L.clamp) {
-      if (L.packed) return o8 ? launch_sampled_variant<true, true, kOct8>(b, list, n_list, lds, s)
-                              : launch_sampled_variant<true, true, kOct16>(b, list, n_list, lds, s);
-      return o8 ? launch_sampled_variant<true, false, kOct8>(b, list, n_list, lds, s)
-                : launch_sampled_variant<true, false, kOct16>(b, list, n_list, lds, s);
+    switch (b.geom.gather) {
+    case kOct8: return layout.template operator()<kOct8>(b);
+    case kOctD: return layout.template operator()<kOctD>(b);
+    case kOct16: return layout.template operator()<kOct16>(b);
+    default: return hipErrorInvalidValue;
     }
-    if (L.packed) return o8 ? launch_sampled_variant<false, true, kOct8>(b, list, n_list, lds, s)
-                            : launch_sampled_variant<false, true, kOct16>(b, list, n_list, lds, s);
-    return o8 ? launch_sampled_variant<false, false, kOct8>(b, list, n_list, lds, s)
-              : launch_sampled_variant<false, false, kOct16>(b, list, n_list, lds, s);
   };
   const int32_t step = transforms_per_launch(L.chunks, sampled_block(lds));
   for (int32_t t0 = 0; t0 < L.n; t0 += step) {
@@ -524,19 +575,16 @@ static hipError_t allow_big_lds_nt() {
   hipError_t e;
   if ((e = allow_big_lds<kOct16, NT>()) != hipSuccess) return e;
   if ((e = allow_big_lds<kOct8, NT>()) != hipSuccess) return e;
+  if ((e = allow_big_lds<kOctD, NT>()) != hipSuccess) return e;
   return allow_big_lds<kCopy16, NT>();
 }
 
-template <int NT>
+template <int GL, int NT>
 static hipError_t allow_sampled_lds() {
-  const void* fns[8] = {(const void*)hist_sampled_kernel<false, false, kOct16, NT>,
-                        (const void*)hist_sampled_kernel<true, false, kOct16, NT>,
-                        (const void*)hist_sampled_kernel<false, true, kOct16, NT>,
-                        (const void*)hist_sampled_kernel<true, true, kOct16, NT>,
-                        (const void*)hist_sampled_kernel<false, false, kOct8, NT>,
-                        (const void*)hist_sampled_kernel<true, false, kOct8, NT>,
-                        (const void*)hist_sampled_kernel<false, true, kOct8, NT>,
-                        (const void*)hist_sampled_kernel<true, true, kOct8, NT>};
+  const void* fns[4] = {(const void*)hist_sampled_kernel<false, false, GL, NT>,
+                        (const void*)hist_sampled_kernel<true, false, GL, NT>,
+                        (const void*)hist_sampled_kernel<false, true, GL, NT>,
+                        (const void*)hist_sampled_kernel<true, true, GL, NT>};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kHardLdsMax);
     if (e != hipSuccess || (e = lds_register(f)) != hipSuccess) return e;
@@ -544,14 +592,23 @@ static hipError_t allow_sampled_lds() {
   return hipSuccess;
 }
 
+template <int NT>
+static hipError_t allow_sampled_lds_nt() {
+  hipError_t e;
+  if ((e = allow_sampled_lds<kOct16, NT>()) != hipSuccess) return e;
+  if ((e = allow_sampled_lds<kOct8, NT>()) != hipSuccess) return e;
+  return allow_sampled_lds<kOctD, NT>();
+}
+
 hipError_t configure_hard_kernels() {
   hipError_t e;
-  if ((e = allow_sampled_lds<512>()) != hipSuccess) return e;
-  if ((e = allow_sampled_lds<1024>()) != hipSuccess) return e;
+  if ((e = allow_sampled_lds_nt<512>()) != hipSuccess) return e;
+  if ((e = allow_sampled_lds_nt<1024>()) != hipSuccess) return e;
   if ((e = allow_big_lds_nt<256>()) != hipSuccess) return e;
   if ((e = allow_big_lds_nt<512>()) != hipSuccess) return e;
   if ((e = allow_big_lds_nt<1024>()) != hipSuccess) return e;
   if ((e = allow_big_lds<kOct16, 1024, true>()) != hipSuccess) return e;
+  if ((e = allow_big_lds<kOctD, 1024, true>()) != hipSuccess) return e;
   return allow_big_lds<kOct8, 1024, true>();
 }
 

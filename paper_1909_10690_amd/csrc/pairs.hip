@@ -43,8 +43,6 @@ __device__ __forceinline__ int find_pair(const int64_t* __restrict__ base, int P
 // table, so without the address space the compiler would use flat accesses.
 typedef const __attribute__((address_space(1))) uint16_t global_u16;
 typedef const __attribute__((address_space(1))) int16_t global_i16;
-typedef const __attribute__((address_space(1))) uint32_t global_cu32;
-typedef const __attribute__((address_space(1))) uint4_t global_cu4;
 typedef const __attribute__((address_space(1))) float global_f32;
 typedef __attribute__((address_space(1))) uint8_t global_out8;
 typedef __attribute__((address_space(1))) uint32_t global_out32;
@@ -121,46 +119,44 @@ __device__ __forceinline__ void for_each_item(const PairDesc* __restrict__ pairs
   }
 }
 
-// Fixed bins of every pair, one wave per chunk of kPrepFixedChunk
-// consecutive voxels of a pair's fixed volume: every lane busy whatever the
-// row length.  Full chunks of a u8 volume are read and their bins written in
-// 16-byte accesses, 16 voxels per lane (with four bytes per lane the pass
-// waited on one short load per wave at a time); otherwise lane l takes
-// voxels l, l + 64, ..., so each access of the wave covers consecutive
-// voxels.
+// Fixed bins of every pair in the sweep's order (fixed_run_x), one wave per
+// chunk of kPrepFixedChunk consecutive stored bytes of a pair's fixed volume:
+// every lane busy whatever the row length.  Rows of whole runs (nx a multiple
+// of 64) and full chunks of a u8 volume are handled a run at a time, four
+// stored bytes per lane; otherwise lane l takes bytes l, l + 64, ...
 __global__ void prep_fixed_kernel(PairsArgs a, int64_t chunks) {
   for_each_item(a.pairs, a.fchunk_base, a.n_pairs, chunks, [&](const PairDesc& d, int64_t c, int lane) {
     const int64_t nvox = (int64_t)d.geom.fnx * d.geom.fny * d.geom.fnz;
     const int64_t c0 = c * kPrepFixedChunk;
     global_out8* __restrict__ out = (global_out8*)d.geom.fbins;
-    // the form is chosen for the whole chunk (a full chunk of an aligned u8
-    // volume, or not), so every voxel of it is written once
-    if (d.fdtype == 0 && c0 + kPrepFixedChunk <= nvox && (((uintptr_t)d.fixed | (uintptr_t)out) & 15) == 0) {
-      const int64_t v0 = c0 + kPrepFixedLane * lane;  // a multiple of 16: 16-byte aligned accesses
-      const uint4_t w = *(global_cu4*)((global_u8*)d.fixed + v0);
-      uint4_t o;
+    auto bin8 = [&](uint32_t u) {
+      return fixed_bin_int((int32_t)u, (int32_t)d.flo, (int32_t)d.fhi, (uint32_t)d.geom.bins, d.fdiv);
+    };
+    if (d.fdtype == 0 && d.geom.fnx % kFixedRun == 0 && c0 + kPrepFixedChunk <= nvox) {
+      global_u8* __restrict__ src = (global_u8*)d.fixed + c0;
+      uint32_t v[kPrepFixedLane];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint32_t bj = 0;
+      for (int k = 0; k < kPrepFixedLane; ++k)  // all loads before the first store
+        v[k] = src[256 * (k >> 2) + kFixedRun * (lane >> 4) + kTileX * (k & 3) + (lane & 15)];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-          bj |= fixed_bin_int((int32_t)((w[j] >> (8 * k)) & 0xFFu), (int32_t)d.flo, (int32_t)d.fhi,
-                              (uint32_t)d.geom.bins, d.fdiv) << (8 * k);
-        o[j] = bj;
-      }
-      *(global_out4*)(out + v0) = o;
+      for (int k = 0; k < kPrepFixedLane / 4; ++k)
+        *(global_out32*)(out + c0 + 256 * k + 4 * lane) =
+            bin8(v[4 * k]) | (bin8(v[4 * k + 1]) << 8) | (bin8(v[4 * k + 2]) << 16) | (bin8(v[4 * k + 3]) << 24);
       return;
     }
+    const uint32_t nx = (uint32_t)d.geom.fnx;
     for (int k = 0; k < kPrepFixedLane; ++k) {
-      const int64_t v = c0 + lane + 64 * k;
-      if (v >= nvox) break;
+      const int64_t p = c0 + lane + 64 * k;
+      if (p >= nvox) break;
+      const uint32_t row = (uint32_t)p / nx;  // nvox < 2^28
+      const size_t v = (size_t)row * nx + (size_t)fixed_run_x((int32_t)((uint32_t)p - row * nx), (int32_t)nx);
       uint32_t b;
       if (d.fdtype == 3)
         b = fixed_bin_real((double)((global_f32*)d.fixed)[v], d.flo, d.fhi, d.geom.bins);
       else
         b = fixed_bin_int(load_int(d.fixed, d.fdtype, v), (int32_t)d.flo, (int32_t)d.fhi,
                           (uint32_t)d.geom.bins, d.fdiv);
-      out[v] = (uint8_t)b;
+      out[p] = (uint8_t)b;
     }
   });
 }

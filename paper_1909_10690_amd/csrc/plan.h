@@ -87,6 +87,18 @@ inline int64_t planned_slabs(int64_t voxels, int64_t n, int64_t slots, int32_t b
 
 constexpr int kTileX = 16, kTileY = 4;  // a wave64 covers 16 x 4 fixed voxels at a time
 
+// Fixed bins of the hard sweeps.  Each whole run of kFixedRun voxels of a row
+// is stored so that the four bytes at 4 dx hold voxels dx, 16 + dx, 32 + dx
+// and 48 + dx: the bins a lane needs in four consecutive x steps of 16, in
+// one 32-bit load.  The rest of a row (fewer than kFixedRun voxels) stays in
+// order.  x of the voxel stored at position p of a row of nx:
+constexpr int32_t kFixedRun = 64;
+constexpr int32_t fixed_run_x(int32_t p, int32_t nx) {
+  if (p >= nx / kFixedRun * kFixedRun) return p;
+  const int32_t r = p & (kFixedRun - 1);
+  return (p - r) + (r >> 2) + kTileX * (r & 3);
+}
+
 // One wave's walk over its share of a slab: groups of kTileY consecutive
 // rows of one slice with exact Q32 row coordinates.  Either each wave takes
 // a contiguous share of the slab's row groups (GroupWalk), or the waves

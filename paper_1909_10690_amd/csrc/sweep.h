@@ -10,12 +10,15 @@
 namespace gemi {
 
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+typedef short short2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int uint2_t __attribute__((ext_vector_type(2)));
 typedef unsigned int uint4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 // Device-memory bytes: loads through such a pointer are global, not flat,
 // also when the pointer itself was read from memory.
 typedef const __attribute__((address_space(1))) uint8_t global_u8;
+typedef uint32_t unaligned32 __attribute__((aligned(1)));
+typedef const __attribute__((address_space(1))) unaligned32 global_unaligned32;
 
 // Loads of one record of a buffer whose descriptor has a stride: the
 // hardware forms base + index * stride, so the index needs no shift.
@@ -33,6 +36,23 @@ __device__ __forceinline__ uint32_t lerp_x(uint32_t pair, uint32_t wpack) {
                                 __builtin_bit_cast(ushort2_t, wpack), pair & 0xFFFFu, false);
 }
 
+// The same from a record word -(v0 + v1) | (v1 - v0) << 16 (kOctD), with
+// `weights` -2^15 low and w - 2^15 high:
+// (v0 + v1) 2^15 + (v1 - v0) (w - 2^15) = v0 (2^16 - w) + v1 w, one signed dot
+// product (below 2^30: the clamp changes nothing, and keeps the compiler from
+// the accumulating form, whose register it would have to clear first).
+__device__ __forceinline__ uint32_t lerp_xd(uint32_t rec, uint32_t weights) {
+  return (uint32_t)__builtin_amdgcn_sdot2(__builtin_bit_cast(short2_t, rec), __builtin_bit_cast(short2_t, weights), 0,
+                                          true);
+}
+
+// (float)(q >> 16): one instruction (the compiler shifts and converts).
+__device__ __forceinline__ float high16_f32(uint32_t q) {
+  float f;
+  asm("v_cvt_f32_u32_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1" : "=v"(f) : "v"(q));
+  return f;
+}
+
 // Exact bin of V = sum over corners, from the four exact x-lerps.
 static __device__ __noinline__ uint32_t exact_bin(uint32_t a00, uint32_t a10, uint32_t a01, uint32_t a11,
                                            uint32_t wy, uint32_t wz, uint32_t B, Divider div) {
@@ -44,22 +64,35 @@ static __device__ __noinline__ uint32_t exact_bin(uint32_t a00, uint32_t a10, ui
   return div_small(X, div);
 }
 
-constexpr double kEdge = 1.0 / 536870912.0;  // 2^-29
+// The bin of a hard sweep is read off an fp32 value and redone in integers
+// where rounding could matter.  With p = V B / (R 2^48) < B the exact bin
+// position, the sweep forms u = kBinBase + p + 4 ulp (ulp: that of u, 2^-16 for
+// kBinBase = 128, up to 128 bins; 2^-15 for 256, above).  V comes from the four
+// exact x-lerps with five roundings on sums of non-negative terms (to float,
+// a product and an fma per axis), the scale is rounded once and u once, so
+// |error| <= 6 2^-24 p + ulp / 2 <= 3.5 ulp (p < kBinBase).  So the integer
+// part of u is the bin when its fraction is at least 8 ulp; otherwise (1.2e-4
+// of positions, 2.4e-4 above 128 bins, and those exactly on an edge)
+// exact_bin decides.
+constexpr uint32_t kBinGuard = 8;  // ulp
+// kBinBase + 4 ulp; 16-bit counters take any bin count, u32 ones at most 128
+constexpr float bin_base(bool packed) { return (packed ? 256.0f : 128.0f) * (1.0f + 4.0f / 8388608.0f); }
 
 // Per-launch constants of the hard-binned step of one fixed voxel: the
 // moving gather volume, its upper coordinates, the bin scale and the LDS
-// histogram's byte address.
+// histogram's row pitch.
 struct HardStep {
   __amdgpu_buffer_rsrc_t rsrc;
   uint64_t topx, topy, topz;
   uint32_t NY, MX, Bu, row_bytes, row_cells;
-  double scale;
+  float scale;     // B / (R 2^48)
+  uint32_t shift2;  // 2, in a vector register
   Divider div;
 
   int32_t to_row, to_slice;  // kCopy16: bytes to the next row, next slice
 
   // gather: the layout the kernel's GL instance reads
-  __device__ __forceinline__ HardStep(const HardGeom& g, uint32_t* lds_hist, int32_t gather) {
+  __device__ __forceinline__ HardStep(const HardGeom& g, bool packed, int32_t gather) {
     topx = (uint64_t)(g.mnx - 1) << 32;
     topy = (uint64_t)(g.mny - 1) << 32;
     topz = (uint64_t)(g.mnz - 1) << 32;
@@ -75,7 +108,9 @@ struct HardStep {
     // (packed counters)
     row_bytes = 4u * (uint32_t)hist_row_words(g.bins, false);
     row_cells = 2u * (uint32_t)hist_row_words(g.bins, true);
-    scale = g.scale;
+    scale = (float)g.scale;
+    shift2 = 2;
+    asm("" : "+v"(shift2));
     div = g.div;
   }
 
@@ -100,59 +135,79 @@ struct HardStep {
     const uint32_t ix = (uint32_t)(cx >> 32), iy = (uint32_t)(cy >> 32), iz = (uint32_t)(cz >> 32);
     // rows iz ny + iy < ny nz <= 2^24 and edges <= 4096: 24-bit operands
     const uint32_t vox = mad24(mad24(iz, NY, iy), MX, ix);
-    uint4_t oc;
-    if (GL == kOct8) {
-      // bytes (x,y), (x1,y), (x,y1), (x1,y1) of slice z in .x, of z1 in .y
-      const uint2_t d = struct_load_b64(rsrc, (int)vox, 0, 0, 0);
-      oc.x = __builtin_amdgcn_perm(0u, d.x, 0x0C010C00u);  // (b0, b1) as 16-bit halves
-      oc.y = __builtin_amdgcn_perm(0u, d.x, 0x0C030C02u);  // (b2, b3)
-      oc.z = __builtin_amdgcn_perm(0u, d.y, 0x0C010C00u);
-      oc.w = __builtin_amdgcn_perm(0u, d.y, 0x0C030C02u);
-    } else if (GL == kCopy16) {
-      oc.x = struct_load_b32(rsrc, (int)vox, 0, 0, 0);
-      oc.y = struct_load_b32(rsrc, (int)vox, 0, to_row, 0);
-      oc.z = struct_load_b32(rsrc, (int)vox, 0, to_slice, 0);
-      oc.w = struct_load_b32(rsrc, (int)vox, 0, to_slice + to_row, 0);
+    const uint32_t fx = (uint32_t)cx, fy = (uint32_t)cy, fz = (uint32_t)cz;
+    uint32_t a00, a10, a01, a11;  // the exact x-lerps of the four rows
+    if (GL == kOctD) {
+      const uint4_t oc = struct_load_b128(rsrc, (int)vox, 0, 0, 0);
+      const uint32_t w = (fx & 0xFFFF0000u) ^ 0x80008000u;
+      a00 = lerp_xd(oc.x, w);
+      a10 = lerp_xd(oc.y, w);
+      a01 = lerp_xd(oc.z, w);
+      a11 = lerp_xd(oc.w, w);
     } else {
-      oc = struct_load_b128(rsrc, (int)vox, 0, 0, 0);
+      uint4_t oc;
+      if (GL == kOct8) {
+        // bytes (x,y), (x1,y), (x,y1), (x1,y1) of slice z in .x, of z1 in .y
+        const uint2_t d = struct_load_b64(rsrc, (int)vox, 0, 0, 0);
+        oc.x = __builtin_amdgcn_perm(0u, d.x, 0x0C010C00u);  // (b0, b1) as 16-bit halves
+        oc.y = __builtin_amdgcn_perm(0u, d.x, 0x0C030C02u);  // (b2, b3)
+        oc.z = __builtin_amdgcn_perm(0u, d.y, 0x0C010C00u);
+        oc.w = __builtin_amdgcn_perm(0u, d.y, 0x0C030C02u);
+      } else if (GL == kCopy16) {
+        oc.x = struct_load_b32(rsrc, (int)vox, 0, 0, 0);
+        oc.y = struct_load_b32(rsrc, (int)vox, 0, to_row, 0);
+        oc.z = struct_load_b32(rsrc, (int)vox, 0, to_slice, 0);
+        oc.w = struct_load_b32(rsrc, (int)vox, 0, to_slice + to_row, 0);
+      } else {
+        oc = struct_load_b128(rsrc, (int)vox, 0, 0, 0);
+      }
+      // (65535 - wx) in the low half, wx in the high half: the high halves of
+      // ~fx and fx, one byte permute
+      const uint32_t wpack = __builtin_amdgcn_perm(fx, ~fx, 0x07060302u);
+      a00 = lerp_x(oc.x, wpack);
+      a10 = lerp_x(oc.y, wpack);
+      a01 = lerp_x(oc.z, wpack);
+      a11 = lerp_x(oc.w, wpack);
     }
-    bin_count<PACKED>(oc, fixed_bin(), (uint32_t)cx, (uint32_t)cy, (uint32_t)cz, lds_hist);
-  }
-
-  // The moving bin from the 16-bit corner pairs oc and the Q32 fractions,
-  // exactly, and the count of cell [fb][bin].
-  template <bool PACKED>
-  __device__ __forceinline__ void bin_count(const uint4_t& oc, uint32_t fb, uint32_t fx, uint32_t fy,
-                                            uint32_t fz, uint32_t* lds_hist) const {
-    // (65535 - wx) in the low half, wx in the high half: the high halves of
-    // ~fx and fx, one byte permute
-    const uint32_t wpack = __builtin_amdgcn_perm(fx, ~fx, 0x07060302u);
-    const uint32_t a00 = lerp_x(oc.x, wpack), a10 = lerp_x(oc.y, wpack);
-    const uint32_t a01 = lerp_x(oc.z, wpack), a11 = lerp_x(oc.w, wpack);
-    const uint32_t wy = fy >> 16, wz = fz >> 16;
-    const double wyd = (double)wy, wzd = (double)wz;
-    const double A00 = (double)a00, A10 = (double)a10, A01 = (double)a01, A11 = (double)a11;
-    const double uyd = 65536.0 - wyd;
-    const double b0 = fma(A10, wyd, A00 * uyd);         // exact, < 2^48
-    const double b1 = fma(A11, wyd, A01 * uyd);         // exact, < 2^48
-    const double V = fma(b1 - b0, wzd, b0 * 65536.0);  // exact value rounded once
-    // the bin position shifted up by kEdge: its floor is the bin unless the
-    // exact position lies within kEdge of a bin edge, which is when the
-    // fraction falls below 2 kEdge (the rounding errors are far smaller)
-    const double tb = fma(V, scale, kEdge);
-    uint32_t bm = (uint32_t)tb;
-    if (__builtin_amdgcn_fract(tb) < 2.0 * kEdge) bm = exact_bin(a00, a10, a01, a11, wy, wz, Bu, div);
+    // the moving bin: y- and z-lerps, scale and base in fp32 (see kBinGuard)
+    const float wy = high16_f32(fy), wz = high16_f32(fz);
+    const float uy = 65536.0f - wy, uz = 65536.0f - wz;
+    const float b0 = fmaf((float)a10, wy, (float)a00 * uy);
+    const float b1 = fmaf((float)a11, wy, (float)a01 * uy);
+    const float u = fmaf(fmaf(b1, wz, b0 * uz), scale, bin_base(PACKED));
+    // bits 16..22 (PACKED: doubled, 16..23) hold the bin, the low 16 bits the
+    // fraction
+    const uint32_t bits = PACKED ? 2u * __builtin_bit_cast(uint32_t, u) : __builtin_bit_cast(uint32_t, u);
+    // one 16-bit compare and a branch of the whole wave; the lanes concerned
+    // are looked for behind it
+    constexpr uint32_t guard = PACKED ? 2u * kBinGuard : kBinGuard;
+    uint64_t near_edge;
+    asm("v_cmp_gt_u16_e64 %0, %1, %2" : "=s"(near_edge) : "n"(guard), "v"(bits));
+    auto exact = [&](uint32_t& cell, uint32_t shift) {
+      uint32_t b = bits;
+      asm volatile("" : "+v"(b));
+      if ((b & 0xFFFFu) < guard) cell = exact_bin(a00, a10, a01, a11, fy >> 16, fz >> 16, Bu, div) << shift;
+    };
+    const uint32_t fb = fixed_bin();
     if (PACKED) {
       // 16-bit cell of counter [fb][bm]; the row pitch is even, so the
       // cell's word and half follow from it directly
+      uint32_t bm = (bits >> 16) & 0xFFu;
+      if (near_edge != 0) exact(bm, 0);
       const uint32_t cell = __umul24(fb, row_cells) + bm;
       atomicAdd(&lds_hist[cell >> 1], 1u << ((cell & 1u) * 16u));
     } else {
-      // LDS byte address of counter [fb][bm], formed directly: a mul24 and
-      // a shift-add.  The kernels that sweep keep no static LDS, so their
-      // dynamic histogram starts at address 0 (lds_guard checks this at
-      // launch) and needs no base.
-      const uint32_t addr = (bm << 2) + __umul24(fb, row_bytes);
+      // LDS byte address of counter [fb][bm], formed directly: byte 2 of u
+      // (up to 128 bins bit 23, the exponent's last, is 0) shifted in one
+      // instruction, and a multiply-add.  The kernels that sweep keep no
+      // static LDS, so their dynamic histogram starts at address 0 (lds_guard
+      // checks this at launch) and needs no base.
+      uint32_t bm4;
+      asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2"
+          : "=v"(bm4)
+          : "v"(shift2), "v"(bits));
+      if (near_edge != 0) exact(bm4, 2);
+      const uint32_t addr = mad24(fb, row_bytes, bm4);
       __hip_atomic_fetch_add((lds_u32*)(size_t)addr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   }
@@ -212,60 +267,73 @@ __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, 
   Walk w;
   w.init(M, g.fny, g.fnz, chunks, chunk, wave, NW, dx, dy);
   const int64_t sx = w.step[0], sy = w.step[1], sz = w.step[2];
-  const HardStep hs(g, lds_hist, GL);
-  // fixed bins through a buffer descriptor: the lane's offset within the
-  // tile in a vector register, the tile's in a scalar one (fixed voxels
-  // < 2^28: 32-bit offsets)
+  const HardStep hs(g, PACKED, GL);
+  // Fixed bins: the row's address in scalar registers, the lane's offset in a
+  // vector register.  Every load, however narrow, costs the texture unit as
+  // much as the moving gather, so the bins come four x steps to a 32-bit load:
+  // in each whole 64-voxel run of a row they are stored in the order
+  // fixed_run_x.
   const uint32_t fnx = (uint32_t)g.fnx;
-  const __amdgpu_buffer_rsrc_t frsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)g.fbins, (short)0, (int)(fnx * (uint32_t)g.fny * (uint32_t)g.fnz), 0x00020000);
-  const int lane_f = (int)(dy * fnx + dx);
+  global_u8* const fbins = (global_u8*)g.fbins;
+  const uint32_t lane_f = dy * fnx + dx, lane_f4 = dy * fnx + 4 * dx;
   const int32_t full = (int32_t)(fnx / kTileX);      // x steps every lane of the tile takes
+  const int32_t runs = (int32_t)(fnx / kFixedRun) * (kFixedRun / kTileX);  // of these, in whole runs
   const bool tail = (uint32_t)dx < fnx % kTileX;  // the lane takes one more
   const bool has_tail = fnx % kTileX != 0;
   RowRanges ranges;
   if (RANGES) ranges.init(Md, g, lane);
 
-  if constexpr (!RANGES) {
-    for (; w.g < w.g1; w.next()) {
-      if (w.j0 + dy >= g.fny) continue;
-      uint32_t soff = ((uint32_t)w.k * (uint32_t)g.fny + (uint32_t)w.j0) * fnx;
-      int64_t qx = w.r[0] + w.lane_off[0], qy = w.r[1] + w.lane_off[1], qz = w.r[2] + w.lane_off[2];
-      auto fixed_bin = [&] { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(frsrc, lane_f, (int)soff, 0); };
-      for (int32_t it = 0; it < full; ++it, soff += kTileX, qx += sx, qy += sy, qz += sz)
-        hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
-      if (tail) hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
-    }
-    return;
-  }
   for (; w.g < w.g1; w.next()) {
-    // x steps [u0, c0) and [c1, u1) test each voxel, [c0, c1) has every
-    // lane inside; with EXCLUDE no lane counts outside [u0, u1)
-    const RowSpans sp = ranges.spans(w.j0, w.k, full, !CLAMP);
+    // x steps [c0, c1) have every lane inside; with EXCLUDE no lane counts
+    // outside [u0, u1)
+    RowSpans sp{0, full, full, full};
+    if (RANGES) sp = ranges.spans(w.j0, w.k, full, !CLAMP);
     const int32_t j = w.j0 + dy;
     if (j >= g.fny) continue;
-    const uint32_t row = ((uint32_t)w.k * (uint32_t)g.fny + (uint32_t)w.j0) * fnx;
-    uint32_t soff = row + (uint32_t)sp.u0 * kTileX;
+    global_u8* const row = fbins + ((uint32_t)w.k * (uint32_t)g.fny + (uint32_t)w.j0) * fnx;  // < 2^28
     int64_t qx = w.r[0] + w.lane_off[0], qy = w.r[1] + w.lane_off[1], qz = w.r[2] + w.lane_off[2];
-    if (sp.u0 > 0) {
+    if (RANGES && sp.u0 > 0) {
       qx += sx * sp.u0;
       qy += sy * sp.u0;
       qz += sz * sp.u0;
     }
-    auto fixed_bin = [&] { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(frsrc, lane_f, (int)soff, 0); };
+    // whole runs with every lane inside, four x steps at a time: [c0, c1)
+    const int32_t c0 = (sp.c0 + 3) & ~3, c1 = (sp.c1 < runs ? sp.c1 : runs) & ~3;
     int32_t it = sp.u0;
-    for (; it < sp.c0; ++it, soff += kTileX, qx += sx, qy += sy, qz += sz)
-      hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
-    for (; it < sp.c1; ++it, soff += kTileX, qx += sx, qy += sy, qz += sz)
-      hs.count<CLAMP, PACKED, GL, false>(qx, qy, qz, fixed_bin, lds_hist);
-    for (; it < sp.u1; ++it, soff += kTileX, qx += sx, qy += sy, qz += sz)
-      hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
+    uint32_t bins4 = 0;  // the lane's bins of steps it, it + 1, ... of the run
+    auto load_run = [&] { return *(global_unaligned32*)(row + (uint32_t)(it >> 2) * kFixedRun + lane_f4); };
+    auto checked = [&](int32_t end) {
+      if ((it & 3) != 0 && it < runs) bins4 = load_run() >> (8 * (it & 3));  // a start within a run
+      for (; it < (end < runs ? end : runs); ++it, bins4 >>= 8, qx += sx, qy += sy, qz += sz) {
+        if ((it & 3) == 0) bins4 = load_run();
+        hs.count<CLAMP, PACKED, GL>(qx, qy, qz, [&] { return bins4 & 0xFFu; }, lds_hist);
+      }
+    };
+    if (RANGES && c0 < c1) {
+      checked(c0);
+      for (; it < c1; it += 4) {
+        bins4 = load_run();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          hs.count<CLAMP, PACKED, GL, false>(qx, qy, qz, [&] { return (bins4 >> (8 * k)) & 0xFFu; }, lds_hist);
+          qx += sx;
+          qy += sy;
+          qz += sz;
+          asm("" : "+v"(qx), "+v"(qy), "+v"(qz));  // step by step: not each from the first, with twice the adds
+        }
+      }
+    }
+    checked(sp.u1);
+    for (; it < sp.u1; ++it, qx += sx, qy += sy, qz += sz)  // past the last whole run
+      hs.count<CLAMP, PACKED, GL>(
+          qx, qy, qz, [&] { return (uint32_t)row[(uint32_t)it * kTileX + lane_f]; }, lds_hist);
     if (has_tail && tail) {
-      soff = row + (uint32_t)full * kTileX;
-      qx = w.r[0] + sx * full + w.lane_off[0];
-      qy = w.r[1] + sy * full + w.lane_off[1];
-      qz = w.r[2] + sz * full + w.lane_off[2];
-      hs.count<CLAMP, PACKED, GL>(qx, qy, qz, fixed_bin, lds_hist);
+      if (RANGES) {
+        qx = w.r[0] + sx * full + w.lane_off[0];
+        qy = w.r[1] + sy * full + w.lane_off[1];
+        qz = w.r[2] + sz * full + w.lane_off[2];
+      }
+      hs.count<CLAMP, PACKED, GL>(qx, qy, qz, [&] { return (uint32_t)row[(uint32_t)full * kTileX + lane_f]; }, lds_hist);
     }
   }
 }

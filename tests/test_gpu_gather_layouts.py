@@ -124,3 +124,31 @@ def test_preparation_switches_layout(ctx):
             mi, _, h = ctx.eval(F, M, x, 64, q, flags=flags, want_hist=True, out=out[n], workspace=ws, stream=side)
         side.synchronize()
         assert torch.equal(h, want[n]), (n, flags)
+
+
+@pytest.mark.parametrize("nx", [15, 63, 64, 65, 79, 128, 150])
+@pytest.mark.parametrize("hi,bins", [(255, 128), (16383, 128), (16383, 129), (16384, 64), (65535, 256), (4095, 2),
+                                     (4095, 97)])
+def test_sweep_runs_and_records(ctx, nx, hi, bins):
+    """Rows of and around whole 64-voxel runs; moving ranges on both sides of
+    each record form (8-bit corners, differences up to 2^14, 16-bit corners);
+    bin counts on both sides of the 16-bit counters, thin slabs and bricks."""
+    import torch
+    from paper_1909_10690_amd import binding as B
+    shape = (nx, 9, 6)
+    rng = np.random.default_rng(nx + hi + bins)
+    dt = np.uint8 if hi == 255 else np.uint16
+    f = inputs.random_volume(rng, shape, np.uint8, 0, 255)
+    m = inputs.random_volume(rng, shape, dt, 0, hi)
+    mats = edge_transforms(shape, rng)
+    print(f"runs nx={nx} hi={hi} bins={bins}", flush=True)
+    F, M = device_volume(f, 0, 255, 1), device_volume(m, 0, hi, 0)
+    for clamp in (0, 1):
+        omi, oov, oh = oracle.eval_hard(oracle.volume(f, 0, 255), oracle.volume(m, 0, hi), mats, bins, (1.0,),
+                                        boundary=clamp, want_hist=True)
+        for flags in (clamp, clamp | B.COMPACT_SLABS):
+            mi, ov, h = ctx.eval(F, M, torch.from_numpy(mats).cuda(), bins, (1.0,), flags=flags, want_hist=True)
+            torch.cuda.synchronize()
+            assert np.array_equal(h.cpu().numpy().astype(np.uint32), oh), flags
+            assert np.array_equal(ov.cpu().numpy(), oov)
+            assert np.all(np.abs(mi.cpu().numpy() - omi) <= 1e-12 * np.maximum(1.0, np.abs(omi)))

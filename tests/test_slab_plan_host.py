@@ -1,4 +1,4 @@
-"""CPU test of the hard sweeps' slab count (csrc/plan.h, planned_slabs),
+"""CPU tests of the hard sweeps' stored bin order and slab count (csrc/plan.h),
 compiled with g++: a multiple of 8 in range, never below the L2 bound, and
 above it never so many that a workgroup's voxels are few beside its table."""
 import os
@@ -33,6 +33,43 @@ int main() {
   return bad != 0;
 }
 """
+
+
+RUNS = r"""
+#include "plan.h"
+#include <initializer_list>
+#include <stdio.h>
+#include <vector>
+using namespace gemi;
+int main() {
+  int bad = 0;
+  for (int nx = 2; nx <= 300; ++nx) {
+    std::vector<int> seen(nx, 0);
+    for (int p = 0; p < nx; ++p) {
+      const int x = fixed_run_x(p, nx);
+      if (x < 0 || x >= nx) { ++bad; continue; }
+      ++seen[x];
+    }
+    for (int x = 0; x < nx; ++x) bad += seen[x] != 1;
+    // step it of lane dx of a whole run: byte it % 4 of the word at 4 dx
+    for (int it = 0; it < nx / kFixedRun * 4; ++it)
+      for (int dx = 0; dx < kTileX; ++dx)
+        bad += fixed_run_x((it >> 2) * kFixedRun + 4 * dx + (it & 3), nx) != it * kTileX + dx;
+  }
+  printf(bad ? "FAIL %d\n" : "OK\n", bad);
+  return bad != 0;
+}
+"""
+
+
+def test_fixed_runs(tmp_path):
+    """The stored order of the fixed bins is a permutation of each row, and
+    holds the bins where the sweep reads them."""
+    src, exe = tmp_path / "r.cpp", tmp_path / "r"
+    src.write_text(RUNS)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-I", CSRC, "-o", str(exe), str(src)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
 
 
 def test_planned_slabs(tmp_path):
