@@ -370,12 +370,13 @@ struct TimedLaunch {
   }
 };
 
-// The layout a hard-binned call prepares, and its path in the record of the
-// last preparation.
-int32_t call_gather(const mi_volume* m, int32_t n, int32_t flags) {
-  return hard_gather(m->lo, m->hi, n, (flags & MI_VOLUMES_UNCHANGED) != 0, (flags & MI_COMPACT_SLABS) != 0);
+// Whether a hard-binned call sweeps bricks, the layout it prepares, and its
+// path in the record of the last preparation.
+bool call_brick(int32_t flags, const HardTune& tune) { return (flags & MI_COMPACT_SLABS) && tune.block == 1024; }
+int32_t call_gather(const mi_volume* m, int32_t n, int32_t flags, const HardTune& tune) {
+  return hard_gather(desc(m), n, (flags & MI_VOLUMES_UNCHANGED) != 0, call_brick(flags, tune));
 }
-int hard_prep_path(int32_t gather) { return gather == kCopy16 ? 4 : 1; }
+int hard_prep_path(int32_t gather, bool brick) { return 8 + 2 * gather + (brick ? 1 : 0); }
 
 // Slabs per transform that keep one slab's share of the moving gather
 // volume near 1.5 MiB: the workgroups of an XCD sweep one slab for many
@@ -388,14 +389,15 @@ int64_t l2_slabs(size_t gather_volume_bytes) {
 }
 
 // Workgroups per transform for the histogram sweep.  The fixed volume is
-// swept in groups of 4 rows; a transform's groups are split into slabs:
+// swept in groups of 4 rows (bricks: rods); a transform's groups are split
+// into slabs:
 // planned_slabs' best count, in slab-major order at least as many as keep a
 // slab's moving footprint in an XCD's L2 (l2_slabs), a multiple of 8 (one
 // share per XCD), and -- with 16-bit packed LDS counters -- few enough voxels
 // per workgroup that no counter can exceed 65535.
 int plan_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins, bool packed,
-                const HardTune& tune, int32_t gather) {
-  const int64_t groups = (int64_t)((f->ny + 3) / 4) * f->nz;
+                const HardTune& tune, int32_t gather, bool brick) {
+  const int64_t groups = brick ? RodWalk::rods(f->nx, f->ny, f->nz) : (int64_t)((f->ny + 3) / 4) * f->nz;
   int64_t c;
   if (tune.chunks) {
     c = tune.chunks;
@@ -408,7 +410,7 @@ int plan_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, i
   }
   if (c > groups) c = groups;
   if (packed) {
-    const int64_t per = 65535 / (4 * (int64_t)f->nx);  // groups per workgroup
+    const int64_t per = 65535 / (brick ? 16 * kRodX : 4 * (int64_t)f->nx);  // groups per workgroup
     const int64_t need = (groups + per - 1) / per;
     if (c < need) c = need;
   }
@@ -492,7 +494,7 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   void* gvol = ws + L.gvol;
   // a sampled call always prepares (its list is not part of the record)
   if (smp || !reuse_prep(ctx, flags, prep_key(2, ws, L, fixed, moving, bins))) {
-    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, false, s)) != hipSuccess) return hip_fail(e, "prebin");
+    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, kVoxelOrder, s)) != hipSuccess) return hip_fail(e, "prebin");
     if ((e = launch_row_map(fb, voxels(fixed), bins, rows, s)) != hipSuccess) return hip_fail(e, "row map");
     if ((e = launch_tile_mask(fb, fixed->nx, fixed->ny, fixed->nz, (uint32_t*)(ws + L.tmask), s)) != hipSuccess)
       return hip_fail(e, "tile mask");
@@ -623,6 +625,8 @@ struct PairsPlan {
   std::vector<int64_t> fchunk_base, mchunk_base, t_base, xcd_base;  // xcd_base: [8][P+1]
   int64_t total_t = 0;
   bool oct8 = true;    // every moving range <= 256: 8-bit corners for all pairs
+  bool tiled = true;   // octs in tiles: every padded volume within the gathers' reach
+  int32_t gather() const { return (oct8 ? kOct8 : kOct16) | (tiled ? kTiled : 0); }
   bool packed = false;  // 16-bit LDS counters
 };
 
@@ -653,8 +657,8 @@ int plan_pairs(const mi_pair* pairs, int32_t n_pairs, int32_t bins, int32_t n_q,
     if (pr.n_transforms > 0 && !pr.transforms) return MI_ERR_NULL;
     // slabs of about tune.slab_voxels voxels (at most 65535 with 16-bit
     // counters), 8 or more, a multiple of 8
-    const int64_t groups = (int64_t)((pr.fixed.ny + 3) / 4) * pr.fixed.nz;
-    const int64_t gvox = 4 * (int64_t)pr.fixed.nx;
+    const int64_t groups = RodWalk::rods(pr.fixed.nx, pr.fixed.ny, pr.fixed.nz);
+    const int64_t gvox = 16 * kRodX;
     const int64_t target = packed ? std::min<int64_t>(65535, tune.slab_voxels) : tune.slab_voxels;
     int64_t per = target / gvox;
     if (per < 1) per = 1;
@@ -662,11 +666,7 @@ int plan_pairs(const mi_pair* pairs, int32_t n_pairs, int32_t bins, int32_t n_q,
     if (c < 8) c = 8;
     c = ((c + 7) / 8) * 8;
     plan.chunks[p] = (int32_t)c;
-    plan.fchunk_base[p + 1] =
-        plan.fchunk_base[p] + ((int64_t)voxels(&pr.fixed) + kPrepFixedChunk - 1) / kPrepFixedChunk;
-    const int64_t mplane = (int64_t)pr.moving.nx * pr.moving.ny;
-    plan.mchunk_base[p + 1] = plan.mchunk_base[p] + (mplane + kPrepPlaneRun - 1) / kPrepPlaneRun *
-                                                        ((pr.moving.nz + kPrepSlices - 1) / kPrepSlices);
+    plan.fchunk_base[p + 1] = plan.fchunk_base[p] + ((int64_t)voxels(&pr.fixed) + kPrepChunk - 1) / kPrepChunk;
     plan.t_base[p + 1] = plan.t_base[p] + pr.n_transforms;
     for (int x = 0; x < 8; ++x)
       plan.xcd_base[(size_t)x * (P + 1) + p + 1] =
@@ -701,12 +701,18 @@ int plan_pairs(const mi_pair* pairs, int32_t n_pairs, int32_t bins, int32_t n_q,
   w += align256(reduce_part_bytes(plan.total_t, bins, n_q));
   plan.oct8 = true;
   for (int p = 0; p < P; ++p) plan.oct8 = plan.oct8 && oct8_range(pairs[p].moving.lo, pairs[p].moving.hi);
+  plan.tiled = true;
+  for (int p = 0; p < P; ++p)
+    plan.tiled = plan.tiled && gather_volume_bytes(plan.gather(), pairs[p].moving.nx, pairs[p].moving.ny,
+                                                   pairs[p].moving.nz) <= kMaxGatherBytes;
   for (int p = 0; p < P; ++p) {
+    const mi_volume& mv = pairs[p].moving;
+    const size_t records = gather_volume_bytes(plan.gather(), mv.nx, mv.ny, mv.nz) / gather_record(plan.gather());
+    plan.mchunk_base[p + 1] = plan.mchunk_base[p] + (int64_t)((records + kPrepChunk - 1) / kPrepChunk);
     plan.fbins[p] = w;
     w += align256(voxels(&pairs[p].fixed));
     plan.gvol[p] = w;
-    const mi_volume& mv = pairs[p].moving;
-    w += align256(plan.oct8 ? oct8_volume_bytes(mv.nx, mv.ny, mv.nz) : oct_volume_bytes(mv.nx, mv.ny, mv.nz));
+    w += align256(gather_volume_bytes(plan.gather(), mv.nx, mv.ny, mv.nz));
   }
   plan.total = w;
   return MI_OK;
@@ -881,14 +887,13 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   hipError_t e;
   uint8_t* fb = (uint8_t*)(ws + L.fbins);
   void* gvol = ws + L.gvol;
-  const int32_t gather = call_gather(moving, smp ? kCopyTransforms + 1 : n, flags);  // samples: always octs
+  const bool brick = !smp && call_brick(flags, tune);
+  const int32_t gather = smp ? oct_gather(moving->lo, moving->hi) : call_gather(moving, n, flags, tune);
   const size_t bb = (size_t)bins * bins;
   // a sampled call always prepares (its list is not part of the record)
-  if (prepare && (smp || !reuse_prep(ctx, flags, prep_key(hard_prep_path(gather), ws, L, fixed, moving, bins)))) {
-    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, smp == nullptr, s)) != hipSuccess) return hip_fail(e, "prebin");
-    e = gather == kCopy16 ? launch_pack_copy(desc(moving), (uint16_t*)gvol, s)
-        : gather == kOct8 ? launch_pack_oct8(desc(moving), (uint2*)gvol, s)
-                          : launch_pack_octs(desc(moving), gather == kOctD, (uint4*)gvol, s);
+  if (prepare && (smp || !reuse_prep(ctx, flags, prep_key(hard_prep_path(gather, brick), ws, L, fixed, moving, bins)))) {
+    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, smp ? kVoxelOrder : (brick ? kCubeOrder : kRunOrder), s)) != hipSuccess) return hip_fail(e, "prebin");
+    e = launch_pack_moving(desc(moving), gather, gvol, s);
     if (e != hipSuccess) return hip_fail(e, "pack");
   }
   if ((e = launch_fill_u32(hist, bb * n, 0u, s)) != hipSuccess) return hip_fail(e, "fill");
@@ -906,7 +911,7 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   H.packed = use_packed(tune, bins) ? 1 : 0;
   H.block = tune.block;
   H.slab_major = tune.slab_major;
-  H.brick = (flags & MI_COMPACT_SLABS) ? 1 : 0;
+  H.brick = brick ? 1 : 0;
   uint2* list = (uint2*)(ws + L.list);
   unsigned long long* nlist = (unsigned long long*)(ws + L.nlist);
   if (smp) {
@@ -918,7 +923,7 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
     H.packed = bins > 128 ? 1 : 0;
     H.chunks = plan_sampled_chunks(ctx, expected_samples(fixed, *smp), n);
   } else {
-    H.chunks = plan_chunks(ctx, fixed, moving, n, bins, H.packed != 0, tune, gather);
+    H.chunks = plan_chunks(ctx, fixed, moving, n, bins, H.packed != 0, tune, gather, brick);
   }
   // one launch covers at most 2^31 - 1 workgroups: split the transforms
   int64_t per_launch = 0x7FFFFFFFll / H.chunks;
@@ -1105,7 +1110,12 @@ PairsTune pairs_tune_for(const mi_context* ctx, const mi_pair* pairs, int32_t n_
   const TuneKey k = pairs_tune_key(pairs, n_pairs, bins, flags);
   for (const auto& e : ctx->pairs_tuned)
     if (e.first == k) return e.second;
-  return PairsTune();
+  // 1024 threads where the table leaves room for fewer than four workgroups
+  // in a CU's LDS (as the sampled sweeps; 4 pairs of up to 256^3, 128 bins, 16
+  // transforms each: 943 -> 770 us of sweep)
+  PairsTune t;
+  if (4 * hist_lds_bytes(bins, bins > 128) > 160 * 1024) t.block = 1024;
+  return t;
 }
 
 // Key of a pairs preparation: every pair's volumes, bins, workspace, layout.
@@ -1143,7 +1153,7 @@ int run_pairs(mi_context* ctx, const mi_pair* pairs, int32_t n_pairs, int32_t bi
     d.transforms = pr.transforms;
     d.geo = geometry(&pr.fixed, &pr.moving);
     d.geom = make_hard_geom(desc(&pr.fixed), desc(&pr.moving), (const uint8_t*)(ws + plan.fbins[p]),
-                            (const void*)(ws + plan.gvol[p]), plan.oct8 ? kOct8 : kOct16, bins);  // one layout for the launch
+                            (const void*)(ws + plan.gvol[p]), plan.gather(), bins);  // one layout for the launch
     d.fdtype = pr.fixed.dtype;
     d.mdtype = pr.moving.dtype;
     d.flo = pr.fixed.lo;
@@ -1197,7 +1207,7 @@ int run_pairs(mi_context* ctx, const mi_pair* pairs, int32_t n_pairs, int32_t bi
   L.moving_chunks = plan.mchunk_base[P];
   L.clamp = (flags & MI_BOUNDARY_CLAMP) ? 1 : 0;
   L.packed = plan.packed ? 1 : 0;
-  L.oct8 = plan.oct8 ? 1 : 0;
+  L.gather = plan.gather();
   L.cu_count = ctx->cu_count;
   L.block = tune.block;
   const size_t bb = (size_t)bins * bins;
@@ -1410,16 +1420,18 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   }
   const bool was_timing = ctx->timing;
   ctx->timing = false;
-  // fixed bins and octs once
+  // fixed bins and moving volume, again when a candidate's layout differs
   st = launch_hard_hist(ctx, fixed, moving, transforms, n, bins, flags, hist, ws, L, s,
                         ctx->hard_default, true);
+  bool prepared_brick = call_brick(flags, ctx->hard_default);
   hipEvent_t t0 = nullptr, t1 = nullptr;
   if (st == MI_OK && ((e = hipEventCreate(&t0)) != hipSuccess || (e = hipEventCreate(&t1)) != hipSuccess))
     st = hip_fail(e, "tune events");
   HardTune best = ctx->hard_default;
   float best_ms = 3.4e38f;
   HardTune base = ctx->hard_default;
-  base.chunks = plan_chunks(ctx, fixed, moving, n, bins, use_packed(base, bins), base, call_gather(moving, n, flags));
+  base.chunks = plan_chunks(ctx, fixed, moving, n, bins, use_packed(base, bins), base, call_gather(moving, n, flags, base),
+                            call_brick(flags, base));
   const int32_t chunk_opts[3] = {base.chunks / 2, base.chunks, base.chunks * 2};
   // LDS counter layouts: u32 or packed 16-bit pairs (only packed fits above 128 bins)
   const int32_t n_layouts = bins > 128 ? 1 : 2;
@@ -1437,7 +1449,10 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
         float total = 0;
         for (int rep = 0; rep < 3 && st == MI_OK; ++rep) {
           if ((e = hipEventRecord(t0, s)) != hipSuccess) { st = hip_fail(e, "tune"); break; }
-          st = launch_hard_hist(ctx, fixed, moving, transforms, n, bins, flags, hist, ws, L, s, cand, false);
+          const bool prepare = rep == 0 && call_brick(flags, cand) != prepared_brick;  // the first run is not timed
+          if (prepare) ctx->last_prep.clear();
+          st = launch_hard_hist(ctx, fixed, moving, transforms, n, bins, flags, hist, ws, L, s, cand, prepare);
+          prepared_brick = call_brick(flags, cand);
           if (st != MI_OK) break;
           if ((e = hipEventRecord(t1, s)) != hipSuccess || (e = hipEventSynchronize(t1)) != hipSuccess) {
             st = hip_fail(e, "tune");
@@ -1540,7 +1555,9 @@ int mi_eval(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   key_q(key, q, n_q);
   st = graph_run(ctx, key, s, body);
   // the graph prepared them
-  ctx->last_prep = prep_key(parzen ? 2 : hard_prep_path(call_gather(moving, n, run_flags)), ws, L, fixed, moving, bins);
+  const HardTune tune = tune_for(ctx, fixed, moving, n, bins, flags);
+  const int path = parzen ? 2 : hard_prep_path(call_gather(moving, n, run_flags, tune), call_brick(run_flags, tune));
+  ctx->last_prep = prep_key(path, ws, L, fixed, moving, bins);
   return st;
 }
 

@@ -221,92 +221,16 @@ __device__ __forceinline__ void block_work(int32_t chunks, int32_t n, int32_t ba
   }
 }
 
-// The same walk in brick order: the row groups of a slice are cut along y
-// into blocks of `yb` groups and a block is visited slice by slice before
-// the next, so a slab -- a contiguous range of that numbering -- is a brick
-// of whole x rows, about as many rows deep (4 yb) as slices long.  A thin
-// slab of whole slices leaves its moving footprint under a small change of
-// rotation; a brick keeps much of it, so the transforms a slab meets in turn
-// reuse the XCD's L2 when they rotate widely (a rotation map).  Row
-// coordinates stay exact: stepped by kTileY M[:,1] inside a block row and
-// recomputed at each wrap.
-struct GroupWalkBrick {
-  int64_t g, g1;
-  int32_t j0, k;
-  int32_t G, nz, yb, b0, b1;  // y groups, slices, block width, current block [b0, b1)
-  int64_t r[3], lane_off[3], step[3], adv[3], m1[3], m2[3], m3[3];
-
-  __host__ __device__ __forceinline__ void init(const int64_t* Mq, int32_t fny, int32_t fnz,
-                                                int32_t chunks, uint32_t chunk, int wave, int nwaves,
-                                                int dx, int dy) {
-    G = (fny + kTileY - 1) / kTileY;
-    nz = fnz;
-    const int64_t groups = (int64_t)G * fnz;
-    const int64_t s0 = groups * chunk / chunks, s1 = groups * (chunk + 1) / chunks;
-    g = s0 + (s1 - s0) * wave / nwaves;
-    g1 = s0 + (s1 - s0) * (wave + 1) / nwaves;
-    // bricks of 4 yb rows by per_slab / yb slices, twice as many rows as
-    // slices (yb = sqrt(per_slab / 2)): on a 51^3 rotation map of a
-    // 256x256x180 volume 4.61 s, against 5.53 s for square bricks and
-    // 5.3-6.1 s for other widths
-    const int64_t per_slab = (groups + chunks - 1) / chunks;
-    const int32_t w = (int32_t)sqrt((double)per_slab * 0.5);
-    yb = w < 1 ? 1 : (w > G ? G : w);
-    const int64_t full = G / yb, per_full = (int64_t)yb * fnz;
-    b0 = 0;
-    b1 = G;
-    k = 0;
-    j0 = 0;
-    if (g < g1) {
-      if (g < full * per_full) {
-        const int64_t blk = g / per_full, rem = g - blk * per_full;
-        b0 = (int32_t)blk * yb;
-        b1 = b0 + yb;
-        k = (int32_t)(rem / yb);
-        j0 = (b0 + (int32_t)(rem - (int64_t)k * yb)) * kTileY;
-      } else {  // the last, narrower block (G not a multiple of yb)
-        const int64_t rem = g - full * per_full;
-        b0 = (int32_t)full * yb;
-        const int32_t bw = G - b0;
-        k = (int32_t)(rem / bw);
-        j0 = (b0 + (int32_t)(rem - (int64_t)k * bw)) * kTileY;
-      }
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int64_t m0 = Mq[4 * a];
-      m1[a] = Mq[4 * a + 1];
-      m2[a] = Mq[4 * a + 2];
-      m3[a] = Mq[4 * a + 3];
-      r[a] = m1[a] * j0 + m2[a] * k + m3[a];
-      lane_off[a] = m0 * dx + m1[a] * dy;
-      step[a] = m0 * kTileX;
-      adv[a] = m1[a] * kTileY;
-    }
-  }
-
-  __host__ __device__ __forceinline__ void next() {
-    ++g;
-    j0 += kTileY;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) r[a] += adv[a];
-    if (j0 >= b1 * kTileY) {
-      j0 = b0 * kTileY;
-      if (++k >= nz) {
-        k = 0;
-        b0 = b1;
-        b1 = b1 + yb < G ? b1 + yb : G;
-        j0 = b0 * kTileY;
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a) r[a] = m1[a] * j0 + m2[a] * k + m3[a];
-    }
-  }
+// Host-side launch descriptions.
+struct VolumeDesc {
+  const void* data;
+  int32_t nx, ny, nz, dtype;
+  double lo, hi;
 };
 
 // Geometry of one fixed/moving pair for the hard-binned sweep.
 struct HardGeom {
-  const uint8_t* fbins;  // fixed bins, [fnz][fny][fnx], rows in the order fixed_run_x
+  const uint8_t* fbins;  // fixed bins, [fnz][fny][fnx], rows in the sweep's FixedOrder
   const void* gvol;      // moving gather volume in layout `gather`
   int32_t fnx, fny, fnz;
   int32_t mnx, mny, mnz;
@@ -317,16 +241,10 @@ struct HardGeom {
   Divider div;   // floor(X / R) for the exact fallback
 };
 
-// Host-side launch descriptions.
-struct VolumeDesc {
-  const void* data;
-  int32_t nx, ny, nz, dtype;
-  double lo, hi;
-};
 
 struct HardLaunch {
   const double* transforms;  // [n][12]
-  const uint8_t* fbins;      // fixed-volume bins, [fnz][fny][fnx], rows in the order fixed_run_x
+  const uint8_t* fbins;      // fixed-volume bins, [fnz][fny][fnx], rows in the sweep's FixedOrder
   const void* gvol;          // moving gather volume in layout `gather` (Gather)
   VolumeDesc fixed, moving;
   uint32_t* hist;  // [n][B][B]
@@ -336,7 +254,7 @@ struct HardLaunch {
   int32_t packed;  // 1: two 16-bit counters per LDS word (bins > 128)
   int32_t block;   // threads per workgroup: 256, 512 or 1024
   int32_t slab_major;  // workgroup order: 1 slab-major, 0 transform-major
-  int32_t brick;       // 1: slabs as bricks (GroupWalkBrick; 1024-thread launches)
+  int32_t brick;       // 1: slabs as bricks of rods (RodWalk; 1024-thread launches)
   // processing order (launch_order_transforms), or NULL: the workgroups of
   // slot t sweep transform order[t] - order_t0; order_t0 is the batch index
   // of this launch's first transform
@@ -392,12 +310,16 @@ inline size_t moving_copy_bytes(int32_t nx, int32_t ny, int32_t nz) {
 // row's difference and negated sum, from which a signed dot product forms the
 // exact x-lerp in one instruction instead of two; octs of 8-bit corners; the
 // plain copy.
-enum Gather : int32_t { kOct16 = 0, kOct8 = 1, kCopy16 = 2, kOctD = 3 };
+// kTiled (brick sweeps): octs in tiles (tiled_index).
+enum Gather : int32_t { kOct16 = 0, kOct8 = 1, kCopy16 = 2, kOctD = 3, kTiled = 4 };
+__host__ __device__ constexpr int32_t gather_base(int32_t gather) { return gather & 3; }
 __host__ __device__ constexpr int32_t gather_record(int32_t gather) {
-  return gather == kOct8 ? 8 : (gather == kCopy16 ? 2 : 16);
+  return gather_base(gather) == kOct8 ? 8 : (gather == kCopy16 ? 2 : 16);
 }
 inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_t nz) {
-  return gather == kCopy16 ? moving_copy_bytes(nx, ny, nz) : (size_t)nx * ny * nz * gather_record(gather);
+  if (gather == kCopy16) return moving_copy_bytes(nx, ny, nz);
+  const bool rec8 = gather_base(gather) == kOct8;
+  return (gather & kTiled ? tiled_records(nx, ny, nz, rec8) : (size_t)nx * ny * nz) * gather_record(gather);
 }
 // A gather instruction costs the texture unit about the same whatever its
 // width, so a sweep over an oct volume (one gather per voxel) runs twice as
@@ -409,9 +331,15 @@ inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_
 // and 97, four 257 and 229, six 328 and 338; 128^3 u8, 64 bins, four 66 and
 // 65, six 80 and 86).
 constexpr int32_t kCopyTransforms = 4;
-inline int32_t hard_gather(double lo, double hi, int32_t n, bool reused, bool brick) {
-  if (n <= kCopyTransforms && !reused && !brick) return kCopy16;
+inline int32_t oct_gather(double lo, double hi) {
   return oct8_range(lo, hi) ? kOct8 : (hi - lo < 16384.0 ? kOctD : kOct16);
+}
+inline int32_t hard_gather(const VolumeDesc& m, int32_t n, bool reused, bool brick) {
+  if (n <= kCopyTransforms && !reused && !brick) return kCopy16;
+  // tiles where they need no padding: the workspace's region is the octs'
+  const int32_t oct = oct_gather(m.lo, m.hi);
+  const bool fits = tiled_records(m.nx, m.ny, m.nz, oct == kOct8) == (size_t)m.nx * m.ny * m.nz;
+  return brick && fits ? oct | kTiled : oct;
 }
 
 // Bytes of the 16-bit quad volume of an integer moving volume on the Parzen
@@ -571,11 +499,16 @@ hipError_t launch_compose(const double* P, int64_t n, const Geometry& g, double*
 // G_P[r][3] = G_M[r][3] / msp[r].
 hipError_t launch_grad_physical(double* grad, int64_t rows, const Geometry& g, hipStream_t s);
 hipError_t launch_fill_f64(double* p, size_t n, hipStream_t s);
-// sweep_order: the bins in the order the hard sweeps read (fixed_run_x), else
-// in voxel order.
-hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, bool sweep_order, hipStream_t s);
-hipError_t launch_pack_octs(const VolumeDesc& m, bool differences, uint4* out, hipStream_t s);
-hipError_t launch_pack_oct8(const VolumeDesc& m, uint2* out, hipStream_t s);
+// The order of a fixed volume's bins: voxel order, or that the thin-slab
+// (fixed_run_x) or brick (cube_run_x) sweeps read.
+enum FixedOrder : int32_t { kVoxelOrder = 0, kRunOrder = 1, kCubeOrder = 2 };
+template <int ORDER>
+__host__ __device__ constexpr int32_t stored_x(int32_t p, int32_t nx) {
+  return ORDER == kRunOrder ? fixed_run_x(p, nx) : (ORDER == kCubeOrder ? cube_run_x(p, nx) : p);
+}
+hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, FixedOrder order, hipStream_t s);
+// The moving volume in layout `gather`.
+hipError_t launch_pack_moving(const VolumeDesc& m, int32_t gather, void* out, hipStream_t s);
 hipError_t launch_pack_copy(const VolumeDesc& m, uint16_t* out, hipStream_t s);
 hipError_t launch_pack_copy_f32(const VolumeDesc& m, float* out, hipStream_t s);
 hipError_t launch_hist_hard(const HardLaunch& L, hipStream_t s);
@@ -600,17 +533,15 @@ struct PairDesc {
   int32_t n_t, chunks;       // transforms, slabs (a multiple of 8)
 };
 
-// Pairs' preparation, one wave per item: fixed volumes in chunks of
-// consecutive voxels (16 per lane); moving volumes in runs of kPrepPlaneRun
-// voxels of an xy plane (two per lane) through blocks of kPrepSlices slices.
-constexpr int kPrepFixedLane = 16, kPrepFixedChunk = 64 * kPrepFixedLane;
-constexpr int kPrepPlaneRun = 128, kPrepSlices = 8;
+// Pairs' preparation, one wave per item: chunks of consecutive stored bytes
+// of a fixed volume, of consecutive records of a moving volume (16 per lane).
+constexpr int kPrepLane = 16, kPrepChunk = 64 * kPrepLane;
 
 struct PairsArgs {
   const PairDesc* pairs;
   int32_t n_pairs;
-  const int64_t* fchunk_base;  // [P+1] prefix of kPrepFixedChunk-voxel chunks of the fixed volumes
-  const int64_t* mchunk_base;  // [P+1] prefix of (plane run, slice block) items of the moving volumes
+  const int64_t* fchunk_base;  // [P+1] prefix of kPrepChunk-voxel chunks of the fixed volumes
+  const int64_t* mchunk_base;  // [P+1] prefix of kPrepChunk-record chunks of the moving volumes
   const int64_t* t_base;     // [P+1] prefix of transforms
   const int64_t* xcd_base;   // [8][P+1] prefix of work items per XCD
   unsigned long long* counters;  // [8] work-queue heads
@@ -625,7 +556,7 @@ struct PairsLaunch {
   int64_t total_t, fixed_chunks, moving_chunks;
   int32_t clamp, packed, cu_count;
   int32_t block;  // threads per workgroup of the sweep: 256, 512 or 1024
-  int32_t oct8;  // every pair's moving volume packed with 8-bit corners
+  int32_t gather;  // layout of every pair's moving volume
 };
 
 // The transforms gathered and composed; with `volumes` also the pairs'

@@ -120,12 +120,12 @@ hipError_t launch_fill_f64(double* p, size_t n, hipStream_t s) {
 // fixed-volume binning, once per call
 // ---------------------------------------------------------------------------
 
-// The bins in voxel order, or (SWEEP) in the order the hard sweeps read them
-// (fixed_run_x), four stored bytes of a row per thread.
-template <bool SWEEP, typename F>
+// The bins in voxel order, or in the order a hard sweep reads them
+// (FixedOrder), four stored bytes of a row per thread.
+template <int ORDER, typename F>
 __device__ __forceinline__ void prebin(int32_t nx, uint32_t rows, uint8_t* __restrict__ out, F&& bin) {
   const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
-  if (!SWEEP) {
+  if (ORDER == kVoxelOrder) {
     const uint32_t nvox = rows * (uint32_t)nx;  // < 2^28
     for (uint32_t i = i0; i < nvox; i += step) out[i] = (uint8_t)bin(i);
     return;
@@ -136,7 +136,7 @@ __device__ __forceinline__ void prebin(int32_t nx, uint32_t rows, uint8_t* __res
     uint32_t b[4];
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k)
-      b[k] = p0 + k < (uint32_t)nx ? bin(base + (uint32_t)fixed_run_x((int32_t)(p0 + k), nx)) : 0u;
+      b[k] = p0 + k < (uint32_t)nx ? bin(base + (uint32_t)stored_x<ORDER>((int32_t)(p0 + k), nx)) : 0u;
     if (((base + p0) & 3) == 0 && p0 + 4 <= (uint32_t)nx) {
       *(uint32_t*)(out + base + p0) = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
     } else {
@@ -145,49 +145,53 @@ __device__ __forceinline__ void prebin(int32_t nx, uint32_t rows, uint8_t* __res
   }
 }
 
-template <bool SWEEP, typename T>
+template <int ORDER, typename T>
 __global__ __launch_bounds__(256) void prebin_int_kernel(const T* __restrict__ u, int32_t nx, uint32_t rows, int32_t lo,
                                                          int32_t hi, uint32_t bins, Divider div,
                                                          uint8_t* __restrict__ out) {
-  prebin<SWEEP>(nx, rows, out, [&](uint32_t i) { return fixed_bin_int((int32_t)u[i], lo, hi, bins, div); });
+  prebin<ORDER>(nx, rows, out, [&](uint32_t i) { return fixed_bin_int((int32_t)u[i], lo, hi, bins, div); });
 }
 
-template <bool SWEEP>
+template <int ORDER>
 __global__ __launch_bounds__(256) void prebin_f32_kernel(const float* __restrict__ u, int32_t nx, uint32_t rows,
                                                          double lo, double hi, int32_t bins,
                                                          uint8_t* __restrict__ out) {
-  prebin<SWEEP>(nx, rows, out, [&](uint32_t i) { return fixed_bin_real((double)u[i], lo, hi, bins); });
+  prebin<ORDER>(nx, rows, out, [&](uint32_t i) { return fixed_bin_real((double)u[i], lo, hi, bins); });
 }
 
-template <bool SWEEP>
+template <int ORDER>
 static hipError_t prebin_variant(const VolumeDesc& f, int bins, uint8_t* out, hipStream_t s) {
   const size_t nvox = (size_t)f.nx * f.ny * f.nz;
   const uint32_t rows = (uint32_t)f.ny * (uint32_t)f.nz;
-  const unsigned grid = fill_grid(SWEEP ? (size_t)rows * ((f.nx + 3) / 4) : nvox);
+  const unsigned grid = fill_grid(ORDER != kVoxelOrder ? (size_t)rows * ((f.nx + 3) / 4) : nvox);
   const int32_t lo = (int32_t)f.lo, hi = (int32_t)f.hi;
   const Divider d = f.dtype == 3 ? Divider{0, 0} : make_divider((uint32_t)(hi - lo + 1));
   switch (f.dtype) {
   case 0:
-    hipLaunchKernelGGL((prebin_int_kernel<SWEEP, uint8_t>), dim3(grid), dim3(256), 0, s, (const uint8_t*)f.data, f.nx,
+    hipLaunchKernelGGL((prebin_int_kernel<ORDER, uint8_t>), dim3(grid), dim3(256), 0, s, (const uint8_t*)f.data, f.nx,
                        rows, lo, hi, (uint32_t)bins, d, out);
     break;
   case 1:
-    hipLaunchKernelGGL((prebin_int_kernel<SWEEP, uint16_t>), dim3(grid), dim3(256), 0, s, (const uint16_t*)f.data, f.nx,
+    hipLaunchKernelGGL((prebin_int_kernel<ORDER, uint16_t>), dim3(grid), dim3(256), 0, s, (const uint16_t*)f.data, f.nx,
                        rows, lo, hi, (uint32_t)bins, d, out);
     break;
   case 2:
-    hipLaunchKernelGGL((prebin_int_kernel<SWEEP, int16_t>), dim3(grid), dim3(256), 0, s, (const int16_t*)f.data, f.nx,
+    hipLaunchKernelGGL((prebin_int_kernel<ORDER, int16_t>), dim3(grid), dim3(256), 0, s, (const int16_t*)f.data, f.nx,
                        rows, lo, hi, (uint32_t)bins, d, out);
     break;
   default:
-    hipLaunchKernelGGL((prebin_f32_kernel<SWEEP>), dim3(grid), dim3(256), 0, s, (const float*)f.data, f.nx, rows, f.lo,
+    hipLaunchKernelGGL((prebin_f32_kernel<ORDER>), dim3(grid), dim3(256), 0, s, (const float*)f.data, f.nx, rows, f.lo,
                        f.hi, bins, out);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, bool sweep_order, hipStream_t s) {
-  return sweep_order ? prebin_variant<true>(f, bins, out, s) : prebin_variant<false>(f, bins, out, s);
+hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, FixedOrder order, hipStream_t s) {
+  switch (order) {
+  case kRunOrder: return prebin_variant<kRunOrder>(f, bins, out, s);
+  case kCubeOrder: return prebin_variant<kCubeOrder>(f, bins, out, s);
+  default: return prebin_variant<kVoxelOrder>(f, bins, out, s);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -246,7 +250,7 @@ __global__ void pack_oct8_kernel(const T* __restrict__ v, int32_t nx, int32_t ny
   }
 }
 
-hipError_t launch_pack_oct8(const VolumeDesc& m, uint2* out, hipStream_t s) {
+static hipError_t launch_pack_oct8(const VolumeDesc& m, uint2* out, hipStream_t s) {
   const dim3 grid((unsigned)((m.nx + 255) / 256), (unsigned)m.ny, (unsigned)m.nz);
   const int32_t lo = (int32_t)m.lo, hi = (int32_t)m.hi;
   if (m.dtype == 0)
@@ -281,8 +285,54 @@ static hipError_t pack_octs_variant(const VolumeDesc& m, uint4* out, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_pack_octs(const VolumeDesc& m, bool differences, uint4* out, hipStream_t s) {
-  return differences ? pack_octs_variant<true>(m, out, s) : pack_octs_variant<false>(m, out, s);
+// Octs in tiles (tiled_index), one record per thread: records of a tile are
+// neighbours in memory, so the stores are whole lines and the reads of a
+// tile's eight or sixteen records mostly hit the same ones (256x256x180 u16:
+// 88 us against 36 for rows of octs, which a map of rotations repays in one
+// transform of its hundreds).
+template <typename T, int BASE>
+__global__ __launch_bounds__(256) void pack_tiled_kernel(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz,
+                                                         int32_t lo, int32_t hi, void* __restrict__ out) {
+  constexpr uint32_t kx = BASE == kOct8 ? 4 : 2;  // tile width
+  const uint32_t n = (uint32_t)nx * (uint32_t)ny * (uint32_t)nz;  // < 2^28
+  auto c = [&](uint32_t i) -> uint32_t { return clamp_offset((int32_t)v[i], lo, hi); };
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const uint32_t tile = i / (4 * kx), low = i - tile * (4 * kx);
+    const uint32_t tr = tile / ((uint32_t)nx / kx), tz = tr / ((uint32_t)ny / 2);
+    const uint32_t x = (tile - tr * ((uint32_t)nx / kx)) * kx + low % kx;
+    const uint32_t y = (tr - tz * ((uint32_t)ny / 2)) * 2 + low / kx % 2, z = 2 * tz + low / (2 * kx);
+    const uint32_t a = (z * (uint32_t)ny + y) * (uint32_t)nx + x;
+    const uint32_t dx = x + 1 < (uint32_t)nx ? 1 : 0, dy = y + 1 < (uint32_t)ny ? (uint32_t)nx : 0;
+    const uint32_t dz = z + 1 < (uint32_t)nz ? (uint32_t)nx * (uint32_t)ny : 0;
+    if (BASE == kOct8) {
+      ((uint2*)out)[i] = make_uint2(c(a) | (c(a + dx) << 8) | (c(a + dy) << 16) | (c(a + dy + dx) << 24),
+                                    c(a + dz) | (c(a + dz + dx) << 8) | (c(a + dz + dy) << 16) | (c(a + dz + dy + dx) << 24));
+    } else {
+      auto pair = [&](uint32_t r) -> uint32_t {
+        const uint32_t v0 = c(r), v1 = c(r + dx);
+        return BASE == kOctD ? ((0u - v0 - v1) & 0xFFFFu) | ((v1 - v0) << 16) : v0 | (v1 << 16);
+      };
+      ((uint4*)out)[i] = make_uint4(pair(a), pair(a + dy), pair(a + dz), pair(a + dz + dy));
+    }
+  }
+}
+
+template <int BASE>
+static hipError_t pack_tiled_variant(const VolumeDesc& m, void* out, hipStream_t s) {
+  const unsigned grid = fill_grid((size_t)m.nx * m.ny * m.nz);
+  const int32_t lo = (int32_t)m.lo, hi = (int32_t)m.hi;
+  if (m.dtype == 0)
+    hipLaunchKernelGGL((pack_tiled_kernel<uint8_t, BASE>), dim3(grid), dim3(256), 0, s, (const uint8_t*)m.data, m.nx,
+                       m.ny, m.nz, lo, hi, out);
+  else if (m.dtype == 1)
+    hipLaunchKernelGGL((pack_tiled_kernel<uint16_t, BASE>), dim3(grid), dim3(256), 0, s, (const uint16_t*)m.data, m.nx,
+                       m.ny, m.nz, lo, hi, out);
+  else if (m.dtype == 2)
+    hipLaunchKernelGGL((pack_tiled_kernel<int16_t, BASE>), dim3(grid), dim3(256), 0, s, (const int16_t*)m.data, m.nx,
+                       m.ny, m.nz, lo, hi, out);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 // out[i] = clamp(v[i], lo, hi) - lo as 16 bits (moving_copy_bytes), 8 voxels
@@ -316,6 +366,19 @@ hipError_t launch_pack_copy(const VolumeDesc& m, uint16_t* out, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t launch_pack_moving(const VolumeDesc& m, int32_t gather, void* out, hipStream_t s) {
+  switch (gather) {
+  case kOct16: return pack_octs_variant<false>(m, (uint4*)out, s);
+  case kOctD: return pack_octs_variant<true>(m, (uint4*)out, s);
+  case kOct8: return launch_pack_oct8(m, (uint2*)out, s);
+  case kCopy16: return launch_pack_copy(m, (uint16_t*)out, s);
+  case kOct16 | kTiled: return pack_tiled_variant<kOct16>(m, out, s);
+  case kOctD | kTiled: return pack_tiled_variant<kOctD>(m, out, s);
+  case kOct8 | kTiled: return pack_tiled_variant<kOct8>(m, out, s);
+  default: return hipErrorInvalidValue;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // the histogram sweep
 // ---------------------------------------------------------------------------
@@ -338,7 +401,7 @@ struct HardArgs {
 // scratch) so that two of them, 8 waves per SIMD, share a CU next to two
 // 64 KiB LDS histograms; the sweep waits on its gathers and gains from the
 // extra waves.  Smaller workgroups keep their registers.
-// BRICK: slabs as bricks (GroupWalkBrick) rather than thin slabs.
+// BRICK: slabs as bricks (sweep_rods) rather than thin slabs.
 template <bool CLAMP, bool PACKED, int GL, int NT, bool BRICK = false>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 ? 8 : 1)))
 void hist_hard_kernel(HardArgs a) {
@@ -353,8 +416,8 @@ void hist_hard_kernel(HardArgs a) {
   const bool ok = quantize_transform_wave(Md, Mq);
   __syncthreads();
   if (ok) {
-    if (BRICK)  // bricks keep the per-voxel test (row ranges measured 0.7% slower on rotation maps)
-      sweep_hard<CLAMP, PACKED, GL, NT / 64, GroupWalkBrick, false>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
+    if (BRICK)
+      sweep_rods<CLAMP, PACKED, GL, NT / 64>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
     else
       sweep_hard<CLAMP, PACKED, GL, NT / 64>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
   }
@@ -451,9 +514,17 @@ static hipError_t launch_nt(const HardArgs& a, int n, bool clamp, bool packed, s
   case kOct8: return launch_layout<kOct8, NT, BRICK>(a, n, clamp, packed, lds, s);
   case kOctD: return launch_layout<kOctD, NT, BRICK>(a, n, clamp, packed, lds, s);
   case kOct16: return launch_layout<kOct16, NT, BRICK>(a, n, clamp, packed, lds, s);
-  default:
-    if constexpr (BRICK) return hipErrorInvalidValue;  // the copy serves thin slabs only
-    else return launch_layout<kCopy16, NT, BRICK>(a, n, clamp, packed, lds, s);
+  }
+  if constexpr (BRICK) {  // tiles serve bricks only, the copy thin slabs only
+    switch (a.geom.gather) {
+    case kOct8 | kTiled: return launch_layout<kOct8 | kTiled, NT, BRICK>(a, n, clamp, packed, lds, s);
+    case kOctD | kTiled: return launch_layout<kOctD | kTiled, NT, BRICK>(a, n, clamp, packed, lds, s);
+    case kOct16 | kTiled: return launch_layout<kOct16 | kTiled, NT, BRICK>(a, n, clamp, packed, lds, s);
+    default: return hipErrorInvalidValue;
+    }
+  } else {
+    return a.geom.gather == kCopy16 ? launch_layout<kCopy16, NT, BRICK>(a, n, clamp, packed, lds, s)
+                                    : hipErrorInvalidValue;
   }
 }
 
@@ -609,7 +680,10 @@ hipError_t configure_hard_kernels() {
   if ((e = allow_big_lds_nt<1024>()) != hipSuccess) return e;
   if ((e = allow_big_lds<kOct16, 1024, true>()) != hipSuccess) return e;
   if ((e = allow_big_lds<kOctD, 1024, true>()) != hipSuccess) return e;
-  return allow_big_lds<kOct8, 1024, true>();
+  if ((e = allow_big_lds<kOct8, 1024, true>()) != hipSuccess) return e;
+  if ((e = allow_big_lds<kOct16 | kTiled, 1024, true>()) != hipSuccess) return e;
+  if ((e = allow_big_lds<kOctD | kTiled, 1024, true>()) != hipSuccess) return e;
+  return allow_big_lds<kOct8 | kTiled, 1024, true>();
 }
 
 // ---------------------------------------------------------------------------

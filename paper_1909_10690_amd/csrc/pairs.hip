@@ -9,18 +9,19 @@
 // transform into its LDS histogram, adds the histogram into the
 // transform's HBM histogram and clears it.  Items are ordered pair-major,
 // then slab-major, so the workgroups of an XCD work on one slab of one pair
-// at a time and share its moving footprint in L2.  A slab is a brick of
-// whole x rows (GroupWalkBrick): the footprints of a pair's transforms on a
-// compact brick overlap more than on a thin slab of whole slices, whose
-// rotated images spread over many moving slices (16 rigid transforms of
-// +-10 degrees: 23.1 -> 21.8 ms, the L2 misses being the sweep's limit).
+// at a time and share its moving footprint in L2.  A slab is a compact brick
+// of rods (RodWalk), swept as sweep_rods has it.  What bounds the sweep is
+// the vector unit, at about 46 instructions a wave step of 64 samples, with
+// the L1's line fills behind: 24 pairs of 64^3 to 256^3 voxels, 16 rigid
+// transforms each, 64 bins: 2068 us a sweep with bricks of whole x rows over
+// untiled octs, 2283 with rods over untiled octs, 1885 with rods over tiles.
 // Every workgroup leaves the loop once its queue is empty, so the grid
 // always drains.
 //
-// Per-pair fixed bins and moving oct volumes are prepared by two kernels
-// over the items of all pairs (runs of 1024 consecutive fixed voxels; runs
-// of 128 voxels of a moving xy plane through 8 slices), one wave per item,
-// and the transforms are gathered into one array for the MI reduction.
+// Per-pair fixed bins and moving octs are prepared by two kernels over the
+// items of all pairs (runs of 1024 stored bytes, runs of 1024 records), one
+// wave per item, and the transforms are gathered into one array for the MI
+// reduction.
 #include "common.h"
 #include "sweep.h"
 
@@ -43,6 +44,7 @@ __device__ __forceinline__ int find_pair(const int64_t* __restrict__ base, int P
 // table, so without the address space the compiler would use flat accesses.
 typedef const __attribute__((address_space(1))) uint16_t global_u16;
 typedef const __attribute__((address_space(1))) int16_t global_i16;
+typedef const __attribute__((address_space(1))) uint4_t global_cu4;
 typedef const __attribute__((address_space(1))) float global_f32;
 typedef __attribute__((address_space(1))) uint8_t global_out8;
 typedef __attribute__((address_space(1))) uint32_t global_out32;
@@ -119,37 +121,39 @@ __device__ __forceinline__ void for_each_item(const PairDesc* __restrict__ pairs
   }
 }
 
-// Fixed bins of every pair in the sweep's order (fixed_run_x), one wave per
-// chunk of kPrepFixedChunk consecutive stored bytes of a pair's fixed volume:
+// Fixed bins of every pair in the sweep's order (cube_run_x), one wave per
+// chunk of kPrepChunk consecutive stored bytes of a pair's fixed volume:
 // every lane busy whatever the row length.  Rows of whole runs (nx a multiple
-// of 64) and full chunks of a u8 volume are handled a run at a time, four
-// stored bytes per lane; otherwise lane l takes bytes l, l + 64, ...
+// of 16) and full chunks of an aligned u8 volume are handled a run per lane,
+// in 16-byte accesses; otherwise lane l takes bytes l, l + 64, ...
 __global__ void prep_fixed_kernel(PairsArgs a, int64_t chunks) {
   for_each_item(a.pairs, a.fchunk_base, a.n_pairs, chunks, [&](const PairDesc& d, int64_t c, int lane) {
     const int64_t nvox = (int64_t)d.geom.fnx * d.geom.fny * d.geom.fnz;
-    const int64_t c0 = c * kPrepFixedChunk;
+    const int64_t c0 = c * kPrepChunk;
     global_out8* __restrict__ out = (global_out8*)d.geom.fbins;
     auto bin8 = [&](uint32_t u) {
       return fixed_bin_int((int32_t)u, (int32_t)d.flo, (int32_t)d.fhi, (uint32_t)d.geom.bins, d.fdiv);
     };
-    if (d.fdtype == 0 && d.geom.fnx % kFixedRun == 0 && c0 + kPrepFixedChunk <= nvox) {
-      global_u8* __restrict__ src = (global_u8*)d.fixed + c0;
-      uint32_t v[kPrepFixedLane];
+    if (d.fdtype == 0 && d.geom.fnx % kCubeRun == 0 && c0 + kPrepChunk <= nvox &&
+        (((uintptr_t)d.fixed | (uintptr_t)out) & 15) == 0) {
+      const uint4_t v = *(global_cu4*)((global_u8*)d.fixed + c0 + kPrepLane * lane);
+      uint4_t o;
 #pragma unroll
-      for (int k = 0; k < kPrepFixedLane; ++k)  // all loads before the first store
-        v[k] = src[256 * (k >> 2) + kFixedRun * (lane >> 4) + kTileX * (k & 3) + (lane & 15)];
+      for (int j = 0; j < 4; ++j) {  // stored word j: byte j of each of the run's four words
+        uint32_t b = 0;
 #pragma unroll
-      for (int k = 0; k < kPrepFixedLane / 4; ++k)
-        *(global_out32*)(out + c0 + 256 * k + 4 * lane) =
-            bin8(v[4 * k]) | (bin8(v[4 * k + 1]) << 8) | (bin8(v[4 * k + 2]) << 16) | (bin8(v[4 * k + 3]) << 24);
+        for (int k = 0; k < 4; ++k) b |= bin8((v[k] >> (8 * j)) & 0xFFu) << (8 * k);
+        o[j] = b;
+      }
+      *(global_out4*)(out + c0 + kPrepLane * lane) = o;
       return;
     }
     const uint32_t nx = (uint32_t)d.geom.fnx;
-    for (int k = 0; k < kPrepFixedLane; ++k) {
+    for (int k = 0; k < kPrepLane; ++k) {
       const int64_t p = c0 + lane + 64 * k;
       if (p >= nvox) break;
       const uint32_t row = (uint32_t)p / nx;  // nvox < 2^28
-      const size_t v = (size_t)row * nx + (size_t)fixed_run_x((int32_t)((uint32_t)p - row * nx), (int32_t)nx);
+      const size_t v = (size_t)row * nx + (size_t)cube_run_x((int32_t)((uint32_t)p - row * nx), (int32_t)nx);
       uint32_t b;
       if (d.fdtype == 3)
         b = fixed_bin_real((double)((global_f32*)d.fixed)[v], d.flo, d.fhi, d.geom.bins);
@@ -162,95 +166,101 @@ __global__ void prep_fixed_kernel(PairsArgs a, int64_t chunks) {
 }
 
 // Moving oct volumes of every pair, with the layout and clamping of the
-// single-pair path.  An item is a run of kPrepPlaneRun voxels of an xy
-// plane through a block of kPrepSlices consecutive slices: lane l takes
-// plane voxels 2l and 2l + 1 of the run at every slice of the block.  The
-// lane loads the source rows y and y + 1 of each slice of the block and of
-// the one after it once, all before its first store, and the entries of
-// slice z take slice z + 1's rows from registers; so a source row is
-// fetched once per block instead of once for its own slice and again for
-// the slice below (with flat chunks the moving preparation fetched 2.5x
-// its source volume).  Each 16-byte store of the wave covers consecutive
-// entries.
+// single-pair path, one wave per chunk of kPrepChunk consecutive records.
+// Tiled 8-bit octs of a u8 volume: a tile is 4 x 2 x 2 records; lane l of a
+// pass takes the four records of one tile row (l & 3) of tile l / 4, from the
+// five bytes of each of its four source rows, and stores 32 bytes, so the
+// wave stores 2 KiB of consecutive records.  Otherwise a record per lane at a
+// time.
 __global__ void prep_moving_kernel(PairsArgs a, int64_t items) {
   for_each_item(a.pairs, a.mchunk_base, a.n_pairs, items, [&](const PairDesc& d, int64_t c, int lane) {
     const uint32_t nx = (uint32_t)d.geom.mnx, ny = (uint32_t)d.geom.mny, nz = (uint32_t)d.geom.mnz;
-    const uint32_t plane = nx * ny;  // nvox < 2^28
-    const uint32_t runs = (plane + kPrepPlaneRun - 1) / kPrepPlaneRun;
-    const uint32_t zb = (uint32_t)c / runs, run = (uint32_t)c - zb * runs;
-    const uint32_t z0 = zb * kPrepSlices;
-    const uint32_t nzb = nz - z0 < (uint32_t)kPrepSlices ? nz - z0 : (uint32_t)kPrepSlices;  // slices in the block
-    const uint32_t vp = run * kPrepPlaneRun + 2u * (uint32_t)lane;  // plane index of the lane's first voxel
-    if (vp >= plane) return;
-    if (d.geom.gather == kOct8 && d.mdtype == 0 && (nx & 1) == 0 && ((uintptr_t)d.moving & 1) == 0) {
-      // u8 rows of even length: the lane's two voxels (vp even) lie in one
-      // row.  Per slice and source row (y, y + 1 clamped): a 2-byte load at
-      // x and the byte at x + 2 (clamped to the last column).
-      const uint32_t y = vp / nx, x = vp - y * nx;
-      const size_t ry0 = vp, ry1 = y + 1 < ny ? (size_t)vp + nx : (size_t)vp;
-      const uint32_t xn = x + 2 < nx ? 2u : nx - 1u - x;  // offset of the byte after the pair
+    const uint32_t plane = nx * ny;
+    const int32_t base = gather_base(d.geom.gather);
+    const bool tiled = (d.geom.gather & kTiled) != 0, o8 = base == kOct8;
+    const uint32_t px = (uint32_t)tile_pad_x((int32_t)nx, o8), py = (uint32_t)tile_pad((int32_t)ny);
+    const uint32_t records = d.geom.gvol_bytes / (o8 ? 8u : 16u);  // < 2^32
+    const uint32_t c0 = (uint32_t)c * kPrepChunk;
+    if (d.geom.gather == (kOct8 | kTiled) && d.mdtype == 0 && nx >= 4) {
       global_u8* __restrict__ mv = (global_u8*)d.moving;
-      uint32_t w[kPrepSlices + 1][2], e[kPrepSlices + 1][2];
+      const uint32_t tx = px / 4, ty = py / 2;
+      const bool ident = d.mlo == 0 && d.mhi == 255;  // 8-bit corners: the clamp changes nothing then
 #pragma unroll
-      for (int k = 0; k <= kPrepSlices; ++k) {
-        uint32_t z = z0 + (uint32_t)k;
-        z = z < nz ? z : nz - 1;  // slice z0 + nzb is the block's last slice + 1, clamped
-        if ((uint32_t)k > nzb) z = z0;  // past the block: a valid slice, not used
-        const size_t sz = (size_t)z * plane;
-        w[k][0] = ((global_u16*)(mv + sz + ry0))[0];
-        e[k][0] = mv[sz + ry0 + xn];
-        w[k][1] = ((global_u16*)(mv + sz + ry1))[0];
-        e[k][1] = mv[sz + ry1 + xn];
-      }
-      // with 8-bit corners R <= 256, so the clamp is the identity exactly
-      // when the range is 0..255
-      const bool ident = d.mlo == 0 && d.mhi == 255;
-      uint32_t cw[kPrepSlices + 1][2], t[kPrepSlices + 1][2];  // (x, x+1) and (x+1, x+2) in bytes 0, 1
+      for (uint32_t k = 0; k < kPrepChunk / 256; ++k) {
+        const uint32_t i = c0 + 256 * k + 4 * (uint32_t)lane;  // the first of four records
+        if (i >= records) break;
+        const uint32_t tile = i / 16, tr = tile / tx, tz = tr / ty;
+        uint32_t y = (tr - tz * ty) * 2 + (lane & 1), z = tz * 2 + ((lane >> 1) & 1);
+        y = y < ny ? y : ny - 1;  // padding: any defined contents
+        z = z < nz ? z : nz - 1;
+        // four bytes from x, or the row's last four shifted down (beyond the
+        // row: its last byte)
+        const uint32_t x = (tile - tr * tx) * 4, xs = x + 4 <= nx ? x : nx - 4, sh = 8 * (x - xs);
+        const uint32_t a0 = z * plane + y * nx + xs;
+        const uint32_t dy = y + 1 < ny ? nx : 0, dz = z + 1 < nz ? plane : 0, last = x + 4 < nx ? 4u : nx - 1 - xs;
+        const uint32_t rows[4] = {a0, a0 + dy, a0 + dz, a0 + dz + dy};
+        uint32_t w[4], e[4];  // bytes x .. x + 3 and x + 4 (clamped) of each source row
 #pragma unroll
-      for (int k = 0; k <= kPrepSlices; ++k)
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          uint32_t b0 = w[k][r] & 0xFFu, b1 = w[k][r] >> 8, b2 = e[k][r];
-          if (!ident) {
-            b0 = clamp_offset((int32_t)b0, d.mlo, d.mhi);
-            b1 = clamp_offset((int32_t)b1, d.mlo, d.mhi);
-            b2 = clamp_offset((int32_t)b2, d.mlo, d.mhi);
-          }
-          cw[k][r] = b0 | (b1 << 8);
-          t[k][r] = b1 | (b2 << 8);
+        for (int r = 0; r < 4; ++r) {
+          w[r] = *(global_unaligned32*)(mv + rows[r]);
+          e[r] = mv[rows[r] + last];
+          if (sh) w[r] = (w[r] >> sh) | ((e[r] * 0x01010101u) << (32 - sh));
         }
+        if (!ident) {
 #pragma unroll
-      for (int k = 0; k < kPrepSlices; ++k) {
-        if ((uint32_t)k >= nzb) break;
-        // entries: byte 4 dz + 2 dy + dx' (layout of pack_oct8_kernel)
-        *(global_out4*)((global_out2*)d.geom.gvol + (size_t)(z0 + k) * plane + vp) =
-            uint4_t{cw[k][0] | (cw[k][1] << 16), cw[k + 1][0] | (cw[k + 1][1] << 16),
-                    t[k][0] | (t[k][1] << 16), t[k + 1][0] | (t[k + 1][1] << 16)};
+          for (int r = 0; r < 4; ++r) {
+            uint32_t o = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) o |= clamp_offset((int32_t)((w[r] >> (8 * b)) & 0xFFu), d.mlo, d.mhi) << (8 * b);
+            w[r] = o;
+            e[r] = clamp_offset((int32_t)e[r], d.mlo, d.mhi);
+          }
+        }
+        // records: byte 4 dz + 2 dy + dx' (layout of pack_oct8_kernel)
+        auto pair = [&](int r, int j) -> uint32_t {  // bytes j, j + 1 of row r
+          return j < 3 ? (w[r] >> (8 * j)) & 0xFFFFu : (w[r] >> 24) | (e[r] << 8);
+        };
+        uint4_t o[2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          o[j >> 1][2 * (j & 1)] = pair(0, j) | (pair(1, j) << 16);
+          o[j >> 1][2 * (j & 1) + 1] = pair(2, j) | (pair(3, j) << 16);
+        }
+        global_out4* __restrict__ out = (global_out4*)((global_out2*)d.geom.gvol + i);
+        out[0] = o[0];
+        out[1] = o[1];
       }
       return;
     }
     auto val = [&](size_t i) -> uint32_t { return clamp_offset(load_int(d.moving, d.mdtype, i), d.mlo, d.mhi); };
-    for (uint32_t j = 0; j < 2; ++j) {
-      const uint32_t v = vp + j;
-      if (v >= plane) break;
-      const uint32_t y = v / nx, x = v - y * nx;
-      const size_t row0 = (size_t)v - x, row1 = y + 1 < ny ? row0 + nx : row0;  // rows y, y + 1 (clamped)
-      const uint32_t x1 = x + 1 < nx ? x + 1 : nx - 1;
-      for (uint32_t k = 0; k < nzb; ++k) {
-        const uint32_t z = z0 + k;
-        const size_t s0 = (size_t)z * plane, s1 = z + 1 < nz ? s0 + plane : s0;  // slices z, z + 1 (clamped)
-        const size_t a0 = s0 + row0, a1 = s0 + row1, b0 = s1 + row0, b1 = s1 + row1;
-        const size_t out = s0 + v;
-        if (d.geom.gather == kOct8) {
-          // 8-bit corners: byte 4 dz + 2 dy + dx' (layout of pack_oct8_kernel)
-          ((global_out2*)d.geom.gvol)[out] =
-              uint2_t{val(a0 + x) | (val(a0 + x1) << 8) | (val(a1 + x) << 16) | (val(a1 + x1) << 24),
-                      val(b0 + x) | (val(b0 + x1) << 8) | (val(b1 + x) << 16) | (val(b1 + x1) << 24)};
-        } else {
-          ((global_out4*)d.geom.gvol)[out] =
-              uint4_t{val(a0 + x) | (val(a0 + x1) << 16), val(a1 + x) | (val(a1 + x1) << 16),
-                      val(b0 + x) | (val(b0 + x1) << 16), val(b1 + x) | (val(b1 + x1) << 16)};
-        }
+    const uint32_t kx = o8 ? 4 : 2;  // tile width
+    for (uint32_t k = 0; k < kPrepLane; ++k) {
+      const uint32_t out = c0 + 64 * k + (uint32_t)lane;
+      if (out >= records) break;
+      uint32_t x, y, z;
+      if (tiled) {
+        const uint32_t tile = out / (4 * kx), low = out - tile * (4 * kx);
+        const uint32_t tr = tile / (px / kx), tz = tr / (py / 2);
+        x = (tile - tr * (px / kx)) * kx + low % kx;
+        y = (tr - tz * (py / 2)) * 2 + low / kx % 2;
+        z = 2 * tz + low / (2 * kx);
+        if (x >= nx || y >= ny || z >= nz) continue;  // padding: never gathered
+      } else {
+        const uint32_t row = out / nx;
+        x = out - row * nx;
+        z = row / ny;
+        y = row - z * ny;
+      }
+      const uint32_t v = z * plane + y * nx + x;
+      const uint32_t dx = x + 1 < nx ? 1 : 0, dy = y + 1 < ny ? nx : 0, dz = z + 1 < nz ? plane : 0;
+      if (o8) {
+        ((global_out2*)d.geom.gvol)[out] =
+            uint2_t{val(v) | (val(v + dx) << 8) | (val(v + dy) << 16) | (val(v + dy + dx) << 24),
+                    val(v + dz) | (val(v + dz + dx) << 8) | (val(v + dz + dy) << 16) | (val(v + dz + dy + dx) << 24)};
+      } else {
+        ((global_out4*)d.geom.gvol)[out] =
+            uint4_t{val(v) | (val(v + dx) << 16), val(v + dy) | (val(v + dy + dx) << 16),
+                    val(v + dz) | (val(v + dz + dx) << 16), val(v + dz + dy) | (val(v + dz + dy + dx) << 16)};
       }
     }
   });
@@ -314,7 +324,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void hi
       int64_t Ms[12];
 #pragma unroll
       for (int e = 0; e < 12; ++e) Ms[e] = uniform64(Mq[e]);
-      sweep_hard<CLAMP, PACKED, GL, NT / 64, GroupWalkBrick, false>(geom, Md, Ms, chunks, chunk, lds_hist);
+      sweep_rods<CLAMP, PACKED, GL, NT / 64>(geom, Md, Ms, chunks, chunk, lds_hist);
     }
     __syncthreads();
     if (ok) flush_hist<PACKED, NT>(lds_hist, B, a.hist + (size_t)t * B * B, true);
@@ -383,7 +393,13 @@ static hipError_t pairs_layout(const PairsLaunch& L, hipStream_t s) {
 }
 
 hipError_t launch_pairs_hist(const PairsLaunch& L, hipStream_t s) {
-  return L.oct8 ? pairs_layout<kOct8>(L, s) : pairs_layout<kOct16>(L, s);
+  switch (L.gather) {
+  case kOct8 | kTiled: return pairs_layout<kOct8 | kTiled>(L, s);
+  case kOct16 | kTiled: return pairs_layout<kOct16 | kTiled>(L, s);
+  case kOct8: return pairs_layout<kOct8>(L, s);
+  case kOct16: return pairs_layout<kOct16>(L, s);
+  default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace gemi

@@ -99,6 +99,89 @@ constexpr int32_t fixed_run_x(int32_t p, int32_t nx) {
   return (p - r) + (r >> 2) + kTileX * (r & 3);
 }
 
+// The same for brick sweeps, whose lanes step by 4 along x: in each whole run
+// of 16 voxels the four bytes at 4 dx hold voxels dx, 4 + dx, 8 + dx, 12 + dx.
+constexpr int32_t kCubeRun = 16;
+constexpr int32_t cube_run_x(int32_t p, int32_t nx) {
+  if (p >= nx / kCubeRun * kCubeRun) return p;
+  const int32_t r = p & (kCubeRun - 1);
+  return (p - r) + (r >> 2) + 4 * (r & 3);
+}
+
+// Tiled octs of a moving volume: the records of a block of 2 x 2 x 2 voxels
+// (16-byte records) or 4 x 2 x 2 (8-byte ones) share a 128-byte line, x
+// fastest, then y, z; blocks in x, y, z order, the last ones padded.
+constexpr int32_t tile_pad_x(int32_t nx, bool rec8) { return rec8 ? (nx + 3) & ~3 : (nx + 1) & ~1; }
+constexpr int32_t tile_pad(int32_t n) { return (n + 1) & ~1; }
+constexpr size_t tiled_records(int32_t nx, int32_t ny, int32_t nz, bool rec8) {
+  return (size_t)tile_pad_x(nx, rec8) * (size_t)tile_pad(ny) * (size_t)tile_pad(nz);
+}
+// Record index of voxel (ix, iy, iz), px and py the padded extents:
+constexpr uint32_t tiled_index(uint32_t ix, uint32_t iy, uint32_t iz, uint32_t px, uint32_t py, bool rec8) {
+  // ((block z * blocks y + block y) * blocks x + block x) * records + place,
+  // written as a linear form less what the low bits add too much
+  const uint32_t lx = ix & (rec8 ? 3u : 1u), ly = iy & 1u, lz = iz & 1u, s = rec8 ? 4u : 2u;
+  return (iz * (py / 2) + iy) * (2 * px) + 4 * ix - 3 * lx - (2 * px - s) * ly - (px * py - 2 * s) * lz;
+}
+
+// A slab's walk in brick sweeps.  The fixed volume is cut into rods of 64 x 4
+// x 4 voxels (cubes of 4 x 4 x 4, one wave step each, along x), numbered by
+// x segment, then by blocks of yb rods along y, then z, then y within the
+// block; a slab is a contiguous range of that numbering, so about yb by yb
+// rods of one segment: nearly a cube of the fixed volume, whose image stays
+// compact under any rotation.  The waves take a slab's rods in turn, so
+// that neighbouring rods are swept at the same time.
+constexpr int32_t kRodX = 64;
+struct RodWalk {
+  int64_t u, u1;
+  int32_t xs, b0, bw, gz, gy;  // x segment, y block and its width, z, y within the block
+  int32_t Gy, Gz, yb;
+
+  static constexpr int64_t rods(int32_t fnx, int32_t fny, int32_t fnz) {
+    return (int64_t)((fnx + kRodX - 1) / kRodX) * ((fny + 3) / 4) * ((fnz + 3) / 4);
+  }
+
+  constexpr void init(int32_t fnx, int32_t fny, int32_t fnz, int32_t chunks, uint32_t chunk, int wave) {
+    Gy = (fny + 3) / 4;
+    Gz = (fnz + 3) / 4;
+    const int64_t n = rods(fnx, fny, fnz);
+    u = n * chunk / chunks;
+    u1 = n * (chunk + 1) / chunks;
+    const int32_t per = (int32_t)((n + chunks - 1) / chunks);
+    yb = 1;
+    while (yb < Gy && yb * yb < per) ++yb;
+    const int32_t plane = Gy * Gz;  // <= 2^20
+    xs = (int32_t)(u / plane);
+    const int32_t rem = (int32_t)(u - (int64_t)xs * plane);
+    b0 = rem / (yb * Gz) * yb;
+    bw = Gy - b0 < yb ? Gy - b0 : yb;
+    gz = (rem - b0 * Gz) / bw;
+    gy = rem - b0 * Gz - gz * bw;
+    next(wave);
+  }
+
+  constexpr void next(int32_t rods) {
+    u += rods;
+    gy += rods;
+    while (gy >= bw) {
+      gy -= bw;
+      if (++gz == Gz) {
+        gz = 0;
+        b0 += bw;
+        if (b0 == Gy) {
+          b0 = 0;
+          ++xs;
+        }
+        // the rods left over keep their place in the next block's numbering
+        bw = Gy - b0 < yb ? Gy - b0 : yb;
+      }
+    }
+  }
+  constexpr int32_t x0() const { return xs * kRodX; }
+  constexpr int32_t j0() const { return (b0 + gy) * 4; }
+  constexpr int32_t k0() const { return gz * 4; }
+};
+
 // One wave's walk over its share of a slab: groups of kTileY consecutive
 // rows of one slice with exact Q32 row coordinates.  Either each wave takes
 // a contiguous share of the slab's row groups (GroupWalk), or the waves

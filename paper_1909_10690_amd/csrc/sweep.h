@@ -90,6 +90,7 @@ struct HardStep {
   Divider div;
 
   int32_t to_row, to_slice;  // kCopy16: bytes to the next row, next slice
+  uint32_t ny2, mx2, low_y, low_z;  // kTiled: the constants of tiled_index
 
   // gather: the layout the kernel's GL instance reads
   __device__ __forceinline__ HardStep(const HardGeom& g, bool packed, int32_t gather) {
@@ -103,6 +104,12 @@ struct HardStep {
     rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)g.gvol, (short)gather_record(gather), (int)g.gvol_bytes, 0x00020000);
     to_row = 2 * g.mnx;
     to_slice = 2 * g.mnx * g.mny;
+    const bool rec8 = gather_base(gather) == kOct8;
+    const uint32_t s = rec8 ? 4u : 2u, px = (uint32_t)tile_pad_x(g.mnx, rec8), py = (uint32_t)tile_pad(g.mny);
+    ny2 = py / 2;
+    mx2 = 2 * px;
+    low_y = mx2 - s;
+    low_z = px * py - 2 * s;  // < 2^24
     Bu = (uint32_t)g.bins;
     // LDS histogram row pitch: in bytes (u32 counters), in 16-bit cells
     // (packed counters)
@@ -134,10 +141,15 @@ struct HardStep {
     }
     const uint32_t ix = (uint32_t)(cx >> 32), iy = (uint32_t)(cy >> 32), iz = (uint32_t)(cz >> 32);
     // rows iz ny + iy < ny nz <= 2^24 and edges <= 4096: 24-bit operands
-    const uint32_t vox = mad24(mad24(iz, NY, iy), MX, ix);
+    uint32_t vox;
+    if (GL & kTiled)  // tiled_index
+      vox = mad24(mad24(iz, ny2, iy), mx2, 4 * ix) -
+            mad24(iz & 1u, low_z, mad24(iy & 1u, low_y, 3u * (ix & (gather_base(GL) == kOct8 ? 3u : 1u))));
+    else
+      vox = mad24(mad24(iz, NY, iy), MX, ix);
     const uint32_t fx = (uint32_t)cx, fy = (uint32_t)cy, fz = (uint32_t)cz;
     uint32_t a00, a10, a01, a11;  // the exact x-lerps of the four rows
-    if (GL == kOctD) {
+    if (gather_base(GL) == kOctD) {
       const uint4_t oc = struct_load_b128(rsrc, (int)vox, 0, 0, 0);
       const uint32_t w = (fx & 0xFFFF0000u) ^ 0x80008000u;
       a00 = lerp_xd(oc.x, w);
@@ -146,7 +158,7 @@ struct HardStep {
       a11 = lerp_xd(oc.w, w);
     } else {
       uint4_t oc;
-      if (GL == kOct8) {
+      if (gather_base(GL) == kOct8) {
         // bytes (x,y), (x1,y), (x,y1), (x1,y1) of slice z in .x, of z1 in .y
         const uint2_t d = struct_load_b64(rsrc, (int)vox, 0, 0, 0);
         oc.x = __builtin_amdgcn_perm(0u, d.x, 0x0C010C00u);  // (b0, b1) as 16-bit halves
@@ -245,16 +257,13 @@ struct RowRanges {
   }
 };
 
-// Sweeps one slab of the fixed volume for one transform (Mq) into the
-// workgroup's LDS histogram.  NW waves share the slab's 4-row groups, in
-// the order of Walk (thin slabs, or bricks).
+// Sweeps one thin slab of the fixed volume for one transform (Mq) into the
+// workgroup's LDS histogram.  NW waves share the slab's 4-row groups.
 // GL: the moving volume's layout (Gather); kOct8 corners (one 64-bit gather)
 // are unpacked into the 16-bit pairs of the x-lerp with byte permutes.
 // Md: the transform as stored; Mq: its Q32 rounding, in scalar registers
-// (quantize_transform_wave).  RANGES false: every
-// voxel is tested (the range lanes' registers would not fit a kernel already
-// at its register budget).
-template <bool CLAMP, bool PACKED, int GL, int NW, typename Walk = GroupWalk, bool RANGES = true>
+// (quantize_transform_wave).
+template <bool CLAMP, bool PACKED, int GL, int NW>
 __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, const int64_t* Mq,
                                            int32_t chunks, uint32_t chunk, uint32_t* lds_hist) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -264,7 +273,7 @@ __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, 
   // the walk's row coordinates and steps are then scalar values, and only
   // the lane offsets take vector registers
   const int64_t* M = Mq;
-  Walk w;
+  GroupWalk w;
   w.init(M, g.fny, g.fnz, chunks, chunk, wave, NW, dx, dy);
   const int64_t sx = w.step[0], sy = w.step[1], sz = w.step[2];
   const HardStep hs(g, PACKED, GL);
@@ -281,18 +290,17 @@ __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, 
   const bool tail = (uint32_t)dx < fnx % kTileX;  // the lane takes one more
   const bool has_tail = fnx % kTileX != 0;
   RowRanges ranges;
-  if (RANGES) ranges.init(Md, g, lane);
+  ranges.init(Md, g, lane);
 
   for (; w.g < w.g1; w.next()) {
     // x steps [c0, c1) have every lane inside; with EXCLUDE no lane counts
     // outside [u0, u1)
-    RowSpans sp{0, full, full, full};
-    if (RANGES) sp = ranges.spans(w.j0, w.k, full, !CLAMP);
+    const RowSpans sp = ranges.spans(w.j0, w.k, full, !CLAMP);
     const int32_t j = w.j0 + dy;
     if (j >= g.fny) continue;
     global_u8* const row = fbins + ((uint32_t)w.k * (uint32_t)g.fny + (uint32_t)w.j0) * fnx;  // < 2^28
     int64_t qx = w.r[0] + w.lane_off[0], qy = w.r[1] + w.lane_off[1], qz = w.r[2] + w.lane_off[2];
-    if (RANGES && sp.u0 > 0) {
+    if (sp.u0 > 0) {
       qx += sx * sp.u0;
       qy += sy * sp.u0;
       qz += sz * sp.u0;
@@ -309,7 +317,7 @@ __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, 
         hs.count<CLAMP, PACKED, GL>(qx, qy, qz, [&] { return bins4 & 0xFFu; }, lds_hist);
       }
     };
-    if (RANGES && c0 < c1) {
+    if (c0 < c1) {
       checked(c0);
       for (; it < c1; it += 4) {
         bins4 = load_run();
@@ -328,13 +336,85 @@ __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, 
       hs.count<CLAMP, PACKED, GL>(
           qx, qy, qz, [&] { return (uint32_t)row[(uint32_t)it * kTileX + lane_f]; }, lds_hist);
     if (has_tail && tail) {
-      if (RANGES) {
-        qx = w.r[0] + sx * full + w.lane_off[0];
-        qy = w.r[1] + sy * full + w.lane_off[1];
-        qz = w.r[2] + sz * full + w.lane_off[2];
-      }
+      qx = w.r[0] + sx * full + w.lane_off[0];
+      qy = w.r[1] + sy * full + w.lane_off[1];
+      qz = w.r[2] + sz * full + w.lane_off[2];
       hs.count<CLAMP, PACKED, GL>(qx, qy, qz, [&] { return (uint32_t)row[(uint32_t)full * kTileX + lane_f]; }, lds_hist);
     }
+  }
+}
+
+// Sweeps one brick of the fixed volume (RodWalk) for one transform into the
+// workgroup's LDS histogram; arguments as sweep_hard.  For transforms that
+// rotate widely: a wave's 64 voxels are a cube, whose moving image touches
+// about half the cache lines of a 16 x 4 tile's whichever way it is turned, and
+// with tiled octs (kTiled) half of those again -- the sweep is bound by the
+// lines its gathers touch and fetch (729 rotations of up to 180 degrees,
+// 256x256x180 u16 at 128 bins: 36.8 ms with 16 x 4 tiles in bricks of whole x
+// rows, 18.6 with rods and tiles).  Each wave classes its rod by the extreme
+// coordinates over the rod: outside the moving volume on some axis (skipped
+// when EXCLUDE), inside on all (no test per voxel), or mixed.
+template <bool CLAMP, bool PACKED, int GL, int NW>
+__device__ __forceinline__ void sweep_rods(const HardGeom& g, const double* Md, const int64_t* Mq, int32_t chunks,
+                                           uint32_t chunk, uint32_t* lds_hist) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int dx = lane & 3, dy = (lane >> 2) & 3, dz = lane >> 4;
+  const HardStep hs(g, PACKED, GL);
+  const int64_t sx = 4 * Mq[0], sy = 4 * Mq[4], sz = 4 * Mq[8];
+  const int64_t ox = Mq[0] * dx + Mq[1] * dy + Mq[2] * dz;
+  const int64_t oy = Mq[4] * dx + Mq[5] * dy + Mq[6] * dz;
+  const int64_t oz = Mq[8] * dx + Mq[9] * dy + Mq[10] * dz;
+  // lane a < 3: the matrix row of axis a, the least and greatest offsets over
+  // a rod and the upper coordinate
+  const int axis = lane < 3 ? lane : 0;
+  const double* mrow = Md + 4 * axis;
+  const int64_t m0 = __double2ll_rn(mrow[0] * 4294967296.0), m1 = __double2ll_rn(mrow[1] * 4294967296.0);
+  const int64_t m2 = __double2ll_rn(mrow[2] * 4294967296.0), m3 = __double2ll_rn(mrow[3] * 4294967296.0);
+  const int64_t ex = m0 * (kRodX - 1), ey = m1 * 3, ez = m2 * 3;
+  const int64_t omin = (ex < 0 ? ex : 0) + (ey < 0 ? ey : 0) + (ez < 0 ? ez : 0);
+  const int64_t omax = (ex > 0 ? ex : 0) + (ey > 0 ? ey : 0) + (ez > 0 ? ez : 0);
+  const int64_t top = (int64_t)((axis == 0 ? g.mnx : (axis == 1 ? g.mny : g.mnz)) - 1) << 32;
+  const uint32_t fnx = (uint32_t)g.fnx, fplane = fnx * (uint32_t)g.fny;
+  const uint32_t lane_f = dz * fplane + dy * fnx + dx, lane_f4 = lane_f + 3 * dx;
+  global_u8* const fbins = (global_u8*)g.fbins;
+  RodWalk w;
+  w.init(g.fnx, g.fny, g.fnz, chunks, chunk, wave);
+  for (; w.u < w.u1; w.next(NW)) {
+    const int32_t x0 = w.x0(), j0 = w.j0(), k0 = w.k0();
+    const int64_t r = m0 * x0 + m1 * j0 + m2 * k0 + m3;
+    // lanes past axis 2 repeat axis 0
+    const bool inside = __builtin_amdgcn_ballot_w64(r + omin < 0 || r + omax > top) == 0;
+    if (!CLAMP && __builtin_amdgcn_ballot_w64(r + omax < 0 || r + omin > top) != 0) continue;
+    auto lane_value = [&](int a) {
+      return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)((uint64_t)r >> 32), a) << 32) |
+                       (uint32_t)__builtin_amdgcn_readlane((uint32_t)r, a));
+    };
+    int64_t qx = lane_value(0) + ox, qy = lane_value(1) + oy, qz = lane_value(2) + oz;
+    if (j0 + dy >= g.fny || k0 + dz >= g.fnz) continue;
+    global_u8* const rod = fbins + ((uint32_t)k0 * fplane + (uint32_t)j0 * fnx + (uint32_t)x0);  // < 2^28
+    const int32_t width = g.fnx - x0 < kRodX ? g.fnx - x0 : kRodX;
+    const int32_t runs = width / kCubeRun;  // whole runs of 16 voxels, four steps each
+    for (int32_t run = 0; run < runs; ++run) {
+      const uint32_t bins4 = *(global_unaligned32*)(rod + (uint32_t)run * kCubeRun + lane_f4);
+      auto steps = [&]<bool CHECK>() {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          hs.template count<CLAMP, PACKED, GL, CHECK>(qx, qy, qz, [&] { return (bins4 >> (8 * k)) & 0xFFu; }, lds_hist);
+          qx += sx;
+          qy += sy;
+          qz += sz;
+          asm("" : "+v"(qx), "+v"(qy), "+v"(qz));  // step by step: not each from the first, with twice the adds
+        }
+      };
+      if (inside)
+        steps.template operator()<false>();
+      else
+        steps.template operator()<true>();
+    }
+    for (int32_t x = runs * kCubeRun; x < width; x += 4, qx += sx, qy += sy, qz += sz)  // the rest of the row
+      if (x + dx < width)
+        hs.count<CLAMP, PACKED, GL>(qx, qy, qz, [&] { return (uint32_t)rod[(uint32_t)x + lane_f]; }, lds_hist);
   }
 }
 

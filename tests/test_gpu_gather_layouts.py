@@ -152,3 +152,58 @@ def test_sweep_runs_and_records(ctx, nx, hi, bins):
             assert np.array_equal(h.cpu().numpy().astype(np.uint32), oh), flags
             assert np.array_equal(ov.cpu().numpy(), oov)
             assert np.all(np.abs(mi.cpu().numpy() - omi) <= 1e-12 * np.maximum(1.0, np.abs(omi)))
+
+
+TILED = [(2, 2, 2), (4, 2, 2), (6, 4, 2), (16, 4, 6), (64, 10, 8), (84, 6, 14)]  # whole tiles, no padding
+
+
+@pytest.mark.parametrize("shape", TILED)
+@pytest.mark.parametrize("mdt,hi,bins", [(np.uint8, 255, 64), (np.uint8, 200, 256), (np.uint16, 4095, 128),
+                                         (np.uint16, 65535, 129)])
+def test_brick_tiles(ctx, shape, mdt, hi, bins):
+    """Bricks over tiles of octs: moving volumes of one tile and more, fixed
+    volumes of their extents and ragged ones around a rod and a run."""
+    import torch
+    from paper_1909_10690_amd import binding as B
+    rng = np.random.default_rng(sum(shape) + hi + bins)
+    m = inputs.random_volume(rng, shape, mdt, 0, hi)
+    for fs in (shape, (67, 5, 3), (17, 9, 2)):
+        f = inputs.random_volume(rng, fs, np.uint8, 0, 255)
+        mats = edge_transforms(fs, rng)
+        print(f"tiles moving={shape} fixed={fs} hi={hi} bins={bins}", flush=True)
+        F, M = device_volume(f, 0, 255, 1), device_volume(m, 0, hi, 0)
+        for clamp in (0, 1):
+            omi, oov, oh = oracle.eval_hard(oracle.volume(f, 0, 255), oracle.volume(m, 0, hi), mats, bins, (1.0,),
+                                            boundary=clamp, want_hist=True)
+            mi, ov, h = ctx.eval(F, M, torch.from_numpy(mats).cuda(), bins, (1.0,), flags=clamp | B.COMPACT_SLABS,
+                                 want_hist=True)
+            torch.cuda.synchronize()
+            assert np.array_equal(h.cpu().numpy().astype(np.uint32), oh), (fs, clamp)
+            assert np.array_equal(ov.cpu().numpy(), oov)
+            assert np.all(np.abs(mi.cpu().numpy() - omi) <= 1e-12 * np.maximum(1.0, np.abs(omi)))
+
+
+@pytest.mark.parametrize("mdt,lo,hi,shift", [(np.uint8, 0, 255, 0), (np.uint8, 0, 255, 3), (np.uint8, 9, 200, 1),
+                                             (np.int16, -100, 100, 0), (np.uint16, 0, 65535, 1)])
+@pytest.mark.parametrize("bins", [32, 128, 200])
+def test_pair_tiles(ctx, mdt, lo, hi, shift, bins):
+    """Padded tiles of pairs: moving extents on both sides of whole tiles,
+    rows shorter than one, unaligned sources."""
+    import torch
+    rng = np.random.default_rng(hi + shift + bins)
+    shapes = [(2, 2, 2), (3, 5, 2), (4, 3, 3), (5, 2, 7), (6, 6, 5), (7, 4, 4), (33, 19, 6), (64, 8, 8), (130, 9, 5)]
+    pairs, want = [], []
+    for i, ms in enumerate(shapes):
+        fs = shapes[(i + 3) % len(shapes)]
+        f = inputs.random_volume(rng, fs, np.uint8, 0, 255)
+        m = inputs.random_volume(rng, ms, mdt, *((0, 255) if mdt == np.uint8 else (lo, hi)))
+        mats = edge_transforms(fs, rng)
+        pairs.append((device_volume(f, 0, 255, shift), device_volume(m, lo, hi, shift), torch.from_numpy(mats).cuda()))
+        want.append([oracle.eval_hard(oracle.volume(f, 0, 255), oracle.volume(m, lo, hi), mats, bins, (1.0,),
+                                      boundary=c)[0] for c in (0, 1)])
+    for clamp in (0, 1):
+        print(f"pair tiles {np.dtype(mdt).name} {lo}..{hi} bins={bins} clamp={clamp}", flush=True)
+        got = ctx.eval_pairs(pairs, bins, (1.0,), flags=clamp)
+        torch.cuda.synchronize()
+        w = np.concatenate([x[clamp] for x in want])
+        assert np.all(np.abs(got.cpu().numpy() - w) <= 1e-12 * np.maximum(1.0, np.abs(w)))
