@@ -22,25 +22,27 @@ namespace {
 constexpr double kInvSqrt2 = 0.70710678118654752440;
 constexpr double kInvSqrt3 = 0.57735026918962576451;
 constexpr int kPathThreads = 256;
+constexpr int kSinkThreads = 1024;
 
-unsigned path_grid(int64_t n) {
-  const int64_t g = (n + kPathThreads - 1) / kPathThreads;
-  return (unsigned)(g < 8192 ? (g > 0 ? g : 1) : 8192);
+unsigned path_grid(int64_t n, int threads, int64_t most) {
+  const int64_t g = (n + threads - 1) / threads;
+  return (unsigned)(g < most ? (g > 0 ? g : 1) : most);
 }
 }  // namespace
 
 __global__ __launch_bounds__(kPathThreads) void path_next_kernel(const double* __restrict__ f, int32_t nx,
                                                                  int32_t ny, int32_t nz, double sign,
-                                                                 int32_t* __restrict__ next) {
-  const int64_t n = (int64_t)nx * ny * nz;
-  for (int64_t p = blockIdx.x * (int64_t)kPathThreads + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * kPathThreads) {
-    const int32_t x = (int32_t)(p % nx);
-    const int64_t r = p / nx;
-    const int32_t y = (int32_t)(r % ny), z = (int32_t)(r / ny);
+                                                                 int32_t* __restrict__ next,
+                                                                 int64_t* __restrict__ stats) {
+  if (blockIdx.x == 0 && threadIdx.x < 4) stats[threadIdx.x] = threadIdx.x == 3 ? INT64_MAX : 0;  // see path_sink_kernel
+  const uint32_t n = (uint32_t)nx * (uint32_t)ny * (uint32_t)nz;  // < 2^31
+  for (uint32_t p = blockIdx.x * kPathThreads + threadIdx.x; p < n; p += gridDim.x * kPathThreads) {
+    const uint32_t r = p / (uint32_t)nx;
+    const int32_t x = (int32_t)(p - r * (uint32_t)nx);
+    const int32_t z = (int32_t)(r / (uint32_t)ny), y = (int32_t)(r - (uint32_t)z * (uint32_t)ny);
     const double fp = sign * f[p];
     double best = 0.0;
-    int64_t arg = p;
+    uint32_t arg = p;
     for (int dz = -1; dz <= 1; ++dz) {
       const int32_t zz = z + dz;
       if (zz < 0 || zz >= nz) continue;
@@ -51,7 +53,7 @@ __global__ __launch_bounds__(kPathThreads) void path_next_kernel(const double* _
           const int32_t xx = x + dx;
           const int k = (dx != 0) + (dy != 0) + (dz != 0);
           if (xx < 0 || xx >= nx || k == 0) continue;
-          const int64_t q = ((int64_t)zz * ny + yy) * nx + xx;
+          const uint32_t q = ((uint32_t)zz * (uint32_t)ny + (uint32_t)yy) * (uint32_t)nx + (uint32_t)xx;
           const double w = k == 1 ? 1.0 : (k == 2 ? kInvSqrt2 : kInvSqrt3);
           const double s = (sign * f[q] - fp) * w;
           if (s > best) {
@@ -65,96 +67,91 @@ __global__ __launch_bounds__(kPathThreads) void path_next_kernel(const double* _
   }
 }
 
-// Follows each point's successors to the extremum its path ends at.  The
-// step bound n is never reached by a strictly rising path; it only makes
-// the loop's end independent of the data.
-__global__ __launch_bounds__(kPathThreads) void path_sink_kernel(const int32_t* __restrict__ next, int64_t n,
-                                                                 int32_t* __restrict__ sink) {
-  for (int64_t p = blockIdx.x * (int64_t)kPathThreads + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * kPathThreads) {
-    int32_t q = (int32_t)p;
-    for (int64_t step = 0; step < n; ++step) {
-      const int32_t r = next[q];
-      if (r == q) break;
-      q = r;
+// Follows each point's successors to the extremum its path ends at, and
+// gathers the map's figures over the points: extrema, points that end where
+// the centre does, and the smallest Chebyshev distance from the centre of a
+// point that ends elsewhere.  The step bound n is never reached by a strictly
+// rising path; it only makes the loops' end independent of the data.
+//
+// While it runs, stats holds: [0] extrema << 32 | basin (n < 2^31), [1] the
+// workgroups done, [3] the distance; the last workgroup replaces them by
+//   [0] extrema, [1] sink of the centre, [2] points ending there,
+//   [3] capture radius: one less than the nearest point that ends elsewhere,
+//   or, when every point ends at the centre's extremum, the grid's largest
+//   Chebyshev distance from the centre.
+// What bounds it: the chains of dependent loads, and the atomics on one line,
+// about 11 ns each, hence few large workgroups and three of them per workgroup
+// (a 51^3 map: with three per wave of 256-thread workgroups the figures alone
+// took 76 us, with their own launches for start and end 94 us a call; now
+// 17).
+__global__ __launch_bounds__(kSinkThreads) void path_sink_kernel(const int32_t* __restrict__ next, int32_t nx,
+                                                                 int32_t ny, int32_t nz, int32_t cx, int32_t cy,
+                                                                 int32_t cz, int32_t* __restrict__ sink,
+                                                                 int64_t* __restrict__ stats) {
+  const uint32_t n = (uint32_t)nx * (uint32_t)ny * (uint32_t)nz;  // < 2^31
+  auto follow = [&](uint32_t p) -> uint32_t {
+    for (uint32_t step = 0; step < n; ++step) {
+      const uint32_t r = (uint32_t)next[p];
+      if (r == p) break;
+      p = r;
     }
-    sink[p] = q;
-  }
-}
-
-// stats: [0] extrema, [1] sink of the centre, [2] points ending there,
-// [3] (while counting) smallest Chebyshev distance from the centre of a
-// point ending elsewhere.
-__global__ void path_stats_init_kernel(int64_t* stats) {
-  if (threadIdx.x == 0) {
-    stats[0] = 0;
-    stats[1] = 0;
-    stats[2] = 0;
-    stats[3] = INT64_MAX;
-  }
-}
-
-__global__ __launch_bounds__(kPathThreads) void path_stats_kernel(const int32_t* __restrict__ next,
-                                                                  const int32_t* __restrict__ sink,
-                                                                  int32_t nx, int32_t ny, int32_t nz,
-                                                                  int32_t cx, int32_t cy, int32_t cz,
-                                                                  int64_t* __restrict__ stats) {
-  const int64_t n = (int64_t)nx * ny * nz;
-  const int32_t target = sink[((int64_t)cz * ny + cy) * nx + cx];
-  uint64_t extrema = 0, basin = 0;
-  int64_t dmin = INT64_MAX;
-  for (int64_t p = blockIdx.x * (int64_t)kPathThreads + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * kPathThreads) {
-    extrema += next[p] == (int32_t)p;
-    if (sink[p] == target) {
-      ++basin;
+    return p;
+  };
+  const uint32_t target = follow(((uint32_t)cz * (uint32_t)ny + (uint32_t)cy) * (uint32_t)nx + (uint32_t)cx);
+  uint64_t counts = 0;  // extrema << 32 | basin
+  uint32_t dmin = UINT32_MAX;
+  for (uint32_t p = blockIdx.x * kSinkThreads + threadIdx.x; p < n; p += gridDim.x * kSinkThreads) {
+    const uint32_t q = follow(p);
+    sink[p] = (int32_t)q;
+    counts += q == p ? 1ull << 32 : 0;
+    if (q == target) {
+      ++counts;
     } else {
-      const int32_t x = (int32_t)(p % nx);
-      const int64_t r = p / nx;
-      const int32_t y = (int32_t)(r % ny), z = (int32_t)(r / ny);
-      const int64_t d = max(abs(x - cx), max(abs(y - cy), abs(z - cz)));
+      const uint32_t r = p / (uint32_t)nx;
+      const int32_t x = (int32_t)(p - r * (uint32_t)nx);
+      const int32_t z = (int32_t)(r / (uint32_t)ny), y = (int32_t)(r - (uint32_t)z * (uint32_t)ny);
+      const uint32_t d = (uint32_t)max(abs(x - cx), max(abs(y - cy), abs(z - cz)));
       dmin = d < dmin ? d : dmin;
     }
   }
   for (int off = 32; off > 0; off >>= 1) {
-    extrema += __shfl_xor(extrema, off, 64);
-    basin += __shfl_xor(basin, off, 64);
-    const int64_t o = __shfl_xor(dmin, off, 64);
+    counts += __shfl_xor(counts, off, 64);
+    const uint32_t o = __shfl_xor(dmin, off, 64);
     dmin = o < dmin ? o : dmin;
   }
+  __shared__ uint64_t wave_counts[kSinkThreads / 64];
+  __shared__ uint32_t wave_dmin[kSinkThreads / 64];
   if ((threadIdx.x & 63) == 0) {
-    atomicAdd((unsigned long long*)&stats[0], (unsigned long long)extrema);
-    atomicAdd((unsigned long long*)&stats[2], (unsigned long long)basin);
-    atomicMin((unsigned long long*)&stats[3], (unsigned long long)dmin);
+    wave_counts[threadIdx.x >> 6] = counts;
+    wave_dmin[threadIdx.x >> 6] = dmin;
   }
-}
-
-// Capture radius: one less than the nearest point that ends elsewhere, or,
-// when every point ends at the centre's extremum, the grid's largest
-// Chebyshev distance from the centre.
-__global__ void path_stats_final_kernel(const int32_t* __restrict__ sink, int32_t nx, int32_t ny, int32_t nz,
-                                        int32_t cx, int32_t cy, int32_t cz, int64_t* stats) {
+  __syncthreads();
   if (threadIdx.x != 0) return;
-  stats[1] = sink[((int64_t)cz * ny + cy) * nx + cx];
-  if (stats[3] == INT64_MAX) {
-    const int32_t ex = max(cx, nx - 1 - cx), ey = max(cy, ny - 1 - cy), ez = max(cz, nz - 1 - cz);
-    stats[3] = max(ex, max(ey, ez));
-  } else {
-    stats[3] -= 1;
+  for (int w = 1; w < kSinkThreads / 64; ++w) {
+    counts += wave_counts[w];
+    dmin = wave_dmin[w] < dmin ? wave_dmin[w] : dmin;
   }
+  uint64_t* st = (uint64_t*)stats;
+  if (counts) __hip_atomic_fetch_add(&st[0], counts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (dmin != UINT32_MAX) __hip_atomic_fetch_min(&st[3], (uint64_t)dmin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // both are done before the ticket
+  if (__hip_atomic_fetch_add(&st[1], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1) return;
+  asm volatile("" ::: "memory");
+  const uint64_t all = __hip_atomic_load(&st[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t near = __hip_atomic_load(&st[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int32_t ex = max(cx, nx - 1 - cx), ey = max(cy, ny - 1 - cy), ez = max(cz, nz - 1 - cz);
+  stats[0] = (int64_t)(all >> 32);
+  stats[1] = target;
+  stats[2] = (int64_t)(all & 0xFFFFFFFFull);
+  stats[3] = near == (uint64_t)INT64_MAX ? max(ex, max(ey, ez)) : (int64_t)near - 1;
 }
 
 hipError_t launch_map_paths(const PathsLaunch& L, hipStream_t s) {
   const int64_t n = (int64_t)L.nx * L.ny * L.nz;
-  const unsigned g = path_grid(n);
-  hipLaunchKernelGGL(path_next_kernel, dim3(g), dim3(kPathThreads), 0, s, L.values, L.nx, L.ny, L.nz,
-                     L.sign, L.next);
-  hipLaunchKernelGGL(path_sink_kernel, dim3(g), dim3(kPathThreads), 0, s, L.next, n, L.sink);
-  hipLaunchKernelGGL(path_stats_init_kernel, dim3(1), dim3(64), 0, s, L.stats);
-  hipLaunchKernelGGL(path_stats_kernel, dim3(g), dim3(kPathThreads), 0, s, L.next, L.sink, L.nx, L.ny, L.nz,
-                     L.cx, L.cy, L.cz, L.stats);
-  hipLaunchKernelGGL(path_stats_final_kernel, dim3(1), dim3(64), 0, s, L.sink, L.nx, L.ny, L.nz, L.cx, L.cy,
-                     L.cz, L.stats);
+  hipLaunchKernelGGL(path_next_kernel, dim3(path_grid(n, kPathThreads, 8192)), dim3(kPathThreads), 0, s, L.values, L.nx,
+                     L.ny, L.nz, L.sign, L.next, L.stats);
+  hipLaunchKernelGGL(path_sink_kernel, dim3(path_grid(n, kSinkThreads, 2048)), dim3(kSinkThreads), 0, s, L.next, L.nx,
+                     L.ny, L.nz, L.cx, L.cy, L.cz, L.sink, L.stats);
   return hipGetLastError();
 }
 
