@@ -492,8 +492,20 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   RowMap* rows = (RowMap*)(ws + L.rowmap);
   const bool fq = moving->dtype == MI_F32;
   void* gvol = ws + L.gvol;
+  const size_t bb = (size_t)bins * bins;
+  double* table = (double*)(ws + L.table);
+  uint64_t* count = (uint64_t*)(ws + L.count);
+  unsigned long long* nlist = (unsigned long long*)(ws + L.nlist);
   // a sampled call always prepares (its list is not part of the record)
-  if (smp || !reuse_prep(ctx, flags, prep_key(2, ws, L, fixed, moving, bins))) {
+  const bool prepare = smp || !reuse_prep(ctx, flags, prep_key(2, ws, L, fixed, moving, bins));
+  ClearList clear;
+  clear.add(table, 8 * bb * n);
+  clear.add(count, 8 * (size_t)n);
+  if (grad_out) clear.add(grad_out, 8 * (size_t)n * n_q * 12);
+  if (prepare) clear.add(rows->used, sizeof rows->used);
+  if (smp) clear.add(nlist, 8);
+  if ((e = launch_clear(clear, s)) != hipSuccess) return hip_fail(e, "clear");
+  if (prepare) {
     if ((e = launch_prebin_fixed(desc(fixed), bins, fb, kVoxelOrder, s)) != hipSuccess) return hip_fail(e, "prebin");
     if ((e = launch_row_map(fb, voxels(fixed), bins, rows, s)) != hipSuccess) return hip_fail(e, "row map");
     if ((e = launch_tile_mask(fb, fixed->nx, fixed->ny, fixed->nz, (uint32_t*)(ws + L.tmask), s)) != hipSuccess)
@@ -505,22 +517,12 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
     if (e != hipSuccess) return hip_fail(e, "pack");
   }
   uint2* list = (uint2*)(ws + L.list);
-  unsigned long long* nlist = (unsigned long long*)(ws + L.nlist);
   if (smp) {
     ctx->last_prep.clear();
-    if ((e = launch_fill_u32((uint32_t*)nlist, 2, 0u, s)) != hipSuccess) return hip_fail(e, "fill");
     if ((e = launch_sample_list(fb, fixed->nx, fixed->ny, fixed->nz, smp->fraction, smp->seed, list, nlist, s)) !=
         hipSuccess)
       return hip_fail(e, "sample list");
   }
-  const size_t bb = (size_t)bins * bins;
-  double* table = (double*)(ws + L.table);
-  uint64_t* count = (uint64_t*)(ws + L.count);
-  if ((e = launch_fill_f64(table, bb * n, s)) != hipSuccess) return hip_fail(e, "fill");
-  if ((e = launch_fill_u32((uint32_t*)count, 2 * (size_t)n, 0u, s)) != hipSuccess) return hip_fail(e, "fill");
-  if (grad_out && (e = launch_fill_f64(grad_out, (size_t)n * n_q * 12, s)) != hipSuccess)
-    return hip_fail(e, "fill");
-
   ParzenLaunch P;
   memset(&P, 0, sizeof P);
   ParzenArgs& a = P.args;
@@ -890,13 +892,19 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   const bool brick = !smp && call_brick(flags, tune);
   const int32_t gather = smp ? oct_gather(moving->lo, moving->hi) : call_gather(moving, n, flags, tune);
   const size_t bb = (size_t)bins * bins;
+  uint64_t* count = (uint64_t*)(ws + L.count);
+  unsigned long long* nlist = (unsigned long long*)(ws + L.nlist);
+  ClearList clear;
+  clear.add(hist, 4 * bb * n);
+  clear.add(count, 8 * (size_t)n);
+  if (smp) clear.add(nlist, 8);
+  if ((e = launch_clear(clear, s)) != hipSuccess) return hip_fail(e, "clear");
   // a sampled call always prepares (its list is not part of the record)
   if (prepare && (smp || !reuse_prep(ctx, flags, prep_key(hard_prep_path(gather, brick), ws, L, fixed, moving, bins)))) {
     if ((e = launch_prebin_fixed(desc(fixed), bins, fb, smp ? kVoxelOrder : (brick ? kCubeOrder : kRunOrder), s)) != hipSuccess) return hip_fail(e, "prebin");
     e = launch_pack_moving(desc(moving), gather, gvol, s);
     if (e != hipSuccess) return hip_fail(e, "pack");
   }
-  if ((e = launch_fill_u32(hist, bb * n, 0u, s)) != hipSuccess) return hip_fail(e, "fill");
   HardLaunch H{};
   H.transforms = transforms;
   H.fbins = fb;
@@ -905,6 +913,7 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   H.fixed = desc(fixed);
   H.moving = desc(moving);
   H.hist = hist;
+  H.count = count;
   H.n = n;
   H.bins = bins;
   H.clamp = (flags & MI_BOUNDARY_CLAMP) ? 1 : 0;
@@ -913,10 +922,8 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   H.slab_major = tune.slab_major;
   H.brick = brick ? 1 : 0;
   uint2* list = (uint2*)(ws + L.list);
-  unsigned long long* nlist = (unsigned long long*)(ws + L.nlist);
   if (smp) {
     ctx->last_prep.clear();
-    if ((e = launch_fill_u32((uint32_t*)nlist, 2, 0u, s)) != hipSuccess) return hip_fail(e, "fill");
     if ((e = launch_sample_list(fb, fixed->nx, fixed->ny, fixed->nz, smp->fraction, smp->seed, list, nlist, s)) !=
         hipSuccess)
       return hip_fail(e, "sample list");
@@ -944,6 +951,7 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
     part.n = (int32_t)(n - t0 < per_launch ? n - t0 : per_launch);
     part.transforms = transforms + 12 * t0;
     part.hist = hist + bb * t0;
+    part.count = count + t0;
     if (ordered) {
       part.order = order + t0;
       part.order_t0 = t0;
@@ -1200,6 +1208,7 @@ int run_pairs(mi_context* ctx, const mi_pair* pairs, int32_t n_pairs, int32_t bi
   a.counters = (unsigned long long*)(ws + plan.counters);
   a.transforms = (double*)(ws + plan.transforms);
   a.hist = (uint32_t*)(ws + plan.hist);
+  a.count = (uint64_t*)(ws + plan.count);
   a.bins = bins;
   a.transform_major = tune.transform_major;
   L.total_t = plan.total_t;
@@ -1213,8 +1222,11 @@ int run_pairs(mi_context* ctx, const mi_pair* pairs, int32_t n_pairs, int32_t bi
   const size_t bb = (size_t)bins * bins;
   auto body = [&]() -> int {
     hipError_t err;
-    if ((err = launch_fill_u32((uint32_t*)a.counters, 16, 0u, s)) != hipSuccess) return hip_fail(err, "fill");
-    if ((err = launch_fill_u32(a.hist, bb * plan.total_t, 0u, s)) != hipSuccess) return hip_fail(err, "fill");
+    ClearList clear;
+    clear.add(a.counters, 64);
+    clear.add(a.hist, 4 * bb * plan.total_t);
+    clear.add(a.count, 8 * plan.total_t);
+    if ((err = launch_clear(clear, s)) != hipSuccess) return hip_fail(err, "clear");
     if ((err = launch_pairs_prep(L, s, prepare)) != hipSuccess) return hip_fail(err, "pairs prep");
     {
       TimedLaunch tl(ctx, 3, s);
@@ -1225,7 +1237,7 @@ int run_pairs(mi_context* ctx, const mi_pair* pairs, int32_t n_pairs, int32_t bi
     ReduceLaunch R;
     memset(&R, 0, sizeof R);
     R.hist = a.hist;
-    R.count = (uint64_t*)(ws + plan.count);
+    R.count = a.count;
     R.part = (double*)(ws + plan.part);
     R.transforms = a.transforms;
     R.n = (int32_t)plan.total_t;

@@ -248,6 +248,7 @@ struct HardLaunch {
   const void* gvol;          // moving gather volume in layout `gather` (Gather)
   VolumeDesc fixed, moving;
   uint32_t* hist;  // [n][B][B]
+  uint64_t* count;  // [n]: each transform's sum of counts is added
   int32_t gather;
   int32_t n, bins, clamp;
   int32_t chunks;  // workgroups per transform, multiple of 8
@@ -383,13 +384,10 @@ __host__ __device__ inline void slice_rows(int B, int S, int s, int& r0, int& r1
   r1 = (int)(((int64_t)B * (s + 1)) / S);
 }
 
-// Slices with at most this many cells and marginals keep p and ln p in LDS.
-constexpr int kMaxSliceCells = 2304;
-
 struct ReduceLaunch {
   const uint32_t* hist;  // [n][B][B] counts, or NULL when `table` is used
   const double* table;   // [n][B][B] Parzen masses, or NULL
-  uint64_t* count;       // [n] N: given with a table; summed from hist otherwise
+  uint64_t* count;       // [n] N < 2^28; the upper 32 bits are 0 before and after
   double* part;          // reduce_part_bytes(n, B, n_q) of partial sums
   const double* transforms;
   int32_t n, bins;
@@ -491,14 +489,25 @@ hipError_t lds_register(const void* kernel);
 // keep no static LDS.
 hipError_t lds_guard(const void* kernel, size_t dynamic, size_t configured_max, bool at_zero = false);
 
-hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t value, hipStream_t s);
+// Zeroes up to kMax arrays (4-byte aligned, whole words) in one launch.
+struct ClearList {
+  static constexpr int32_t kMax = 5;
+  uint32_t* p[kMax] = {};
+  size_t words[kMax] = {};
+  int32_t n = 0;
+  void add(void* q, size_t bytes) {
+    if (bytes == 0) return;
+    p[n] = (uint32_t*)q;
+    words[n++] = bytes / 4;
+  }
+};
+hipError_t launch_clear(const ClearList& l, hipStream_t s);
 // Index-space matrices M[n][12] of the caller's physical matrices P[n][12].
 hipError_t launch_compose(const double* P, int64_t n, const Geometry& g, double* M, hipStream_t s);
 // d MI / d P from d MI / d M in place, rows of 12 (gradients of `rows`
 // transform-entropy pairs): G_P[r][c] = (G_M[r][c] fsp[c] + G_M[r][3] forg[c]) / msp[r],
 // G_P[r][3] = G_M[r][3] / msp[r].
 hipError_t launch_grad_physical(double* grad, int64_t rows, const Geometry& g, hipStream_t s);
-hipError_t launch_fill_f64(double* p, size_t n, hipStream_t s);
 // The order of a fixed volume's bins: voxel order, or that the thin-slab
 // (fixed_run_x) or brick (cube_run_x) sweeps read.
 enum FixedOrder : int32_t { kVoxelOrder = 0, kRunOrder = 1, kCubeOrder = 2 };
@@ -547,6 +556,7 @@ struct PairsArgs {
   unsigned long long* counters;  // [8] work-queue heads
   double* transforms;        // [T][12], gathered and composed to index space
   uint32_t* hist;            // [T][B][B]
+  uint64_t* count;           // [T]: sums of the counts
   int32_t bins;
   int32_t transform_major;   // work-item order within a pair: 0 slab-major, 1 transform-major
 };

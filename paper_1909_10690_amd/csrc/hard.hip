@@ -85,16 +85,15 @@ hipError_t lds_guard(const void* kernel, size_t dynamic, size_t configured_max, 
   return hipErrorInvalidValue;
 }
 
-__global__ void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
-__global__ void fill_f64_kernel(double* __restrict__ p, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x)
-    p[i] = 0.0;
+// The arrays one after the other: each in 16-byte stores where its address
+// and length allow.
+__global__ __launch_bounds__(256) void clear_kernel(ClearList l) {
+  const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+  for (int k = 0; k < l.n; ++k) {
+    const size_t n = l.words[k], quads = ((uintptr_t)l.p[k] & 15) == 0 ? n / 4 : 0;
+    for (size_t i = i0; i < quads; i += step) ((uint4_t*)l.p[k])[i] = uint4_t{0u, 0u, 0u, 0u};
+    for (size_t i = 4 * quads + i0; i < n; i += step) l.p[k][i] = 0;
+  }
 }
 
 static unsigned fill_grid(size_t n) {
@@ -104,15 +103,11 @@ static unsigned fill_grid(size_t n) {
   return (unsigned)g;
 }
 
-hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t value, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(fill_grid(n)), dim3(256), 0, s, p, n, value);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_f64(double* p, size_t n, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_f64_kernel, dim3(fill_grid(n)), dim3(256), 0, s, p, n);
+hipError_t launch_clear(const ClearList& l, hipStream_t s) {
+  size_t most = 0;
+  for (int k = 0; k < l.n; ++k) most = l.words[k] > most ? l.words[k] : most;
+  if (most == 0) return hipSuccess;
+  hipLaunchKernelGGL(clear_kernel, dim3(fill_grid((most + 3) / 4)), dim3(256), 0, s, l);
   return hipGetLastError();
 }
 
@@ -390,6 +385,7 @@ constexpr size_t kHardLdsMax = 160 * 1024;
 struct HardArgs {
   const double* transforms;
   uint32_t* hist;
+  uint64_t* count;
   HardGeom geom;
   int32_t n, chunks;
   int32_t slab_major;     // 1: consecutive workgroups of an XCD share a slab
@@ -422,7 +418,7 @@ void hist_hard_kernel(HardArgs a) {
       sweep_hard<CLAMP, PACKED, GL, NT / 64>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
   }
   __syncthreads();
-  if (ok) flush_hist<PACKED, NT>(lds_hist, B, a.hist + (size_t)t * B * B, false);
+  if (ok) flush_hist<PACKED, NT>(lds_hist, B, a.hist + (size_t)t * B * B, a.count + t, false);
 }
 
 // Sampled sweep: the workgroup's share of the sample list (entries
@@ -460,7 +456,7 @@ __global__ __launch_bounds__(NT) void hist_sampled_kernel(HardArgs a, const uint
       }
     }
     __syncthreads();
-    if (ok) flush_hist<PACKED, NT>(lds_hist, B, out, true);
+    if (ok) flush_hist<PACKED, NT>(lds_hist, B, out, a.count + t, true);
   }
 }
 
@@ -553,6 +549,7 @@ hipError_t launch_hist_hard(const HardLaunch& L, hipStream_t s) {
   HardArgs a;
   a.transforms = L.transforms;
   a.hist = L.hist;
+  a.count = L.count;
   a.geom = make_hard_geom(L.fixed, L.moving, L.fbins, L.gvol, L.gather, L.bins);
   a.n = L.n;
   a.chunks = L.chunks;
@@ -570,6 +567,7 @@ hipError_t launch_hist_hard(const HardLaunch& L, hipStream_t s) {
     b.n = L.n - t0 < step ? L.n - t0 : step;
     b.transforms = a.transforms + 12 * (size_t)t0;
     b.hist = a.hist + (size_t)t0 * L.bins * L.bins;
+    b.count = a.count + t0;
     if (ordered) {
       b.order = L.order + t0;
       b.order_base = (uint32_t)(L.order_t0 + t0);
@@ -593,6 +591,7 @@ hipError_t launch_hist_sampled(const HardLaunch& L, const uint2* list, const uns
   HardArgs a;
   a.transforms = L.transforms;
   a.hist = L.hist;
+  a.count = L.count;
   a.geom = make_hard_geom(L.fixed, L.moving, L.fbins, L.gvol, L.gather, L.bins);
   a.n = L.n;
   a.chunks = L.chunks;
@@ -621,6 +620,7 @@ hipError_t launch_hist_sampled(const HardLaunch& L, const uint2* list, const uns
     b.n = L.n - t0 < step ? L.n - t0 : step;
     b.transforms = a.transforms + 12 * (size_t)t0;
     b.hist = a.hist + (size_t)t0 * L.bins * L.bins;
+    b.count = a.count + t0;
     const hipError_t e = one(b);
     if (e != hipSuccess) return e;
   }

@@ -327,7 +327,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void hi
       sweep_rods<CLAMP, PACKED, GL, NT / 64>(geom, Md, Ms, chunks, chunk, lds_hist);
     }
     __syncthreads();
-    if (ok) flush_hist<PACKED, NT>(lds_hist, B, a.hist + (size_t)t * B * B, true);
+    if (ok) flush_hist<PACKED, NT>(lds_hist, B, a.hist + (size_t)t * B * B, a.count + t, true);
     __syncthreads();
   }
 }

@@ -176,7 +176,6 @@ __global__ __launch_bounds__(256) void remap_rows_kernel(uint8_t* __restrict__ f
 
 hipError_t launch_row_map(uint8_t* fbins, size_t nvox, int32_t bins, RowMap* m, hipStream_t s) {
   hipError_t e;
-  if ((e = launch_fill_u32(m->used, 256, 0u, s)) != hipSuccess) return e;
   const size_t blocks = (nvox / 16 + 255) / 256;
   const unsigned grid = (unsigned)(blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks));
   hipLaunchKernelGGL(rows_used_kernel, dim3(grid), dim3(256), 0, s, (const uint8_t*)fbins, nvox, m->used);

@@ -434,11 +434,14 @@ __device__ __forceinline__ void clear_hist(uint32_t* lds_hist, int B) {
 // A row holds at most 256 counter words (B <= 256), four per lane, so each
 // row is unrolled into four fixed chunks whose addresses differ from the
 // first by immediate offsets.
+// The counts' sum is added to *count, by one atomic per call: the waves' sums
+// meet in a padding word of the first row, which is 0 before and after.
 template <bool PACKED, int NT>
 __device__ __forceinline__ void flush_hist(uint32_t* lds_hist, int B, uint32_t* __restrict__ out,
-                                           bool rezero) {
+                                           uint64_t* __restrict__ count, bool rezero) {
   const int pitch = hist_row_words(B, PACKED), used = PACKED ? (B + 1) / 2 : B;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  uint32_t sum = 0;
   for (int r = wave; r < B; r += NT / 64) {
     uint32_t* __restrict__ row = out + (size_t)r * B;
     uint32_t* src = lds_hist + r * pitch;
@@ -452,12 +455,23 @@ __device__ __forceinline__ void flush_hist(uint32_t* lds_hist, int B, uint32_t* 
       if (v == 0) continue;
       if (rezero) src[w] = 0;
       if (PACKED) {
+        sum += (v & 0xFFFFu) + (v >> 16);
         if (v & 0xFFFFu) atomicAdd(&row[2 * w], v & 0xFFFFu);
         if (v >> 16) atomicAdd(&row[2 * w + 1], v >> 16);  // never set past the row's last bin
       } else {
+        sum += v;
         atomicAdd(&row[w], v);
       }
     }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  if (lane == 0 && sum) atomicAdd(&lds_hist[used], sum);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t all = lds_hist[used];
+    if (all) atomicAdd((unsigned long long*)count, (unsigned long long)all);
+    lds_hist[used] = 0;
   }
 }
 
