@@ -506,10 +506,10 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   if (smp) clear.add(nlist, 8);
   if ((e = launch_clear(clear, s)) != hipSuccess) return hip_fail(e, "clear");
   if (prepare) {
-    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, kVoxelOrder, s)) != hipSuccess) return hip_fail(e, "prebin");
-    if ((e = launch_row_map(fb, voxels(fixed), bins, rows, s)) != hipSuccess) return hip_fail(e, "row map");
-    if ((e = launch_tile_mask(fb, fixed->nx, fixed->ny, fixed->nz, (uint32_t*)(ws + L.tmask), s)) != hipSuccess)
-      return hip_fail(e, "tile mask");
+    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, kVoxelOrder, s, rows->used)) != hipSuccess)
+      return hip_fail(e, "prebin");
+    if ((e = launch_slots(fb, fixed->nx, fixed->ny, fixed->nz, bins, rows, (uint32_t*)(ws + L.tmask), s)) != hipSuccess)
+      return hip_fail(e, "slots");
     if (smp)
       e = fq ? launch_pack_copy_f32(desc(moving), (float*)gvol, s) : launch_pack_copy(desc(moving), (uint16_t*)gvol, s);
     else

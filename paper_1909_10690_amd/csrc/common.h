@@ -515,7 +515,10 @@ template <int ORDER>
 __host__ __device__ constexpr int32_t stored_x(int32_t p, int32_t nx) {
   return ORDER == kRunOrder ? fixed_run_x(p, nx) : (ORDER == kCubeOrder ? cube_run_x(p, nx) : p);
 }
-hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, FixedOrder order, hipStream_t s);
+// In voxel order, used[256] (if given, zeroed before) gets a 1 for every bin
+// that some voxel falls in.
+hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, FixedOrder order, hipStream_t s,
+                               uint32_t* used = nullptr);
 // The moving volume in layout `gather`.
 hipError_t launch_pack_moving(const VolumeDesc& m, int32_t gather, void* out, hipStream_t s);
 hipError_t launch_pack_copy(const VolumeDesc& m, uint16_t* out, hipStream_t s);
@@ -578,9 +581,10 @@ HardGeom make_hard_geom(const VolumeDesc& fixed, const VolumeDesc& moving, const
 hipError_t launch_mi_reduce(const ReduceLaunch& L, hipStream_t s);
 hipError_t launch_pack_quads_f32(const VolumeDesc& m, float4* out, hipStream_t s);
 hipError_t launch_pack_quads16(const VolumeDesc& m, uint2* out, hipStream_t s);
-hipError_t launch_row_map(uint8_t* fbins, size_t nvox, int32_t bins, RowMap* m, hipStream_t s);
-// Tile masks of the slotted fixed volume (see kSlotGroup).
-hipError_t launch_tile_mask(const uint8_t* slots, int32_t nx, int32_t ny, int32_t nz, uint32_t* mask, hipStream_t s);
+// The row map of m->used, the fixed bins turned into slots in place, and the
+// tile and row group masks (see kSlotGroup).
+hipError_t launch_slots(uint8_t* fbins, int32_t nx, int32_t ny, int32_t nz, int32_t bins, RowMap* m, uint32_t* mask,
+                        hipStream_t s);
 hipError_t launch_parzen_fwd(const ParzenLaunch& L, hipStream_t s);
 hipError_t launch_parzen_sampled_fwd(const ParzenLaunch& L, const uint2* list, const unsigned long long* n_list,
                                      hipStream_t s);

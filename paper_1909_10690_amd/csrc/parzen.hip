@@ -101,131 +101,111 @@ hipError_t launch_pack_quads_f32(const VolumeDesc& m, float4* out, hipStream_t s
   return hipGetLastError();
 }
 
+// Four words at any address.
+typedef unsigned int unaligned128 __attribute__((ext_vector_type(4), aligned(1)));
+
 // ---------------------------------------------------------------------------
 // occupied fixed-bin rows
 // ---------------------------------------------------------------------------
 
-// used[b] = 1 for every bin b that some fixed voxel falls in.  Each thread
-// scans 16 consecutive voxels and marks a bin only where it differs from
-// the previous voxel and is not yet marked, so long runs of one bin (air)
-// cost no LDS writes.
-__global__ __launch_bounds__(256) void rows_used_kernel(const uint8_t* __restrict__ fb, size_t n,
-                                                        uint32_t* __restrict__ used) {
-  __shared__ uint32_t u[256];
-  u[threadIdx.x] = 0;
+// Row map, slots and tile masks of a call in one pass over the fixed bins.
+// Every workgroup forms the map (rank of each occupied row among the occupied
+// ones) from `used` for itself, the first one stores it.  A wave per row group
+// (kTileY rows of one slice), a lane per wave tile of it: the lane's bins
+// become slots in place, the OR of their slot groups is the tile's mask, and
+// the wave's OR the row group's.  Bound by launches and latency on small
+// volumes: map, remapping, tile and row masks had a launch each and the bins a
+// second and third pass (512x512x300: 136 us, now 40; 128^3: 26 us, now 8).
+__global__ __launch_bounds__(256) void slots_kernel(uint8_t* __restrict__ fb, int32_t nx, int32_t ny, int32_t nz,
+                                                    int32_t bins, RowMap* __restrict__ m,
+                                                    uint32_t* __restrict__ mask) {
+  __shared__ uint32_t slot[256], wave_used[4];
+  const int r = threadIdx.x, wave = r >> 6, lane = r & 63;
+  const bool used = r < bins && m->used[r] != 0;
+  const uint64_t mine = __builtin_amdgcn_ballot_w64(used);
+  if (lane == 0) wave_used[wave] = (uint32_t)__popcll(mine);
   __syncthreads();
-  const size_t n16 = n / 16;
-  const uint4* __restrict__ v = (const uint4*)fb;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x) {
-    const uint4 w = v[i];
-    const uint32_t words[4] = {w.x, w.y, w.z, w.w};
-    uint32_t prev = 0x100u;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const uint32_t b = (words[k >> 2] >> ((k & 3) * 8)) & 0xFFu;
-      if (b != prev && !u[b]) u[b] = 1u;
-      prev = b;
-    }
+  uint32_t rank = (uint32_t)__popcll(mine & ((1ull << lane) - 1)), total = 0;
+  for (int w = 0; w < 4; ++w) {
+    rank += w < wave ? wave_used[w] : 0u;
+    total += wave_used[w];
   }
-  if (blockIdx.x == 0)
-    for (size_t i = n16 * 16 + threadIdx.x; i < n; i += blockDim.x) u[fb[i]] = 1u;
-  __syncthreads();
-  if (u[threadIdx.x]) used[threadIdx.x] = 1u;
-}
-
-// Slots: rank of each occupied row among the occupied rows (one workgroup).
-__global__ __launch_bounds__(256) void row_map_kernel(RowMap* m, int32_t bins) {
-  __shared__ uint32_t pre[256];
-  const int r = threadIdx.x;
-  const uint32_t used = (r < bins && m->used[r]) ? 1u : 0u;
-  pre[r] = used;
-  __syncthreads();
-  if (r == 0) {
-    uint32_t sum = 0;
-    for (int i = 0; i < 256; ++i) {
-      const uint32_t u = pre[i];
-      pre[i] = sum;
-      sum += u;
-    }
-    m->n_slots = sum;
+  slot[r] = used ? rank : 0u;
+  if (blockIdx.x == 0) {
+    m->slot_of_row[r] = used ? rank : 0u;
+    if (used) m->row_of_slot[rank] = (uint32_t)r;
+    if (r == 0) m->n_slots = total;
   }
   __syncthreads();
-  m->slot_of_row[r] = used ? pre[r] : 0u;
-  if (used) m->row_of_slot[pre[r]] = (uint32_t)r;
-}
-
-// fbins[i] <- slot of fbins[i], 16 voxels per thread.
-__global__ __launch_bounds__(256) void remap_rows_kernel(uint8_t* __restrict__ fb, size_t n,
-                                                         const RowMap* __restrict__ m) {
-  __shared__ uint32_t slot[256];
-  slot[threadIdx.x] = m->slot_of_row[threadIdx.x];
-  __syncthreads();
-  const size_t n16 = n / 16;
-  uint4* __restrict__ v = (uint4*)fb;
-  auto map4 = [&](uint32_t w) -> uint32_t {
-    return slot[w & 0xFFu] | (slot[(w >> 8) & 0xFFu] << 8) | (slot[(w >> 16) & 0xFFu] << 16) |
-           (slot[w >> 24] << 24);
-  };
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x) {
-    const uint4 w = v[i];
-    v[i] = make_uint4(map4(w.x), map4(w.y), map4(w.z), map4(w.w));
-  }
-  if (blockIdx.x == 0)
-    for (size_t i = n16 * 16 + threadIdx.x; i < n; i += blockDim.x) fb[i] = (uint8_t)slot[fb[i]];
-}
-
-hipError_t launch_row_map(uint8_t* fbins, size_t nvox, int32_t bins, RowMap* m, hipStream_t s) {
-  hipError_t e;
-  const size_t blocks = (nvox / 16 + 255) / 256;
-  const unsigned grid = (unsigned)(blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks));
-  hipLaunchKernelGGL(rows_used_kernel, dim3(grid), dim3(256), 0, s, (const uint8_t*)fbins, nvox, m->used);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(row_map_kernel, dim3(1), dim3(256), 0, s, m, bins);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(remap_rows_kernel, dim3(grid), dim3(256), 0, s, fbins, nvox, (const RowMap*)m);
-  return hipGetLastError();
-}
-
-// One thread per wave tile (kTileX x kTileY voxels of one slice): the OR of
-// the slot groups of its voxels.
-__global__ __launch_bounds__(256) void tile_mask_kernel(const uint8_t* __restrict__ slots, int32_t nx, int32_t ny,
-                                                        int32_t nz, uint32_t* __restrict__ mask) {
   const int32_t XT = (nx + kTileX - 1) / kTileX, G = (ny + kTileY - 1) / kTileY;
-  const int64_t tiles = (int64_t)G * nz * XT;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tiles; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t g = t / XT;
-    const int32_t xt = (int32_t)(t - g * XT);
+  const int64_t groups = (int64_t)G * nz;
+  uint32_t* __restrict__ row_mask = mask + groups * XT;
+  for (int64_t g = blockIdx.x * 4ll + wave; g < groups; g += gridDim.x * 4ll) {
     const int32_t k = (int32_t)(g / G), j0 = (int32_t)(g - (int64_t)k * G) * kTileY;
-    const int32_t x0 = xt * kTileX, x1 = min(nx, x0 + kTileX);
-    uint32_t m = 0;
-    for (int32_t j = j0; j < min(ny, j0 + kTileY); ++j) {
-      const uint8_t* row = slots + ((int64_t)k * ny + j) * nx;
-      for (int32_t x = x0; x < x1; ++x) m |= 1u << (row[x] / kSlotGroup);
+    uint32_t all = 0;
+    for (int32_t t = lane; t < XT; t += 64) {
+      const int32_t x0 = t * kTileX;
+      uint8_t* const tile = fb + ((int64_t)k * ny + j0) * nx + x0;
+      const int32_t rows = min(kTileY, ny - j0), cols = min(kTileX, nx - x0);
+      uint32_t bits = 0;
+      auto map = [&](uint32_t b) -> uint32_t {
+        const uint32_t s = slot[b];
+        bits |= 1u << (s / kSlotGroup);
+        return s;
+      };
+      const bool whole = cols == kTileX && rows == kTileY;
+      unaligned128 v[kTileY];  // all loads before the first store; past the tile its last voxels again
+      if (whole) {
+#pragma unroll
+        for (int j = 0; j < kTileY; ++j) v[j] = *(const unaligned128*)(tile + (int64_t)j * nx);
+      } else {
+#pragma unroll
+        for (int j = 0; j < kTileY; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            uint32_t o = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o |= (uint32_t)tile[(int64_t)min(j, rows - 1) * nx + min(4 * i + c, cols - 1)] << (8 * c);
+            v[j][i] = o;
+          }
+      }
+#pragma unroll
+      for (int j = 0; j < kTileY; ++j) {
+        uint32_t prev = v[j][0] & 0xFFu, s = map(prev);  // a run of one bin is looked up once
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint32_t o = 0;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const uint32_t b = (v[j][i] >> (8 * c)) & 0xFFu;
+            if (b != prev) s = map(b);
+            prev = b;
+            o |= s << (8 * c);
+          }
+          v[j][i] = o;
+        }
+        if (whole) {
+          *(unaligned128*)(tile + (int64_t)j * nx) = v[j];
+        } else {
+#pragma unroll
+          for (int c = 0; c < kTileX; ++c)
+            if (j < rows && c < cols) tile[(int64_t)j * nx + c] = (uint8_t)(v[j][c >> 2] >> (8 * (c & 3)));
+        }
+      }
+      mask[g * XT + t] = bits;
+      all |= bits;
     }
-    mask[t] = m;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) all |= __shfl_xor(all, off, 64);
+    if (lane == 0) row_mask[g] = all;
   }
 }
 
-// One thread per row group: the OR of its tiles' masks, after the tiles.
-__global__ __launch_bounds__(256) void row_mask_kernel(int32_t XT, int64_t groups, uint32_t* __restrict__ mask) {
-  const uint32_t* __restrict__ tiles = mask;
-  uint32_t* __restrict__ rows = mask + groups * XT;
-  for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < groups; g += (int64_t)gridDim.x * blockDim.x) {
-    uint32_t m = 0;
-    for (int32_t t = 0; t < XT; ++t) m |= tiles[g * XT + t];
-    rows[g] = m;
-  }
-}
-
-hipError_t launch_tile_mask(const uint8_t* slots, int32_t nx, int32_t ny, int32_t nz, uint32_t* mask, hipStream_t s) {
-  const int64_t tiles = parzen_tiles(nx, ny, nz);
-  const int64_t blocks = (tiles + 255) / 256;
-  hipLaunchKernelGGL(tile_mask_kernel, dim3((unsigned)(blocks < 8192 ? (blocks > 0 ? blocks : 1) : 8192)), dim3(256),
-                     0, s, slots, nx, ny, nz, mask);
-  const int64_t groups = parzen_row_groups(ny, nz);
-  const int64_t gblocks = (groups + 255) / 256;
-  hipLaunchKernelGGL(row_mask_kernel, dim3((unsigned)(gblocks < 8192 ? (gblocks > 0 ? gblocks : 1) : 8192)),
-                     dim3(256), 0, s, (int32_t)((nx + kTileX - 1) / kTileX), groups, mask);
+hipError_t launch_slots(uint8_t* fbins, int32_t nx, int32_t ny, int32_t nz, int32_t bins, RowMap* m, uint32_t* mask,
+                        hipStream_t s) {
+  const int64_t blocks = (parzen_row_groups(ny, nz) + 3) / 4;
+  hipLaunchKernelGGL(slots_kernel, dim3((unsigned)(blocks < 4096 ? (blocks > 0 ? blocks : 1) : 4096)), dim3(256), 0, s,
+                     fbins, nx, ny, nz, bins, m, mask);
   return hipGetLastError();
 }
 
