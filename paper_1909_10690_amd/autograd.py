@@ -38,7 +38,11 @@ def centred_matrices(params: torch.Tensor, centre) -> torch.Tensor:
     (A.flat, t), differentiably."""
     A = params[:, :9].reshape(-1, 3, 3)
     t = params[:, 9:]
-    c = torch.as_tensor(centre, dtype=params.dtype, device=params.device).reshape(3)
+    if isinstance(centre, torch.Tensor):
+        c = torch.as_tensor(centre, dtype=params.dtype, device=params.device)
+    else:  # a copy of its own, which need not wait for the device to have reached it
+        c = torch.tensor(centre, dtype=params.dtype).to(params.device, non_blocking=True)
+    c = c.reshape(3)
     off = c + t - (A @ c.unsqueeze(-1)).squeeze(-1)
     return torch.cat([A, off.unsqueeze(-1)], dim=2).reshape(-1, 12)
 
