@@ -481,13 +481,12 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
                const ParzenTune* tune_override = nullptr) {
   const ParzenTune tune = tune_override ? *tune_override : parzen_tune_for(ctx, fixed, moving, n, bins, flags);
   hipError_t e;
-  // the caller's physical matrices -> index-space matrices in the workspace
-  {
-    double* M = (double*)(ws + L.xf);
-    if ((e = launch_compose(transforms, n, geometry(fixed, moving), M, s)) != hipSuccess)
-      return hip_fail(e, "compose");
-    transforms = M;
-  }
+  Prepare pre;
+  pre.P = transforms;
+  pre.M = (double*)(ws + L.xf);
+  pre.n = n;
+  pre.geo = geometry(fixed, moving);
+  transforms = pre.M;
   uint8_t* fb = (uint8_t*)(ws + L.fbins);
   RowMap* rows = (RowMap*)(ws + L.rowmap);
   const bool fq = moving->dtype == MI_F32;
@@ -498,23 +497,28 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   unsigned long long* nlist = (unsigned long long*)(ws + L.nlist);
   // a sampled call always prepares (its list is not part of the record)
   const bool prepare = smp || !reuse_prep(ctx, flags, prep_key(2, ws, L, fixed, moving, bins));
-  ClearList clear;
-  clear.add(table, 8 * bb * n);
-  clear.add(count, 8 * (size_t)n);
-  if (grad_out) clear.add(grad_out, 8 * (size_t)n * n_q * 12);
-  if (prepare) clear.add(rows->used, sizeof rows->used);
-  if (smp) clear.add(nlist, 8);
-  if ((e = launch_clear(clear, s)) != hipSuccess) return hip_fail(e, "clear");
+  pre.clear.add(table, 8 * bb * n);
+  pre.clear.add(count, 8 * (size_t)n);
+  if (grad_out) pre.clear.add(grad_out, 8 * (size_t)n * n_q * 12);
+  if (prepare) pre.clear.add(rows->used, sizeof rows->used);
+  if (smp) pre.clear.add(nlist, 8);
+  const bool copy = prepare && smp && !fq;
+  if (copy) {
+    pre.gvol = gvol;
+    pre.m = desc(moving);
+    pre.gather = kCopy16;
+  }
+  if ((e = launch_prepare(pre, s)) != hipSuccess) return hip_fail(e, "prepare");
   if (prepare) {
-    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, kVoxelOrder, s, rows->used)) != hipSuccess)
-      return hip_fail(e, "prebin");
+    if ((e = launch_prebin_voxels(desc(fixed), bins, fb, rows->used, s)) != hipSuccess) return hip_fail(e, "prebin");
     if ((e = launch_slots(fb, fixed->nx, fixed->ny, fixed->nz, bins, rows, (uint32_t*)(ws + L.tmask), s)) != hipSuccess)
       return hip_fail(e, "slots");
-    if (smp)
-      e = fq ? launch_pack_copy_f32(desc(moving), (float*)gvol, s) : launch_pack_copy(desc(moving), (uint16_t*)gvol, s);
-    else
-      e = fq ? launch_pack_quads_f32(desc(moving), (float4*)gvol, s) : launch_pack_quads16(desc(moving), (uint2*)gvol, s);
-    if (e != hipSuccess) return hip_fail(e, "pack");
+    if (!copy) {
+      e = smp  ? launch_pack_copy_f32(desc(moving), (float*)gvol, s)
+          : fq ? launch_pack_quads_f32(desc(moving), (float4*)gvol, s)
+               : launch_pack_quads16(desc(moving), (uint2*)gvol, s);
+      if (e != hipSuccess) return hip_fail(e, "pack");
+    }
   }
   uint2* list = (uint2*)(ws + L.list);
   if (smp) {
@@ -881,9 +885,11 @@ int graph_run(mi_context* ctx, const std::vector<uint64_t>& key, hipStream_t s, 
 
 // ---- the hard-binned path ---------------------------------------------------
 
-// Fixed bins, moving volume, zeroed histograms and the sweep (no reduction).
-int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
-                     const double* transforms, int32_t n, int32_t bins, int32_t flags,
+// Index-space matrices of the caller's (unless `physical` is NULL: they are
+// there), fixed bins, moving volume, zeroed histograms and the sweep (no
+// reduction).
+int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving, const double* physical,
+                     double* transforms, int32_t n, int32_t bins, int32_t flags,
                      uint32_t* hist, char* ws, const Layout& L, hipStream_t s,
                      const HardTune& tune, bool prepare, const SampleSpec* smp = nullptr) {
   hipError_t e;
@@ -894,17 +900,25 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   const size_t bb = (size_t)bins * bins;
   uint64_t* count = (uint64_t*)(ws + L.count);
   unsigned long long* nlist = (unsigned long long*)(ws + L.nlist);
-  ClearList clear;
-  clear.add(hist, 4 * bb * n);
-  clear.add(count, 8 * (size_t)n);
-  if (smp) clear.add(nlist, 8);
-  if ((e = launch_clear(clear, s)) != hipSuccess) return hip_fail(e, "clear");
+  Prepare pre;
+  pre.P = physical;
+  pre.M = transforms;
+  pre.n = n;
+  pre.geo = geometry(fixed, moving);
+  pre.clear.add(hist, 4 * bb * n);
+  pre.clear.add(count, 8 * (size_t)n);
+  if (smp) pre.clear.add(nlist, 8);
   // a sampled call always prepares (its list is not part of the record)
   if (prepare && (smp || !reuse_prep(ctx, flags, prep_key(hard_prep_path(gather, brick), ws, L, fixed, moving, bins)))) {
-    if ((e = launch_prebin_fixed(desc(fixed), bins, fb, smp ? kVoxelOrder : (brick ? kCubeOrder : kRunOrder), s)) != hipSuccess) return hip_fail(e, "prebin");
-    e = launch_pack_moving(desc(moving), gather, gvol, s);
-    if (e != hipSuccess) return hip_fail(e, "pack");
+    pre.fbins = fb;
+    pre.f = desc(fixed);
+    pre.bins = bins;
+    pre.order = smp ? kVoxelOrder : (brick ? kCubeOrder : kRunOrder);
+    pre.gvol = gvol;
+    pre.m = desc(moving);
+    pre.gather = gather;
   }
+  if ((e = launch_prepare(pre, s)) != hipSuccess) return hip_fail(e, "prepare");
   HardLaunch H{};
   H.transforms = transforms;
   H.fbins = fb;
@@ -969,19 +983,15 @@ int run_hard(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
              int32_t flags, double* mi_out, uint64_t* overlap_out, uint32_t* hist_out, char* ws,
              const Layout& L, hipStream_t s, const HardTune& tune, const SampleSpec* smp = nullptr) {
   uint32_t* hist = hist_out ? hist_out : (uint32_t*)(ws + L.hist);
-  // the caller's physical matrices -> index-space matrices in the workspace
   double* M = (double*)(ws + L.xf);
-  hipError_t ce = launch_compose(transforms, n, geometry(fixed, moving), M, s);
-  if (ce != hipSuccess) return hip_fail(ce, "compose");
-  transforms = M;
-  int st = launch_hard_hist(ctx, fixed, moving, transforms, n, bins, flags, hist, ws, L, s, tune, true, smp);
+  int st = launch_hard_hist(ctx, fixed, moving, transforms, M, n, bins, flags, hist, ws, L, s, tune, true, smp);
   if (st != MI_OK) return st;
   ReduceLaunch R;
   memset(&R, 0, sizeof R);
   R.hist = hist;
   R.count = (uint64_t*)(ws + L.count);
   R.part = (double*)(ws + L.part);
-  R.transforms = transforms;
+  R.transforms = M;
   R.n = n;
   R.bins = bins;
   R.q = qlist(q, n_q, flags);
@@ -1222,11 +1232,11 @@ int run_pairs(mi_context* ctx, const mi_pair* pairs, int32_t n_pairs, int32_t bi
   const size_t bb = (size_t)bins * bins;
   auto body = [&]() -> int {
     hipError_t err;
-    ClearList clear;
-    clear.add(a.counters, 64);
-    clear.add(a.hist, 4 * bb * plan.total_t);
-    clear.add(a.count, 8 * plan.total_t);
-    if ((err = launch_clear(clear, s)) != hipSuccess) return hip_fail(err, "clear");
+    Prepare pre;
+    pre.clear.add(a.counters, 64);
+    pre.clear.add(a.hist, 4 * bb * plan.total_t);
+    pre.clear.add(a.count, 8 * plan.total_t);
+    if ((err = launch_prepare(pre, s)) != hipSuccess) return hip_fail(err, "prepare");
     if ((err = launch_pairs_prep(L, s, prepare)) != hipSuccess) return hip_fail(err, "pairs prep");
     {
       TimedLaunch tl(ctx, 3, s);
@@ -1423,18 +1433,11 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   if ((e = hipSetDevice(ctx->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
   char* ws = (char*)workspace;
   uint32_t* hist = (uint32_t*)(ws + L.hist);
-  // the caller's physical matrices -> index-space matrices, once
-  {
-    double* M = (double*)(ws + L.xf);
-    if ((e = launch_compose(transforms, n, geometry(fixed, moving), M, s)) != hipSuccess)
-      return hip_fail(e, "compose");
-    transforms = M;
-  }
+  double* M = (double*)(ws + L.xf);
   const bool was_timing = ctx->timing;
   ctx->timing = false;
   // fixed bins and moving volume, again when a candidate's layout differs
-  st = launch_hard_hist(ctx, fixed, moving, transforms, n, bins, flags, hist, ws, L, s,
-                        ctx->hard_default, true);
+  st = launch_hard_hist(ctx, fixed, moving, transforms, M, n, bins, flags, hist, ws, L, s, ctx->hard_default, true);
   bool prepared_brick = call_brick(flags, ctx->hard_default);
   hipEvent_t t0 = nullptr, t1 = nullptr;
   if (st == MI_OK && ((e = hipEventCreate(&t0)) != hipSuccess || (e = hipEventCreate(&t1)) != hipSuccess))
@@ -1463,7 +1466,7 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
           if ((e = hipEventRecord(t0, s)) != hipSuccess) { st = hip_fail(e, "tune"); break; }
           const bool prepare = rep == 0 && call_brick(flags, cand) != prepared_brick;  // the first run is not timed
           if (prepare) ctx->last_prep.clear();
-          st = launch_hard_hist(ctx, fixed, moving, transforms, n, bins, flags, hist, ws, L, s, cand, prepare);
+          st = launch_hard_hist(ctx, fixed, moving, nullptr, M, n, bins, flags, hist, ws, L, s, cand, prepare);
           prepared_brick = call_brick(flags, cand);
           if (st != MI_OK) break;
           if ((e = hipEventRecord(t1, s)) != hipSuccess || (e = hipEventSynchronize(t1)) != hipSuccess) {

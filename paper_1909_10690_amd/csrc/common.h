@@ -489,7 +489,7 @@ hipError_t lds_register(const void* kernel);
 // keep no static LDS.
 hipError_t lds_guard(const void* kernel, size_t dynamic, size_t configured_max, bool at_zero = false);
 
-// Zeroes up to kMax arrays (4-byte aligned, whole words) in one launch.
+// Up to kMax arrays to zero (4-byte aligned, whole words).
 struct ClearList {
   static constexpr int32_t kMax = 5;
   uint32_t* p[kMax] = {};
@@ -501,9 +501,6 @@ struct ClearList {
     words[n++] = bytes / 4;
   }
 };
-hipError_t launch_clear(const ClearList& l, hipStream_t s);
-// Index-space matrices M[n][12] of the caller's physical matrices P[n][12].
-hipError_t launch_compose(const double* P, int64_t n, const Geometry& g, double* M, hipStream_t s);
 // d MI / d P from d MI / d M in place, rows of 12 (gradients of `rows`
 // transform-entropy pairs): G_P[r][c] = (G_M[r][c] fsp[c] + G_M[r][3] forg[c]) / msp[r],
 // G_P[r][3] = G_M[r][3] / msp[r].
@@ -515,13 +512,28 @@ template <int ORDER>
 __host__ __device__ constexpr int32_t stored_x(int32_t p, int32_t nx) {
   return ORDER == kRunOrder ? fixed_run_x(p, nx) : (ORDER == kCubeOrder ? cube_run_x(p, nx) : p);
 }
-// In voxel order, used[256] (if given, zeroed before) gets a 1 for every bin
-// that some voxel falls in.
-hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, FixedOrder order, hipStream_t s,
-                               uint32_t* used = nullptr);
-// The moving volume in layout `gather`.
-hipError_t launch_pack_moving(const VolumeDesc& m, int32_t gather, void* out, hipStream_t s);
-hipError_t launch_pack_copy(const VolumeDesc& m, uint16_t* out, hipStream_t s);
+// The bins in voxel order; used[256], if given (zeroed before), gets a 1 for
+// every bin that some voxel falls in.
+hipError_t launch_prebin_voxels(const VolumeDesc& f, int bins, uint8_t* out, uint32_t* used, hipStream_t s);
+
+// What a call does before its sweep, in one launch; each part only if given.
+struct Prepare {
+  // index-space matrices M[n][12] of the caller's physical matrices P[n][12]
+  const double* P = nullptr;
+  double* M = nullptr;
+  int64_t n = 0;
+  Geometry geo = {};
+  ClearList clear;
+  // the fixed volume's bins, in an order of FixedOrder
+  uint8_t* fbins = nullptr;
+  VolumeDesc f = {};
+  int32_t bins = 0, order = 0;
+  // the integer moving volume in layout `gather`
+  void* gvol = nullptr;
+  VolumeDesc m = {};
+  int32_t gather = 0;
+};
+hipError_t launch_prepare(const Prepare& p, hipStream_t s);
 hipError_t launch_pack_copy_f32(const VolumeDesc& m, float* out, hipStream_t s);
 hipError_t launch_hist_hard(const HardLaunch& L, hipStream_t s);
 // Random subsampling (sample.hip): the kept fixed voxels as list entries

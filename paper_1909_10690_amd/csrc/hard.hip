@@ -30,6 +30,7 @@
 #include "common.h"
 #include "sweep.h"
 
+#include <algorithm>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -86,9 +87,9 @@ hipError_t lds_guard(const void* kernel, size_t dynamic, size_t configured_max, 
 }
 
 // The arrays one after the other: each in 16-byte stores where its address
-// and length allow.
-__global__ __launch_bounds__(256) void clear_kernel(ClearList l) {
-  const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+// and length allow.  Block b of nb.
+__device__ __forceinline__ void clear_arrays(const ClearList& l, uint32_t b, uint32_t nb) {
+  const size_t i0 = b * (size_t)256 + threadIdx.x, step = (size_t)nb * 256;
   for (int k = 0; k < l.n; ++k) {
     const size_t n = l.words[k], quads = ((uintptr_t)l.p[k] & 15) == 0 ? n / 4 : 0;
     for (size_t i = i0; i < quads; i += step) ((uint4_t*)l.p[k])[i] = uint4_t{0u, 0u, 0u, 0u};
@@ -103,14 +104,6 @@ static unsigned fill_grid(size_t n) {
   return (unsigned)g;
 }
 
-hipError_t launch_clear(const ClearList& l, hipStream_t s) {
-  size_t most = 0;
-  for (int k = 0; k < l.n; ++k) most = l.words[k] > most ? l.words[k] : most;
-  if (most == 0) return hipSuccess;
-  hipLaunchKernelGGL(clear_kernel, dim3(fill_grid((most + 3) / 4)), dim3(256), 0, s, l);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // fixed-volume binning, once per call
 // ---------------------------------------------------------------------------
@@ -121,8 +114,8 @@ hipError_t launch_clear(const ClearList& l, hipStream_t s) {
 // given, gets a 1 for every bin some voxel falls in.
 template <int ORDER, typename F>
 __device__ __forceinline__ void prebin(int32_t nx, uint32_t rows, uint8_t* __restrict__ out,
-                                       uint32_t* __restrict__ used, F&& bin) {
-  const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+                                       uint32_t* __restrict__ used, uint32_t block, uint32_t nb, F&& bin) {
+  const uint32_t i0 = block * 256 + threadIdx.x, step = nb * 256;
   if (ORDER == kVoxelOrder) {
     __shared__ uint32_t seen[256];
     if (used) {
@@ -144,7 +137,7 @@ __device__ __forceinline__ void prebin(int32_t nx, uint32_t rows, uint8_t* __res
       }
       ((uint4*)out)[i] = make_uint4(w[0], w[1], w[2], w[3]);
     }
-    if (blockIdx.x == 0 && threadIdx.x < nvox - 16 * n16) {
+    if (block == 0 && threadIdx.x < nvox - 16 * n16) {
       const uint32_t i = 16 * n16 + threadIdx.x, b = bin(i);
       out[i] = (uint8_t)b;
       if (used) seen[b] = 1u;
@@ -170,59 +163,58 @@ __device__ __forceinline__ void prebin(int32_t nx, uint32_t rows, uint8_t* __res
   }
 }
 
-template <int ORDER, typename T>
-__global__ __launch_bounds__(256) void prebin_int_kernel(const T* __restrict__ u, int32_t nx, uint32_t rows, int32_t lo,
-                                                         int32_t hi, uint32_t bins, Divider div,
-                                                         uint8_t* __restrict__ out, uint32_t* __restrict__ used) {
-  prebin<ORDER>(nx, rows, out, used, [&](uint32_t i) { return fixed_bin_int((int32_t)u[i], lo, hi, bins, div); });
-}
-
+// Block `block` of nb of the binning of volume f into `bins` bins; div: of its
+// integer range.
 template <int ORDER>
-__global__ __launch_bounds__(256) void prebin_f32_kernel(const float* __restrict__ u, int32_t nx, uint32_t rows,
-                                                         double lo, double hi, int32_t bins,
-                                                         uint8_t* __restrict__ out, uint32_t* __restrict__ used) {
-  prebin<ORDER>(nx, rows, out, used, [&](uint32_t i) { return fixed_bin_real((double)u[i], lo, hi, bins); });
-}
-
-template <int ORDER>
-static hipError_t prebin_variant(const VolumeDesc& f, int bins, uint8_t* out, uint32_t* used, hipStream_t s) {
-  const size_t nvox = (size_t)f.nx * f.ny * f.nz;
+__device__ __forceinline__ void prebin_volume(const VolumeDesc& f, int32_t bins, Divider div, uint8_t* __restrict__ out,
+                                              uint32_t* __restrict__ used, uint32_t block, uint32_t nb) {
   const uint32_t rows = (uint32_t)f.ny * (uint32_t)f.nz;
-  const unsigned grid = fill_grid(ORDER != kVoxelOrder ? (size_t)rows * ((f.nx + 3) / 4) : nvox / 16);
   const int32_t lo = (int32_t)f.lo, hi = (int32_t)f.hi;
-  const Divider d = f.dtype == 3 ? Divider{0, 0} : make_divider((uint32_t)(hi - lo + 1));
-  switch (f.dtype) {
-  case 0:
-    hipLaunchKernelGGL((prebin_int_kernel<ORDER, uint8_t>), dim3(grid), dim3(256), 0, s, (const uint8_t*)f.data, f.nx,
-                       rows, lo, hi, (uint32_t)bins, d, out, used);
-    break;
-  case 1:
-    hipLaunchKernelGGL((prebin_int_kernel<ORDER, uint16_t>), dim3(grid), dim3(256), 0, s, (const uint16_t*)f.data, f.nx,
-                       rows, lo, hi, (uint32_t)bins, d, out, used);
-    break;
-  case 2:
-    hipLaunchKernelGGL((prebin_int_kernel<ORDER, int16_t>), dim3(grid), dim3(256), 0, s, (const int16_t*)f.data, f.nx,
-                       rows, lo, hi, (uint32_t)bins, d, out, used);
-    break;
-  default:
-    hipLaunchKernelGGL((prebin_f32_kernel<ORDER>), dim3(grid), dim3(256), 0, s, (const float*)f.data, f.nx, rows, f.lo,
-                       f.hi, bins, out, used);
+  auto whole = [&]<typename T>(const T* __restrict__ u) {
+    prebin<ORDER>(f.nx, rows, out, used, block, nb,
+                  [&](uint32_t i) { return fixed_bin_int((int32_t)u[i], lo, hi, (uint32_t)bins, div); });
+  };
+  switch (f.dtype) {  // the same for every thread
+  case 0: whole((const uint8_t*)f.data); break;
+  case 1: whole((const uint16_t*)f.data); break;
+  case 2: whole((const int16_t*)f.data); break;
+  default: {
+    const float* __restrict__ u = (const float*)f.data;
+    prebin<ORDER>(f.nx, rows, out, used, block, nb,
+                  [&](uint32_t i) { return fixed_bin_real((double)u[i], f.lo, f.hi, bins); });
   }
-  return hipGetLastError();
+  }
 }
 
-hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, FixedOrder order, hipStream_t s,
-                               uint32_t* used) {
-  switch (order) {
-  case kRunOrder: return prebin_variant<kRunOrder>(f, bins, out, nullptr, s);
-  case kCubeOrder: return prebin_variant<kCubeOrder>(f, bins, out, nullptr, s);
-  default: return prebin_variant<kVoxelOrder>(f, bins, out, used, s);
-  }
+static Divider fixed_divider(const VolumeDesc& f) {
+  return f.dtype == 3 ? Divider{0, 0} : make_divider((uint32_t)((int32_t)f.hi - (int32_t)f.lo + 1));
+}
+
+__global__ __launch_bounds__(256) void prebin_kernel(VolumeDesc f, int32_t bins, Divider div,
+                                                     uint8_t* __restrict__ out, uint32_t* __restrict__ used) {
+  prebin_volume<kVoxelOrder>(f, bins, div, out, used, blockIdx.x, gridDim.x);
+}
+
+hipError_t launch_prebin_voxels(const VolumeDesc& f, int bins, uint8_t* out, uint32_t* used, hipStream_t s) {
+  const size_t nvox = (size_t)f.nx * f.ny * f.nz;
+  hipLaunchKernelGGL(prebin_kernel, dim3(fill_grid(nvox / 16)), dim3(256), 0, s, f, bins, fixed_divider(f), out, used);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // moving oct volume, once per call
 // ---------------------------------------------------------------------------
+
+// A preparation block's row part: 256 voxels of row (y, z).
+struct RowBlock {
+  int32_t x0, y, z;
+  __device__ __forceinline__ RowBlock(int32_t nx, int32_t ny, uint32_t block) {
+    const uint32_t per = ((uint32_t)nx + 255) / 256, row = block / per;
+    x0 = (int32_t)(256 * (block - row * per));
+    z = (int32_t)(row / (uint32_t)ny);
+    y = (int32_t)(row - (uint32_t)z * (uint32_t)ny);
+  }
+};
 
 // out[z][y][x] holds the eight 16-bit clamped, offset intensities
 // v' = clamp(v, lo, hi) - lo of the voxel's 2x2x2 neighbourhood, so one
@@ -234,10 +226,12 @@ hipError_t launch_prebin_fixed(const VolumeDesc& f, int bins, uint8_t* out, Fixe
 // along that axis vanishes.
 // DIFF (kOctD): each word holds -(v0' + v1') in its low half and v1' - v0' in
 // its high half instead.
+// Block `block`: 256 voxels of a row.
 template <typename T, bool DIFF>
-__global__ void pack_octs_kernel(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz,
-                                 int32_t lo, int32_t hi, uint4* __restrict__ out) {
-  const int32_t y = blockIdx.y, z = blockIdx.z;
+__device__ __forceinline__ void pack_octs(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz, int32_t lo,
+                                          int32_t hi, uint4* __restrict__ out, uint32_t block) {
+  const RowBlock rb(nx, ny, block);
+  const int32_t y = rb.y, z = rb.z;
   uint4* __restrict__ orow = out + ((size_t)z * ny + y) * nx;
   const T* __restrict__ r00 = v + ((size_t)z * ny + y) * nx;
   const T* __restrict__ r10 = r00 + (y + 1 < ny ? nx : 0);
@@ -245,7 +239,8 @@ __global__ void pack_octs_kernel(const T* __restrict__ v, int32_t nx, int32_t ny
   const T* __restrict__ r01 = r00 + dz;
   const T* __restrict__ r11 = r10 + dz;
   auto c = [&](T raw) -> uint32_t { return clamp_offset((int32_t)raw, lo, hi); };
-  for (int32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < nx; x += gridDim.x * blockDim.x) {
+  const int32_t x = rb.x0 + (int32_t)threadIdx.x;
+  if (x < nx) {
     const int32_t x1 = x + 1 < nx ? x + 1 : nx - 1;
     auto pair = [&](const T* r) -> uint32_t {
       const uint32_t v0 = c(r[x]), v1 = c(r[x1]);
@@ -259,9 +254,10 @@ __global__ void pack_octs_kernel(const T* __restrict__ v, int32_t nx, int32_t ny
 // 4 dz + 2 dy + dx' of the element holds (x + dx', y + dy, z + dz), dx' = 0
 // for x and 1 for x1.
 template <typename T>
-__global__ void pack_oct8_kernel(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz,
-                                 int32_t lo, int32_t hi, uint2* __restrict__ out) {
-  const int32_t y = blockIdx.y, z = blockIdx.z;
+__device__ __forceinline__ void pack_oct8(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz, int32_t lo,
+                                          int32_t hi, uint2* __restrict__ out, uint32_t block) {
+  const RowBlock rb(nx, ny, block);
+  const int32_t y = rb.y, z = rb.z;
   uint2* __restrict__ orow = out + ((size_t)z * ny + y) * nx;
   const T* __restrict__ r00 = v + ((size_t)z * ny + y) * nx;
   const T* __restrict__ r10 = r00 + (y + 1 < ny ? nx : 0);
@@ -269,46 +265,12 @@ __global__ void pack_oct8_kernel(const T* __restrict__ v, int32_t nx, int32_t ny
   const T* __restrict__ r01 = r00 + dz;
   const T* __restrict__ r11 = r10 + dz;
   auto c = [&](T raw) -> uint32_t { return clamp_offset((int32_t)raw, lo, hi); };
-  for (int32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < nx; x += gridDim.x * blockDim.x) {
+  const int32_t x = rb.x0 + (int32_t)threadIdx.x;
+  if (x < nx) {
     const int32_t x1 = x + 1 < nx ? x + 1 : nx - 1;
     orow[x] = make_uint2(c(r00[x]) | (c(r00[x1]) << 8) | (c(r10[x]) << 16) | (c(r10[x1]) << 24),
                          c(r01[x]) | (c(r01[x1]) << 8) | (c(r11[x]) << 16) | (c(r11[x1]) << 24));
   }
-}
-
-static hipError_t launch_pack_oct8(const VolumeDesc& m, uint2* out, hipStream_t s) {
-  const dim3 grid((unsigned)((m.nx + 255) / 256), (unsigned)m.ny, (unsigned)m.nz);
-  const int32_t lo = (int32_t)m.lo, hi = (int32_t)m.hi;
-  if (m.dtype == 0)
-    hipLaunchKernelGGL(pack_oct8_kernel<uint8_t>, grid, dim3(256), 0, s, (const uint8_t*)m.data,
-                       m.nx, m.ny, m.nz, lo, hi, out);
-  else if (m.dtype == 1)
-    hipLaunchKernelGGL(pack_oct8_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t*)m.data,
-                       m.nx, m.ny, m.nz, lo, hi, out);
-  else if (m.dtype == 2)
-    hipLaunchKernelGGL(pack_oct8_kernel<int16_t>, grid, dim3(256), 0, s, (const int16_t*)m.data,
-                       m.nx, m.ny, m.nz, lo, hi, out);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-template <bool DIFF>
-static hipError_t pack_octs_variant(const VolumeDesc& m, uint4* out, hipStream_t s) {
-  const dim3 grid((unsigned)((m.nx + 255) / 256), (unsigned)m.ny, (unsigned)m.nz);
-  const int32_t lo = (int32_t)m.lo, hi = (int32_t)m.hi;
-  if (m.dtype == 0)
-    hipLaunchKernelGGL((pack_octs_kernel<uint8_t, DIFF>), grid, dim3(256), 0, s, (const uint8_t*)m.data, m.nx, m.ny,
-                       m.nz, lo, hi, out);
-  else if (m.dtype == 1)
-    hipLaunchKernelGGL((pack_octs_kernel<uint16_t, DIFF>), grid, dim3(256), 0, s, (const uint16_t*)m.data, m.nx, m.ny,
-                       m.nz, lo, hi, out);
-  else if (m.dtype == 2)
-    hipLaunchKernelGGL((pack_octs_kernel<int16_t, DIFF>), grid, dim3(256), 0, s, (const int16_t*)m.data, m.nx, m.ny,
-                       m.nz, lo, hi, out);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
 }
 
 // Octs in tiles (tiled_index), one record per thread: records of a tile are
@@ -317,12 +279,12 @@ static hipError_t pack_octs_variant(const VolumeDesc& m, uint4* out, hipStream_t
 // 88 us against 36 for rows of octs, which a map of rotations repays in one
 // transform of its hundreds).
 template <typename T, int BASE>
-__global__ __launch_bounds__(256) void pack_tiled_kernel(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz,
-                                                         int32_t lo, int32_t hi, void* __restrict__ out) {
+__device__ __forceinline__ void pack_tiled(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz, int32_t lo,
+                                           int32_t hi, void* __restrict__ out, uint32_t block, uint32_t nb) {
   constexpr uint32_t kx = BASE == kOct8 ? 4 : 2;  // tile width
   const uint32_t n = (uint32_t)nx * (uint32_t)ny * (uint32_t)nz;  // < 2^28
   auto c = [&](uint32_t i) -> uint32_t { return clamp_offset((int32_t)v[i], lo, hi); };
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+  for (uint32_t i = block * 256 + threadIdx.x; i < n; i += nb * 256) {
     const uint32_t tile = i / (4 * kx), low = i - tile * (4 * kx);
     const uint32_t tr = tile / ((uint32_t)nx / kx), tz = tr / ((uint32_t)ny / 2);
     const uint32_t x = (tile - tr * ((uint32_t)nx / kx)) * kx + low % kx;
@@ -343,66 +305,110 @@ __global__ __launch_bounds__(256) void pack_tiled_kernel(const T* __restrict__ v
   }
 }
 
-template <int BASE>
-static hipError_t pack_tiled_variant(const VolumeDesc& m, void* out, hipStream_t s) {
-  const unsigned grid = fill_grid((size_t)m.nx * m.ny * m.nz);
-  const int32_t lo = (int32_t)m.lo, hi = (int32_t)m.hi;
-  if (m.dtype == 0)
-    hipLaunchKernelGGL((pack_tiled_kernel<uint8_t, BASE>), dim3(grid), dim3(256), 0, s, (const uint8_t*)m.data, m.nx,
-                       m.ny, m.nz, lo, hi, out);
-  else if (m.dtype == 1)
-    hipLaunchKernelGGL((pack_tiled_kernel<uint16_t, BASE>), dim3(grid), dim3(256), 0, s, (const uint16_t*)m.data, m.nx,
-                       m.ny, m.nz, lo, hi, out);
-  else if (m.dtype == 2)
-    hipLaunchKernelGGL((pack_tiled_kernel<int16_t, BASE>), dim3(grid), dim3(256), 0, s, (const int16_t*)m.data, m.nx,
-                       m.ny, m.nz, lo, hi, out);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
 // out[i] = clamp(v[i], lo, hi) - lo as 16 bits (moving_copy_bytes), 8 voxels
 // per lane with one load and one 16-byte store where the source is aligned
 // to 8 voxels.
 template <typename T>
-__global__ __launch_bounds__(256) void pack_copy_kernel(const T* __restrict__ v, size_t nvox, int32_t lo,
-                                                          int32_t hi, uint16_t* __restrict__ out) {
+__device__ __forceinline__ void pack_copy(const T* __restrict__ v, size_t nvox, int32_t lo, int32_t hi,
+                                          uint16_t* __restrict__ out, uint32_t block, uint32_t nb) {
   typedef const __attribute__((address_space(1))) T gT;
-  const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+  const size_t i0 = block * (size_t)256 + threadIdx.x, step = (size_t)nb * 256;
   const size_t n8 = ((uintptr_t)v & (8 * sizeof(T) - 1)) == 0 ? nvox / 8 : 0;
   for (size_t i = i0; i < n8; i += step) ((vec4u*)out)[i] = load_offset8((gT*)v + 8 * i, lo, hi);
   for (size_t i = 8 * n8 + i0; i < nvox; i += step) out[i] = (uint16_t)clamp_offset((int32_t)v[i], lo, hi);
 }
 
-hipError_t launch_pack_copy(const VolumeDesc& m, uint16_t* out, hipStream_t s) {
-  const size_t nvox = (size_t)m.nx * m.ny * m.nz;
-  const unsigned grid = fill_grid((nvox + 7) / 8);
+// Block `block` of nb of an integer moving volume in layout `gather`.
+__device__ __forceinline__ void pack_volume(const VolumeDesc& m, int32_t gather, void* __restrict__ out, uint32_t block,
+                                            uint32_t nb) {
   const int32_t lo = (int32_t)m.lo, hi = (int32_t)m.hi;
-  if (m.dtype == 0)
-    hipLaunchKernelGGL(pack_copy_kernel<uint8_t>, dim3(grid), dim3(256), 0, s, (const uint8_t*)m.data, nvox, lo, hi,
-                       out);
-  else if (m.dtype == 1)
-    hipLaunchKernelGGL(pack_copy_kernel<uint16_t>, dim3(grid), dim3(256), 0, s, (const uint16_t*)m.data, nvox, lo,
-                       hi, out);
-  else if (m.dtype == 2)
-    hipLaunchKernelGGL(pack_copy_kernel<int16_t>, dim3(grid), dim3(256), 0, s, (const int16_t*)m.data, nvox, lo, hi,
-                       out);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  auto whole = [&]<typename T>(const T* __restrict__ v) {
+    switch (gather) {
+    case kOct16: pack_octs<T, false>(v, m.nx, m.ny, m.nz, lo, hi, (uint4*)out, block); break;
+    case kOctD: pack_octs<T, true>(v, m.nx, m.ny, m.nz, lo, hi, (uint4*)out, block); break;
+    case kOct8: pack_oct8(v, m.nx, m.ny, m.nz, lo, hi, (uint2*)out, block); break;
+    case kCopy16: pack_copy(v, (size_t)m.nx * m.ny * m.nz, lo, hi, (uint16_t*)out, block, nb); break;
+    case kOct16 | kTiled: pack_tiled<T, kOct16>(v, m.nx, m.ny, m.nz, lo, hi, out, block, nb); break;
+    case kOctD | kTiled: pack_tiled<T, kOctD>(v, m.nx, m.ny, m.nz, lo, hi, out, block, nb); break;
+    case kOct8 | kTiled: pack_tiled<T, kOct8>(v, m.nx, m.ny, m.nz, lo, hi, out, block, nb); break;
+    }
+  };
+  switch (m.dtype) {  // the same for every thread
+  case 0: whole((const uint8_t*)m.data); break;
+  case 1: whole((const uint16_t*)m.data); break;
+  case 2: whole((const int16_t*)m.data); break;
+  }
 }
 
-hipError_t launch_pack_moving(const VolumeDesc& m, int32_t gather, void* out, hipStream_t s) {
-  switch (gather) {
-  case kOct16: return pack_octs_variant<false>(m, (uint4*)out, s);
-  case kOctD: return pack_octs_variant<true>(m, (uint4*)out, s);
-  case kOct8: return launch_pack_oct8(m, (uint2*)out, s);
-  case kCopy16: return launch_pack_copy(m, (uint16_t*)out, s);
-  case kOct16 | kTiled: return pack_tiled_variant<kOct16>(m, out, s);
-  case kOctD | kTiled: return pack_tiled_variant<kOctD>(m, out, s);
-  case kOct8 | kTiled: return pack_tiled_variant<kOct8>(m, out, s);
-  default: return hipErrorInvalidValue;
+static unsigned pack_blocks(const VolumeDesc& m, int32_t gather) {
+  const size_t nvox = (size_t)m.nx * m.ny * m.nz;
+  if (gather == kCopy16) return fill_grid((nvox + 7) / 8);
+  if (gather & kTiled) return fill_grid(nvox);
+  return (unsigned)((m.nx + 255) / 256) * (unsigned)m.ny * (unsigned)m.nz;  // a block per row part, <= 2^24
+}
+
+// ---------------------------------------------------------------------------
+// what a call does before its sweep
+// ---------------------------------------------------------------------------
+
+struct PrepareArgs {
+  Prepare p;
+  Divider div;
+  uint32_t pack, bin, clear;  // workgroups of each part; the transforms take the rest
+};
+
+// The parts depend on nothing but the caller's inputs, so they share a launch,
+// the longest first: a small call (48^3, one transform) is mostly launches of
+// 2 to 3 us.
+__global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
+  uint32_t block = blockIdx.x;
+  if (block < a.pack) {
+    pack_volume(a.p.m, a.p.gather, a.p.gvol, block, a.pack);
+    return;
   }
+  block -= a.pack;
+  if (block < a.bin) {
+    switch (a.p.order) {
+    case kRunOrder: prebin_volume<kRunOrder>(a.p.f, a.p.bins, a.div, a.p.fbins, nullptr, block, a.bin); break;
+    case kCubeOrder: prebin_volume<kCubeOrder>(a.p.f, a.p.bins, a.div, a.p.fbins, nullptr, block, a.bin); break;
+    default: prebin_volume<kVoxelOrder>(a.p.f, a.p.bins, a.div, a.p.fbins, nullptr, block, a.bin);
+    }
+    return;
+  }
+  block -= a.bin;
+  if (block < a.clear) {
+    clear_arrays(a.p.clear, block, a.clear);
+    return;
+  }
+  block -= a.clear;
+  const int64_t step = (gridDim.x - a.pack - a.bin - a.clear) * 256ll;
+  for (int64_t t = block * 256ll + threadIdx.x; t < a.p.n; t += step) {
+    double m[12];
+    compose_index_matrix(a.p.P + 12 * t, a.p.geo, m);
+#pragma unroll
+    for (int e = 0; e < 12; ++e) a.p.M[12 * t + e] = m[e];
+  }
+}
+
+hipError_t launch_prepare(const Prepare& p, hipStream_t s) {
+  PrepareArgs a{p, Divider{0, 0}, 0, 0, 0};
+  if (p.gvol) {
+    if (p.m.dtype > 2) return hipErrorInvalidValue;
+    a.pack = pack_blocks(p.m, p.gather);
+  }
+  if (p.fbins) {
+    a.div = fixed_divider(p.f);
+    const size_t rows = (size_t)p.f.ny * p.f.nz;
+    a.bin = fill_grid(p.order == kVoxelOrder ? rows * p.f.nx / 16 : rows * ((p.f.nx + 3) / 4));
+  }
+  size_t most = 0;
+  for (int k = 0; k < p.clear.n; ++k) most = p.clear.words[k] > most ? p.clear.words[k] : most;
+  if (most) a.clear = fill_grid((most + 3) / 4);
+  const unsigned compose = p.P && p.n > 0 ? std::min(fill_grid((size_t)p.n), 4096u) : 0u;
+  const unsigned grid = a.pack + a.bin + a.clear + compose;
+  if (grid == 0) return hipSuccess;
+  hipLaunchKernelGGL(prepare_kernel, dim3(grid), dim3(256), 0, s, a);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
