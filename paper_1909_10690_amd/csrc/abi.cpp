@@ -378,6 +378,8 @@ int32_t call_gather(const mi_volume* m, int32_t n, int32_t flags, const HardTune
 }
 int hard_prep_path(int32_t gather, bool brick) { return 8 + 2 * gather + (brick ? 1 : 0); }
 
+constexpr size_t kL2Bytes = 4 << 20;  // of an XCD
+
 // Slabs per transform that keep one slab's share of the moving gather
 // volume near 1.5 MiB: the workgroups of an XCD sweep one slab for many
 // transforms at once, and their moving footprint must stay in the XCD's
@@ -952,9 +954,14 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   // one slab for consecutive transforms, so those are put in an order that
   // keeps their moving footprints together (launch_order_transforms; the
   // multi-modal sweep's 1000 transforms 16.8 -> 13.5 ms).  Launches then
-  // start at multiples of the order's sorted blocks.
+  // start at multiples of the order's sorted blocks.  A moving layout within
+  // one XCD's L2 stays there in any order, and sorting takes 5 to 18 us (us a
+  // call sorted and not: 64^3 u16, 64 bins, 120 affines 87 and 79, 1000 of
+  // them 455 and 440; 96^3 u16, 13.5 MiB, 1000 affines 1151 and 1206,
+  // rotations 2629 and 3242).
   uint32_t* order = (uint32_t*)(ws + L.order);
-  const bool ordered = !smp && !H.brick && H.slab_major && n >= 64 && per_launch >= kOrderBlock;
+  const bool ordered = !smp && !H.brick && H.slab_major && n >= 64 && per_launch >= kOrderBlock &&
+                       gather_volume_bytes(gather, moving->nx, moving->ny, moving->nz) > kL2Bytes;
   if (ordered) {
     per_launch -= per_launch % kOrderBlock;
     if ((e = launch_order_transforms(transforms, n, fixed->nx, fixed->ny, fixed->nz, order, s)) != hipSuccess)

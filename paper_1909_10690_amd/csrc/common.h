@@ -330,7 +330,8 @@ inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_
 // copy, so a call that prepares its volumes for a few transforms uses the
 // copy (us a call, oct and copy: 256x256x180 u16, 128 bins, one transform 122
 // and 97, four 257 and 229, six 328 and 338; 128^3 u8, 64 bins, four 66 and
-// 65, six 80 and 86).
+// 65, six 80 and 86, both with preparation and reduction in more launches than
+// now).
 constexpr int32_t kCopyTransforms = 4;
 inline int32_t oct_gather(double lo, double hi) {
   return oct8_range(lo, hi) ? kOct8 : (hi - lo < 16384.0 ? kOctD : kOct16);

@@ -207,3 +207,23 @@ def test_pair_tiles(ctx, mdt, lo, hi, shift, bins):
         torch.cuda.synchronize()
         w = np.concatenate([x[clamp] for x in want])
         assert np.all(np.abs(got.cpu().numpy() - w) <= 1e-12 * np.maximum(1.0, np.abs(w)))
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 64), (68, 64, 61), (80, 64, 64)])
+@pytest.mark.parametrize("n", [64, 4150])
+def test_order_around_the_l2(ctx, shape, n):
+    """Moving layouts of 4 MiB (batch order) and of a little more (processing
+    order, one sorted block and two): every histogram, overlap and MI equals
+    that of the same transform in a batch of 50, which keeps the batch
+    order; the slices of the reduction differ, so MI within 1e-12."""
+    import torch
+    rng = np.random.default_rng(n + shape[0])
+    V = device_volume(inputs.random_volume(rng, shape, np.uint16, 0, 4095), 0, 4095, 0)
+    mats = torch.from_numpy(inputs.random_affines(rng, n, shape, rot=25.0, trans=4.0)).cuda()
+    print(f"order shape={shape} n={n}", flush=True)
+    mi, ov, h = ctx.eval(V, V, mats, 32, (1.0, 1.5), want_hist=True)
+    for t0 in sorted({0, 50, n // 2, n - 50}):
+        mi_s, ov_s, h_s = ctx.eval(V, V, mats[t0:t0 + 50], 32, (1.0, 1.5), want_hist=True)
+        torch.cuda.synchronize()
+        assert torch.equal(h[t0:t0 + 50], h_s) and torch.equal(ov[t0:t0 + 50], ov_s), t0
+        assert torch.all((mi[t0:t0 + 50] - mi_s).abs() <= 1e-12 * torch.clamp(mi_s.abs(), min=1.0))
