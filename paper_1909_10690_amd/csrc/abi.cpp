@@ -504,11 +504,23 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   if (grad_out) pre.clear.add(grad_out, 8 * (size_t)n * n_q * 12);
   if (prepare) pre.clear.add(rows->used, sizeof rows->used);
   if (smp) pre.clear.add(nlist, 8);
+  // a sampled call's moving layout is chosen on the device where the choice
+  // can fall on records (a row rises by one row a step at most, or so)
+  uint32_t* records = nullptr;
+  if (smp) {
+    const double limit = sample_layout_limit(moving->nx, moving->ny, moving->nz, fq);
+    if (limit < 1.0) {
+      records = (uint32_t*)(nlist + 1);  // in the list length's 256 bytes
+      if ((e = launch_sample_layout(pre.P, n, pre.geo, limit, records, s)) != hipSuccess)
+        return hip_fail(e, "sample layout");
+    }
+  }
   const bool copy = prepare && smp && !fq;
   if (copy) {
     pre.gvol = gvol;
     pre.m = desc(moving);
     pre.gather = kCopy16;
+    pre.records = records;
   }
   if ((e = launch_prepare(pre, s)) != hipSuccess) return hip_fail(e, "prepare");
   if (prepare) {
@@ -516,10 +528,12 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
     if ((e = launch_slots(fb, fixed->nx, fixed->ny, fixed->nz, bins, rows, (uint32_t*)(ws + L.tmask), s)) != hipSuccess)
       return hip_fail(e, "slots");
     if (!copy) {
-      e = smp  ? launch_pack_copy_f32(desc(moving), (float*)gvol, s)
+      e = smp  ? launch_pack_copy_f32(desc(moving), (float*)gvol, s, records)
           : fq ? launch_pack_quads_f32(desc(moving), (float4*)gvol, s)
                : launch_pack_quads16(desc(moving), (uint2*)gvol, s);
       if (e != hipSuccess) return hip_fail(e, "pack");
+      if (records && (e = launch_pack_quads_f32(desc(moving), (float4*)gvol, s, records)) != hipSuccess)
+        return hip_fail(e, "pack");
     }
   }
   uint2* list = (uint2*)(ws + L.list);
@@ -553,6 +567,7 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   a.bins = bins;
   a.slab_major = 1;
   a.n_q = n_q;
+  a.records = records;
   a.sscale = (float)((double)(bins - 4) / (moving->hi - moving->lo));
   a.dsdv = (double)(bins - 4) / (moving->hi - moving->lo);
   P.float_quads = fq ? 1 : 0;

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stddef.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "plan.h"
@@ -428,6 +429,7 @@ struct ParzenArgs {
   int32_t mnx, mny, mnz;
   uint32_t gvol_bytes;
   int32_t n, bins, chunks, bands, band_rows, slab_major;
+  const uint32_t* records;  // sampled: see launch_sample_layout, or NULL (the copy)
   int32_t n_q, q0;     // backward: entropies [q0, q0 + NQG) of n_q
   float sscale;        // (B - 4) / (hi - lo)
   double dsdv;         // (B - 4) / (hi - lo), fp64
@@ -533,9 +535,32 @@ struct Prepare {
   void* gvol = nullptr;
   VolumeDesc m = {};
   int32_t gather = 0;
+  // kCopy16 only: where *records is not 0, octs (kOct16) instead
+  const uint32_t* records = nullptr;
 };
+// Layout of a sampled Parzen call's moving volume, chosen on the device, where
+// the matrices are: *records = 1 (octs; float volumes: quads) where the mean
+// over the batch of the rows a step along x rises by, |M[1][0]| / 2 +
+// |M[2][0]|, exceeds `limit`, else 0 (the plain copy).  P: physical matrices.
+hipError_t launch_sample_layout(const double* P, int64_t n, const Geometry& g, double limit, uint32_t* records,
+                                hipStream_t s);
+// The copy's gain is that a line holds several samples of a row; turned, each
+// sample has lines of its own, four of the copy against one of the octs or two
+// of the quads, unless the copy stays in the L2.  Both measured, 64 bins, 100
+// rotations up to +-a about y, 10% of 256x256x180 u16, copy and octs: a = 5
+// degrees 1040 and 1229 us, 10 1473 and 1357, 45 3196 and 1887; 128^3, a = 20
+// 245 and 259, 45 306 and 283; f32, copy and quads: a = 20 2850 and 3066, 45
+// 4058 and 3560.  The limit goes with the root of the copy's bytes: between
+// those sizes, and on the side of the records, which were the only layout.  A
+// copy of less than 1.5 MB stays in the L2 whole: no limit.
+inline double sample_layout_limit(int32_t nx, int32_t ny, int32_t nz, bool f32) {
+  const double mb = (double)moving_copy_bytes(nx, ny, nz) * (f32 ? 2e-6 : 1e-6);
+  return mb < 1.5 ? 1e9 : (f32 ? 1.17 : 0.36) / sqrt(mb);
+}
 hipError_t launch_prepare(const Prepare& p, hipStream_t s);
-hipError_t launch_pack_copy_f32(const VolumeDesc& m, float* out, hipStream_t s);
+// Nothing is written where `records` is given and *records is not 0 (copy) or 0
+// (quads).
+hipError_t launch_pack_copy_f32(const VolumeDesc& m, float* out, hipStream_t s, const uint32_t* records = nullptr);
 hipError_t launch_hist_hard(const HardLaunch& L, hipStream_t s);
 // Random subsampling (sample.hip): the kept fixed voxels as list entries
 // {x | y << 12 | fixed bin << 24, z}; n_list must be zero beforehand.
@@ -592,7 +617,7 @@ hipError_t launch_pairs_hist(const PairsLaunch& L, hipStream_t s);
 HardGeom make_hard_geom(const VolumeDesc& fixed, const VolumeDesc& moving, const uint8_t* fbins,
                         const void* gvol, int32_t gather, int32_t bins);
 hipError_t launch_mi_reduce(const ReduceLaunch& L, hipStream_t s);
-hipError_t launch_pack_quads_f32(const VolumeDesc& m, float4* out, hipStream_t s);
+hipError_t launch_pack_quads_f32(const VolumeDesc& m, float4* out, hipStream_t s, const uint32_t* records = nullptr);
 hipError_t launch_pack_quads16(const VolumeDesc& m, uint2* out, hipStream_t s);
 // The row map of m->used, the fixed bins turned into slots in place, and the
 // tile and row group masks (see kSlotGroup).

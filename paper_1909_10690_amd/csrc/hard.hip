@@ -363,6 +363,11 @@ struct PrepareArgs {
 __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
   uint32_t block = blockIdx.x;
   if (block < a.pack) {
+    if (a.p.records && *a.p.records) {
+      const uint32_t parts = (((uint32_t)a.p.m.nx + 255) / 256) * (uint32_t)a.p.m.ny * (uint32_t)a.p.m.nz;
+      for (uint32_t b = block; b < parts; b += a.pack) pack_volume(a.p.m, kOct16, a.p.gvol, b, a.pack);
+      return;
+    }
     pack_volume(a.p.m, a.p.gather, a.p.gvol, block, a.pack);
     return;
   }

@@ -33,7 +33,9 @@ namespace gemi {
 // out[z][y][x] (z <= nz) = (v'(x,y), v'(x1,y), v'(x,y1), v'(x1,y1)),
 // v' = clamp(v, lo, hi) - lo, neighbour indices clamped, slice nz = nz-1.
 __global__ void pack_quads_f32_kernel(const float* __restrict__ v, int32_t nx, int32_t ny,
-                                      int32_t nz, float lo, float hi, float4* __restrict__ out) {
+                                      int32_t nz, float lo, float hi, float4* __restrict__ out,
+                                      const uint32_t* __restrict__ records) {
+  if (records && !*records) return;
   const int32_t y = blockIdx.y, z = blockIdx.z;
   float4* __restrict__ orow = out + ((size_t)z * ny + y) * nx;
   const int32_t zs = z < nz ? z : nz - 1;
@@ -67,16 +69,18 @@ __global__ void pack_quads16_kernel(const T* __restrict__ v, int32_t nx, int32_t
 // out[i] = clamp(v[i], lo, hi) - lo, then the copy's pad (moving_copy_pad)
 // set to 0 (read with weight 0, so it must be finite).
 __global__ __launch_bounds__(256) void pack_copy_f32_kernel(const float* __restrict__ v, size_t nvox, size_t pad,
-                                                            float lo, float hi, float* __restrict__ out) {
+                                                            float lo, float hi, float* __restrict__ out,
+                                                            const uint32_t* __restrict__ records) {
+  if (records && *records) return;
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nvox + pad; i += (size_t)gridDim.x * blockDim.x)
     out[i] = i < nvox ? fminf(fmaxf(v[i], lo), hi) - lo : 0.0f;
 }
 
-hipError_t launch_pack_copy_f32(const VolumeDesc& m, float* out, hipStream_t s) {
+hipError_t launch_pack_copy_f32(const VolumeDesc& m, float* out, hipStream_t s, const uint32_t* records) {
   const size_t nvox = (size_t)m.nx * m.ny * m.nz, pad = moving_copy_pad(m.nx, m.ny);
   const size_t blocks = (nvox + pad + 255) / 256;
   hipLaunchKernelGGL(pack_copy_f32_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256), 0, s,
-                     (const float*)m.data, nvox, pad, (float)m.lo, (float)m.hi, out);
+                     (const float*)m.data, nvox, pad, (float)m.lo, (float)m.hi, out, records);
   return hipGetLastError();
 }
 
@@ -94,10 +98,10 @@ hipError_t launch_pack_quads16(const VolumeDesc& m, uint2* out, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_pack_quads_f32(const VolumeDesc& m, float4* out, hipStream_t s) {
+hipError_t launch_pack_quads_f32(const VolumeDesc& m, float4* out, hipStream_t s, const uint32_t* records) {
   const dim3 grid(1, (unsigned)m.ny, (unsigned)m.nz + 1);
   hipLaunchKernelGGL(pack_quads_f32_kernel, grid, dim3(256), 0, s, (const float*)m.data, m.nx,
-                     m.ny, m.nz, (float)m.lo, (float)m.hi, out);
+                     m.ny, m.nz, (float)m.lo, (float)m.hi, out, records);
   return hipGetLastError();
 }
 
@@ -426,6 +430,9 @@ __device__ __forceinline__ void row_tiles(const GroupWalkFlex& w, const uint32_t
   }
 }
 
+// How a forward step reads the moving volume.
+enum Fetch { kQuads, kCopy, kOcts };
+
 // Per-launch constants of the forward step of one fixed voxel.
 struct ParzenFwdStep {
   __amdgpu_buffer_rsrc_t rsrc;
@@ -436,7 +443,7 @@ struct ParzenFwdStep {
   int B, pitch;
   float sscale, smax;
 
-  template <bool FQ, bool COPY = false>
+  template <bool FQ, Fetch MODE = kQuads>
   __device__ __forceinline__ static ParzenFwdStep make(const ParzenArgs& a) {
     ParzenFwdStep p;
     p.top[0] = (uint64_t)(a.mnx - 1) << 32;
@@ -447,7 +454,7 @@ struct ParzenFwdStep {
     p.n[2] = a.mnz;
     p.NY = (uint32_t)a.mny;
     p.MX = (uint32_t)a.mnx;
-    p.SZ = (FQ ? (COPY ? 4 : 16) : (COPY ? 2 : 8)) * a.mnx * a.mny;
+    p.SZ = (FQ ? (MODE == kCopy ? 4 : 16) : (MODE == kCopy ? 2 : 8)) * a.mnx * a.mny;
     p.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.gvol, (short)0, (int)a.gvol_bytes, 0x00020000);
     p.B = a.bins;
     p.pitch = parzen_pitch(a.bins);
@@ -478,12 +485,16 @@ struct ParzenFwdStep {
   }
 
   // The voxel's 2x2x2 moving neighbourhood as stored: two float4 quads
-  // (FQ), two 16-bit quads, or (COPY) the pairs (x, x + 1) of four rows of
-  // the plain fp32 or 16-bit copy.
-  template <bool FQ, bool COPY = false>
+  // (FQ), two 16-bit quads, (kCopy) the pairs (x, x + 1) of four rows of the
+  // plain fp32 or 16-bit copy, or (kOcts) one record of 16-bit values.
+  template <bool FQ, Fetch MODE = kQuads>
   __device__ __forceinline__ Raw fetch(uint32_t idx) const {
     Raw d;
-    if (COPY && FQ) {
+    if (MODE == kOcts) {
+      const uint4_t o = __builtin_amdgcn_raw_buffer_load_b128(rsrc, idx * 16u, 0, 0);
+      d.a = uint4_t{o.x, o.y, 0u, 0u};
+      d.b = uint4_t{o.z, o.w, 0u, 0u};
+    } else if (MODE == kCopy && FQ) {
       const int32_t row = 4 * n[0];  // bytes to the next row; SZ: to the next slice
       const uint2_t r00 = __builtin_amdgcn_raw_buffer_load_b64(rsrc, idx * 4u, 0, 0);
       const uint2_t r10 = __builtin_amdgcn_raw_buffer_load_b64(rsrc, idx * 4u, row, 0);
@@ -491,7 +502,7 @@ struct ParzenFwdStep {
       const uint2_t r11 = __builtin_amdgcn_raw_buffer_load_b64(rsrc, idx * 4u, SZ + row, 0);
       d.a = uint4_t{r00.x, r00.y, r10.x, r10.y};
       d.b = uint4_t{r01.x, r01.y, r11.x, r11.y};
-    } else if (COPY) {
+    } else if (MODE == kCopy) {
       const int32_t row = 2 * n[0];
       d.a = uint4_t{__builtin_amdgcn_raw_buffer_load_b32(rsrc, idx * 2u, 0, 0),
                     __builtin_amdgcn_raw_buffer_load_b32(rsrc, idx * 2u, row, 0), 0u, 0u};
@@ -543,12 +554,12 @@ struct ParzenFwdStep {
   // (or CLAMP) and its slot falls in the band's rows, its four B-spline taps
   // go into the LDS table.  Returns whether the voxel took part in this band
   // (each voxel belongs to one band, so the bands' counts add up to N).
-  template <bool FQ, bool CLAMP, bool COPY = false>
+  template <bool FQ, bool CLAMP, Fetch MODE = kQuads>
   __device__ __forceinline__ bool add(const int64_t q[3], int32_t fb, const SweepCtx& sc, int cells, int copy,
                                       unsigned long long* lds_tab) const {
     const Loc l = locate<CLAMP>(q);
     if (!l.inside || fb < sc.r_lo || fb >= sc.r_hi) return false;
-    taps<FQ>(fetch<FQ, COPY>(l.idx), l, fb, sc, cells, copy, lds_tab);
+    taps<FQ>(fetch<FQ, MODE>(l.idx), l, fb, sc, cells, copy, lds_tab);
     return true;
   }
 };
@@ -633,6 +644,7 @@ __global__ __launch_bounds__(NT) void parzen_fwd_kernel(ParzenArgs a) {
 // bytes per voxel, whose lines hold several neighbouring samples of the
 // list, where one record of 16 bytes per voxel took a line per sample
 // (10% of 256x256x180 u16, 64 bins, 1000 translations: 6.83 -> 4.00 ms a call).
+// Batches that turn widely keep the records (launch_sample_layout).
 template <bool FQ, bool CLAMP, int NT>
 __global__ __launch_bounds__(NT) void parzen_sampled_fwd_kernel(ParzenArgs a, const uint2* __restrict__ list,
                                                                 const unsigned long long* __restrict__ n_list) {
@@ -655,18 +667,24 @@ __global__ __launch_bounds__(NT) void parzen_sampled_fwd_kernel(ParzenArgs a, co
   uint32_t taken = 0;
   const int copy = (threadIdx.x & (kHotCopies - 1));
   if (ok) {
-    const ParzenFwdStep ps = ParzenFwdStep::template make<FQ, true>(a);
     const int64_t ns = (int64_t)*n_list;
     const int64_t s0 = ns * sc.chunk / a.chunks, s1 = ns * (sc.chunk + 1) / a.chunks;
-    for (int64_t e = s0 + threadIdx.x; e < s1; e += NT) {
-      const uint2 en = list[e];
-      const int64_t x = en.x & 0xFFFu, y = (en.x >> 12) & 0xFFFu, z = en.y;
-      const int32_t slot = (int32_t)(en.x >> 24);
-      int64_t q[3];
+    auto samples = [&]<Fetch MODE>() {
+      const ParzenFwdStep ps = ParzenFwdStep::template make<FQ, MODE>(a);
+      for (int64_t e = s0 + threadIdx.x; e < s1; e += NT) {
+        const uint2 en = list[e];
+        const int64_t x = en.x & 0xFFFu, y = (en.x >> 12) & 0xFFFu, z = en.y;
+        const int32_t slot = (int32_t)(en.x >> 24);
+        int64_t q[3];
 #pragma unroll
-      for (int r = 0; r < 3; ++r) q[r] = Mq[4 * r] * x + Mq[4 * r + 1] * y + Mq[4 * r + 2] * z + Mq[4 * r + 3];
-      taken += ps.add<FQ, CLAMP, true>(q, slot, sc, cells, copy, lds_tab);
-    }
+        for (int r = 0; r < 3; ++r) q[r] = Mq[4 * r] * x + Mq[4 * r + 1] * y + Mq[4 * r + 2] * z + Mq[4 * r + 3];
+        taken += ps.template add<FQ, CLAMP, MODE>(q, slot, sc, cells, copy, lds_tab);
+      }
+    };
+    if (a.records && *a.records)
+      samples.template operator()<FQ ? kQuads : kOcts>();
+    else
+      samples.template operator()<kCopy>();
   }
   if (taken) atomicAdd(&lds_count, taken);
   __syncthreads();

@@ -227,3 +227,34 @@ def test_order_around_the_l2(ctx, shape, n):
         torch.cuda.synchronize()
         assert torch.equal(h[t0:t0 + 50], h_s) and torch.equal(ov[t0:t0 + 50], ov_s), t0
         assert torch.all((mi[t0:t0 + 50] - mi_s).abs() <= 1e-12 * torch.clamp(mi_s.abs(), min=1.0))
+
+
+@pytest.mark.parametrize("mdt,shape", [(np.uint16, (101, 100, 93)), (np.uint8, (160, 101, 90)),
+                                       (np.float32, (130, 129, 125))])
+@pytest.mark.parametrize("clamp", [0, 1])
+def test_sampled_parzen_records(ctx, mdt, shape, clamp):
+    """Sampled Parzen batches on volumes large enough for the choice of the
+    moving layout: shifts (the copy), wide turns (records) and both."""
+    import torch
+    from paper_1909_10690_amd import binding as B
+    rng = np.random.default_rng(shape[0])
+    lo, hi = RANGES[mdt]
+    fs = (40, 33, 21)
+    f = inputs.random_volume(rng, fs, np.uint8, 0, 255)
+    m = inputs.random_volume(rng, shape, mdt, lo, hi)
+    turned = inputs.random_affines(rng, 4, fs, rot=60, trans=2)
+    turned[:, :3] *= 3.0  # over the whole moving volume
+    turned[:, 4:7] *= 3.0
+    turned[:, 8:11] *= 3.0
+    shifts = np.stack([T.translation(v) for v in ((0, 0, 0), (3, -2.5, 1), (0.5, 4, 9))]).reshape(-1, 12)
+    F, M = device_volume(f, 0, 255, 0), device_volume(m, lo, hi, 1)
+    for mats in (shifts, turned, np.concatenate([shifts, turned])):
+        print(f"sampled Parzen records {np.dtype(mdt).name} {shape} clamp={clamp} n={len(mats)}", flush=True)
+        mi, ov, _ = ctx.eval_sampled(F, M, torch.from_numpy(mats).cuda(), 16, (1.0, 1.5), fraction=0.6,
+                                     flags=clamp | B.HIST_PARZEN)
+        omi, on = oracle.eval_parzen(oracle.volume(f, 0, 255), oracle.volume(m, lo, hi), mats, 16, (1.0, 1.5),
+                                     boundary=clamp, sample=(0.6, 0))
+        torch.cuda.synchronize()
+        assert np.array_equal(ov.cpu().numpy(), on)
+        err = np.abs(mi.cpu().numpy() - omi) / np.maximum(1.0, np.abs(omi))
+        assert err.max() <= 1e-6, err.max()
