@@ -332,13 +332,22 @@ inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_
 // copy (us a call, oct and copy: 256x256x180 u16, 128 bins, one transform 122
 // and 97, four 257 and 229, six 328 and 338; 128^3 u8, 64 bins, four 66 and
 // 65, six 80 and 86, both with preparation and reduction in more launches than
-// now).
+// now).  Turned widely, the copy's four gathers each have lines of their own:
+// beyond the L2s (kCopyBytes) it serves one or two transforms of a 16-bit
+// volume (us a call, copy and octs, 256x256x180 turned by 0, 30 and 60 degrees
+// about y: two transforms of u16 95, 179, 221 and 124, 193, 240, four 146, 307,
+// 424 and 168, 220, 263; one of u8 75, 130, 156 and 108, 126, 148; 128^3 u16,
+// four: 53, 72, 82 with the copy).
 constexpr int32_t kCopyTransforms = 4;
+constexpr size_t kCopyBytes = 8 << 20;
 inline int32_t oct_gather(double lo, double hi) {
   return oct8_range(lo, hi) ? kOct8 : (hi - lo < 16384.0 ? kOctD : kOct16);
 }
 inline int32_t hard_gather(const VolumeDesc& m, int32_t n, bool reused, bool brick) {
-  if (n <= kCopyTransforms && !reused && !brick) return kCopy16;
+  if (!reused && !brick) {
+    const bool large = moving_copy_bytes(m.nx, m.ny, m.nz) > kCopyBytes;
+    if (large ? n <= 2 && !oct8_range(m.lo, m.hi) : n <= kCopyTransforms) return kCopy16;
+  }
   // tiles where they need no padding: the workspace's region is the octs'
   const int32_t oct = oct_gather(m.lo, m.hi);
   const bool fits = tiled_records(m.nx, m.ny, m.nz, oct == kOct8) == (size_t)m.nx * m.ny * m.nz;
