@@ -97,13 +97,6 @@ __device__ __forceinline__ void clear_arrays(const ClearList& l, uint32_t b, uin
   }
 }
 
-static unsigned fill_grid(size_t n) {
-  size_t g = (n + 255) / 256;
-  if (g > 8192) g = 8192;
-  if (g == 0) g = 1;
-  return (unsigned)g;
-}
-
 // ---------------------------------------------------------------------------
 // fixed-volume binning, once per call
 // ---------------------------------------------------------------------------
@@ -197,7 +190,7 @@ __global__ __launch_bounds__(256) void prebin_kernel(VolumeDesc f, int32_t bins,
 
 hipError_t launch_prebin_voxels(const VolumeDesc& f, int bins, uint8_t* out, uint32_t* used, hipStream_t s) {
   const size_t nvox = (size_t)f.nx * f.ny * f.nz;
-  hipLaunchKernelGGL(prebin_kernel, dim3(fill_grid(nvox / 16)), dim3(256), 0, s, f, bins, fixed_divider(f), out, used);
+  hipLaunchKernelGGL(prebin_kernel, dim3(fill_blocks(nvox / 16)), dim3(256), 0, s, f, bins, fixed_divider(f), out, used);
   return hipGetLastError();
 }
 
@@ -322,11 +315,18 @@ __device__ __forceinline__ void pack_copy(const T* __restrict__ v, size_t nvox, 
 __device__ __forceinline__ void pack_volume(const VolumeDesc& m, int32_t gather, void* __restrict__ out, uint32_t block,
                                             uint32_t nb) {
   const int32_t lo = (int32_t)m.lo, hi = (int32_t)m.hi;
+  const uint32_t parts = row_parts(m.nx, m.ny, m.nz);
   auto whole = [&]<typename T>(const T* __restrict__ v) {
     switch (gather) {
-    case kOct16: pack_octs<T, false>(v, m.nx, m.ny, m.nz, lo, hi, (uint4*)out, block); break;
-    case kOctD: pack_octs<T, true>(v, m.nx, m.ny, m.nz, lo, hi, (uint4*)out, block); break;
-    case kOct8: pack_oct8(v, m.nx, m.ny, m.nz, lo, hi, (uint2*)out, block); break;
+    case kOct16:
+      for (uint32_t b = block; b < parts; b += nb) pack_octs<T, false>(v, m.nx, m.ny, m.nz, lo, hi, (uint4*)out, b);
+      break;
+    case kOctD:
+      for (uint32_t b = block; b < parts; b += nb) pack_octs<T, true>(v, m.nx, m.ny, m.nz, lo, hi, (uint4*)out, b);
+      break;
+    case kOct8:
+      for (uint32_t b = block; b < parts; b += nb) pack_oct8(v, m.nx, m.ny, m.nz, lo, hi, (uint2*)out, b);
+      break;
     case kCopy16: pack_copy(v, (size_t)m.nx * m.ny * m.nz, lo, hi, (uint16_t*)out, block, nb); break;
     case kOct16 | kTiled: pack_tiled<T, kOct16>(v, m.nx, m.ny, m.nz, lo, hi, out, block, nb); break;
     case kOctD | kTiled: pack_tiled<T, kOctD>(v, m.nx, m.ny, m.nz, lo, hi, out, block, nb); break;
@@ -342,9 +342,9 @@ __device__ __forceinline__ void pack_volume(const VolumeDesc& m, int32_t gather,
 
 static unsigned pack_blocks(const VolumeDesc& m, int32_t gather) {
   const size_t nvox = (size_t)m.nx * m.ny * m.nz;
-  if (gather == kCopy16) return fill_grid((nvox + 7) / 8);
-  if (gather & kTiled) return fill_grid(nvox);
-  return (unsigned)((m.nx + 255) / 256) * (unsigned)m.ny * (unsigned)m.nz;  // a block per row part, <= 2^24
+  if (gather == kCopy16) return fill_blocks((nvox + 7) / 8);
+  if (gather & kTiled) return fill_blocks(nvox);
+  return row_part_blocks(row_parts(m.nx, m.ny, m.nz));
 }
 
 // ---------------------------------------------------------------------------
@@ -354,7 +354,7 @@ static unsigned pack_blocks(const VolumeDesc& m, int32_t gather) {
 struct PrepareArgs {
   Prepare p;
   Divider div;
-  uint32_t pack, bin, clear;  // workgroups of each part; the transforms take the rest
+  PrepareBlocks blocks;
 };
 
 // The parts depend on nothing but the caller's inputs, so they share a launch,
@@ -362,32 +362,27 @@ struct PrepareArgs {
 // 2 to 3 us.
 __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
   uint32_t block = blockIdx.x;
-  if (block < a.pack) {
-    if (a.p.records && *a.p.records) {
-      const uint32_t parts = (((uint32_t)a.p.m.nx + 255) / 256) * (uint32_t)a.p.m.ny * (uint32_t)a.p.m.nz;
-      for (uint32_t b = block; b < parts; b += a.pack) pack_volume(a.p.m, kOct16, a.p.gvol, b, a.pack);
-      return;
-    }
-    pack_volume(a.p.m, a.p.gather, a.p.gvol, block, a.pack);
+  const PrepareBlocks& nb = a.blocks;
+  if (block < nb.pack) {
+    pack_volume(a.p.m, a.p.records && *a.p.records ? (int32_t)kOct16 : a.p.gather, a.p.gvol, block, nb.pack);
     return;
   }
-  block -= a.pack;
-  if (block < a.bin) {
+  block -= nb.pack;
+  if (block < nb.bin) {
     switch (a.p.order) {
-    case kRunOrder: prebin_volume<kRunOrder>(a.p.f, a.p.bins, a.div, a.p.fbins, nullptr, block, a.bin); break;
-    case kCubeOrder: prebin_volume<kCubeOrder>(a.p.f, a.p.bins, a.div, a.p.fbins, nullptr, block, a.bin); break;
-    default: prebin_volume<kVoxelOrder>(a.p.f, a.p.bins, a.div, a.p.fbins, nullptr, block, a.bin);
+    case kRunOrder: prebin_volume<kRunOrder>(a.p.f, a.p.bins, a.div, a.p.fbins, nullptr, block, nb.bin); break;
+    case kCubeOrder: prebin_volume<kCubeOrder>(a.p.f, a.p.bins, a.div, a.p.fbins, nullptr, block, nb.bin); break;
+    default: prebin_volume<kVoxelOrder>(a.p.f, a.p.bins, a.div, a.p.fbins, nullptr, block, nb.bin);
     }
     return;
   }
-  block -= a.bin;
-  if (block < a.clear) {
-    clear_arrays(a.p.clear, block, a.clear);
+  block -= nb.bin;
+  if (block < nb.clear) {
+    clear_arrays(a.p.clear, block, nb.clear);
     return;
   }
-  block -= a.clear;
-  const int64_t step = (gridDim.x - a.pack - a.bin - a.clear) * 256ll;
-  for (int64_t t = block * 256ll + threadIdx.x; t < a.p.n; t += step) {
+  block -= nb.clear;
+  for (int64_t t = block * 256ll + threadIdx.x; t < a.p.n; t += nb.compose * 256ll) {
     double m[12];
     compose_index_matrix(a.p.P + 12 * t, a.p.geo, m);
 #pragma unroll
@@ -396,23 +391,24 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
 }
 
 hipError_t launch_prepare(const Prepare& p, hipStream_t s) {
-  PrepareArgs a{p, Divider{0, 0}, 0, 0, 0};
+  PrepareArgs a{p, Divider{0, 0}, {}};
+  PrepareBlocks& nb = a.blocks;
   if (p.gvol) {
     if (p.m.dtype > 2) return hipErrorInvalidValue;
-    a.pack = pack_blocks(p.m, p.gather);
+    nb.pack = pack_blocks(p.m, p.gather);
   }
   if (p.fbins) {
     a.div = fixed_divider(p.f);
     const size_t rows = (size_t)p.f.ny * p.f.nz;
-    a.bin = fill_grid(p.order == kVoxelOrder ? rows * p.f.nx / 16 : rows * ((p.f.nx + 3) / 4));
+    nb.bin = fill_blocks(p.order == kVoxelOrder ? rows * p.f.nx / 16 : rows * ((p.f.nx + 3) / 4));
   }
   size_t most = 0;
   for (int k = 0; k < p.clear.n; ++k) most = p.clear.words[k] > most ? p.clear.words[k] : most;
-  if (most) a.clear = fill_grid((most + 3) / 4);
-  const unsigned compose = p.P && p.n > 0 ? std::min(fill_grid((size_t)p.n), 4096u) : 0u;
-  const unsigned grid = a.pack + a.bin + a.clear + compose;
-  if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL(prepare_kernel, dim3(grid), dim3(256), 0, s, a);
+  if (most) nb.clear = fill_blocks((most + 3) / 4);
+  if (p.P && p.n > 0) nb.compose = std::min(fill_blocks((size_t)p.n), 4096u);
+  if (nb.total() == 0) return hipSuccess;
+  if (!nb.fits()) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(prepare_kernel, dim3(nb.total()), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

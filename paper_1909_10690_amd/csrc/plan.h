@@ -23,6 +23,28 @@ inline int32_t transforms_per_launch(int64_t workgroups_per_transform, int32_t t
   return (int32_t)(m < 1 ? 1 : (m > 0x7FFFFFFF ? 0x7FFFFFFF : m));
 }
 
+// Workgroups of 256 threads for n items, one a thread (beyond 8192 workgroups
+// in turns).
+constexpr uint32_t fill_blocks(size_t n) {
+  const size_t g = (n + 255) / 256;
+  return (uint32_t)(g > 8192 ? 8192 : (g < 1 ? 1 : g));
+}
+
+// Row parts of a volume (256 voxels of a row each, fewer at a row's end; at most
+// 2^24), and the workgroups of 256 threads that take them: one each up to 2^22,
+// in turns beyond, because a workgroup for each of 2^24 would wrap a launch.
+constexpr uint32_t row_parts(int32_t nx, int32_t ny, int32_t nz) {
+  return (((uint32_t)nx + 255) / 256) * (uint32_t)ny * (uint32_t)nz;
+}
+constexpr uint32_t row_part_blocks(uint32_t parts) { return parts < (1u << 22) ? parts : 1u << 22; }
+
+// Workgroups of 256 threads of each part of a preparation launch.
+struct PrepareBlocks {
+  uint32_t pack = 0, bin = 0, clear = 0, compose = 0;
+  constexpr uint32_t total() const { return pack + bin + clear + compose; }
+  constexpr bool fits() const { return (int64_t)total() * 256 <= kMaxWorkItemsPerLaunch; }
+};
+
 // 32-bit words per fixed-bin row of a hard sweep's LDS histogram: the row's
 // counters (u32, or two 16-bit ones per word when packed) and a pad that
 // makes the row width odd and not 1 modulo 32.  Unpadded rows of a
