@@ -1158,11 +1158,14 @@ PairsTune pairs_tune_for(const mi_context* ctx, const mi_pair* pairs, int32_t n_
   return t;
 }
 
-// Key of a pairs preparation: every pair's volumes, bins, workspace, layout.
+// Key of a pairs preparation: every pair's volumes and where its bins and
+// octs lie, bins, workspace, layout.  (The regions' offsets depend on the
+// numbers of transforms and entropies.)
 std::vector<uint64_t> pairs_prep_key(const mi_pair* pairs, int32_t n_pairs, int32_t bins, const void* ws,
-                                     bool oct8) {
-  std::vector<uint64_t> k = {(uint64_t)n_pairs, (uint64_t)bins, (uint64_t)(uintptr_t)ws, oct8 ? 1u : 0u};
-  for (int p = 0; p < n_pairs; ++p)
+                                     const PairsPlan& plan) {
+  std::vector<uint64_t> k = {(uint64_t)n_pairs, (uint64_t)bins, (uint64_t)(uintptr_t)ws, (uint64_t)plan.gather()};
+  for (int p = 0; p < n_pairs; ++p) {
+    k.insert(k.end(), {(uint64_t)plan.fbins[p], (uint64_t)plan.gvol[p]});
     for (const mi_volume* v : {&pairs[p].fixed, &pairs[p].moving}) {
       uint64_t lo, hi;
       memcpy(&lo, &v->lo, 8);
@@ -1170,6 +1173,7 @@ std::vector<uint64_t> pairs_prep_key(const mi_pair* pairs, int32_t n_pairs, int3
       k.insert(k.end(), {(uint64_t)(uintptr_t)v->data, (uint64_t)v->nx, (uint64_t)v->ny, (uint64_t)v->nz,
                          (uint64_t)v->dtype, lo, hi});
     }
+  }
   return k;
 }
 
@@ -1769,7 +1773,7 @@ int mi_eval_pairs(mi_context* ctx, const mi_pair* pairs, int32_t n_pairs, int32_
   if ((st = plan_pairs(pairs, n_pairs, bins, n_q, flags, plan, tune)) != MI_OK) return st;
   // the pairs' preparation (fixed bins, oct volumes) is kept in the
   // workspace and reused when the caller asserts unchanged volumes
-  std::vector<uint64_t> pkey = pairs_prep_key(pairs, n_pairs, bins, workspace, plan.oct8);
+  std::vector<uint64_t> pkey = pairs_prep_key(pairs, n_pairs, bins, workspace, plan);
   const bool prepare = !((flags & MI_VOLUMES_UNCHANGED) && pkey == ctx->last_pairs_prep);
   ctx->last_prep.clear();  // the pairs' layout overwrites any single-pair preparation
   st = run_pairs(ctx, pairs, n_pairs, bins, q, n_q, flags, mi_out, (char*)workspace, (hipStream_t)stream, plan,
