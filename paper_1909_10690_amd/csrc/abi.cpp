@@ -1594,11 +1594,18 @@ int mi_eval(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   key_volume(key, fixed);
   key_volume(key, moving);
   key_q(key, q, n_q);
+  int path = 2;
+  if (!parzen) {
+    // the launch shape decides what the graph prepares, so a graph serves the
+    // shape it was captured with only
+    const HardTune tune = tune_for(ctx, fixed, moving, n, bins, flags);
+    key.insert(key.end(), {(uint64_t)tune.block, (uint64_t)tune.slab_major, (uint64_t)tune.chunks,
+                           (uint64_t)(tune.packed + 1)});
+    path = hard_prep_path(call_gather(moving, n, run_flags, tune), call_brick(run_flags, tune));
+  }
   st = graph_run(ctx, key, s, body);
   // the graph prepared them
-  const HardTune tune = tune_for(ctx, fixed, moving, n, bins, flags);
-  const int path = parzen ? 2 : hard_prep_path(call_gather(moving, n, run_flags, tune), call_brick(run_flags, tune));
-  ctx->last_prep = prep_key(path, ws, L, fixed, moving, bins);
+  ctx->last_prep = st == MI_OK ? prep_key(path, ws, L, fixed, moving, bins) : std::vector<uint64_t>();
   return st;
 }
 
@@ -1714,7 +1721,8 @@ int mi_grad(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   key_volume(key, moving);
   key_q(key, q, n_q);
   st = graph_run(ctx, key, s, body);
-  ctx->last_prep = prep_key(2, workspace, L, fixed, moving, bins);  // the graph prepared them
+  // the graph prepared them
+  ctx->last_prep = st == MI_OK ? prep_key(2, workspace, L, fixed, moving, bins) : std::vector<uint64_t>();
   return st;
 }
 

@@ -49,3 +49,51 @@ def test_pairs_of_other_batch_sizes(ctx):
         got = ctx.eval_pairs(p, 40, q, flags=B.VOLUMES_UNCHANGED, workspace=ws)
         torch.cuda.synchronize()
         assert torch.equal(got.cpu(), want[k]), k
+
+
+@pytest.mark.parametrize("shape_line", ["256 1 64 0", "512 0 32 1", "1024 1 64 0"])
+def test_graph_then_another_launch_shape(tmp_path, monkeypatch, shape_line):
+    """A graph captured under one launch shape (read from a cache file), a
+    tuning that may pick another, the graph's call again, then a call that
+    reuses what it prepared: the bins' order and the octs' layout follow the
+    shape (1024 threads sweep bricks here, 256 and 512 thin slabs, and whichever
+    kind the tuning picks, a start from the other changes)."""
+    import torch
+    from paper_1909_10690_amd import binding as B
+    rng = np.random.default_rng(5)
+    shape = (64, 32, 24)
+    F = B.Volume.from_numpy(inputs.random_volume(rng, shape, np.uint8, 0, 255), 0, 255)
+    M = B.Volume.from_numpy(inputs.random_volume(rng, shape, np.uint16, 0, 4000), 0, 4000)
+    tr = torch.from_numpy(inputs.random_affines(rng, 8, shape)).cuda()
+    path = tmp_path / "tune.txt"
+    # class of these volumes: extents, dtype, bins, boundary, 2^3 transforms, 16-bit corners
+    path.write_text(f"gemi-tune 64 32 24 64 32 24 1 64 0 3 0 {shape_line}\n")
+    assert B.read_tune_cache(str(path))[0]["block"] == int(shape_line.split()[0])
+    monkeypatch.setenv("MI_TUNE_CACHE", str(path))
+    ctx = B.Context(0)
+    want = ctx.eval(F, M, tr, 64)[0].cpu()
+    ws = torch.empty(ctx.workspace_size(F, M, 8, 64, 1, B.COMPACT_SLABS), dtype=torch.uint8, device="cuda")
+    out, side = torch.empty((8, 1), dtype=torch.float64, device="cuda"), torch.cuda.Stream()
+
+    def graph():
+        with torch.cuda.stream(side):
+            ctx.eval(F, M, tr, 64, flags=B.COMPACT_SLABS | B.USE_GRAPH, want_overlap=False, out=out, workspace=ws,
+                     stream=side)
+        side.synchronize()
+        assert torch.equal(out.cpu(), want)
+
+    def reuse():
+        got = ctx.eval(F, M, tr, 64, flags=B.COMPACT_SLABS | B.VOLUMES_UNCHANGED, workspace=ws)[0]
+        torch.cuda.synchronize()
+        assert torch.equal(got.cpu(), want)
+
+    torch.cuda.synchronize()
+    for _ in range(2):
+        graph()
+        reuse()
+    ctx.tune(F, M, tr, 64, flags=B.COMPACT_SLABS)
+    print(f"from {shape_line} tuned to {B.read_tune_cache(str(path))[0]['block']} threads", flush=True)
+    for _ in range(2):
+        graph()
+        reuse()
+    ctx.close()
