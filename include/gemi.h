@@ -122,11 +122,12 @@ extern "C" {
 #define MI_HIST_PARZEN 0x100
 /* Capture the call's kernels into a HIP graph the first time a call with
  * exactly these arguments (pointers, sizes, q, flags, workspace, stream) and
- * launch shape (mi_tune; hard-binned calls) is seen, and replay the graph on later identical calls: one launch instead
- * of several.  Needs a non-NULL stream; ignored (eager launches) on the
- * NULL stream or while kernel timing is enabled.  Device data behind the
- * pointers may change between replays (e.g. transforms updated in place);
- * the context keeps the 16 most recent graphs. */
+ * launch shape (mi_tune; hard-binned calls) is seen, and replay the graph on
+ * later identical calls: one launch instead of several.  Needs a non-NULL
+ * stream; ignored (eager launches) on the NULL stream or while kernel timing
+ * is enabled.  Device data behind the pointers may change between replays
+ * (e.g. transforms updated in place); the context keeps the 16 most recent
+ * graphs. */
 #define MI_USE_GRAPH 0x1000
 /* The caller asserts that fixed, moving, bins, the boundary flag and the
  * workspace are those of the previous call on this context that prepared

@@ -317,6 +317,8 @@ struct mi_context {
   bool parzen_env = false;    // MI_TUNE_PARZEN_* set: parzen_default replaces the shape by bins
   ParzenTune parzen_default;  // launch shape when no tuned entry matches (with parzen_env)
   std::vector<uint64_t> last_pairs_prep;  // pairs, bins and workspace of the last pairs preparation
+  const char* pairs_ws = nullptr;         // where it lies
+  size_t pairs_ws_bytes = 0;
   std::string tune_file;                            // MI_TUNE_CACHE, if set
   std::vector<GraphEntry> graphs;                   // MI_USE_GRAPH replays, oldest first
 };
@@ -345,6 +347,12 @@ bool reuse_prep(mi_context* ctx, int32_t flags, std::vector<uint64_t> key) {
   if ((flags & MI_VOLUMES_UNCHANGED) && key == ctx->last_prep) return true;
   ctx->last_prep = std::move(key);
   return false;
+}
+
+// Forgets the pairs' preparation when a call is about to write where it lies.
+void forget_pairs_prep(mi_context* ctx, const void* ws, size_t bytes) {
+  const char* p = (const char*)ws;
+  if (p < ctx->pairs_ws + ctx->pairs_ws_bytes && ctx->pairs_ws < p + bytes) ctx->last_pairs_prep.clear();
 }
 
 // Brackets one kernel launch with timing events when timing is enabled.
@@ -1440,6 +1448,7 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
     if (!workspace || workspace_bytes < PL.total) return MI_ERR_WORKSPACE;
     if (!ctx) return MI_ERR_NULL;
     if (n == 0) return MI_OK;
+    forget_pairs_prep(ctx, workspace, PL.total);
     hipError_t pe;
     if ((pe = hipSetDevice(ctx->device)) != hipSuccess) return hip_fail(pe, "hipSetDevice");
     const bool was = ctx->timing;
@@ -1454,6 +1463,7 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   if (!workspace || workspace_bytes < L.total) return MI_ERR_WORKSPACE;
   if (!ctx) return MI_ERR_NULL;
   if (n == 0) return MI_OK;
+  forget_pairs_prep(ctx, workspace, L.total);
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
   if ((e = hipSetDevice(ctx->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
@@ -1571,6 +1581,7 @@ int mi_eval(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   if (!workspace || workspace_bytes < L.total) return MI_ERR_WORKSPACE;
   if (!ctx) return MI_ERR_NULL;
   if (n == 0) return MI_OK;
+  forget_pairs_prep(ctx, workspace, L.total);
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
   if ((e = hipSetDevice(ctx->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
@@ -1586,7 +1597,11 @@ int mi_eval(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
     return run_hard(ctx, fixed, moving, transforms, n, bins, q, n_q, run_flags, mi_out, overlap_out,
                     hist_out, ws, L, s, tune_for(ctx, fixed, moving, n, bins, flags));
   };
-  if (!graph) return body();
+  if (!graph) {
+    st = body();
+    if (st != MI_OK) ctx->last_prep.clear();
+    return st;
+  }
   std::vector<uint64_t> key = {1, (uint64_t)(uintptr_t)transforms, (uint64_t)n, (uint64_t)bins,
                                (uint64_t)flags, (uint64_t)(uintptr_t)mi_out,
                                (uint64_t)(uintptr_t)overlap_out, (uint64_t)(uintptr_t)hist_out,
@@ -1662,6 +1677,7 @@ int mi_eval_sampled(mi_context* ctx, const mi_volume* fixed, const mi_volume* mo
   if (!workspace || workspace_bytes < L.total) return MI_ERR_WORKSPACE;
   if (!ctx) return MI_ERR_NULL;
   if (n == 0) return MI_OK;
+  forget_pairs_prep(ctx, workspace, L.total);
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
   if ((e = hipSetDevice(ctx->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
@@ -1703,6 +1719,7 @@ int mi_grad(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   if (!workspace || workspace_bytes < L.total) return MI_ERR_WORKSPACE;
   if (!ctx) return MI_ERR_NULL;
   if (n == 0) return MI_OK;
+  forget_pairs_prep(ctx, workspace, L.total);
   hipError_t e;
   if ((e = hipSetDevice(ctx->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
   hipStream_t s = (hipStream_t)stream;
@@ -1712,7 +1729,11 @@ int mi_grad(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
     return run_parzen(ctx, fixed, moving, transforms, n, bins, q, n_q, run_flags, mi_out, nullptr,
                       grad_out, (char*)workspace, L, s);
   };
-  if (!graph) return body();
+  if (!graph) {
+    st = body();
+    if (st != MI_OK) ctx->last_prep.clear();
+    return st;
+  }
   std::vector<uint64_t> key = {2, (uint64_t)(uintptr_t)transforms, (uint64_t)n, (uint64_t)bins,
                                (uint64_t)flags, (uint64_t)(uintptr_t)mi_out,
                                (uint64_t)(uintptr_t)grad_out, (uint64_t)(uintptr_t)workspace,
@@ -1787,6 +1808,8 @@ int mi_eval_pairs(mi_context* ctx, const mi_pair* pairs, int32_t n_pairs, int32_
   st = run_pairs(ctx, pairs, n_pairs, bins, q, n_q, flags, mi_out, (char*)workspace, (hipStream_t)stream, plan,
                  tune, prepare);
   ctx->last_pairs_prep = st == MI_OK ? pkey : std::vector<uint64_t>();
+  ctx->pairs_ws = (const char*)workspace;
+  ctx->pairs_ws_bytes = plan.total;
   return st;
 }
 
@@ -1879,6 +1902,8 @@ int mi_probe_lds_atomics(mi_context* ctx, void* scratch, size_t scratch_bytes, v
   const int32_t blocks = 2 * ctx->cu_count;
   const size_t need = (size_t)blocks * 1024 * 4;
   if (scratch_bytes < need || scratch_bytes < ((size_t)4 << 20)) return MI_ERR_WORKSPACE;
+  ctx->last_prep.clear();  // the scratch may be a workspace
+  forget_pairs_prep(ctx, scratch, need);
   hipError_t e;
   if ((e = hipSetDevice(ctx->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
   hipStream_t s = (hipStream_t)stream;

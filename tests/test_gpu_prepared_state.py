@@ -97,3 +97,37 @@ def test_graph_then_another_launch_shape(tmp_path, monkeypatch, shape_line):
         graph()
         reuse()
     ctx.close()
+
+
+def test_pairs_and_single_calls_share_a_workspace(ctx):
+    """Single-pair calls of every kind, and the LDS probe, between pairs calls
+    that may reuse their preparation on the same workspace, and the reverse."""
+    import torch
+    from paper_1909_10690_amd import binding as B
+    pairs = pair_set(73)
+    F, M, tr = pairs[0]
+    same = B.VOLUMES_UNCHANGED
+    ws = torch.empty(1 << 26, dtype=torch.uint8, device="cuda")
+    want = ctx.eval_pairs(pairs, 40).cpu()
+    single = ctx.eval(F, M, tr, 40)[0].cpu()
+
+    def probe():
+        ctx._ws, kept = ws, ctx._ws
+        ctx.probe_lds_atomics()
+        ctx._ws = kept
+
+    others = {"eval": lambda: ctx.eval(F, M, tr, 40, workspace=ws),
+              "sampled": lambda: ctx.eval_sampled(F, M, tr, 40, fraction=0.5, workspace=ws),
+              "grad": lambda: ctx.grad(F, M, tr, 40, workspace=ws),
+              "tune": lambda: ctx.tune(F, M, tr, 40, workspace=ws),
+              "probe": probe,
+              "eval further in": lambda: ctx.eval(F, M, tr, 40, workspace=ws[4096:])}
+    for name, call in others.items():
+        print(f"pairs around {name}", flush=True)
+        for _ in range(2):
+            assert torch.equal(ctx.eval_pairs(pairs, 40, flags=same, workspace=ws).cpu(), want), name
+        call()
+        assert torch.equal(ctx.eval_pairs(pairs, 40, flags=same, workspace=ws).cpu(), want), name
+        assert torch.equal(ctx.eval(F, M, tr, 40, flags=same, workspace=ws)[0].cpu(), single), name
+    probe()
+    assert torch.equal(ctx.eval(F, M, tr, 40, flags=same, workspace=ws)[0].cpu(), single)
