@@ -41,6 +41,9 @@ def centred_matrices(params: torch.Tensor, centre) -> torch.Tensor:
     if isinstance(centre, torch.Tensor):
         c = torch.as_tensor(centre, dtype=params.dtype, device=params.device)
     else:  # a copy of its own, which need not wait for the device to have reached it
+        if params.is_cuda and torch.cuda.is_current_stream_capturing():
+            # a graph would keep the address of host memory that is gone at its replay
+            raise RuntimeError("a centre in host memory cannot be captured into a graph: pass a device tensor")
         c = torch.tensor(centre, dtype=params.dtype).to(params.device, non_blocking=True)
     c = c.reshape(3)
     off = c + t - (A @ c.unsqueeze(-1)).squeeze(-1)
