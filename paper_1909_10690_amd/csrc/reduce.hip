@@ -274,8 +274,16 @@ __global__ __launch_bounds__(kBlock) void mi_reduce_kernel(ReduceLaunch L) {
   }
   if (S > 1) {
     // Hand the slice's sums over and take a ticket; the last slice merges them
-    // all in slice order.  The sums are stored and read as agent-scope atomics
-    // (the slices run on several XCDs) and are complete before the ticket.
+    // all in slice order.  The slices run on several XCDs, whose L2s do not see
+    // each other's lines: `part` and the ticket are read and written by
+    // agent-scope atomics alone (never by plain accesses): on gfx950 those are
+    // coherent over the XCDs (the loads and stores go past the L2s), and a wave's
+    // s_waitcnt vmcnt(0) returns when its stores are done for all of them.  So
+    // every sum stands before its ticket counts, and the loads behind the last
+    // ticket, issued after its value came back, find them.  A release fence here
+    // and an acquire fence there would also write back and invalidate the whole
+    // L2, which nothing here needs: 64 transforms of 128 bins 33.6 -> 38.0 us a
+    // call, 200 of 64 bins 48.7 -> 54.9.
     uint64_t* part = (uint64_t*)L.part + ((size_t)t * S * n_q * 3 + (size_t)lane) * 2;
     const size_t stride = (size_t)n_q * 6;  // words of a slice
     if (iq < n_q) {
