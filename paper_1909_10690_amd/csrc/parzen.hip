@@ -114,14 +114,15 @@ typedef unsigned int unaligned128 __attribute__((ext_vector_type(4), aligned(1))
 
 // Row map, slots and tile masks of a call in one pass over the fixed bins.
 // Every workgroup forms the map (rank of each occupied row among the occupied
-// ones) from `used` for itself, the first one stores it.  A wave per row group
-// (kTileY rows of one slice), a lane per wave tile of it: the lane's bins
-// become slots in place, the OR of their slot groups is the tile's mask, and
-// the wave's OR the row group's.  Bound by launches and latency on small
+// ones) from `used` for itself, the first one stores it.  `span` lanes
+// (slots_span) per row group (kTileY rows of one slice), a lane per wave tile of
+// it: the lane's bins become slots in place, the OR of their slot groups is the
+// tile's mask, and the span's OR the row group's.  Bound by launches and latency on small
 // volumes: map, remapping, tile and row masks had a launch each and the bins a
-// second and third pass (512x512x300: 136 us, now 40; 128^3: 26 us, now 8).
+// second and third pass (512x512x300: 136 us, 40 in one pass with a wave per row
+// group, about 20 now; 128^3: 26, 8 and 6 us).
 __global__ __launch_bounds__(256) void slots_kernel(uint8_t* __restrict__ fb, int32_t nx, int32_t ny, int32_t nz,
-                                                    int32_t bins, RowMap* __restrict__ m,
+                                                    int32_t bins, int32_t span, RowMap* __restrict__ m,
                                                     uint32_t* __restrict__ mask) {
   __shared__ uint32_t slot[256], wave_used[4];
   const int r = threadIdx.x, wave = r >> 6, lane = r & 63;
@@ -144,10 +145,12 @@ __global__ __launch_bounds__(256) void slots_kernel(uint8_t* __restrict__ fb, in
   const int32_t XT = (nx + kTileX - 1) / kTileX, G = (ny + kTileY - 1) / kTileY;
   const int64_t groups = (int64_t)G * nz;
   uint32_t* __restrict__ row_mask = mask + groups * XT;
-  for (int64_t g = blockIdx.x * 4ll + wave; g < groups; g += gridDim.x * 4ll) {
+  const int32_t per = 64 / span, sub = lane / span;  // row groups a wave takes, this lane's
+  for (int64_t g0 = (blockIdx.x * 4ll + wave) * per; g0 < groups; g0 += gridDim.x * 4ll * per) {
+    const int64_t g = g0 + sub;
     const int32_t k = (int32_t)(g / G), j0 = (int32_t)(g - (int64_t)k * G) * kTileY;
     uint32_t all = 0;
-    for (int32_t t = lane; t < XT; t += 64) {
+    for (int32_t t = lane & (span - 1); t < XT && g < groups; t += span) {
       const int32_t x0 = t * kTileX;
       uint8_t* const tile = fb + ((int64_t)k * ny + j0) * nx + x0;
       const int32_t rows = min(kTileY, ny - j0), cols = min(kTileX, nx - x0);
@@ -199,17 +202,18 @@ __global__ __launch_bounds__(256) void slots_kernel(uint8_t* __restrict__ fb, in
       mask[g * XT + t] = bits;
       all |= bits;
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) all |= __shfl_xor(all, off, 64);
-    if (lane == 0) row_mask[g] = all;
+    for (int off = span >> 1; off > 0; off >>= 1) all |= __shfl_xor(all, off, 64);
+    if ((lane & (span - 1)) == 0 && g < groups) row_mask[g] = all;
   }
 }
 
 hipError_t launch_slots(uint8_t* fbins, int32_t nx, int32_t ny, int32_t nz, int32_t bins, RowMap* m, uint32_t* mask,
                         hipStream_t s) {
-  const int64_t blocks = (parzen_row_groups(ny, nz) + 3) / 4;
+  const int64_t groups = parzen_row_groups(ny, nz);
+  const int32_t span = slots_span(nx);
+  const int64_t blocks = (groups * span + 255) / 256;
   hipLaunchKernelGGL(slots_kernel, dim3((unsigned)(blocks < 4096 ? (blocks > 0 ? blocks : 1) : 4096)), dim3(256), 0, s,
-                     fbins, nx, ny, nz, bins, m, mask);
+                     fbins, nx, ny, nz, bins, span, m, mask);
   return hipGetLastError();
 }
 

@@ -204,6 +204,18 @@ struct RodWalk {
   constexpr int32_t k0() const { return gz * 4; }
 };
 
+// Lanes per row group of the pass that turns fixed bins into slots: a lane per
+// wave tile, rounded up to a power of two, so that a wave of 64 takes 64 / span
+// row groups and few of its lanes idle (whole Parzen calls on one transform
+// without overlap, us, a wave per row group and this: 2x512x512 137 and 44,
+// 16x256x256 62 and 43, 128^3 49 and 47, 256x256x180 77 and 66, 512x512x300 190
+// and 169).
+constexpr int32_t slots_span(int32_t nx) {
+  int32_t span = 1;
+  while (span < 64 && span * kTileX < nx) span *= 2;
+  return span;
+}
+
 // One wave's walk over its share of a slab: groups of kTileY consecutive
 // rows of one slice with exact Q32 row coordinates.  Either each wave takes
 // a contiguous share of the slab's row groups (GroupWalk), or the waves
