@@ -11,14 +11,10 @@
 
 namespace gemi {
 
-// a * b + c with 24-bit unsigned operands a, b and b uniform
-// (v_mad_u32_u24, full rate; left to itself the compiler may pick the
-// quarter-rate 64-bit multiply-add).
-__device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t r;
-  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
-  return r;
-}
+// a * b + c with 24-bit unsigned operands (v_mad_u32_u24, full rate; a plain
+// product may become the quarter-rate 64-bit multiply-add).
+__device__ uint32_t mul24(uint32_t a, uint32_t b) __asm("llvm.amdgcn.mul.u24.i32");
+__device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) { return mul24(a, b) + c; }
 
 constexpr int kMaxQ = 16;
 constexpr int kBlock = 256;  // threads per workgroup of the reduction kernels (4 wave64)
@@ -123,12 +119,16 @@ __device__ __forceinline__ bool quantize_transform_wave(const double* __restrict
 // A value every lane holds alike, moved to scalar registers.  A value
 // computed by vector instructions stays in vector registers otherwise, and
 // the compiler drops a readfirstlane builtin of a value it knows is uniform,
-// so the move is written out.
+// so the value passes through an empty asm first, which hides that.  (Not the
+// instruction itself in asm: gfx950 needs a wait state between a vector write
+// and a v_readfirstlane of that register, and two before a vector instruction
+// uses the scalar result; the compiler keeps these for its own instructions
+// only, and where its code around the asm left none, a stale value was read.)
 __device__ __forceinline__ int64_t uniform64(int64_t v) {
-  uint32_t lo, hi;
-  asm volatile("v_readfirstlane_b32 %0, %1" : "=s"(lo) : "v"((uint32_t)v));
-  asm volatile("v_readfirstlane_b32 %0, %1" : "=s"(hi) : "v"((uint32_t)((uint64_t)v >> 32)));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
+  uint32_t lo = (uint32_t)v, hi = (uint32_t)((uint64_t)v >> 32);
+  asm("" : "+v"(lo), "+v"(hi));
+  return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(hi) << 32) |
+                   (uint32_t)__builtin_amdgcn_readfirstlane(lo));
 }
 
 // ---------------------------------------------------------------------------
