@@ -407,7 +407,8 @@ int64_t l2_slabs(size_t gather_volume_bytes) {
 // per workgroup that no counter can exceed 65535.
 int plan_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins, bool packed,
                 const HardTune& tune, int32_t gather, bool brick) {
-  const int64_t groups = brick ? RodWalk::rods(f->nx, f->ny, f->nz) : (int64_t)((f->ny + 3) / 4) * f->nz;
+  const Rods rods = rods_for(f->nx, f->ny, f->nz);
+  const int64_t groups = brick ? rods.count(f->ny, f->nz) : (int64_t)((f->ny + 3) / 4) * f->nz;
   int64_t c;
   if (tune.chunks) {
     c = tune.chunks;
@@ -420,7 +421,7 @@ int plan_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, i
   }
   if (c > groups) c = groups;
   if (packed) {
-    const int64_t per = 65535 / (brick ? 16 * kRodX : 4 * (int64_t)f->nx);  // groups per workgroup
+    const int64_t per = 65535 / (brick ? 16 * rods.longest(f->nx) : 4 * f->nx);  // groups per workgroup
     const int64_t need = (groups + per - 1) / per;
     if (c < need) c = need;
   }
@@ -688,8 +689,9 @@ int plan_pairs(const mi_pair* pairs, int32_t n_pairs, int32_t bins, int32_t n_q,
     if (pr.n_transforms > 0 && !pr.transforms) return MI_ERR_NULL;
     // slabs of about tune.slab_voxels voxels (at most 65535 with 16-bit
     // counters), 8 or more, a multiple of 8
-    const int64_t groups = RodWalk::rods(pr.fixed.nx, pr.fixed.ny, pr.fixed.nz);
-    const int64_t gvox = 16 * kRodX;
+    const Rods rods = rods_for(pr.fixed.nx, pr.fixed.ny, pr.fixed.nz);
+    const int64_t groups = rods.count(pr.fixed.ny, pr.fixed.nz);
+    const int64_t gvox = 16 * rods.longest(pr.fixed.nx);
     const int64_t target = packed ? std::min<int64_t>(65535, tune.slab_voxels) : tune.slab_voxels;
     int64_t per = target / gvox;
     if (per < 1) per = 1;

@@ -238,6 +238,7 @@ struct HardGeom {
   uint32_t gvol_bytes;
   int32_t gather;        // Gather
   int32_t bins;
+  Rods rods;     // of brick sweeps
   double scale;  // B / (R 2^48), R = moving hi - lo + 1
   Divider div;   // floor(X / R) for the exact fallback
 };

@@ -576,6 +576,7 @@ HardGeom make_hard_geom(const VolumeDesc& fixed, const VolumeDesc& moving, const
   g.mnz = moving.nz;
   g.gvol_bytes = (uint32_t)gather_volume_bytes(gather, moving.nx, moving.ny, moving.nz);
   g.bins = bins;
+  g.rods = rods_for(fixed.nx, fixed.ny, fixed.nz);
   const uint32_t R = (uint32_t)((int32_t)moving.hi - (int32_t)moving.lo + 1);
   g.scale = ldexp((double)bins / (double)R, -48);
   g.div = make_divider(R);

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 namespace gemi {
 
 // A dispatch counts its work-items in 32 bits: a grid of n x (workgroups
@@ -146,33 +148,48 @@ constexpr uint32_t tiled_index(uint32_t ix, uint32_t iy, uint32_t iz, uint32_t p
   return (iz * (py / 2) + iy) * (2 * px) + 4 * ix - 3 * lx - (2 * px - s) * ly - (px * py - 2 * s) * lz;
 }
 
-// A slab's walk in brick sweeps.  The fixed volume is cut into rods of 64 x 4
-// x 4 voxels (cubes of 4 x 4 x 4, one wave step each, along x), numbered by
-// x segment, then by blocks of yb rods along y, then z, then y within the
-// block; a slab is a contiguous range of that numbering, so about yb by yb
-// rods of one segment: nearly a cube of the fixed volume, whose image stays
-// compact under any rotation.  The waves take a slab's rods in turn, so
-// that neighbouring rods are swept at the same time.
+// The rods that brick sweeps cut the fixed volume into: segments of the x axis,
+// all `width` voxels but the last, by 16 rows, 2^ly along y and 16 / 2^ly along z
+// (one wave step: 4 voxels of each row).
 constexpr int32_t kRodX = 64;
+struct Rods {
+  int32_t width = kRodX, segments = 1, ly = 2;
+  constexpr int32_t ry() const { return 1 << ly; }
+  constexpr int32_t rz() const { return 16 >> ly; }
+  constexpr int32_t last(int32_t nx) const { return nx - (segments - 1) * width; }
+  constexpr int32_t longest(int32_t nx) const { return last(nx) > width ? last(nx) : width; }
+  constexpr int32_t gy(int32_t ny) const { return (ny + ry() - 1) >> ly; }
+  constexpr int32_t gz(int32_t nz) const { return (nz + rz() - 1) >> (4 - ly); }
+  constexpr int64_t count(int32_t ny, int32_t nz) const { return (int64_t)segments * gy(ny) * gz(nz); }
+};
+constexpr Rods cube_rods(int32_t nx) { return Rods{kRodX, (nx + kRodX - 1) / kRodX, 2}; }
+
+// A slab's walk in brick sweeps: the rods are numbered by
+// x segment, then by blocks of yb rods along y, then z, then y within the
+// block; a slab is a contiguous range of that numbering, so a block of one
+// segment about as high as deep: nearly a cube of the fixed volume, whose image
+// stays compact under any rotation.  The waves take a slab's rods in turn, so
+// that neighbouring rods are swept at the same time.
 struct RodWalk {
   int64_t u, u1;
   int32_t xs, b0, bw, gz, gy;  // x segment, y block and its width, z, y within the block
   int32_t Gy, Gz, yb;
-
-  static constexpr int64_t rods(int32_t fnx, int32_t fny, int32_t fnz) {
-    return (int64_t)((fnx + kRodX - 1) / kRodX) * ((fny + 3) / 4) * ((fnz + 3) / 4);
-  }
+  Rods rods;
 
   constexpr void init(int32_t fnx, int32_t fny, int32_t fnz, int32_t chunks, uint32_t chunk, int wave) {
-    Gy = (fny + 3) / 4;
-    Gz = (fnz + 3) / 4;
-    const int64_t n = rods(fnx, fny, fnz);
+    init(cube_rods(fnx), fny, fnz, chunks, chunk, wave);
+  }
+  constexpr void init(const Rods& r, int32_t fny, int32_t fnz, int32_t chunks, uint32_t chunk, int wave) {
+    rods = r;
+    Gy = r.gy(fny);
+    Gz = r.gz(fnz);
+    const int64_t n = r.count(fny, fnz);
     u = n * chunk / chunks;
     u1 = n * (chunk + 1) / chunks;
     const int32_t per = (int32_t)((n + chunks - 1) / chunks);
     yb = 1;
-    while (yb < Gy && yb * yb < per) ++yb;
-    const int32_t plane = Gy * Gz;  // <= 2^20
+    while (yb < Gy && ((yb * yb) << (2 * r.ly)) < per * 16) ++yb;  // yb ry < per / yb rz
+    const int32_t plane = Gy * Gz;  // <= 2^24
     xs = (int32_t)(u / plane);
     const int32_t rem = (int32_t)(u - (int64_t)xs * plane);
     b0 = rem / (yb * Gz) * yb;
@@ -182,9 +199,9 @@ struct RodWalk {
     next(wave);
   }
 
-  constexpr void next(int32_t rods) {
-    u += rods;
-    gy += rods;
+  constexpr void next(int32_t n) {
+    u += n;
+    gy += n;
     while (gy >= bw) {
       gy -= bw;
       if (++gz == Gz) {
@@ -199,10 +216,41 @@ struct RodWalk {
       }
     }
   }
-  constexpr int32_t x0() const { return xs * kRodX; }
-  constexpr int32_t j0() const { return (b0 + gy) * 4; }
-  constexpr int32_t k0() const { return gz * 4; }
+  constexpr int32_t x0() const { return xs * rods.width; }
+  constexpr int32_t j0() const { return (b0 + gy) << rods.ly; }
+  constexpr int32_t k0() const { return gz << (4 - rods.ly); }
 };
+
+// The rods of a fixed volume.  Segments: about 64 voxels and nearly equal (48 to
+// 96), so that slabs, which are ranges of rods, hold nearly equal work (80x96x96
+// in segments of 64 and 16: 408 us for 216 transforms, of 80: 288).  Rows: the
+// cross-section that leaves the fewest lanes without a voxel, the flatter ones
+// weighted by what they cost where none is left over: the nearer to 4 x 4, the
+// fewer cache lines a wave's image touches.  In a fixed volume of at most 8
+// slices (or rows) the flat ones win by themselves: a turned one lies mostly
+// outside, and their rods are outside as a whole more often (nz = 8: 160, 149,
+// 148 in the terms below).  8 pairs of 256x256xnz u8, 16
+// transforms each, 32 bins, us a call with 4x4, 8x2 and 16x1 rows: nz = 5 138,
+// 120, 110; 9 192, 169, 159; 17 281, 264, 271; 3 of nz = 64 363, 373, 400; 216
+// rotations of up to 180 degrees, 256x256x180 u16: 5428, 5820, 6809.
+inline Rods rods_for(int32_t nx, int32_t ny, int32_t nz) {
+  Rods r;
+  r.segments = nx < 96 ? 1 : (nx + 31) / 64;
+  r.width = (nx + 8 * r.segments) / (16 * r.segments) * 16;
+  if (r.width < 16) r.width = 16;
+  constexpr double weight[5] = {1.15, 1.05, 1.0, 1.05, 1.15};
+  double least = 1e300;
+  for (int32_t ly : {2, 3, 1, 4, 0}) {
+    const Rods c{r.width, 1, ly};
+    const bool thin = (ly > 2 && nz <= 8) || (ly < 2 && ny <= 8);
+    const double cost = (thin ? 0.9 : 1.0) * weight[ly] * (double)c.count(ny, nz);
+    if (cost < least) {
+      least = cost;
+      r.ly = ly;
+    }
+  }
+  return r;
+}
 
 // Lanes per row group of the pass that turns fixed bins into slots: a lane per
 // wave tile, rounded up to a power of two, so that a wave of 64 takes 64 / span

@@ -359,7 +359,8 @@ __device__ __forceinline__ void sweep_rods(const HardGeom& g, const double* Md, 
                                            uint32_t chunk, uint32_t* lds_hist) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int dx = lane & 3, dy = (lane >> 2) & 3, dz = lane >> 4;
+  const Rods rods = g.rods;
+  const int dx = lane & 3, dy = (lane >> 2) & (rods.ry() - 1), dz = lane >> (2 + rods.ly);
   const HardStep hs(g, PACKED, GL);
   const int64_t sx = 4 * Mq[0], sy = 4 * Mq[4], sz = 4 * Mq[8];
   const int64_t ox = Mq[0] * dx + Mq[1] * dy + Mq[2] * dz;
@@ -371,7 +372,7 @@ __device__ __forceinline__ void sweep_rods(const HardGeom& g, const double* Md, 
   const double* mrow = Md + 4 * axis;
   const int64_t m0 = __double2ll_rn(mrow[0] * 4294967296.0), m1 = __double2ll_rn(mrow[1] * 4294967296.0);
   const int64_t m2 = __double2ll_rn(mrow[2] * 4294967296.0), m3 = __double2ll_rn(mrow[3] * 4294967296.0);
-  const int64_t ex = m0 * (kRodX - 1), ey = m1 * 3, ez = m2 * 3;
+  const int64_t ex = m0 * (rods.longest(g.fnx) - 1), ey = m1 * (rods.ry() - 1), ez = m2 * (rods.rz() - 1);
   const int64_t omin = (ex < 0 ? ex : 0) + (ey < 0 ? ey : 0) + (ez < 0 ? ez : 0);
   const int64_t omax = (ex > 0 ? ex : 0) + (ey > 0 ? ey : 0) + (ez > 0 ? ez : 0);
   const int64_t top = (int64_t)((axis == 0 ? g.mnx : (axis == 1 ? g.mny : g.mnz)) - 1) << 32;
@@ -379,7 +380,7 @@ __device__ __forceinline__ void sweep_rods(const HardGeom& g, const double* Md, 
   const uint32_t lane_f = dz * fplane + dy * fnx + dx, lane_f4 = lane_f + 3 * dx;
   global_u8* const fbins = (global_u8*)g.fbins;
   RodWalk w;
-  w.init(g.fnx, g.fny, g.fnz, chunks, chunk, wave);
+  w.init(rods, g.fny, g.fnz, chunks, chunk, wave);
   for (; w.u < w.u1; w.next(NW)) {
     const int32_t x0 = w.x0(), j0 = w.j0(), k0 = w.k0();
     const int64_t r = m0 * x0 + m1 * j0 + m2 * k0 + m3;
@@ -393,7 +394,7 @@ __device__ __forceinline__ void sweep_rods(const HardGeom& g, const double* Md, 
     int64_t qx = lane_value(0) + ox, qy = lane_value(1) + oy, qz = lane_value(2) + oz;
     if (j0 + dy >= g.fny || k0 + dz >= g.fnz) continue;
     global_u8* const rod = fbins + ((uint32_t)k0 * fplane + (uint32_t)j0 * fnx + (uint32_t)x0);  // < 2^28
-    const int32_t width = g.fnx - x0 < kRodX ? g.fnx - x0 : kRodX;
+    const int32_t width = w.xs == rods.segments - 1 ? g.fnx - x0 : rods.width;
     const int32_t runs = width / kCubeRun;  // whole runs of 16 voxels, four steps each
     for (int32_t run = 0; run < runs; ++run) {
       const uint32_t bins4 = *(global_unaligned32*)(rod + (uint32_t)run * kCubeRun + lane_f4);
