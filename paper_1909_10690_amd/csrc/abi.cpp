@@ -1162,8 +1162,14 @@ PairsTune pairs_tune_for(const mi_context* ctx, const mi_pair* pairs, int32_t n_
     if (e.first == k) return e.second;
   // 1024 threads where the table leaves room for fewer than four workgroups
   // in a CU's LDS (as the sampled sweeps; 4 pairs of up to 256^3, 128 bins, 16
-  // transforms each: 943 -> 770 us of sweep)
+  // transforms each: 943 -> 770 us of sweep).  Up to 64 bins, whose tables take
+  // little to clear and flush, slabs of half the size, which keep more
+  // workgroups busy on few pairs (us a call, 131072 and 65536 voxels, 64 bins
+  // u8: 3 of about 100^3, 16 transforms each, 169 and 144, one 256^3, one
+  // transform 207 and 145, 8 of 256x180x128 1325 and 1315, of 256x256x17 271 and
+  // 279; 128 bins: the last two 1378 and 1453, 290 and 316).
   PairsTune t;
+  if (bins <= 64) t.slab_voxels = 65536;
   if (4 * hist_lds_bytes(bins, bins > 128) > 160 * 1024) t.block = 1024;
   return t;
 }

@@ -121,94 +121,146 @@ __device__ __forceinline__ void for_each_item(const PairDesc* __restrict__ pairs
   }
 }
 
+// The bins of 16 consecutive voxels at src (16-byte aligned), a whole run of a
+// row, in stored order: stored byte 4 j + k is voxel 4 k + j.
+template <typename T, typename F>
+__device__ __forceinline__ uint4_t run_bins(const __attribute__((address_space(1))) T* src, F&& bin) {
+  constexpr int W = (int)sizeof(T);  // 16-byte words of the run
+  uint4_t v[W];
+#pragma unroll
+  for (int i = 0; i < W; ++i) v[i] = ((global_cu4*)src)[i];
+  uint4_t o;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint32_t b = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int e = 4 * k + j, per = 16 / W;  // voxels a 16-byte word
+      const uint32_t word = v[e / per][(e % per) * W / 4];
+      T u;
+      if constexpr (W == 4) u = __builtin_bit_cast(T, word);
+      else u = (T)(word >> (8 * ((e * W) & 3)));
+      b |= bin(u) << (8 * k);
+    }
+    o[j] = b;
+  }
+  return o;
+}
+
 // Fixed bins of every pair in the sweep's order (cube_run_x), one wave per
 // chunk of kPrepChunk consecutive stored bytes of a pair's fixed volume:
-// every lane busy whatever the row length.  Rows of whole runs (nx a multiple
-// of 16) and full chunks of an aligned u8 volume are handled a run per lane,
-// in 16-byte accesses; otherwise lane l takes bytes l, l + 64, ...
+// every lane busy whatever the row length.  Full chunks of aligned volumes
+// whose rows are whole runs (nx a multiple of 16) are handled a run per lane,
+// in 16-byte accesses (2 pairs of 256^3 u16: 57 us a byte per lane at a time, 20
+// now); otherwise lane l takes bytes l, l + 64, ..., the row of each found from
+// the one before.
 __global__ void prep_fixed_kernel(PairsArgs a, int64_t chunks) {
   for_each_item(a.pairs, a.fchunk_base, a.n_pairs, chunks, [&](const PairDesc& d, int64_t c, int lane) {
     const int64_t nvox = (int64_t)d.geom.fnx * d.geom.fny * d.geom.fnz;
     const int64_t c0 = c * kPrepChunk;
     global_out8* __restrict__ out = (global_out8*)d.geom.fbins;
-    auto bin8 = [&](uint32_t u) {
-      return fixed_bin_int((int32_t)u, (int32_t)d.flo, (int32_t)d.fhi, (uint32_t)d.geom.bins, d.fdiv);
+    auto bin_int = [&](int32_t u) {
+      return fixed_bin_int(u, (int32_t)d.flo, (int32_t)d.fhi, (uint32_t)d.geom.bins, d.fdiv);
     };
-    if (d.fdtype == 0 && d.geom.fnx % kCubeRun == 0 && c0 + kPrepChunk <= nvox &&
-        (((uintptr_t)d.fixed | (uintptr_t)out) & 15) == 0) {
-      const uint4_t v = *(global_cu4*)((global_u8*)d.fixed + c0 + kPrepLane * lane);
+    auto bin_real = [&](float u) { return fixed_bin_real((double)u, d.flo, d.fhi, d.geom.bins); };
+    if (d.geom.fnx % kCubeRun == 0 && c0 + kPrepChunk <= nvox && (((uintptr_t)d.fixed | (uintptr_t)out) & 15) == 0) {
+      const int64_t at = c0 + kPrepLane * lane;
       uint4_t o;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {  // stored word j: byte j of each of the run's four words
-        uint32_t b = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) b |= bin8((v[k] >> (8 * j)) & 0xFFu) << (8 * k);
-        o[j] = b;
+      switch (d.fdtype) {  // the same for every lane
+      case 0: o = run_bins((global_u8*)d.fixed + at, bin_int); break;
+      case 1: o = run_bins((global_u16*)d.fixed + at, bin_int); break;
+      case 2: o = run_bins((global_i16*)d.fixed + at, bin_int); break;
+      default: o = run_bins((global_f32*)d.fixed + at, bin_real);
       }
-      *(global_out4*)(out + c0 + kPrepLane * lane) = o;
+      *(global_out4*)(out + at) = o;
       return;
     }
     const uint32_t nx = (uint32_t)d.geom.fnx;
-    for (int k = 0; k < kPrepLane; ++k) {
-      const int64_t p = c0 + lane + 64 * k;
-      if (p >= nvox) break;
-      const uint32_t row = (uint32_t)p / nx;  // nvox < 2^28
-      const size_t v = (size_t)row * nx + (size_t)cube_run_x((int32_t)((uint32_t)p - row * nx), (int32_t)nx);
-      uint32_t b;
-      if (d.fdtype == 3)
-        b = fixed_bin_real((double)((global_f32*)d.fixed)[v], d.flo, d.fhi, d.geom.bins);
-      else
-        b = fixed_bin_int(load_int(d.fixed, d.fdtype, v), (int32_t)d.flo, (int32_t)d.fhi,
-                          (uint32_t)d.geom.bins, d.fdiv);
-      out[p] = (uint8_t)b;
+    uint32_t p = (uint32_t)c0 + (uint32_t)lane;  // < 2^28
+    uint32_t base = p / nx * nx, x = p - base;   // the row's first voxel, the place in the row
+    for (int k = 0; k < kPrepLane && p < (uint32_t)nvox; ++k) {
+      const uint32_t v = base + (uint32_t)cube_run_x((int32_t)x, (int32_t)nx);
+      out[p] = (uint8_t)(d.fdtype == 3 ? bin_real(((global_f32*)d.fixed)[v]) : bin_int(load_int(d.fixed, d.fdtype, v)));
+      p += 64;
+      x += 64;
+      if (x >= nx) {
+        const uint32_t rows = nx >= 64 ? 1 : x / nx;
+        base += rows * nx;
+        x -= rows * nx;
+      }
     }
   });
 }
 
+// The voxels x .. x + 4 (8-bit) or x .. x + 3 (16-bit) of the row whose voxel x
+// lies at index at, past the row's end its last one again (left: voxels of the
+// row from x on).  Loads at any address; at the volume's end they start earlier,
+// so that they stay within.
+template <typename T>
+__device__ __forceinline__ uint64_t row_words(const void* vol, uint32_t at, uint32_t left, uint32_t nvox) {
+  const uint32_t from = at + 4 <= nvox ? at : nvox - 4;  // nvox >= 8
+  if constexpr (sizeof(T) == 1) {
+    global_u8* const p = (global_u8*)vol;
+    uint32_t v = *(global_unaligned32*)(p + from) >> (8 * (at - from));
+    const uint32_t end = p[at + (left > 4 ? 4u : left - 1)];
+    if (left < 4) v = (v & ((1u << (8 * left)) - 1)) | ((end * 0x01010101u) << (8 * left));
+    return v | ((uint64_t)end << 32);
+  } else {
+    uint64_t v = *(global_unaligned64*)((global_u8*)vol + 2 * (size_t)from) >> (16 * (at - from));
+    if (left < 4) {
+      const uint64_t keep = (1ull << (16 * left)) - 1, last = (v >> (16 * (left - 1))) & 0xFFFFu;
+      v = (v & keep) | ((last * 0x0001000100010001ull) & ~keep);
+    }
+    return v;
+  }
+}
+
 // Moving oct volumes of every pair, with the layout and clamping of the
 // single-pair path, one wave per chunk of kPrepChunk consecutive records.
-// Tiled 8-bit octs of a u8 volume: a tile is 4 x 2 x 2 records; lane l of a
-// pass takes the four records of one tile row (l & 3) of tile l / 4, from the
-// five bytes of each of its four source rows, and stores 32 bytes, so the
-// wave stores 2 KiB of consecutive records.  Otherwise a record per lane at a
-// time.
+// In tiles, a lane takes the records of one tile row (4 of 8 bytes, or 2 of 16),
+// 32 bytes, so that a wave's stores are 2 KiB of consecutive records, from one
+// or two loads of each of its four source rows (2 pairs of 256^3 u16: 214 us,
+// with a load a corner 271; u8: 94 us with a 4-byte and a 1-byte load a row, 106
+// with one of 8 bytes).  Untiled, or 16-bit voxels in 8-bit
+// corners: a record per lane at a time.
 __global__ void prep_moving_kernel(PairsArgs a, int64_t items) {
   for_each_item(a.pairs, a.mchunk_base, a.n_pairs, items, [&](const PairDesc& d, int64_t c, int lane) {
     const uint32_t nx = (uint32_t)d.geom.mnx, ny = (uint32_t)d.geom.mny, nz = (uint32_t)d.geom.mnz;
-    const uint32_t plane = nx * ny;
+    const uint32_t plane = nx * ny, nvox = plane * nz;
     const int32_t base = gather_base(d.geom.gather);
     const bool tiled = (d.geom.gather & kTiled) != 0, o8 = base == kOct8;
     const uint32_t px = (uint32_t)tile_pad_x((int32_t)nx, o8), py = (uint32_t)tile_pad((int32_t)ny);
     const uint32_t records = d.geom.gvol_bytes / (o8 ? 8u : 16u);  // < 2^32
     const uint32_t c0 = (uint32_t)c * kPrepChunk;
-    if (d.geom.gather == (kOct8 | kTiled) && d.mdtype == 0 && nx >= 4) {
-      global_u8* __restrict__ mv = (global_u8*)d.moving;
-      const uint32_t tx = px / 4, ty = py / 2;
-      const bool ident = d.mlo == 0 && d.mhi == 255;  // 8-bit corners: the clamp changes nothing then
+    // Tile rows: REC records of a row to a lane; f(records' first index, the
+    // four source rows from voxel x on).
+    auto tile_rows = [&]<typename T, uint32_t REC>(auto&& f) {
+      const uint32_t tx = px / REC, ty = py / 2;
 #pragma unroll
-      for (uint32_t k = 0; k < kPrepChunk / 256; ++k) {
-        const uint32_t i = c0 + 256 * k + 4 * (uint32_t)lane;  // the first of four records
+      for (uint32_t k = 0; k < kPrepChunk / (64 * REC); ++k) {
+        const uint32_t i = c0 + 64 * REC * k + REC * (uint32_t)lane;
         if (i >= records) break;
-        const uint32_t tile = i / 16, tr = tile / tx, tz = tr / ty;
+        const uint32_t tile = i / (4 * REC), tr = tile / tx, tz = tr / ty;
         uint32_t y = (tr - tz * ty) * 2 + (lane & 1), z = tz * 2 + ((lane >> 1) & 1);
         y = y < ny ? y : ny - 1;  // padding: any defined contents
         z = z < nz ? z : nz - 1;
-        // four bytes from x, or the row's last four shifted down (beyond the
-        // row: its last byte)
-        const uint32_t x = (tile - tr * tx) * 4, xs = x + 4 <= nx ? x : nx - 4, sh = 8 * (x - xs);
-        const uint32_t a0 = z * plane + y * nx + xs;
-        const uint32_t dy = y + 1 < ny ? nx : 0, dz = z + 1 < nz ? plane : 0, last = x + 4 < nx ? 4u : nx - 1 - xs;
-        const uint32_t rows[4] = {a0, a0 + dy, a0 + dz, a0 + dz + dy};
-        uint32_t w[4], e[4];  // bytes x .. x + 3 and x + 4 (clamped) of each source row
+        const uint32_t x = (tile - tr * tx) * REC;  // < nx
+        const uint32_t at = z * plane + y * nx + x, dy = y + 1 < ny ? nx : 0, dz = z + 1 < nz ? plane : 0;
+        const uint64_t rows[4] = {row_words<T>(d.moving, at, nx - x, nvox), row_words<T>(d.moving, at + dy, nx - x, nvox),
+                                  row_words<T>(d.moving, at + dz, nx - x, nvox),
+                                  row_words<T>(d.moving, at + dz + dy, nx - x, nvox)};
+        f(i, rows);
+      }
+    };
+    if (tiled && o8 && d.mdtype == 0) {
+      const bool ident = d.mlo == 0 && d.mhi == 255;  // 8-bit corners: the clamp changes nothing then
+      tile_rows.template operator()<uint8_t, 4>([&](uint32_t i, const uint64_t (&rows)[4]) {
+        uint32_t w[4], e[4];  // voxels x .. x + 3 and x + 4 of each source row
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          w[r] = *(global_unaligned32*)(mv + rows[r]);
-          e[r] = mv[rows[r] + last];
-          if (sh) w[r] = (w[r] >> sh) | ((e[r] * 0x01010101u) << (32 - sh));
-        }
-        if (!ident) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
+          w[r] = (uint32_t)rows[r];
+          e[r] = (uint32_t)(rows[r] >> 32) & 0xFFu;
+          if (!ident) {
             uint32_t o = 0;
 #pragma unroll
             for (int b = 0; b < 4; ++b) o |= clamp_offset((int32_t)((w[r] >> (8 * b)) & 0xFFu), d.mlo, d.mhi) << (8 * b);
@@ -216,7 +268,7 @@ __global__ void prep_moving_kernel(PairsArgs a, int64_t items) {
             e[r] = clamp_offset((int32_t)e[r], d.mlo, d.mhi);
           }
         }
-        // records: byte 4 dz + 2 dy + dx' (layout of pack_oct8_kernel)
+        // records: byte 4 dz + 2 dy + dx' (layout of pack_oct8)
         auto pair = [&](int r, int j) -> uint32_t {  // bytes j, j + 1 of row r
           return j < 3 ? (w[r] >> (8 * j)) & 0xFFFFu : (w[r] >> 24) | (e[r] << 8);
         };
@@ -229,6 +281,31 @@ __global__ void prep_moving_kernel(PairsArgs a, int64_t items) {
         global_out4* __restrict__ out = (global_out4*)((global_out2*)d.geom.gvol + i);
         out[0] = o[0];
         out[1] = o[1];
+      });
+      return;
+    }
+    if (tiled && !o8) {
+      auto records2 = [&]<typename T>() {
+        tile_rows.template operator()<T, 2>([&](uint32_t i, const uint64_t (&rows)[4]) {
+          uint4_t o[2];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            uint32_t v[3];
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+              v[b] = clamp_offset((int32_t)(T)(rows[r] >> (8 * sizeof(T) * b)), d.mlo, d.mhi);
+            o[0][r] = v[0] | (v[1] << 16);
+            o[1][r] = v[1] | (v[2] << 16);
+          }
+          global_out4* __restrict__ out = (global_out4*)d.geom.gvol + i;
+          out[0] = o[0];
+          out[1] = o[1];
+        });
+      };
+      switch (d.mdtype) {  // the same for every lane
+      case 0: records2.template operator()<uint8_t>(); break;
+      case 1: records2.template operator()<uint16_t>(); break;
+      default: records2.template operator()<int16_t>();
       }
       return;
     }

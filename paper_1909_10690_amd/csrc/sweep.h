@@ -19,6 +19,8 @@ typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef const __attribute__((address_space(1))) uint8_t global_u8;
 typedef uint32_t unaligned32 __attribute__((aligned(1)));
 typedef const __attribute__((address_space(1))) unaligned32 global_unaligned32;
+typedef uint64_t unaligned64 __attribute__((aligned(1)));
+typedef const __attribute__((address_space(1))) unaligned64 global_unaligned64;
 
 // Loads of one record of a buffer whose descriptor has a stride: the
 // hardware forms base + index * stride, so the index needs no shift.
