@@ -131,7 +131,8 @@ int check_common(const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins
 // Workspace layout (each region 256-byte aligned):
 //   index-space matrices f64[n][12] (the caller's physical ones composed)
 //   fixed bins   u8[nvox_fixed]
-//   hard:        moving oct volume u16x8[mnz][mny][mnx],
+//   hard:        moving oct volume u16x8[mnz][mny][mnx] (room for padded tiles
+//                of it with MI_COMPACT_SLABS),
 //                hist u32[n][B][B]          (only when the caller passes no hist_out)
 //                count u64[n], MI partial sums (reduce_part_bytes)
 //   Parzen:      16-bit quad volume (integer moving volume) or f32x4 quad volume
@@ -143,13 +144,18 @@ int check_common(const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins
 //   Parzen grad: + table marginals f64[n][2B], dMI/dp tables f32[n][n_q][B][B]
 //   sampled:     + sample list u32x2[nvox_fixed] and its length u64
 struct Layout {
-  size_t xf = 0, order = 0, fbins = 0, gvol = 0, hist = 0, rowmap = 0, tmask = 0, table = 0, count = 0, part = 0,
+  size_t xf = 0, order = 0, fbins = 0, gvol = 0, gvol_bytes = 0, hist = 0, rowmap = 0, tmask = 0, table = 0, count = 0, part = 0,
          marg = 0, gtab = 0, list = 0, nlist = 0, total = 0;
 };
 
 
+// Bytes of the hard path's octs in tiles (brick sweeps), the last tiles padded.
+size_t tiled_bytes(const mi_volume* m) {
+  return gather_volume_bytes(oct_gather(m->lo, m->hi) | kTiled, m->nx, m->ny, m->nz);
+}
+
 Layout layout(const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins, int32_t n_q,
-              bool parzen, bool grad, bool need_hist, bool sampled = false) {
+              bool parzen, bool grad, bool need_hist, bool sampled = false, bool tiles = false) {
   Layout L;
   size_t off = 0;
   L.xf = off;
@@ -161,7 +167,8 @@ Layout layout(const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins, i
   const size_t bb = (size_t)bins * bins;
   if (!parzen) {
     L.gvol = off;
-    off += align256(hard_gather_bytes(m));
+    L.gvol_bytes = tiles ? tiled_bytes(m) : hard_gather_bytes(m);
+    off += align256(L.gvol_bytes);
     L.hist = off;
     if (need_hist) off += align256(bb * 4 * (size_t)n);
     L.count = off;
@@ -196,6 +203,17 @@ Layout layout(const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins, i
   }
   L.total = off;
   return L;
+}
+
+// Layout of a hard-binned call (not sampled) in at most `limit` bytes: with
+// MI_COMPACT_SLABS there is room for padded tiles if it fits, so that a smaller
+// workspace, sized without the flag, serves as before.
+Layout hard_layout(const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins, int32_t n_q, bool need_hist,
+                   int32_t flags, size_t limit) {
+  const Layout L = layout(f, m, n, bins, n_q, false, false, need_hist);
+  if (!(flags & MI_COMPACT_SLABS) || tiled_bytes(m) > kMaxGatherBytes) return L;
+  const Layout T = layout(f, m, n, bins, n_q, false, false, need_hist, false, true);
+  return T.total <= limit ? T : L;
 }
 
 VolumeDesc desc(const mi_volume* v) {
@@ -381,8 +399,8 @@ struct TimedLaunch {
 // Whether a hard-binned call sweeps bricks, the layout it prepares, and its
 // path in the record of the last preparation.
 bool call_brick(int32_t flags, const HardTune& tune) { return (flags & MI_COMPACT_SLABS) && tune.block == 1024; }
-int32_t call_gather(const mi_volume* m, int32_t n, int32_t flags, const HardTune& tune) {
-  return hard_gather(desc(m), n, (flags & MI_VOLUMES_UNCHANGED) != 0, call_brick(flags, tune));
+int32_t call_gather(const mi_volume* m, const Layout& L, int32_t n, int32_t flags, const HardTune& tune) {
+  return hard_gather(desc(m), n, (flags & MI_VOLUMES_UNCHANGED) != 0, call_brick(flags, tune), L.gvol_bytes);
 }
 int hard_prep_path(int32_t gather, bool brick) { return 8 + 2 * gather + (brick ? 1 : 0); }
 
@@ -923,7 +941,7 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   uint8_t* fb = (uint8_t*)(ws + L.fbins);
   void* gvol = ws + L.gvol;
   const bool brick = !smp && call_brick(flags, tune);
-  const int32_t gather = smp ? oct_gather(moving->lo, moving->hi) : call_gather(moving, n, flags, tune);
+  const int32_t gather = smp ? oct_gather(moving->lo, moving->hi) : call_gather(moving, L, n, flags, tune);
   const size_t bb = (size_t)bins * bins;
   uint64_t* count = (uint64_t*)(ws + L.count);
   unsigned long long* nlist = (unsigned long long*)(ws + L.nlist);
@@ -1439,7 +1457,9 @@ int mi_workspace_size(mi_context*, const mi_volume* fixed, const mi_volume* movi
   if (st != MI_OK) return st;
   if (n_q < 1 || n_q > MI_MAX_Q) return MI_ERR_Q;
   if ((flags & MI_SAMPLED) && for_grad) return MI_ERR_UNSUPPORTED;
-  *bytes = layout(fixed, moving, n, bins, n_q, parzen, for_grad, true, (flags & MI_SAMPLED) != 0).total;
+  const bool sampled = (flags & MI_SAMPLED) != 0;
+  *bytes = (parzen || sampled ? layout(fixed, moving, n, bins, n_q, parzen, for_grad, true, sampled)
+                              : hard_layout(fixed, moving, n, bins, n_q, true, flags, SIZE_MAX)).total;
   return MI_OK;
 }
 
@@ -1467,7 +1487,7 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
     ctx->last_prep.clear();
     return r;
   }
-  const Layout L = layout(fixed, moving, n, bins, 1, false, false, true);
+  const Layout L = hard_layout(fixed, moving, n, bins, 1, true, flags, workspace_bytes);
   if (!workspace || workspace_bytes < L.total) return MI_ERR_WORKSPACE;
   if (!ctx) return MI_ERR_NULL;
   if (n == 0) return MI_OK;
@@ -1489,7 +1509,7 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   HardTune best = ctx->hard_default;
   float best_ms = 3.4e38f;
   HardTune base = ctx->hard_default;
-  base.chunks = plan_chunks(ctx, fixed, moving, n, bins, use_packed(base, bins), base, call_gather(moving, n, flags, base),
+  base.chunks = plan_chunks(ctx, fixed, moving, n, bins, use_packed(base, bins), base, call_gather(moving, L, n, flags, base),
                             call_brick(flags, base));
   const int32_t chunk_opts[3] = {base.chunks / 2, base.chunks, base.chunks * 2};
   // LDS counter layouts: u32 or packed 16-bit pairs (only packed fits above 128 bins)
@@ -1585,7 +1605,8 @@ int mi_eval(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   if ((st = check_q(q, n_q)) != MI_OK) return st;
   if (n > 0 && (!transforms || !mi_out)) return MI_ERR_NULL;
   if (parzen && hist_out) return MI_ERR_UNSUPPORTED;
-  const Layout L = layout(fixed, moving, n, bins, n_q, parzen, false, hist_out == nullptr);
+  const Layout L = parzen ? layout(fixed, moving, n, bins, n_q, true, false, true)
+                          : hard_layout(fixed, moving, n, bins, n_q, hist_out == nullptr, flags, workspace_bytes);
   if (!workspace || workspace_bytes < L.total) return MI_ERR_WORKSPACE;
   if (!ctx) return MI_ERR_NULL;
   if (n == 0) return MI_OK;
@@ -1619,12 +1640,12 @@ int mi_eval(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   key_q(key, q, n_q);
   int path = 2;
   if (!parzen) {
-    // the launch shape decides what the graph prepares, so a graph serves the
-    // shape it was captured with only
+    // the launch shape and the room for tiles decide what the graph prepares,
+    // so a graph serves those it was captured with only
     const HardTune tune = tune_for(ctx, fixed, moving, n, bins, flags);
     key.insert(key.end(), {(uint64_t)tune.block, (uint64_t)tune.slab_major, (uint64_t)tune.chunks,
-                           (uint64_t)(tune.packed + 1)});
-    path = hard_prep_path(call_gather(moving, n, run_flags, tune), call_brick(run_flags, tune));
+                           (uint64_t)(tune.packed + 1), (uint64_t)L.gvol_bytes});
+    path = hard_prep_path(call_gather(moving, L, n, run_flags, tune), call_brick(run_flags, tune));
   }
   st = graph_run(ctx, key, s, body);
   // the graph prepared them
@@ -1643,7 +1664,8 @@ int mi_eval_noalloc(mi_context* ctx, const mi_volume* fixed, const mi_volume* mo
   if ((st = check_q(q, n_q)) != MI_OK) return st;
   if (n > 0 && (!transforms || !mi_out)) return MI_ERR_NULL;
   if (parzen && hist_out) return MI_ERR_UNSUPPORTED;
-  const Layout L = layout(fixed, moving, n, bins, n_q, parzen, false, hist_out == nullptr);
+  const Layout L = parzen ? layout(fixed, moving, n, bins, n_q, true, false, true)
+                          : hard_layout(fixed, moving, n, bins, n_q, hist_out == nullptr, flags, MI_NOALLOC_SCRATCH_BYTES);
   if (L.total > MI_NOALLOC_SCRATCH_BYTES) return MI_ERR_TOO_LARGE;
   if (!ctx) return MI_ERR_NULL;
   if (n == 0) return MI_OK;

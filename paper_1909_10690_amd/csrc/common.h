@@ -344,15 +344,14 @@ constexpr size_t kCopyBytes = 8 << 20;
 inline int32_t oct_gather(double lo, double hi) {
   return oct8_range(lo, hi) ? kOct8 : (hi - lo < 16384.0 ? kOctD : kOct16);
 }
-inline int32_t hard_gather(const VolumeDesc& m, int32_t n, bool reused, bool brick) {
+// room: bytes of the workspace's region for it.
+inline int32_t hard_gather(const VolumeDesc& m, int32_t n, bool reused, bool brick, size_t room) {
   if (!reused && !brick) {
     const bool large = moving_copy_bytes(m.nx, m.ny, m.nz) > kCopyBytes;
     if (large ? n <= 2 && !oct8_range(m.lo, m.hi) : n <= kCopyTransforms) return kCopy16;
   }
-  // tiles where they need no padding: the workspace's region is the octs'
   const int32_t oct = oct_gather(m.lo, m.hi);
-  const bool fits = tiled_records(m.nx, m.ny, m.nz, oct == kOct8) == (size_t)m.nx * m.ny * m.nz;
-  return brick && fits ? oct | kTiled : oct;
+  return brick && gather_volume_bytes(oct | kTiled, m.nx, m.ny, m.nz) <= room ? oct | kTiled : oct;
 }
 
 // Bytes of the 16-bit quad volume of an integer moving volume on the Parzen

@@ -275,13 +275,15 @@ template <typename T, int BASE>
 __device__ __forceinline__ void pack_tiled(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz, int32_t lo,
                                            int32_t hi, void* __restrict__ out, uint32_t block, uint32_t nb) {
   constexpr uint32_t kx = BASE == kOct8 ? 4 : 2;  // tile width
-  const uint32_t n = (uint32_t)nx * (uint32_t)ny * (uint32_t)nz;  // < 2^28
+  const uint32_t px = (uint32_t)tile_pad_x(nx, BASE == kOct8), py = (uint32_t)tile_pad(ny);
+  const uint32_t n = (uint32_t)tiled_records(nx, ny, nz, BASE == kOct8);  // < 2^29
   auto c = [&](uint32_t i) -> uint32_t { return clamp_offset((int32_t)v[i], lo, hi); };
   for (uint32_t i = block * 256 + threadIdx.x; i < n; i += nb * 256) {
     const uint32_t tile = i / (4 * kx), low = i - tile * (4 * kx);
-    const uint32_t tr = tile / ((uint32_t)nx / kx), tz = tr / ((uint32_t)ny / 2);
-    const uint32_t x = (tile - tr * ((uint32_t)nx / kx)) * kx + low % kx;
-    const uint32_t y = (tr - tz * ((uint32_t)ny / 2)) * 2 + low / kx % 2, z = 2 * tz + low / (2 * kx);
+    const uint32_t tr = tile / (px / kx), tz = tr / (py / 2);
+    const uint32_t x = (tile - tr * (px / kx)) * kx + low % kx;
+    const uint32_t y = (tr - tz * (py / 2)) * 2 + low / kx % 2, z = 2 * tz + low / (2 * kx);
+    if (x >= (uint32_t)nx || y >= (uint32_t)ny || z >= (uint32_t)nz) continue;  // padding: never gathered
     const uint32_t a = (z * (uint32_t)ny + y) * (uint32_t)nx + x;
     const uint32_t dx = x + 1 < (uint32_t)nx ? 1 : 0, dy = y + 1 < (uint32_t)ny ? (uint32_t)nx : 0;
     const uint32_t dz = z + 1 < (uint32_t)nz ? (uint32_t)nx * (uint32_t)ny : 0;
@@ -343,7 +345,7 @@ __device__ __forceinline__ void pack_volume(const VolumeDesc& m, int32_t gather,
 static unsigned pack_blocks(const VolumeDesc& m, int32_t gather) {
   const size_t nvox = (size_t)m.nx * m.ny * m.nz;
   if (gather == kCopy16) return fill_blocks((nvox + 7) / 8);
-  if (gather & kTiled) return fill_blocks(nvox);
+  if (gather & kTiled) return fill_blocks(tiled_records(m.nx, m.ny, m.nz, gather_base(gather) == kOct8));
   return row_part_blocks(row_parts(m.nx, m.ny, m.nz));
 }
 
