@@ -405,6 +405,10 @@ int32_t call_gather(const mi_volume* m, const Layout& L, int32_t n, int32_t flag
 int hard_prep_path(int32_t gather, bool brick) { return 8 + 2 * gather + (brick ? 1 : 0); }
 
 constexpr size_t kL2Bytes = 4 << 20;  // of an XCD
+// A moving layout that fills the last-level cache, whose slabs are aligned with the
+// slices (aligned_rounds; 192^3 u16, 16 transforms, 108 MiB: 346 us unaligned, 367
+// aligned).
+constexpr size_t kAlignBytes = 256 << 20;
 
 // Slabs per transform that keep one slab's share of the moving gather
 // volume near 1.5 MiB: the workgroups of an XCD sweep one slab for many
@@ -423,10 +427,15 @@ int64_t l2_slabs(size_t gather_volume_bytes) {
 // slab's moving footprint in an XCD's L2 (l2_slabs), a multiple of 8 (one
 // share per XCD), and -- with 16-bit packed LDS counters -- few enough voxels
 // per workgroup that no counter can exceed 65535.
+// Thin slabs over large moving layouts are aligned with the slices
+// (aligned_rounds), and one or two transforms have a second split for when they
+// are turned (turned_slabs).
 int plan_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, int32_t n, int32_t bins, bool packed,
-                const HardTune& tune, int32_t gather, bool brick) {
+                const HardTune& tune, int32_t gather, bool brick, SlabSplit* split) {
   const Rods rods = rods_for(f->nx, f->ny, f->nz);
   const int64_t groups = brick ? rods.count(f->ny, f->nz) : (int64_t)((f->ny + 3) / 4) * f->nz;
+  const int64_t per = packed ? 65535 / (brick ? 16 * rods.longest(f->nx) : 4 * f->nx) : groups;  // groups a workgroup
+  SlabSplit turned{0, 0, 0};
   int64_t c;
   if (tune.chunks) {
     c = tune.chunks;
@@ -434,16 +443,22 @@ int plan_chunks(const mi_context* ctx, const mi_volume* f, const mi_volume* m, i
     // workgroups a CU holds: 32 waves, 160 KiB of LDS
     const int64_t resident = std::max<int64_t>(
         1, std::min<int64_t>(2048 / tune.block, (int64_t)(160 * 1024 / hist_lds_bytes(bins, packed))));
-    const int64_t l2 = tune.slab_major ? l2_slabs(gather_volume_bytes(gather, m->nx, m->ny, m->nz)) : 1;
-    c = planned_slabs((int64_t)voxels(f), n, resident * ctx->cu_count, bins, l2);
+    const int32_t flat = gather & kChoose ? (int32_t)kCopy16 : gather;
+    const size_t flat_bytes = gather_volume_bytes(flat, m->nx, m->ny, m->nz);
+    const int64_t l2 = tune.slab_major ? l2_slabs(flat_bytes) : 1, slots = resident * ctx->cu_count;
+    c = planned_slabs((int64_t)voxels(f), n, slots, bins, l2);
+    if (!brick && flat_bytes >= kAlignBytes) c = aligned_rounds(c, f->nz, n, slots, l2);
+    // (with one workgroup a CU no turn made planned_slabs' count the worse one)
+    if (!brick && !packed && n <= kTurnTransforms && tune.slab_major && resident >= 2 &&
+        gather_volume_bytes(gather, m->nx, m->ny, m->nz) > kTurnBytes)
+      turned = turned_slabs(f->ny, f->nz, n, slots, tune.block / 64);
   }
   if (c > groups) c = groups;
-  if (packed) {
-    const int64_t per = 65535 / (brick ? 16 * rods.longest(f->nx) : 4 * f->nx);  // groups per workgroup
-    const int64_t need = (groups + per - 1) / per;
-    if (c < need) c = need;
-  }
+  const int64_t need = (groups + per - 1) / per;
+  if (c < need) c = need;
   c = ((c + 7) / 8) * 8;
+  split[0] = SlabSplit{(int32_t)c, (int32_t)c, f->nz};
+  split[1] = turned.chunks ? turned : split[0];
   return (int)c;
 }
 
@@ -954,6 +969,16 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   pre.clear.add(count, 8 * (size_t)n);
   if (smp) pre.clear.add(nlist, 8);
   // a sampled call always prepares (its list is not part of the record)
+  HardLaunch H{};
+  H.packed = use_packed(tune, bins) ? 1 : 0;
+  if (!smp) plan_chunks(ctx, fixed, moving, n, bins, H.packed != 0, tune, gather, brick, H.split);
+  const bool two_counts = memcmp(&H.split[0], &H.split[1], sizeof(SlabSplit)) != 0;
+  if (gather & kChoose) {
+    pre.weight = octs_weight(desc(fixed), desc(moving), n);
+    pre.clamp = (flags & MI_BOUNDARY_CLAMP) ? 1 : 0;
+  }
+  if (pre.weight > 0.0f || two_counts)  // no processing order then, whose place the choices take
+    H.choice = pre.choice = (uint32_t*)(ws + L.order);
   if (prepare && (smp || !reuse_prep(ctx, flags, prep_key(hard_prep_path(gather, brick), ws, L, fixed, moving, bins)))) {
     pre.fbins = fb;
     pre.f = desc(fixed);
@@ -964,7 +989,6 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
     pre.gather = gather;
   }
   if ((e = launch_prepare(pre, s)) != hipSuccess) return hip_fail(e, "prepare");
-  HardLaunch H{};
   H.transforms = transforms;
   H.fbins = fb;
   H.gvol = gvol;
@@ -976,7 +1000,6 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
   H.n = n;
   H.bins = bins;
   H.clamp = (flags & MI_BOUNDARY_CLAMP) ? 1 : 0;
-  H.packed = use_packed(tune, bins) ? 1 : 0;
   H.block = tune.block;
   H.slab_major = tune.slab_major;
   H.brick = brick ? 1 : 0;
@@ -987,12 +1010,11 @@ int launch_hard_hist(mi_context* ctx, const mi_volume* fixed, const mi_volume* m
         hipSuccess)
       return hip_fail(e, "sample list");
     H.packed = bins > 128 ? 1 : 0;
-    H.chunks = plan_sampled_chunks(ctx, expected_samples(fixed, *smp), n);
-  } else {
-    H.chunks = plan_chunks(ctx, fixed, moving, n, bins, H.packed != 0, tune, gather, brick);
+    const int32_t c = plan_sampled_chunks(ctx, expected_samples(fixed, *smp), n);
+    H.split[0] = H.split[1] = SlabSplit{c, c, 0};
   }
   // one launch covers at most 2^31 - 1 workgroups: split the transforms
-  int64_t per_launch = 0x7FFFFFFFll / H.chunks;
+  int64_t per_launch = 0x7FFFFFFFll / std::max(H.split[0].chunks, H.split[1].chunks);
   // Thin slabs in slab-major order: the workgroups resident on an XCD sweep
   // one slab for consecutive transforms, so those are put in an order that
   // keeps their moving footprints together (launch_order_transforms; the
@@ -1509,8 +1531,9 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   HardTune best = ctx->hard_default;
   float best_ms = 3.4e38f;
   HardTune base = ctx->hard_default;
+  SlabSplit split[2];
   base.chunks = plan_chunks(ctx, fixed, moving, n, bins, use_packed(base, bins), base, call_gather(moving, L, n, flags, base),
-                            call_brick(flags, base));
+                            call_brick(flags, base), split);
   const int32_t chunk_opts[3] = {base.chunks / 2, base.chunks, base.chunks * 2};
   // LDS counter layouts: u32 or packed 16-bit pairs (only packed fits above 128 bins)
   const int32_t n_layouts = bins > 128 ? 1 : 2;
@@ -1530,7 +1553,8 @@ int mi_tune(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
           if ((e = hipEventRecord(t0, s)) != hipSuccess) { st = hip_fail(e, "tune"); break; }
           const bool prepare = rep == 0 && call_brick(flags, cand) != prepared_brick;  // the first run is not timed
           if (prepare) ctx->last_prep.clear();
-          st = launch_hard_hist(ctx, fixed, moving, nullptr, M, n, bins, flags, hist, ws, L, s, cand, prepare);
+          st = launch_hard_hist(ctx, fixed, moving, prepare ? transforms : nullptr, M, n, bins, flags, hist, ws, L, s, cand,
+                                prepare);
           prepared_brick = call_brick(flags, cand);
           if (st != MI_OK) break;
           if ((e = hipEventRecord(t1, s)) != hipSuccess || (e = hipEventSynchronize(t1)) != hipSuccess) {

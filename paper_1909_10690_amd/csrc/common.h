@@ -253,7 +253,10 @@ struct HardLaunch {
   uint64_t* count;  // [n]: each transform's sum of counts is added
   int32_t gather;
   int32_t n, bins, clamp;
-  int32_t chunks;  // workgroups per transform, multiple of 8
+  // workgroups per transform; [1] where choice[1] is not 0 (thin slabs; alike
+  // where there is no choice)
+  SlabSplit split[2];
+  const uint32_t* choice;  // see Prepare, or NULL
   int32_t packed;  // 1: two 16-bit counters per LDS word (bins > 128)
   int32_t block;   // threads per workgroup: 256, 512 or 1024
   int32_t slab_major;  // workgroup order: 1 slab-major, 0 transform-major
@@ -314,13 +317,18 @@ inline size_t moving_copy_bytes(int32_t nx, int32_t ny, int32_t nz) {
 // exact x-lerp in one instruction instead of two; octs of 8-bit corners; the
 // plain copy.
 // kTiled (brick sweeps): octs in tiles (tiled_index).
-enum Gather : int32_t { kOct16 = 0, kOct8 = 1, kCopy16 = 2, kOctD = 3, kTiled = 4 };
+// kChoose (few transforms): the copy, or the octs, chosen on the device.
+enum Gather : int32_t { kOct16 = 0, kOct8 = 1, kCopy16 = 2, kOctD = 3, kTiled = 4, kChoose = 8 };
 __host__ __device__ constexpr int32_t gather_base(int32_t gather) { return gather & 3; }
 __host__ __device__ constexpr int32_t gather_record(int32_t gather) {
   return gather_base(gather) == kOct8 ? 8 : (gather == kCopy16 ? 2 : 16);
 }
 inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_t nz) {
   if (gather == kCopy16) return moving_copy_bytes(nx, ny, nz);
+  if (gather & kChoose) {
+    const size_t copy = moving_copy_bytes(nx, ny, nz), octs = gather_volume_bytes(gather & ~kChoose, nx, ny, nz);
+    return copy > octs ? copy : octs;
+  }
   const bool rec8 = gather_base(gather) == kOct8;
   return (gather & kTiled ? tiled_records(nx, ny, nz, rec8) : (size_t)nx * ny * nz) * gather_record(gather);
 }
@@ -333,26 +341,52 @@ inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_
 // copy (us a call, oct and copy: 256x256x180 u16, 128 bins, one transform 122
 // and 97, four 257 and 229, six 328 and 338; 128^3 u8, 64 bins, four 66 and
 // 65, six 80 and 86, both with preparation and reduction in more launches than
-// now).  Turned widely, the copy's four gathers each have lines of their own:
-// beyond the L2s (kCopyBytes) it serves one or two transforms of a 16-bit
-// volume (us a call, copy and octs, 256x256x180 turned by 0, 30 and 60 degrees
-// about y: two transforms of u16 95, 179, 221 and 124, 193, 240, four 146, 307,
-// 424 and 168, 220, 263; one of u8 75, 130, 156 and 108, 126, 148; 128^3 u16,
-// four: 53, 72, 82 with the copy).
+// now).  Turned, the copy's four gathers each have lines of their own, so such a
+// call chooses on the device (turned_octs) -- a copy under kChooseBytes serves
+// every turn: its lines stay in the L2s, and the choice costs a sweep 0.5 us (48^3).
 constexpr int32_t kCopyTransforms = 4;
-constexpr size_t kCopyBytes = 8 << 20;
+constexpr size_t kCopyBytes = 8 << 20, kChooseBytes = 1 << 20;
 inline int32_t oct_gather(double lo, double hi) {
   return oct8_range(lo, hi) ? kOct8 : (hi - lo < 16384.0 ? kOctD : kOct16);
 }
 // room: bytes of the workspace's region for it.
 inline int32_t hard_gather(const VolumeDesc& m, int32_t n, bool reused, bool brick, size_t room) {
   if (!reused && !brick) {
-    const bool large = moving_copy_bytes(m.nx, m.ny, m.nz) > kCopyBytes;
-    if (large ? n <= 2 && !oct8_range(m.lo, m.hi) : n <= kCopyTransforms) return kCopy16;
+    const size_t copy = moving_copy_bytes(m.nx, m.ny, m.nz);
+    if (n <= (copy > kCopyBytes ? 2 : kCopyTransforms))
+      return copy > kChooseBytes ? oct_gather(m.lo, m.hi) | kChoose : (int32_t)kCopy16;
   }
   const int32_t oct = oct_gather(m.lo, m.hi);
   return brick && gather_volume_bytes(oct | kTiled, m.nx, m.ny, m.nz) <= room ? oct | kTiled : oct;
 }
+
+// Whether such a call takes octs: what the copy's sweep costs more than the
+// octs', over all its transforms, exceeds what the octs cost more to write.  With
+// rho = min(|M[1][0]| / 2 + |M[2][0]|, 1), the rows a step along x rises by, and
+// the voxels that lie inside, a transform's sweep costs about
+// (inside / moving voxels) (0.3 + 1.7 rho^2) min(1.2, copy MB / 14) as much more as
+// the octs cost to write: small copies stay in the L2s (us a call, copy and octs,
+// turned by 0, 30, 60 and 90 degrees about y: 256x256x180 u16, one transform 73
+// and 112, 111 and 118, 125 and 125, 166 and 138; two 98 and 127, 175 and 152, 212
+// and 168, 246 and 184; 192^3, two 67 and 92, 106 and 110, 153 and 127, 216 and
+// 132; 128^3, four 42 and 57, 60 and 60, 68 and 71, 101 and 73; 512x512x64, one, 83
+// and 181, 68 and 155, 66 and 148, 77 and 151).  Octs of 8-bit corners cost 1.6 times
+// less to write (256x256x180 u8, one transform, the same turns: 70 and 100, 108 and
+// 104, 122 and 114, 154 and 122).  The weight of a voxel inside, 0 (the copy) where
+// no turn can tip the choice by much:
+inline float octs_weight(const VolumeDesc& f, const VolumeDesc& m, int32_t n) {
+  const double mb = (double)moving_copy_bytes(m.nx, m.ny, m.nz) * 1e-6, small = mb / 14.0;
+  const double vf = (double)f.nx * f.ny * f.nz, vm = (double)m.nx * m.ny * m.nz;
+  const double w = (small < 1.2 ? small : 1.2) * vf / vm * (oct8_range(m.lo, m.hi) ? 1.6 : 1.0);
+  return n * 2.0 * w > 1.5 ? (float)w : 0.0f;
+}
+
+// A batch of at most so many transforms on a moving volume whose octs take more
+// bytes than that counts as turned or not, on the device (Prepare::choice[1]),
+// and has a slab count for either (turned_slabs).
+constexpr int32_t kTurnTransforms = 2;
+constexpr size_t kTurnBytes = 64 << 20;
+constexpr float kTurnedRise = 0.35f;  // mean |M[2][0]|; turned by 10 degrees the flat count is still the better one
 
 // Bytes of the 16-bit quad volume of an integer moving volume on the Parzen
 // path: per voxel the four (x, y) corners of its neighbourhood in one slice
@@ -546,6 +580,11 @@ struct Prepare {
   int32_t gather = 0;
   // kCopy16 only: where *records is not 0, octs (kOct16) instead
   const uint32_t* records = nullptr;
+  // What the device chooses (n <= kCopyTransforms): [0] 1 where a kChoose volume is
+  // octs (written with it), [1] 1 where the transforms are turned (written with M)
+  uint32_t* choice = nullptr;
+  float weight = 0.0f;  // octs_weight
+  int32_t clamp = 0;
 };
 // Layout of a sampled Parzen call's moving volume, chosen on the device, where
 // the matrices are: *records = 1 (octs; float volumes: quads) where the mean

@@ -344,7 +344,7 @@ __device__ __forceinline__ void pack_volume(const VolumeDesc& m, int32_t gather,
 
 static unsigned pack_blocks(const VolumeDesc& m, int32_t gather) {
   const size_t nvox = (size_t)m.nx * m.ny * m.nz;
-  if (gather == kCopy16) return fill_blocks((nvox + 7) / 8);
+  if (gather == kCopy16 || (gather & kChoose)) return fill_blocks((nvox + 7) / 8);
   if (gather & kTiled) return fill_blocks(tiled_records(m.nx, m.ny, m.nz, gather_base(gather) == kOct8));
   return row_part_blocks(row_parts(m.nx, m.ny, m.nz));
 }
@@ -359,14 +359,51 @@ struct PrepareArgs {
   PrepareBlocks blocks;
 };
 
+// Whether a few transforms take octs (octs_weight), by 4 x 4 x 4 points of the
+// fixed volume, a lane each: the same in every wave.  A lane loads an entry of
+// the matrices (n <= 4), so that the waves wait once: each packs few voxels.
+__device__ __forceinline__ bool turned_octs(const Prepare& p) {
+  static_assert(12 * kCopyTransforms <= 64, "an entry a lane");
+  const int lane = threadIdx.x & 63;
+  const float entry = lane < 12 * (int)p.n ? (float)p.P[lane] : 0.0f;
+  const Geometry& g = p.geo;
+  const float x = (float)g.forg[0] + (float)g.fsp[0] * (((float)(lane & 3) + 0.5f) * 0.25f * (float)(p.f.nx - 1));
+  const float y = (float)g.forg[1] + (float)g.fsp[1] * (((float)((lane >> 2) & 3) + 0.5f) * 0.25f * (float)(p.f.ny - 1));
+  const float z = (float)g.forg[2] + (float)g.fsp[2] * (((float)(lane >> 4) + 0.5f) * 0.25f * (float)(p.f.nz - 1));
+  const float size[3] = {(float)g.msp[0] * (float)(p.m.nx - 1), (float)g.msp[1] * (float)(p.m.ny - 1),
+                         (float)g.msp[2] * (float)(p.m.nz - 1)};
+  const float rise_y = 0.5f * (float)g.fsp[0] / (float)g.msp[1], rise_z = (float)g.fsp[0] / (float)g.msp[2];
+  float sum = 0.0f;
+  for (int t = 0; t < (int)p.n; ++t) {
+    auto P = [&](int e) {
+      return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, entry), 12 * t + e));
+    };
+    bool in = true;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const float q = P(4 * r) * x + P(4 * r + 1) * y + P(4 * r + 2) * z + P(4 * r + 3) - (float)g.morg[r];
+      in = in && q >= 0.0f && q <= size[r];
+    }
+    const float inside = p.clamp ? 64.0f : (float)__popcll(__builtin_amdgcn_ballot_w64(in));
+    const float rho = fminf(fabsf(P(4)) * rise_y + fabsf(P(8)) * rise_z, 1.0f);  // 1 for a NaN
+    sum += inside * (0.3f + 1.7f * rho * rho);
+  }
+  return sum * p.weight > 64.0f;
+}
+
 // The parts depend on nothing but the caller's inputs, so they share a launch,
 // the longest first: a small call (48^3, one transform) is mostly launches of
 // 2 to 3 us.
-__global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
+__global__ __launch_bounds__(256, 8) void prepare_kernel(PrepareArgs a) {
   uint32_t block = blockIdx.x;
   const PrepareBlocks& nb = a.blocks;
   if (block < nb.pack) {
-    pack_volume(a.p.m, a.p.records && *a.p.records ? (int32_t)kOct16 : a.p.gather, a.p.gvol, block, nb.pack);
+    int32_t gather = a.p.records && *a.p.records ? (int32_t)kOct16 : a.p.gather;
+    if (gather & kChoose) {
+      gather = a.p.weight > 0.0f && turned_octs(a.p) ? gather & ~kChoose : (int32_t)kCopy16;
+      if (a.p.choice && block == 0 && threadIdx.x == 0) a.p.choice[0] = gather == kCopy16 ? 0u : 1u;
+    }
+    pack_volume(a.p.m, gather, a.p.gvol, block, nb.pack);
     return;
   }
   block -= nb.pack;
@@ -384,6 +421,12 @@ __global__ __launch_bounds__(256) void prepare_kernel(PrepareArgs a) {
     return;
   }
   block -= nb.clear;
+  if (a.p.choice && block == 0 && threadIdx.x < 64) {  // n <= kCopyTransforms
+    const float per = (float)a.p.geo.fsp[0] / (float)a.p.geo.msp[2];
+    float rise = (int64_t)threadIdx.x < a.p.n ? fminf(fabsf((float)a.p.P[12 * threadIdx.x + 8]) * per, 1.0f) : 0.0f;
+    for (int off = 32; off > 0; off >>= 1) rise += __shfl_xor(rise, off, 64);
+    if (threadIdx.x == 0) a.p.choice[1] = rise > kTurnedRise * (float)a.p.n ? 1u : 0u;
+  }
   for (int64_t t = block * 256ll + threadIdx.x; t < a.p.n; t += nb.compose * 256ll) {
     double m[12];
     compose_index_matrix(a.p.P + 12 * t, a.p.geo, m);
@@ -397,6 +440,7 @@ hipError_t launch_prepare(const Prepare& p, hipStream_t s) {
   PrepareBlocks& nb = a.blocks;
   if (p.gvol) {
     if (p.m.dtype > 2) return hipErrorInvalidValue;
+    if (p.weight > 0.0f && (!p.choice || !p.P || !p.fbins)) return hipErrorInvalidValue;
     nb.pack = pack_blocks(p.m, p.gather);
   }
   if (p.fbins) {
@@ -408,6 +452,7 @@ hipError_t launch_prepare(const Prepare& p, hipStream_t s) {
   for (int k = 0; k < p.clear.n; ++k) most = p.clear.words[k] > most ? p.clear.words[k] : most;
   if (most) nb.clear = fill_blocks((most + 3) / 4);
   if (p.P && p.n > 0) nb.compose = std::min(fill_blocks((size_t)p.n), 4096u);
+  if (p.choice && p.n > kCopyTransforms) return hipErrorInvalidValue;
   if (nb.total() == 0) return hipSuccess;
   if (!nb.fits()) return hipErrorInvalidValue;
   hipLaunchKernelGGL(prepare_kernel, dim3(nb.total()), dim3(256), 0, s, a);
@@ -427,7 +472,9 @@ struct HardArgs {
   uint32_t* hist;
   uint64_t* count;
   HardGeom geom;
-  int32_t n, chunks;
+  SlabSplit split[2];       // [1] where choice[1] is not 0
+  const uint32_t* choice;   // Prepare::choice, or NULL
+  int32_t n;
   int32_t slab_major;     // 1: consecutive workgroups of an XCD share a slab
   const uint32_t* order;  // processing order (absolute indices) or NULL
   uint32_t order_base;    // absolute index of this launch's first transform
@@ -443,19 +490,35 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 ?
 void hist_hard_kernel(HardArgs a) {
   extern __shared__ uint32_t lds_hist[];
   const int B = a.geom.bins;
+  SlabSplit split = a.split[0];
+  bool octs = false;
+  if constexpr (!BRICK) {
+    if (a.choice) {
+      octs = (GL & kChoose) != 0 && a.choice[0] != 0;
+      if (a.choice[1]) split = a.split[1];
+      // the launch is made for the larger count
+      if ((blockIdx.x >> 3) >= (uint32_t)(split.chunks >> 3) * (uint32_t)a.n) return;
+    }
+  }
   clear_hist<PACKED, NT>(lds_hist, B);
   uint32_t t, chunk, band;
-  block_work(a.chunks, a.n, 1, a.slab_major, t, chunk, band);
+  block_work(split.chunks, a.n, 1, a.slab_major, t, chunk, band);
   if (a.order) t = a.order[t] - a.order_base;
   const double* Md = a.transforms + 12 * (size_t)t;
   int64_t Mq[12];
   const bool ok = quantize_transform_wave(Md, Mq);
   __syncthreads();
   if (ok) {
-    if (BRICK)
-      sweep_rods<CLAMP, PACKED, GL, NT / 64>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
-    else
-      sweep_hard<CLAMP, PACKED, GL, NT / 64>(a.geom, Md, Mq, a.chunks, chunk, lds_hist);
+    if constexpr (BRICK) {
+      sweep_rods<CLAMP, PACKED, GL, NT / 64>(a.geom, Md, Mq, split.chunks, chunk, lds_hist);
+    } else if constexpr ((GL & kChoose) != 0) {
+      if (octs)
+        sweep_hard<CLAMP, PACKED, GL & ~kChoose, NT / 64>(a.geom, Md, Mq, split, chunk, lds_hist);
+      else
+        sweep_hard<CLAMP, PACKED, kCopy16, NT / 64>(a.geom, Md, Mq, split, chunk, lds_hist);
+    } else {
+      sweep_hard<CLAMP, PACKED, GL, NT / 64>(a.geom, Md, Mq, split, chunk, lds_hist);
+    }
   }
   __syncthreads();
   if (ok) flush_hist<PACKED, NT>(lds_hist, B, a.hist + (size_t)t * B * B, a.count + t, false);
@@ -473,11 +536,12 @@ __global__ __launch_bounds__(NT) void hist_sampled_kernel(HardArgs a, const uint
   const int B = a.geom.bins;
   clear_hist<PACKED, NT>(lds_hist, B);
   uint32_t t, chunk, band;
-  block_work(a.chunks, a.n, 1, a.slab_major, t, chunk, band);
+  const int32_t chunks = a.split[0].chunks;
+  block_work(chunks, a.n, 1, a.slab_major, t, chunk, band);
   int64_t Mq[12];
   const bool ok = quantize_transform(a.transforms + 12 * (size_t)t, Mq);
   const int64_t ns = (int64_t)*n_list;
-  const int64_t s0 = ns * chunk / a.chunks, s1 = ns * (chunk + 1) / a.chunks;
+  const int64_t s0 = ns * chunk / chunks, s1 = ns * (chunk + 1) / chunks;
   const int64_t span = PACKED ? 65535 : s1 - s0;
   const HardStep hs(a.geom, PACKED, GL);
   uint32_t* out = a.hist + (size_t)t * B * B;
@@ -511,8 +575,8 @@ static hipError_t launch_sampled_nt(const HardArgs& a, const uint2* list, const 
                                     size_t lds, hipStream_t s) {
   const hipError_t e = lds_guard((const void*)hist_sampled_kernel<CLAMP, PACKED, GL, NT>, lds, kHardLdsMax, true);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((hist_sampled_kernel<CLAMP, PACKED, GL, NT>), dim3((unsigned)(a.n * a.chunks)), dim3(NT), lds,
-                     s, a, list, n_list);
+  hipLaunchKernelGGL((hist_sampled_kernel<CLAMP, PACKED, GL, NT>), dim3((unsigned)(a.n * a.split[0].chunks)), dim3(NT),
+                     lds, s, a, list, n_list);
   return hipGetLastError();
 }
 
@@ -528,8 +592,8 @@ static hipError_t launch_variant(const HardArgs& a, int n, size_t lds, hipStream
   const hipError_t e =
       lds_guard((const void*)hist_hard_kernel<CLAMP, PACKED, GL, NT, BRICK>, lds, kHardLdsMax, true);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((hist_hard_kernel<CLAMP, PACKED, GL, NT, BRICK>), dim3((unsigned)(n * a.chunks)),
-                     dim3(NT), lds, s, a);
+  const int32_t chunks = a.choice ? std::max(a.split[0].chunks, a.split[1].chunks) : a.split[0].chunks;
+  hipLaunchKernelGGL((hist_hard_kernel<CLAMP, PACKED, GL, NT, BRICK>), dim3((unsigned)(n * chunks)), dim3(NT), lds, s, a);
   return hipGetLastError();
 }
 
@@ -551,7 +615,7 @@ static hipError_t launch_nt(const HardArgs& a, int n, bool clamp, bool packed, s
   case kOctD: return launch_layout<kOctD, NT, BRICK>(a, n, clamp, packed, lds, s);
   case kOct16: return launch_layout<kOct16, NT, BRICK>(a, n, clamp, packed, lds, s);
   }
-  if constexpr (BRICK) {  // tiles serve bricks only, the copy thin slabs only
+  if constexpr (BRICK) {  // tiles serve bricks only, the copy few transforms in thin slabs
     switch (a.geom.gather) {
     case kOct8 | kTiled: return launch_layout<kOct8 | kTiled, NT, BRICK>(a, n, clamp, packed, lds, s);
     case kOctD | kTiled: return launch_layout<kOctD | kTiled, NT, BRICK>(a, n, clamp, packed, lds, s);
@@ -559,8 +623,13 @@ static hipError_t launch_nt(const HardArgs& a, int n, bool clamp, bool packed, s
     default: return hipErrorInvalidValue;
     }
   } else {
-    return a.geom.gather == kCopy16 ? launch_layout<kCopy16, NT, BRICK>(a, n, clamp, packed, lds, s)
-                                    : hipErrorInvalidValue;
+    switch (a.geom.gather) {
+    case kCopy16: return launch_layout<kCopy16, NT, BRICK>(a, n, clamp, packed, lds, s);
+    case kOct8 | kChoose: return launch_layout<kOct8 | kChoose, NT, BRICK>(a, n, clamp, packed, lds, s);
+    case kOctD | kChoose: return launch_layout<kOctD | kChoose, NT, BRICK>(a, n, clamp, packed, lds, s);
+    case kOct16 | kChoose: return launch_layout<kOct16 | kChoose, NT, BRICK>(a, n, clamp, packed, lds, s);
+    default: return hipErrorInvalidValue;
+    }
   }
 }
 
@@ -592,14 +661,16 @@ hipError_t launch_hist_hard(const HardLaunch& L, hipStream_t s) {
   a.hist = L.hist;
   a.count = L.count;
   a.geom = make_hard_geom(L.fixed, L.moving, L.fbins, L.gvol, L.gather, L.bins);
+  a.split[0] = L.split[0];
+  a.split[1] = L.split[1];
+  a.choice = L.choice;
   a.n = L.n;
-  a.chunks = L.chunks;
   a.slab_major = L.slab_major;
   a.order = nullptr;
   a.order_base = 0;
   const size_t lds = hist_lds_bytes(L.bins, L.packed);
   if (L.block != 256 && L.block != 512 && L.block != 1024) return hipErrorInvalidValue;
-  int32_t step = transforms_per_launch(L.chunks, L.block);
+  int32_t step = transforms_per_launch(std::max(L.split[0].chunks, L.split[1].chunks), L.block);
   // with an order, launches start at multiples of its sorted blocks
   const bool ordered = L.order && step >= kOrderBlock;
   if (ordered) step -= step % kOrderBlock;
@@ -634,8 +705,9 @@ hipError_t launch_hist_sampled(const HardLaunch& L, const uint2* list, const uns
   a.hist = L.hist;
   a.count = L.count;
   a.geom = make_hard_geom(L.fixed, L.moving, L.fbins, L.gvol, L.gather, L.bins);
+  a.split[0] = a.split[1] = L.split[0];
+  a.choice = nullptr;
   a.n = L.n;
-  a.chunks = L.chunks;
   a.slab_major = 1;
   a.order = nullptr;  // the sampled sweep keeps the batch order
   a.order_base = 0;
@@ -655,7 +727,7 @@ hipError_t launch_hist_sampled(const HardLaunch& L, const uint2* list, const uns
     default: return hipErrorInvalidValue;
     }
   };
-  const int32_t step = transforms_per_launch(L.chunks, sampled_block(lds));
+  const int32_t step = transforms_per_launch(L.split[0].chunks, sampled_block(lds));
   for (int32_t t0 = 0; t0 < L.n; t0 += step) {
     HardArgs b = a;
     b.n = L.n - t0 < step ? L.n - t0 : step;
@@ -688,6 +760,9 @@ static hipError_t allow_big_lds_nt() {
   if ((e = allow_big_lds<kOct16, NT>()) != hipSuccess) return e;
   if ((e = allow_big_lds<kOct8, NT>()) != hipSuccess) return e;
   if ((e = allow_big_lds<kOctD, NT>()) != hipSuccess) return e;
+  if ((e = allow_big_lds<kOct16 | kChoose, NT>()) != hipSuccess) return e;
+  if ((e = allow_big_lds<kOct8 | kChoose, NT>()) != hipSuccess) return e;
+  if ((e = allow_big_lds<kOctD | kChoose, NT>()) != hipSuccess) return e;
   return allow_big_lds<kCopy16, NT>();
 }
 

@@ -105,6 +105,52 @@ inline int64_t planned_slabs(int64_t voxels, int64_t n, int64_t slots, int32_t b
   return best;
 }
 
+// A transform's share of a thin-slab sweep: `chunks` workgroups (a multiple of
+// 8), of which the first `slabs` have a slab each; the slabs divide slab_nz
+// slices evenly (the fixed volume's, or a few more: the last are past its end).
+struct SlabSplit {
+  int32_t chunks, slabs, slab_nz;
+};
+
+// Slabs of whole slices, or of even parts of one, keep the workgroups that run
+// at once on the same rows of neighbouring slices, whose images share cache
+// lines; they matter where the moving layout is far larger than the L2s.
+//
+// Not turned: planned_slabs' count c, or the least count of aligned slabs within
+// 0.7 and 1.1 of it that makes whole rounds (512x512x64 i16, 64 bins, eight
+// transforms: 176 slabs 441 us, 192 384; four: 352 307, 256 264).
+constexpr int64_t aligned_rounds(int64_t c, int32_t nz, int64_t n, int64_t slots, int64_t least) {
+  for (int64_t a = (c * 7 + 9) / 10; a * 10 <= c * 11; ++a)
+    if (a % 8 == 0 && a >= least && (a % nz == 0 || nz % a == 0) && n * a % slots == 0) return a;
+  return c;
+}
+
+// One or two transforms that are turned (the gathers wait longer, and more
+// workgroups overlap their waits): even parts of a slice, the count that takes
+// the fewest steps of a row group a wave over its whole rounds, the nearest to
+// 1.4 workgroups a slot among equals.  Turned by 60 and 90 degrees about y, us a
+// call with planned_slabs' count and this: 256x256x180 u16, 128 bins, one
+// transform 155 and 215, 125 and 166 (the copy), 180 and 186, 125 and 138 (octs), two
+// 245 and 258, 169 and 180; u8, one 146 and 161, 114 and 122.
+inline SlabSplit turned_slabs(int32_t ny, int32_t nz, int64_t n, int64_t slots, int32_t waves) {
+  const int64_t G = (ny + 3) / 4;
+  const double target = 1.4 * (double)slots;
+  SlabSplit best{0, 0, 0};
+  int64_t least = 0;
+  double off = 0.0;
+  for (int64_t j = 1; j <= G && j <= 16; ++j) {
+    const int64_t slabs = nz * j, per = (G + j - 1) / j;  // row groups of the largest slab
+    const int64_t steps = (n * slabs + slots - 1) / slots * ((per + waves - 1) / waves);
+    const double ratio = (double)slabs > target ? (double)slabs / target : target / (double)slabs;
+    if (best.chunks == 0 || steps < least || (steps == least && ratio < off)) {
+      least = steps;
+      off = ratio;
+      best = SlabSplit{(int32_t)((slabs + 7) / 8 * 8), (int32_t)slabs, nz};
+    }
+  }
+  return best;
+}
+
 // ---------------------------------------------------------------------------
 // the fixed-volume walk shared by the sweep kernels
 // ---------------------------------------------------------------------------
@@ -285,10 +331,12 @@ struct GroupWalkT {
   int64_t r[3], lane_off[3], step[3], adv[3], wrap[3];
 
   constexpr void init(const int64_t* Mq, int32_t fny, int32_t fnz, int32_t chunks, uint32_t chunk, int wave,
-                      int nwaves, int dx, int dy, bool interleave = false) {
+                      int nwaves, int dx, int dy, bool interleave = false, int32_t slab_nz = 0) {
     G = (fny + kTileY - 1) / kTileY;
-    const int64_t groups = (int64_t)G * fnz;
-    const int64_t s0 = groups * chunk / chunks, s1 = groups * (chunk + 1) / chunks;
+    // slab_nz: slices that the slabs divide evenly, at least fnz (0: fnz)
+    const int64_t groups = (int64_t)G * fnz, even = slab_nz ? (int64_t)G * slab_nz : groups;
+    const int64_t e0 = even * chunk / chunks, e1 = even * (chunk + 1) / chunks;
+    const int64_t s0 = e0 < groups ? e0 : groups, s1 = e1 < groups ? e1 : groups;
     if (FLEX && interleave) {
       g = s0 + wave;
       g1 = s1;

@@ -267,7 +267,7 @@ struct RowRanges {
 // (quantize_transform_wave).
 template <bool CLAMP, bool PACKED, int GL, int NW>
 __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, const int64_t* Mq,
-                                           int32_t chunks, uint32_t chunk, uint32_t* lds_hist) {
+                                           const SlabSplit& split, uint32_t chunk, uint32_t* lds_hist) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int dx = lane & (kTileX - 1), dy = lane / kTileX;
@@ -276,7 +276,7 @@ __device__ __forceinline__ void sweep_hard(const HardGeom& g, const double* Md, 
   // the lane offsets take vector registers
   const int64_t* M = Mq;
   GroupWalk w;
-  w.init(M, g.fny, g.fnz, chunks, chunk, wave, NW, dx, dy);
+  w.init(M, g.fny, g.fnz, split.slabs, chunk, wave, NW, dx, dy, false, split.slab_nz);
   const int64_t sx = w.step[0], sy = w.step[1], sz = w.step[2];
   const HardStep hs(g, PACKED, GL);
   // Fixed bins: the row's address in scalar registers, the lane's offset in a
