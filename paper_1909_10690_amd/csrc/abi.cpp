@@ -550,10 +550,12 @@ int run_parzen(mi_context* ctx, const mi_volume* fixed, const mi_volume* moving,
   // can fall on records (a row rises by one row a step at most, or so)
   uint32_t* records = nullptr;
   if (smp) {
-    const double limit = sample_layout_limit(moving->nx, moving->ny, moving->nz, fq);
+    const double limit =
+        sample_layout_limit((double)expected_samples(fixed, *smp), smp->fraction,
+                            moving_copy_bytes(moving->nx, moving->ny, moving->nz), n, fq);
     if (limit < 1.0) {
       records = (uint32_t*)(nlist + 1);  // in the list length's 256 bytes
-      if ((e = launch_sample_layout(pre.P, n, pre.geo, limit, records, s)) != hipSuccess)
+      if ((e = launch_sample_layout(pre.P, n, pre.geo, sample_row_weight(smp->fraction), limit, records, s)) != hipSuccess)
         return hip_fail(e, "sample layout");
     }
   }

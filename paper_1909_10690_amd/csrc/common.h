@@ -588,23 +588,11 @@ struct Prepare {
 };
 // Layout of a sampled Parzen call's moving volume, chosen on the device, where
 // the matrices are: *records = 1 (octs; float volumes: quads) where the mean
-// over the batch of the rows a step along x rises by, |M[1][0]| / 2 +
-// |M[2][0]|, exceeds `limit`, else 0 (the plain copy).  P: physical matrices.
-hipError_t launch_sample_layout(const double* P, int64_t n, const Geometry& g, double limit, uint32_t* records,
-                                hipStream_t s);
-// The copy's gain is that a line holds several samples of a row; turned, each
-// sample has lines of its own, four of the copy against one of the octs or two
-// of the quads, unless the copy stays in the L2.  Both measured, 64 bins, 100
-// rotations up to +-a about y, 10% of 256x256x180 u16, copy and octs: a = 5
-// degrees 1040 and 1229 us, 10 1473 and 1357, 45 3196 and 1887; 128^3, a = 20
-// 245 and 259, 45 306 and 283; f32, copy and quads: a = 20 2850 and 3066, 45
-// 4058 and 3560.  The limit goes with the root of the copy's bytes: between
-// those sizes, and on the side of the records, which were the only layout.  A
-// copy of less than 1.5 MB stays in the L2 whole: no limit.
-inline double sample_layout_limit(int32_t nx, int32_t ny, int32_t nz, bool f32) {
-  const double mb = (double)moving_copy_bytes(nx, ny, nz) * (f32 ? 2e-6 : 1e-6);
-  return mb < 1.5 ? 1e9 : (f32 ? 1.17 : 0.36) / sqrt(mb);
-}
+// over the batch (at most 256 matrices of it, evenly spaced) of the rows a step
+// along x rises by, row_weight |M[1][0]| + |M[2][0]|, exceeds `limit`, else 0
+// (the plain copy).  P: physical matrices.
+hipError_t launch_sample_layout(const double* P, int64_t n, const Geometry& g, double row_weight, double limit,
+                                uint32_t* records, hipStream_t s);
 hipError_t launch_prepare(const Prepare& p, hipStream_t s);
 // Nothing is written where `records` is given and *records is not 0 (copy) or 0
 // (quads).

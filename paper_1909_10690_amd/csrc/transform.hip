@@ -28,14 +28,15 @@ __global__ void grad_physical_kernel(double* __restrict__ G, int64_t rows, Geome
 }
 
 __global__ __launch_bounds__(256) void sample_layout_kernel(const double* __restrict__ P, int64_t n, Geometry g,
-                                                            double limit, uint32_t* __restrict__ records) {
+                                                            double row_weight, double limit,
+                                                            uint32_t* __restrict__ records) {
   __shared__ double sum[256];
   const int64_t used = n < 256 ? n : 256;
   double rise = 0.0;
   if ((int64_t)threadIdx.x < used) {
     double m[12];
     compose_index_matrix(P + 12 * ((int64_t)threadIdx.x * n / used), g, m);
-    rise = 0.5 * fabs(m[4]) + fabs(m[8]);
+    rise = row_weight * fabs(m[4]) + fabs(m[8]);
     if (!(rise < 65536.0)) rise = 0.0;  // a rejected matrix
   }
   sum[threadIdx.x] = rise;
@@ -47,10 +48,10 @@ __global__ __launch_bounds__(256) void sample_layout_kernel(const double* __rest
   if (threadIdx.x == 0) *records = sum[0] > limit * (double)used ? 1u : 0u;
 }
 
-hipError_t launch_sample_layout(const double* P, int64_t n, const Geometry& g, double limit, uint32_t* records,
-                                hipStream_t s) {
+hipError_t launch_sample_layout(const double* P, int64_t n, const Geometry& g, double row_weight, double limit,
+                                uint32_t* records, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(sample_layout_kernel, dim3(1), dim3(256), 0, s, P, n, g, limit, records);
+  hipLaunchKernelGGL(sample_layout_kernel, dim3(1), dim3(256), 0, s, P, n, g, row_weight, limit, records);
   return hipGetLastError();
 }
 
