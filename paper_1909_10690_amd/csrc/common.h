@@ -349,7 +349,12 @@ constexpr size_t kCopyBytes = 8 << 20, kChooseBytes = 1 << 20;
 inline int32_t oct_gather(double lo, double hi) {
   return oct8_range(lo, hi) ? kOct8 : (hi - lo < 16384.0 ? kOctD : kOct16);
 }
-// room: bytes of the workspace's region for it.
+// room: bytes of the workspace's region for it.  Tiles of 16-byte records take
+// longer to write than rows, 88 against 36 us at 256x256x180, which brick sweeps
+// win back with the fifth transform or so (us a call, tiles and rows, COMPACT_SLABS,
+// 256x256x180 u16 turned up to +-20 degrees and by 0 to 90: two transforms 162 and
+// 129, 166 and 146, four 234 and 205, 224 and 248, eight 284 and 288, 301 and 372);
+// of 8-byte records no longer.
 inline int32_t hard_gather(const VolumeDesc& m, int32_t n, bool reused, bool brick, size_t room) {
   if (!reused && !brick) {
     const size_t copy = moving_copy_bytes(m.nx, m.ny, m.nz);
@@ -357,6 +362,7 @@ inline int32_t hard_gather(const VolumeDesc& m, int32_t n, bool reused, bool bri
       return copy > kChooseBytes ? oct_gather(m.lo, m.hi) | kChoose : (int32_t)kCopy16;
   }
   const int32_t oct = oct_gather(m.lo, m.hi);
+  if (!reused && oct != kOct8 && n <= kCopyTransforms) return oct;
   return brick && gather_volume_bytes(oct | kTiled, m.nx, m.ny, m.nz) <= room ? oct | kTiled : oct;
 }
 

@@ -269,8 +269,7 @@ __device__ __forceinline__ void pack_oct8(const T* __restrict__ v, int32_t nx, i
 // Octs in tiles (tiled_index), one record per thread: records of a tile are
 // neighbours in memory, so the stores are whole lines and the reads of a
 // tile's eight or sixteen records mostly hit the same ones (256x256x180 u16:
-// 88 us against 36 for rows of octs, which a map of rotations repays in one
-// transform of its hundreds).
+// 88 us against 36 for rows of octs, see hard_gather).
 template <typename T, int BASE>
 __device__ __forceinline__ void pack_tiled(const T* __restrict__ v, int32_t nx, int32_t ny, int32_t nz, int32_t lo,
                                            int32_t hi, void* __restrict__ out, uint32_t block, uint32_t nb) {
