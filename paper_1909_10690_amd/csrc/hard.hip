@@ -475,6 +475,7 @@ struct HardArgs {
   const uint32_t* choice;   // Prepare::choice, or NULL
   int32_t n;
   int32_t slab_major;     // 1: consecutive workgroups of an XCD share a slab
+  int32_t deal;           // bricks: slabs in turn over the XCDs (deal_slabs)
   const uint32_t* order;  // processing order (absolute indices) or NULL
   uint32_t order_base;    // absolute index of this launch's first transform
 };
@@ -502,6 +503,7 @@ void hist_hard_kernel(HardArgs a) {
   clear_hist<PACKED, NT>(lds_hist, B);
   uint32_t t, chunk, band;
   block_work(split.chunks, a.n, 1, a.slab_major, t, chunk, band);
+  if (BRICK && a.deal) chunk = dealt_slab(chunk, (uint32_t)split.chunks);
   if (a.order) t = a.order[t] - a.order_base;
   const double* Md = a.transforms + 12 * (size_t)t;
   int64_t Mq[12];
@@ -665,6 +667,7 @@ hipError_t launch_hist_hard(const HardLaunch& L, hipStream_t s) {
   a.choice = L.choice;
   a.n = L.n;
   a.slab_major = L.slab_major;
+  a.deal = deal_slabs(L.fixed.nx, L.fixed.ny, L.fixed.nz) ? 1 : 0;
   a.order = nullptr;
   a.order_base = 0;
   const size_t lds = hist_lds_bytes(L.bins, L.packed);
@@ -708,6 +711,7 @@ hipError_t launch_hist_sampled(const HardLaunch& L, const uint2* list, const uns
   a.choice = nullptr;
   a.n = L.n;
   a.slab_major = 1;
+  a.deal = 0;
   a.order = nullptr;  // the sampled sweep keeps the batch order
   a.order_base = 0;
   const size_t lds = hist_lds_bytes(L.bins, L.packed);

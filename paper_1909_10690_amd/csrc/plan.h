@@ -211,6 +211,22 @@ struct Rods {
 };
 constexpr Rods cube_rods(int32_t nx) { return Rods{kRodX, (nx + kRodX - 1) / kRodX, 2}; }
 
+// Whether a brick sweep's slabs are dealt to the XCDs in turn, not by eighths of
+// the fixed volume (block_work).  The eighths of a volume that is long in x are its
+// x segments: turned out of a short axis, those away from the middle lie outside the
+// moving volume, and their XCDs idle.  In turn the XCDs fetch more lines twice (us,
+// 100 transforms of 0, up to +-20, 0 to 90 and 90 degrees, by eighths and in turn:
+// 512x512x200 i16 8874 and 8806, 8237 and 8179, 8548 and 6527, 8878 and 4635;
+// 256x256x128 u16 1293 and 1293, 1178 and 1244, 1333 and 1113, 1343 and 856;
+// 64x256x256 681 and 685, 555 and 589, 411 and 588, 333 and 661; 128^3 u8, 216 of up
+// to 180 degrees, 637 and 651).
+constexpr bool deal_slabs(int32_t nx, int32_t ny, int32_t nz) { return nx >= 2 * (ny < nz ? ny : nz); }
+// Slab `chunk` by eighths -> the slab dealt in its place; chunks a multiple of 8.
+constexpr uint32_t dealt_slab(uint32_t chunk, uint32_t chunks) {
+  const uint32_t c8 = chunks >> 3;
+  return (chunk % c8) * 8 + chunk / c8;
+}
+
 // A slab's walk in brick sweeps: the rods are numbered by
 // x segment, then by blocks of yb rods along y, then z, then y within the
 // block; a slab is a contiguous range of that numbering, so a block of one
