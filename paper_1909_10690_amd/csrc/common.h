@@ -351,10 +351,13 @@ inline int32_t oct_gather(double lo, double hi) {
 }
 // room: bytes of the workspace's region for it.  Tiles of 16-byte records take
 // longer to write than rows, 88 against 36 us at 256x256x180, which brick sweeps
-// win back with the fifth transform or so (us a call, tiles and rows, COMPACT_SLABS,
+// win back with about seven transforms (14 volumes of 128x128x48 to 512x512x200 in 5
+// families of angles, mean of rows over tiles: four transforms 0.94, six 0.98, eight
+// 1.01; us a call, tiles and rows, COMPACT_SLABS,
 // 256x256x180 u16 turned up to +-20 degrees and by 0 to 90: two transforms 162 and
 // 129, 166 and 146, four 234 and 205, 224 and 248, eight 284 and 288, 301 and 372);
 // of 8-byte records no longer.
+constexpr int32_t kRowsTransforms = 6;
 inline int32_t hard_gather(const VolumeDesc& m, int32_t n, bool reused, bool brick, size_t room) {
   if (!reused && !brick) {
     const size_t copy = moving_copy_bytes(m.nx, m.ny, m.nz);
@@ -362,7 +365,7 @@ inline int32_t hard_gather(const VolumeDesc& m, int32_t n, bool reused, bool bri
       return copy > kChooseBytes ? oct_gather(m.lo, m.hi) | kChoose : (int32_t)kCopy16;
   }
   const int32_t oct = oct_gather(m.lo, m.hi);
-  if (!reused && oct != kOct8 && n <= kCopyTransforms) return oct;
+  if (!reused && oct != kOct8 && n <= kRowsTransforms) return oct;
   return brick && gather_volume_bytes(oct | kTiled, m.nx, m.ny, m.nz) <= room ? oct | kTiled : oct;
 }
 
