@@ -343,7 +343,10 @@ __device__ __forceinline__ void pack_volume(const VolumeDesc& m, int32_t gather,
 
 static unsigned pack_blocks(const VolumeDesc& m, int32_t gather) {
   const size_t nvox = (size_t)m.nx * m.ny * m.nz;
-  if (gather == kCopy16 || (gather & kChoose)) return fill_blocks((nvox + 7) / 8);
+  // (each block waits for the matrices first: as many as the chip holds at once,
+  // 256x256x180 u16 20.8 us a launch, in 5760 blocks 24.4)
+  if (gather & kChoose) return std::min(fill_blocks((nvox + 7) / 8), 2048u);
+  if (gather == kCopy16) return fill_blocks((nvox + 7) / 8);
   if (gather & kTiled) return fill_blocks(tiled_records(m.nx, m.ny, m.nz, gather_base(gather) == kOct8));
   return row_part_blocks(row_parts(m.nx, m.ny, m.nz));
 }
