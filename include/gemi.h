@@ -147,9 +147,12 @@ extern "C" {
  * the moving volume widely, such as a rotation map: each workgroup sweeps a
  * compact brick instead of a thin slab of whole slices, a wave small cubes
  * of it, so that the moving footprints of the transforms running at once
- * overlap in L2 and a wave's own in few cache lines.  Results are identical; applies to the 1024-thread launch shape (the
- * default); slower for translation-like batches.  Ignored by the Parzen
- * and sampled paths; mi_eval_pairs does not take it (MI_ERR_FLAGS). */
+ * overlap in L2 and a wave's own in few cache lines.  Results are identical;
+ * applies to the 1024-thread launch shape (the default); slower for
+ * translation-like batches.  mi_workspace_size with it adds room for the
+ * moving layout of odd extents; a workspace sized without it serves such a
+ * call too, more slowly.  Ignored by the Parzen and sampled paths;
+ * mi_eval_pairs does not take it (MI_ERR_FLAGS). */
 #define MI_COMPACT_SLABS 0x8000
 /* mi_workspace_size: size the workspace for mi_grad (adds the dMI/dp
  * tables).  Accepted (and implied) by mi_grad; rejected (MI_ERR_FLAGS) by
