@@ -338,10 +338,10 @@ inline size_t gather_volume_bytes(int32_t gather, int32_t nx, int32_t ny, int32_
 // of 1000 of 256x256x180 u16.  But the oct volume is 8 times the moving
 // volume to write and then to fetch, 36 us at that size against 8 us for the
 // copy, so a call that prepares its volumes for a few transforms uses the
-// copy (us a call, oct and copy: 256x256x180 u16, 128 bins, one transform 122
-// and 97, four 257 and 229, six 328 and 338; 128^3 u8, 64 bins, four 66 and
-// 65, six 80 and 86, both with preparation and reduction in more launches than
-// now).  Turned, the copy's four gathers each have lines of their own, so such a
+// copy (us a call, octs and copy, upright: 256x256x180 u16, 128 bins, one transform
+// 112 and 73, two 127 and 98, four 168 and 146 -- but 220 and 307 turned by 30
+// degrees, so beyond kCopyBytes only two; 128^3 u16, 64 bins, four 57 and 42).
+// Turned, the copy's four gathers each have lines of their own, so such a
 // call chooses on the device (turned_octs) -- a copy under kChooseBytes serves
 // every turn: its lines stay in the L2s, and the choice costs a sweep 0.5 us (48^3).
 constexpr int32_t kCopyTransforms = 4;
